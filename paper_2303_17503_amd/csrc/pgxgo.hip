@@ -497,13 +497,91 @@ __device__ __forceinline__ void reset_board(const Lane<N>& L, Row<N>& R, Meta& m
   m.bp = (int)(env_hash(seed, 1u, (uint32_t)L.slot, m.episode) & 1u);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Board-wide sums through LDS: every row lane adds its value to its board's 8-byte cell, every lane reads the sum back
+// (a wavefront's LDS operations execute in program order, so no barrier is needed).  A round of sums uses fresh cells;
+// kTallyRounds rounds are cleared by one store per lane.
+// ------------------------------------------------------------------------------------------------
+// (The sums used to be ballots masked with the board's lanes, per flood and per lane: 39 instructions for a look at one flood,
+// against 14 and one round trip to LDS for all five.)
+constexpr int kBlindSteps = 4;   // growth steps between two looks at the liberties (9x9 and 19x19: 2 and 3 are slower, 6 the same)
+constexpr unsigned kTallyRounds = 8u, kTallyBoards = 8u;
+static_assert(kTallyRounds * kTallyBoards == 64u, "cleared by one store per lane");
+__device__ __forceinline__ void tally_clear(uint64_t* tally, int lane) {
+  wave_lds_fence();
+  tally[lane] = 0u;
+  wave_lds_fence();
+}
+template <int N>
+__device__ __forceinline__ uint64_t tally_board(uint64_t* tally, unsigned round, const Lane<N>& L, uint64_t v) {
+  static_assert(64 / Geo<N>::STRIDE < (int)kTallyBoards, "a cell for every board and for the lanes beyond them");
+  uint64_t* cell = tally + round * kTallyBoards + L.j;
+  __hip_atomic_fetch_add(cell, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  return __hip_atomic_load(cell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
+// The five floods of a ply (the new stone's chain and its four opposing neighbours) side by side.  At 9x9 a dword holds a row
+// of three floods in fields of ten bits (the tenth is always zero in the sets the floods run in, so that nothing crosses
+// between fields), which makes two words of five; at 19x19 every flood has its own word, and a word no board of the wavefront
+// needs any more is left out.  Liberty counts are fields of ten bits in both cases: floods 0-2 in the low half of the sum, 3
+// and 4 in the high half.
+// What bounds a ply of few games is this chain of instructions (one wavefront per SIMD issues one every four cycles).  Against
+// five separate floods with a ballot each: 9x9 x 5001 games, 64 plies in one launch without observation 192 -> 118 us; 9x9 x
+// 4096, one launch per ply 7.4 -> 6.0 us, x 256 6.3 -> 5.4; 19x19 x 1000, draw and ply 9.9 -> 9.2.
+template <int N>
+struct Floods {
+  static constexpr bool PACKED = N == 9;
+  static constexpr int WORDS = PACKED ? 2 : 5;
+  static_assert(N * N < 512, "a count and the bias below fit a field");
+  static constexpr uint32_t kOnes = 1u | (1u << 10) | (1u << 20);
+  static __device__ __forceinline__ void spread(uint32_t (&w)[WORDS], uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, uint32_t x4) {
+    if constexpr (PACKED) { w[0] = x0 | (x1 << 10) | (x2 << 20); w[1] = x3 | (x4 << 10); }
+    else { w[0] = x0; w[1] = x1; w[2] = x2; w[3] = x3; w[4] = x4; }
+  }
+  static __device__ __forceinline__ uint64_t count(const uint32_t (&w)[WORDS]) {
+    uint32_t lo, hi;
+    if constexpr (PACKED) {
+      lo = __popc(w[0] & 0x3FFu) + (__popc(w[0] & (0x3FFu << 10)) << 10) + (__popc(w[0] >> 20) << 20);
+      hi = __popc(w[1] & 0x3FFu) + (__popc(w[1] >> 10) << 10);
+    } else {
+      lo = __popc(w[0]) + (__popc(w[1]) << 10) + (__popc(w[2]) << 20);
+      hi = __popc(w[3]) + (__popc(w[4]) << 10);
+    }
+    return (uint64_t)lo | ((uint64_t)hi << 32);
+  }
+  static __device__ __forceinline__ uint32_t all(uint32_t x, int bit) { return (uint32_t)((int32_t)(x << (31 - bit)) >> 31); }   // every bit = bit `bit` of x
+  // bit 9 of every field whose value is at least `least` (1 or 2)
+  static __device__ __forceinline__ uint32_t reached(uint32_t fields, uint32_t least) { return (fields + kOnes * (512u - least)) & (kOnes << 9); }
+  // takes the floods that have seen two liberties out of the sets of stones just reached
+  static __device__ __forceinline__ void undecided(uint32_t (&open)[WORDS], uint64_t libs) {
+    const uint32_t lo = reached((uint32_t)libs, 2u), hi = reached((uint32_t)(libs >> 32), 2u);
+    if constexpr (PACKED) {
+      open[0] &= ~(lo - (lo >> 9)); open[1] &= ~(hi - (hi >> 9));
+    } else {
+      open[0] &= ~all(lo, 9); open[1] &= ~all(lo, 19); open[2] &= ~all(lo, 29); open[3] &= ~all(hi, 9); open[4] &= ~all(hi, 19);
+    }
+  }
+  // adds the chains with exactly one liberty to the atari sets
+  static __device__ __forceinline__ void atari(const uint32_t (&F)[WORDS], uint64_t libs, uint32_t& aown, uint32_t& aopp) {
+    const uint32_t lo = reached((uint32_t)libs ^ kOnes, 1u) ^ (kOnes << 9), hi = reached((uint32_t)(libs >> 32) ^ kOnes, 1u) ^ (kOnes << 9);
+    if constexpr (PACKED) {
+      const uint32_t a = F[0] & (lo - (lo >> 9)), b = F[1] & (hi - (hi >> 9));
+      aown |= a & 0x1FFu;
+      aopp |= ((a >> 10) & 0x1FFu) | (a >> 20) | (b & 0x1FFu) | (b >> 10);
+    } else {
+      aown |= F[0] & all(lo, 9);
+      aopp |= (F[1] & all(lo, 19)) | (F[2] & all(lo, 29)) | (F[3] & all(hi, 9)) | (F[4] & all(hi, 19));
+    }
+  }
+};
+
 // a3-a8 for every board of the wavefront; registers in, registers out.
 // Out: rewards by player id, `flag` = the terminated output (game ended in this ply, or had ended before),
 // `captured` = the stones this ply removed, `reset` = the board was re-initialised by auto-reset.
 // `hdirty` = which planes of the row record hold a changed history dword (see push_history; all ones after a reset).
 template <int N>
 __device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m, const Rules& cfg, const Move& mv, float& rew0, float& rew1,
-                                           bool& flag, uint32_t& captured, bool& reset, uint32_t& hdirty) {
+                                           bool& flag, uint32_t& captured, bool& reset, uint32_t& hdirty, uint64_t* tally) {
   using G = Geo<N>;
   const bool playing = mv.playing, is_pass = mv.is_pass, illegal = mv.illegal, frozen = mv.frozen;
   const int pr = mv.pr, pc = mv.pc;
@@ -526,67 +604,62 @@ __device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m,
     // opposing chains in atari that touch the new stone lose their last liberty
     int ko_new = -1;
     const uint32_t capseed = nb & aopp;
+    uint32_t released = nb;   // own chains in atari next to these points stop being that: the new stone joins them, or they gain a liberty
+    unsigned round = 0u;      // tally round in use
+    tally_clear(tally, L.lane);
     if (__ballot(capseed != 0u) != 0ull) {
       const uint32_t cap = flood_plain(capseed, aopp);
       if (playing) captured = cap;
       opp &= ~cap; aopp &= ~cap;
-      // own chains in atari next to the vacated points gain a liberty
-      const uint32_t un = flood_plain(aown & dilate(cap), aown);
-      aown &= ~un;
-      // simple ko: exactly one stone taken by a stone without friends whose only liberty is the vacated point
-      bool cap1, cap2, lib1, lib2;
-      board_count(cap, L.seglo, L.seghi, cap1, cap2);
-      board_count(nb & L.full & ~(own | opp), L.seglo, L.seghi, lib1, lib2);
-      const bool lone = !board_any(friends != 0u, L.seglo, L.seghi);
-      const bool cN = board_any((cap & nbN) != 0u, L.seglo, L.seghi), cS = board_any((cap & nbS) != 0u, L.seglo, L.seghi);
-      const bool cW = board_any((cap & nbW) != 0u, L.seglo, L.seghi);
-      const int p = pr * N + pc;
-      if (cap1 && lib1 && lone) ko_new = cN ? p - N : cS ? p + N : cW ? p - 1 : p + 1;
+      released |= dilate(cap);
+      // simple ko: exactly one stone taken by a stone without friends whose only liberty is the vacated point.  One tally of the
+      // stones taken, the new stone's friends and liberties, and the points of the neighbours taken.
+      const uint32_t around = (friends | (nb & ~(own | opp))) & L.full;
+      const uint32_t where = capseed ? (uint32_t)(L.r * N + __ffs(capseed) - 1) : 0u;
+      const uint64_t sum = tally_board(tally, round++, L, (uint64_t)(__popc(cap) | (__popc(around) << 16)) | ((uint64_t)where << 32));
+      if ((uint32_t)sum == 0x10001u) ko_new = (int)(sum >> 32);
     }
     const uint32_t E = L.full & ~(own | opp);
-    // own chains in atari that the new stone joins stop being chains of their own
-    const uint32_t clrseed = friends & aown;
+    const uint32_t clrseed = released & aown;
     if (__ballot(clrseed != 0u) != 0ull) aown &= ~flood_plain(clrseed, aown);
-    // Liberty class of the new stone's chain (flood 0, through own stones) and of the surviving opposing
-    // neighbour chains, which lost the liberty just filled (floods 1-4, through opposing stones).  A flood
-    // leaves the race as soon as two liberties are known; one that converges with a single liberty has
-    // found a whole chain in atari.
-    uint32_t F0 = pbit, F1 = nbN & opp, F2 = nbS & opp, F3 = nbW & opp, F4 = nbE & opp;
-    bool run0 = board_any(F0 != 0u, L.seglo, L.seghi), run1 = board_any(F1 != 0u, L.seglo, L.seghi);
-    bool run2 = board_any(F2 != 0u, L.seglo, L.seghi), run3 = board_any(F3 != 0u, L.seglo, L.seghi);
-    bool run4 = board_any(F4 != 0u, L.seglo, L.seghi);
-    bool at0 = false, at1 = false, at2 = false, at3 = false, at4 = false;
-    auto flood_step = [&](uint32_t& F, uint32_t S, bool& run, bool& at, bool first) {
-      if (!first) {   // after the first look, unexamined growth steps precede each examined one
-#ifndef PGXGO_BLIND
-#define PGXGO_BLIND 4
-#endif
+    // Liberty class of the new stone's chain (flood 0, through own stones) and of the surviving opposing neighbour chains,
+    // which lost the liberty just filled (floods 1-4, through opposing stones).  A flood is decided as soon as two
+    // liberties are known; one that converges with a single liberty has found a whole chain in atari.
+    using FL = Floods<N>;
+    uint32_t F[FL::WORDS], S[FL::WORDS], EE[FL::WORDS];
+    FL::spread(F, pbit, nbN & opp, nbS & opp, nbW & opp, nbE & opp);
+    FL::spread(S, own, opp, opp, opp, opp);
+    FL::spread(EE, E, E, E, E, E);
+    uint64_t libs;   // liberties seen per flood, FL::count's fields
+    uint32_t part[FL::WORDS], open[FL::WORDS];
+    bool run[FL::WORDS];   // a flood of this word is under way in some board of the wavefront
 #pragma unroll
-        for (int b_ = 0; b_ < PGXGO_BLIND; ++b_) F |= dilate(F) & S;
-      }
-      const uint32_t D = dilate(F);
-      const uint32_t Gn = F | (D & S);
-      bool one, two;
-      board_count(D & E, L.seglo, L.seghi, one, two);
-      const bool grew = board_any(Gn != F, L.seglo, L.seghi);
-      const bool conv = run && !two && !grew;
-      at = at || (conv && one);
-      run = run && !two && !conv;
-      F = Gn;
-    };
-    bool first = true;
+    for (int k = 0; k < FL::WORDS; ++k) { part[k] = 0u; run[k] = FL::PACKED || __ballot(F[k] != 0u) != 0ull; }
     for (;;) {
-      const uint64_t r0 = __ballot(run0), r1 = __ballot(run1), r2 = __ballot(run2), r3 = __ballot(run3), r4 = __ballot(run4);
-      if ((r0 | r1 | r2 | r3 | r4) == 0ull) break;
-      if (r0 != 0ull) flood_step(F0, own, run0, at0, first);
-      if (r1 != 0ull) flood_step(F1, opp, run1, at1, first);
-      if (r2 != 0ull) flood_step(F2, opp, run2, at2, first);
-      if (r3 != 0ull) flood_step(F3, opp, run3, at3, first);
-      if (r4 != 0ull) flood_step(F4, opp, run4, at4, first);
-      first = false;
+#pragma unroll
+      for (int k = 0; k < FL::WORDS; ++k) {
+        open[k] = 0u;
+        if (!run[k]) continue;
+#pragma unroll
+        for (int i = 0; i < kBlindSteps; ++i) F[k] |= dilate(F[k]) & S[k];
+        const uint32_t D = dilate(F[k]);
+        const uint32_t G_ = F[k] | (D & S[k]);
+        open[k] = G_ ^ F[k];
+        part[k] = D & EE[k];
+        F[k] = G_;
+      }
+      if (round == kTallyRounds) { tally_clear(tally, L.lane); round = 0u; }
+      libs = tally_board(tally, round++, L, FL::count(part));
+      FL::undecided(open, libs);
+      bool any = false;
+      if constexpr (FL::PACKED) any = __ballot((open[0] | open[1]) != 0u) != 0ull;
+      else {
+#pragma unroll
+        for (int k = 0; k < FL::WORDS; ++k) { run[k] = __ballot(open[k] != 0u) != 0ull; any = any || run[k]; }
+      }
+      if (!any) break;
     }
-    aown |= at0 ? F0 : 0u;
-    aopp |= (at1 ? F1 : 0u) | (at2 ? F2 : 0u) | (at3 ? F3 : 0u) | (at4 ? F4 : 0u);
+    FL::atari(F, libs, aown, aopp);
     if (playing) {
       m.ko = ko_new;
       R.bk = wtm0 ? opp : own; R.wt = wtm0 ? own : opp;
@@ -641,18 +714,18 @@ __device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m,
 }
 template <int N>
 __device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m, const Rules& cfg, const Move& mv, float& rew0, float& rew1,
-                                           bool& flag, uint32_t& captured, bool& reset) {
+                                           bool& flag, uint32_t& captured, bool& reset, uint64_t* tally) {
   uint32_t hdirty;
-  apply_move<N>(L, R, m, cfg, mv, rew0, rew1, flag, captured, reset, hdirty);
+  apply_move<N>(L, R, m, cfg, mv, rew0, rew1, flag, captured, reset, hdirty, tally);
 }
 
 template <int N, bool GATE>
 __device__ __forceinline__ void step_core(const Lane<N>& L, Row<N>& R, Meta& m, const Rules& cfg, bool skip, bool want_pass, bool want_point,
-                                          int pr_in, int pc_in, float& rew0, float& rew1, bool& flag) {
+                                          int pr_in, int pc_in, float& rew0, float& rew1, bool& flag, uint64_t* tally) {
   const Move mv = gate_move<N, GATE>(L, R, m, skip, want_pass, want_point, pr_in, pc_in);
   uint32_t captured;
   bool reset;
-  apply_move<N>(L, R, m, cfg, mv, rew0, rew1, flag, captured, reset);
+  apply_move<N>(L, R, m, cfg, mv, rew0, rew1, flag, captured, reset, tally);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -683,6 +756,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(StepArg
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
+  __shared__ uint64_t tally_all[kWavesPerBlock][64];
   __shared__ uint2 lut[256];
   const int wib = wave_in_block();
   const int wave = piece_of_block() * kWavesPerBlock + wib;
@@ -713,7 +787,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(StepArg
   float rew0, rew1;
   bool flag, reset;
   uint32_t captured, hdirty;
-  apply_move<N>(L, R, m, a.rules, mv, rew0, rew1, flag, captured, reset, hdirty);
+  apply_move<N>(L, R, m, a.rules, mv, rew0, rew1, flag, captured, reset, hdirty, tally_all[wib]);
   if (!skip && L.valid && L.r == 0) {
     *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(rew0, rew1);
     a.term[L.b] = (uint8_t)(flag ? 1 : 0);
@@ -1084,7 +1158,7 @@ __device__ __forceinline__ void sk_clear_tables(const Lane<N>& L, bool flagged, 
 template <int N, bool GATE, bool EARLY, class Hook>
 __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& m, SkGame& g, uint32_t& forb, const Rules& rules, bool skip, bool want_pass,
                                              bool want_point, int pr_in, int pc_in, const uint2* tab_r, uint2* tab_w, uint2* zt, int game,
-                                             uint32_t* scratch, float& rew0, float& rew1, bool& flag, bool pre_a_loaded, const SkWin& pre_a,
+                                             uint32_t* scratch, uint64_t* tally, float& rew0, float& rew1, bool& flag, bool pre_a_loaded, const SkWin& pre_a,
                                              Hook&& board_final) {   // board_final(hdirty): hdirty as from apply_move
   const int c = m.wtm, own = c ? g.nw : g.nb, opp = c ? g.nb : g.nw;
   Move mv = gate_move<N, GATE>(L, R, m, skip, want_pass, want_point, pr_in, pc_in);
@@ -1106,7 +1180,7 @@ __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& 
   bool reset;
   uint32_t captured;
   uint32_t hdirty;
-  apply_move<N>(L, R, m, r0, mv, rew0, rew1, flag, captured, reset, hdirty);
+  apply_move<N>(L, R, m, r0, mv, rew0, rew1, flag, captured, reset, hdirty, tally);
   const bool do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
   if (do_reset) { reset_board<N>(L, R, m, rules.seed); hdirty = ~0u; }   // a board that is reset takes no part in the table work below
   if constexpr (EARLY) {
@@ -1142,7 +1216,7 @@ __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& 
 template <int N, bool GATE, bool POST, class Hook, class Restore>
 __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, Meta& m, SkGame& g, const Rules& rules, bool skip, bool want_pass,
                                                   bool want_point, int pr_in, int pc_in, const uint2* tab_r, uint2* tab_w, uint2* zt, int game,
-                                                  uint32_t* scratch, float& rew0, float& rew1, bool& flag, const SkWin& pre, Hook&& board_final,
+                                                  uint32_t* scratch, uint64_t* tally, float& rew0, float& rew1, bool& flag, const SkWin& pre, Hook&& board_final,
                                                   Restore&& restore) {
   const int c = m.wtm, own1 = (c ? g.nw : g.nb) + 1;
   const uint64_t seg = ((uint64_t)L.seghi << 32) | L.seglo;
@@ -1152,7 +1226,7 @@ __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, M
   bool reset, do_reset = false;
   uint32_t captured = 0u, hdirty = 0u;
   if constexpr (POST) {
-    apply_move<N>(L, R, m, r0, mv, rew0, rew1, flag, captured, reset, hdirty);
+    apply_move<N>(L, R, m, r0, mv, rew0, rew1, flag, captured, reset, hdirty, tally);
     do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
     if (do_reset) { reset_board<N>(L, R, m, rules.seed); hdirty = ~0u; }
     // The window has to be in registers before the caller's stores are issued: loads and stores share one counter.
@@ -1184,7 +1258,7 @@ __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, M
   const bool repeats = mv.playing && hit;
   if (repeats) { mv.playing = false; mv.illegal = true; mv.pr = -100; mv.pc = 0; }
   if constexpr (!POST) {
-    apply_move<N>(L, R, m, r0, mv, rew0, rew1, flag, captured, reset, hdirty);
+    apply_move<N>(L, R, m, r0, mv, rew0, rew1, flag, captured, reset, hdirty, tally);
     do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
     if (do_reset) { reset_board<N>(L, R, m, rules.seed); hdirty = ~0u; }
     board_final(hdirty);
@@ -1195,7 +1269,7 @@ __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, M
     float a0, a1;
     bool f2, rs2;
     uint32_t cap2, hd2;
-    apply_move<N>(L, R, m, r0, again, a0, a1, f2, cap2, rs2, hd2);
+    apply_move<N>(L, R, m, r0, again, a0, a1, f2, cap2, rs2, hd2, tally);
     if (repeats) {
       rew0 = a0; rew1 = a1; flag = f2;
       do_reset = rules.auto_reset != 0;   // the illegal action has ended the game
@@ -1224,6 +1298,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
+  __shared__ uint64_t tally_all[kWavesPerBlock][64];
   __shared__ uint2 lut[256];
   const int wib = wave_in_block();
   const int wave = piece_of_block() * kWavesPerBlock + wib;
@@ -1262,7 +1337,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   };
   if constexpr (MODE == 1) {
     const SkWin pre = sk_window_play<N>(L, tab, g, m, !skip);
-    sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], rew0, rew1, flag, pre,
+    sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag, pre,
                                      board_final, [&](Row<N>& Rr, Meta& mr, bool which) {   // the state is stored below: memory still holds it as loaded
                                        Row<N> T;
                                        load_row<N>(a.planes, rows_total, L, T);
@@ -1271,7 +1346,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
     store_state();
   } else {
     forb = sk_forb_loaded<N>(L, tab, g, R, m, none, lds_mask_all[wib]);
-    sk_step_core<N, true, false>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], rew0, rew1, flag,
+    sk_step_core<N, true, false>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag,
                                  false, none, board_final);
     g.fw = sk_forb_word<N>(L, forb);
   }
@@ -1368,6 +1443,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
+  __shared__ uint64_t tally_all[kWavesPerBlock][64];
   __shared__ uint2 lut[256];
   const int wib = wave_in_block();
   const int wave = piece_of_block() * kWavesPerBlock + wib;
@@ -1397,7 +1473,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
     const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, pr, pc);
     bool reset;
     uint32_t captured;
-    apply_move<N>(L, R, m, a.rules, mv, rew0, rew1, flag, captured, reset);
+    apply_move<N>(L, R, m, a.rules, mv, rew0, rew1, flag, captured, reset, tally_all[wib]);
   } else {
     const int sslot = L.boardok ? src : 0, dslot = L.boardok ? dst : 0;
     SkGame g = L.boardok ? sk_unpack(a.zcur[sslot]) : sk_fresh();
@@ -1415,7 +1491,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
     auto board_final = [&](uint32_t) { if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, a.n, a.obs, a.obs_pitch, lds_obs_all[wib], lut); };
     if constexpr (SK == 1) {
       const SkWin pre = sk_window_play<N>(L, tab_r, g, m, !skip);
-      sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], rew0, rew1, flag, pre,
+      sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag, pre,
                                        board_final, [&](Row<N>& Rr, Meta& mr, bool which) {   // the source slot still holds the state as loaded
                                          Lane<N> Ls = L;
                                          Ls.slot = src;
@@ -1425,7 +1501,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
                                        });
     } else {
       forb = sk_forb_loaded<N>(L, tab_r, g, R, m, none, lds_mask_all[wib]);
-      sk_step_core<N, true, true>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], rew0, rew1, flag,
+      sk_step_core<N, true, true>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag,
                                   false, none, board_final);
       g.fw = sk_forb_word<N>(L, forb);
     }
@@ -1478,6 +1554,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
+  __shared__ uint64_t tally_all[kWavesPerBlock][64];
   __shared__ uint2 lut[256];
   fill_spread_table(lut);
   const int wib = wave_in_block();
@@ -1515,7 +1592,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
     float rew0, rew1;
     bool flag;
     if constexpr (!SK) {
-      step_core<N, false>(L, R, m, a.rules, skip, d.pass, d.point, d.pr, d.pc, rew0, rew1, flag);
+      step_core<N, false>(L, R, m, a.rules, skip, d.pass, d.point, d.pr, d.pc, rew0, rew1, flag, tally_all[wib]);
       legal = legal_row<N>(L, R, m.wtm, m.ko);
     } else {
       SkWin none;
@@ -1525,11 +1602,11 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
         if (obs_t) emit_obs<N, TIGHT, kStoreThroughWhole>(L, R.h, m.wtm, wave, a.B, obs_t, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
       };
       if constexpr (SK == 1) {
-        sk_step_core_play<N, false, false>(L, R, m, g, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], rew0, rew1, flag,
+        sk_step_core_play<N, false, false>(L, R, m, g, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag,
                                            ahead, board_final, [](Row<N>&, Meta&, bool) {});
         ahead = sk_window_play<N>(L, tab, g, m, L.boardok);
       } else {
-        sk_step_core<N, false, true>(L, R, m, g, forb, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], rew0, rew1, flag, false,
+        sk_step_core<N, false, true>(L, R, m, g, forb, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag, false,
                                      none, board_final);
       }
       legal = legal_row<N>(L, R, m.wtm, m.ko) & ~(SK == 2 ? forb : 0u);

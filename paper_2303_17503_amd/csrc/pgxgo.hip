@@ -1546,12 +1546,19 @@ struct RolloutArgs {
   uint2* zt;            // positional superko (SK kernels): per-game tables, per-game current keys, mode 1 / 2
   uint4* zcur;
   int sk_mode;
+  PaceArgs pace;
 };
 
-// SK: 0 = simple ko only, 1 / 2 = positional superko at play time / in the legal mask
-template <int N, bool TIGHT, int SK>
+// The rate that the slots of a paced rollout are laid out for (us for 16 plies of 19x19 x 16384 games, recorded, with 6.0 / 6.2 / 6.3 /
+// 6.4 / 6.6 TB/s: 294 / 285 / 281 / 279 / 299; a step below the best, since above it the gain is soon lost)
+constexpr double kPaceBytesPerSecond = 6.3e12;
+
+// SK: 0 = simple ko only, 1 / 2 = positional superko at play time / in the legal mask.  PACED: recordings that go to DRAM, see Pace;
+// their stores carry the non-temporal hint as well (16 plies of 19x19 x 16384 games at 6.2 TB/s: 286 us with it, 344 without).
+template <int N, bool TIGHT, int SK, bool PACED>
 __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_kernel(RolloutArgs a) {
   using G = Geo<N>;
+  constexpr int ST = PACED ? kStoreStreamWhole : kStoreThroughWhole;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
   __shared__ uint64_t tally_all[kWavesPerBlock][64];
@@ -1584,6 +1591,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
   ahead.home = ~0u; ahead.e = make_uint2(1u, 0u);
   if constexpr (SK == 1) ahead = sk_window_play<N>(L, tab, g, m, L.boardok);
   int slice = 0;
+  Pace pace(PACED, a.pace, (blockIdx.x >> 3) * kWavesPerBlock + wib, (gridDim.x >> 3) * kWavesPerBlock);
   for (int i = 0; i < a.steps; ++i) {   // the same trip count for every wavefront
     const uint32_t t = a.t0 + (uint32_t)i;
     const bool wait = (int64_t)t < start;
@@ -1599,7 +1607,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
       none.home = ~0u; none.e = make_uint2(1u, 0u);
       uint8_t* const obs_t = a.obs ? a.obs + (size_t)slice * a.B * a.obs_pitch : nullptr;
       auto board_final = [&](uint32_t) {
-        if (obs_t) emit_obs<N, TIGHT, kStoreThroughWhole>(L, R.h, m.wtm, wave, a.B, obs_t, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
+        if constexpr (PACED) pace.wait();
+        if (obs_t) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, a.B, obs_t, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
       };
       if constexpr (SK == 1) {
         sk_step_core_play<N, false, false>(L, R, m, g, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag,
@@ -1619,7 +1628,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
       if (a.rew) *(float2*)(a.rew + 2 * e) = skip ? make_float2(0.f, 0.f) : make_float2(rew0, rew1);
       if (a.term) a.term[e] = (uint8_t)((!skip && flag) ? 1 : 0);
     }
-    emit_outputs<N, TIGHT, kStoreThroughWhole>(L, R, legal, m.wtm, wave, a.B, a.mask ? a.mask + sb * a.mask_pitch : nullptr, a.mask_pitch,
+    if constexpr (PACED && !SK) pace.wait();
+    emit_outputs<N, TIGHT, ST>(L, R, legal, m.wtm, wave, a.B, a.mask ? a.mask + sb * a.mask_pitch : nullptr, a.mask_pitch,
                     (!SK && a.obs) ? a.obs + sb * a.obs_pitch : nullptr, a.obs_pitch, lds_mask_all[wib], lds_obs_all[wib], lut, a.wb);
     wave_lds_fence();
     slice = slice + 1 == a.slices ? 0 : slice + 1;
@@ -2017,15 +2027,26 @@ int launch_random(pgxgo_ctx* h, uint32_t seed, uint32_t t, const int32_t* start_
 }
 
 template <int N>
-int launch_rollout(pgxgo_ctx* h, const RolloutArgs& a) {
+int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
   const dim3 grid(blocks_for_wb(h->B, h->wb)), block(64 * kWavesPerBlock);
   const bool tight = tight_pitches<N>(h), sk = h->zt != nullptr;
-  if (tight && sk && h->sk_mode == 1) hipLaunchKernelGGL((go_rollout_kernel<N, true, 1>), grid, block, 0, h->stream, a);
-  else if (tight && sk) hipLaunchKernelGGL((go_rollout_kernel<N, true, 2>), grid, block, 0, h->stream, a);
-  else if (tight) hipLaunchKernelGGL((go_rollout_kernel<N, true, 0>), grid, block, 0, h->stream, a);
-  else if (sk && h->sk_mode == 1) hipLaunchKernelGGL((go_rollout_kernel<N, false, 1>), grid, block, 0, h->stream, a);
-  else if (sk) hipLaunchKernelGGL((go_rollout_kernel<N, false, 2>), grid, block, 0, h->stream, a);
-  else hipLaunchKernelGGL((go_rollout_kernel<N, false, 0>), grid, block, 0, h->stream, a);
+  // bytes written per game and ply: the whole record with the dense and the line-padded pitches, else without the pad
+  const int64_t mask_bytes = tight ? h->mask_pitch : Geo<N>::A, obs_bytes = tight ? h->obs_pitch : Geo<N>::OBS;
+  const double game_bytes = (double)((a.mask ? mask_bytes : 0) + (a.obs ? obs_bytes : 0));
+  auto go = [&](auto tight_c, auto sk_c) {
+    constexpr bool T = decltype(tight_c)::value;
+    constexpr int M = decltype(sk_c)::value;
+    a.pace = pace_args<go_rollout_kernel<N, T, M, true>>(h->B, h->wb, game_bytes, a.slices, kPaceBytesPerSecond, kWavesPerBlock);
+    if (a.pace.ply) hipLaunchKernelGGL((go_rollout_kernel<N, T, M, true>), grid, block, 0, h->stream, a);
+    else hipLaunchKernelGGL((go_rollout_kernel<N, T, M, false>), grid, block, 0, h->stream, a);
+  };
+  auto by_mode = [&](auto tight_c) {
+    if (!sk) go(tight_c, std::integral_constant<int, 0>{});
+    else if (h->sk_mode == 1) go(tight_c, std::integral_constant<int, 1>{});
+    else go(tight_c, std::integral_constant<int, 2>{});
+  };
+  if (tight) by_mode(std::true_type{});
+  else by_mode(std::false_type{});
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
 }

@@ -476,6 +476,7 @@ __device__ __forceinline__ B128 lane_legal(const B128& bk, const B128& wt, const
 }
 
 // a6 / a7: legal mask [122] and observation [11][11][4] of the 64 boards of the wavefront (nb real ones from board b0 on)
+template <int ST = kStoreThrough>
 __device__ __forceinline__ void lane_emit(const B128& bk, const B128& wt, const Meta& m, const B128& legal, bool ok, int lane, int b0, int nb,
                                           uint8_t* mask, uint8_t* obs, uint32_t* lds_mask, uint32_t* lds_obs, const uint2* lut, const uint32_t* lut4) {
   {
@@ -505,8 +506,8 @@ __device__ __forceinline__ void lane_emit(const B128& bk, const B128& wt, const 
     stream_put<16, 1, 14>(lds_obs, O, head + (uint32_t)(OBS * lane));
   }
   wave_lds_fence();
-  if (mask) emit_bytes<64 * A, kStoreThrough>(lds_mask, lut, mask + (size_t)b0 * A, (uint32_t)(nb * A), lane);
-  if (obs) emit_bytes<64 * OBS, kStoreThrough>(lds_obs, lut, obs + (size_t)b0 * OBS, (uint32_t)(nb * OBS), lane);
+  if (mask) emit_bytes<64 * A, ST>(lds_mask, lut, mask + (size_t)b0 * A, (uint32_t)(nb * A), lane);
+  if (obs) emit_bytes<64 * OBS, ST>(lds_obs, lut, obs + (size_t)b0 * OBS, (uint32_t)(nb * OBS), lane);
   wave_lds_fence();
 }
 
@@ -593,6 +594,7 @@ struct RolloutArgs {
   uint8_t* term;           // [slices][B] or null
   uint8_t* mask;           // [slices][B][A] or null
   uint8_t* obs;            // [slices][B][OBS] or null
+  PaceArgs pace;           // board-per-lane kernel
 };
 
 __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_rollout_kernel(RolloutArgs a) {
@@ -629,7 +631,11 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_rollout_kernel(Rollou
   if (L.valid && L.r == 0) a.meta[L.b] = pack_meta(m);
 }
 
+// The rate that the slots of a paced rollout are laid out for (us for 8 plies of 262144 games, recorded, with 6.4 / 6.5 / 6.6 / 6.7 /
+// 6.8 TB/s: 209 / 207 / 205 / 206 / 212, without slots 246; whole lines only, hence faster than Go's ragged runs)
+constexpr double kPaceBytesPerSecond = 6.55e12;
 // the same with a board per lane (very large batches): state of 64 boards in the registers of one wavefront
+template <bool PACED>
 __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_rollout_lane_kernel(RolloutArgs a) {
   __shared__ uint2 lut[256];
   __shared__ uint32_t lut4[256];
@@ -652,6 +658,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_rollout_lane_kernel(R
   B128 bk, wt;
   rows_to_sets(row, bk, wt);
   B128 legal = lane_legal(bk, wt, m);
+  Pace pace(PACED, a.pace, (blockIdx.x >> 3) * kWavesPerBlock + wib, (gridDim.x >> 3) * kWavesPerBlock);
   int slice = 0;
   for (int i = 0; i < a.steps; ++i) {   // the same trip count for every wavefront
     const uint32_t t = a.t0 + (uint32_t)i;
@@ -666,7 +673,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_rollout_lane_kernel(R
       if (a.rew) *(float2*)(a.rew + 2 * e) = ply.skip ? make_float2(0.f, 0.f) : make_float2(ply.rew0, ply.rew1);
       if (a.term) a.term[e] = (uint8_t)((!ply.skip && (ply.ended || ply.frozen)) ? 1 : 0);
     }
-    lane_emit(bk, wt, m, legal, ok, lane, b0, nb, a.mask ? a.mask + sb * A : nullptr, a.obs ? a.obs + sb * OBS : nullptr, lds_mask[wib], lds_obs[wib], lut,
+    if constexpr (PACED) pace.wait();
+    lane_emit<PACED ? kStoreStreamThrough : kStoreThrough>(bk, wt, m, legal, ok, lane, b0, nb, a.mask ? a.mask + sb * A : nullptr, a.obs ? a.obs + sb * OBS : nullptr, lds_mask[wib], lds_obs[wib], lut,
               lut4);
     slice = slice + 1 == a.slices ? 0 : slice + 1;
   }
@@ -933,8 +941,11 @@ int pgxhex_rollout(pgxhex_t h, int32_t steps, int32_t slices, uint32_t seed, uin
   a.rows = h->rows; a.meta = h->meta; a.B = h->B; a.seed_env = h->seed; a.auto_reset = h->auto_reset;
   a.steps = steps; a.slices = slices; a.seed = seed; a.t0 = t0; a.start_t = start_t_dev;
   a.actions = actions_dev; a.rew = rewards_dev; a.term = terminated_dev; a.mask = mask_dev; a.obs = obs_dev;
-  if (board_per_lane(h, true))
-    hipLaunchKernelGGL(hex_rollout_lane_kernel, dim3(lane_blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
+  if (board_per_lane(h, true)) {
+    a.pace = pace_args<hex_rollout_lane_kernel<true>>(h->B, 64, (mask_dev ? A : 0) + (obs_dev ? OBS : 0), slices, kPaceBytesPerSecond, kWavesPerBlock);
+    if (a.pace.ply) hipLaunchKernelGGL(hex_rollout_lane_kernel<true>, dim3(lane_blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
+    else hipLaunchKernelGGL(hex_rollout_lane_kernel<false>, dim3(lane_blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
+  }
   else hipLaunchKernelGGL(hex_rollout_kernel, dim3(blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
   HIPCHK(hipGetLastError());
   return PGXHEX_OK;

@@ -36,6 +36,68 @@ __device__ __forceinline__ int wave_in_block() { return __builtin_amdgcn_readfir
 __device__ __forceinline__ int piece_of_block() { return (int)(blockIdx.x & 7u) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3); }
 
 // ------------------------------------------------------------------------------------------------
+// Pacing of recorded rollouts.  A rollout whose plies go to fresh memory writes at the rate of DRAM, and DRAM is faster when
+// the lines being written at any one time lie close together: thousands of wavefronts that each write their own 18 to 31 KB run
+// whenever they have one reach 5.0 TB/s, the same runs written in the order of their addresses 6.3 TB/s.  So every wavefront
+// gets a time slot per ply: wavefront i of the n that share an eighth of the batch (piece_of_block) starts its stores of ply s no
+// earlier than (s + i / n) * T after it began, T being the time in which memory takes one ply's outputs.  Nothing but time
+// depends on it: a wavefront that is late goes ahead at once, and the wait ends by the clock.
+// Measured with a skeleton of the kernel's stores, 16 slices of 100 MB, 5 us of other work per ply: 337 us without slots,
+// 331 / 259 / 284 / 309 us with T for 7.2 / 6.5 / 5.9 / 5.4 TB/s; staggering only the first ply gains nothing.
+// ------------------------------------------------------------------------------------------------
+// A batch of more wavefronts than the machine holds at once runs in generations: those of a later one start one after the
+// other as their predecessors end, in step already, and share the time of as many as they are.
+struct PaceArgs {
+  uint32_t ply;    // T of a full generation (or of the whole batch if that is smaller), in 1/256 ticks of the constant 100 MHz clock; 0: not paced
+  uint32_t held;   // wavefronts of an eighth that the machine holds at once
+};
+struct Pace {
+  int64_t slot;      // when this wavefront may write its next ply, in 1/256 ticks of the constant 100 MHz clock
+  uint32_t ply;      // T in the same unit
+  __device__ __forceinline__ static int64_t now() { return (int64_t)(__builtin_amdgcn_s_memrealtime() << 8); }
+  // index: this wavefront among the `eighth` wavefronts that write to the same eighth of the batch
+  __device__ __forceinline__ Pace(bool on, PaceArgs a, uint32_t index, uint32_t eighth) : slot(0), ply(a.ply) {
+    if (!on) return;
+    slot = now();
+    if (eighth <= a.held) slot += (int64_t)((uint64_t)ply * index / eighth);
+    else if (index < a.held) slot += (int64_t)((uint64_t)ply * index / a.held);
+    else if (index >= eighth / a.held * a.held) ply = (uint32_t)((uint64_t)ply * (eighth % a.held) / a.held);
+  }
+  __device__ __forceinline__ void wait() {
+    for (int i = 0; i < 8192 && now() < slot; ++i) __builtin_amdgcn_s_sleep(2);   // 128 cycles a turn
+    slot += ply;
+  }
+};
+// PaceArgs::held of a kernel (256 compute units; the kernel's registers and LDS decide); looked up once, 0 = unknown
+template <auto KERNEL>
+inline uint32_t waves_held_per_eighth(int waves_per_block) {
+  static const int blocks = [&] {
+    int n = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)KERNEL, 64 * waves_per_block, 0) == hipSuccess ? n : 0;
+  }();
+  return (uint32_t)(blocks * 32 * waves_per_block);
+}
+// T for a rollout over `slices` output slices of which the wavefronts that are on the machine together write `ply_bytes` bytes per
+// ply; 0: no pacing.  The recording has to outgrow the 256 MB memory-side cache (19x19 x 16384 games, 107 MB per ply, without /
+// with slots: 2 slices 38.6 / 44.3 us, 3 slices 65.2 / 61.8, 16 slices 358 / 281), and a ply has to hold enough bytes for memory
+// and not the plies' own instructions to set the pace (20 MB of 19x19 x 3000 games: 271 / 284 us for 64 plies; 29 MB of
+// 9x9 x 20000: 282 / 206 for 40; 18 MB of Hex x 30000: 359 / 349 for 64).
+inline uint32_t pace_ticks(double ply_bytes, int slices, double bytes_per_second) {
+  constexpr double kMB = 1048576.0;
+  if (slices < 2 || ply_bytes * slices < 280.0 * kMB || ply_bytes < 23.0 * kMB) return 0u;
+  return (uint32_t)(ply_bytes * (256.0 * 1e8 / bytes_per_second));
+}
+// game_bytes: bytes per game and ply, wb: games per wavefront
+template <auto KERNEL>
+inline PaceArgs pace_args(int B, int wb, double game_bytes, int slices, double bytes_per_second, int waves_per_block) {
+  PaceArgs p;
+  p.held = waves_held_per_eighth<KERNEL>(waves_per_block);
+  const double together = 8.0 * p.held * wb;
+  p.ply = pace_ticks((B < together ? B : together) * game_bytes, slices, bytes_per_second);
+  return p;
+}
+
+// ------------------------------------------------------------------------------------------------
 // cross-lane primitives.  All of them must be called with every lane of the wavefront active.
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t from_lane_below(uint32_t x) {  // lane i receives lane i-1, lane 0 receives 0

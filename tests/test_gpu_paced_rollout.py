@@ -1,0 +1,55 @@
+"""Recorded rollouts large enough to be written in time slots (recordings that outgrow the memory-side cache): every slice equals
+what the same plies give one launch each, for dense, line-padded and other pitches, with the repetition rule, and for more games
+than the machine holds at once."""
+import pytest
+import torch
+
+import paper_2303_17503_amd as pg
+
+pytestmark = pytest.mark.gpu
+
+
+def check(make, slices, seed, mask_of, obs_of):
+    rec, one = make(), make()
+    B = rec.B
+    new = lambda *shape, dtype=torch.uint8: torch.zeros(*shape, dtype=dtype, device="cuda")  # noqa: E731
+    mask, obs = new(slices, B, mask_of(rec)), new(slices, B, obs_of(rec))
+    rew, term, act = new(slices, B, 2, dtype=torch.float32), new(slices, B), new(slices, B, dtype=torch.int32)
+    m1, o1, r1, t1, a1 = new(1, B, mask_of(rec)), new(1, B, obs_of(rec)), new(1, B, 2, dtype=torch.float32), new(1, B), new(1, B, dtype=torch.int32)
+    for env in (rec, one):
+        env.rollout(70, seed, 0)
+    for _ in range(2):   # the second launch writes over the first one's slices
+        t = 70 + _ * slices
+        rec.rollout(slices, seed, t, slices=slices, actions=act, rewards=rew, terminated=term, mask=mask, obs=obs)
+        for i in range(slices):
+            one.rollout(1, seed, t + i, actions=a1, rewards=r1, terminated=t1, mask=m1, obs=o1)
+            for name, x, y in (("mask", mask, m1), ("obs", obs, o1), ("rewards", rew, r1), ("terminated", term, t1), ("actions", act, a1)):
+                assert torch.equal(x[i], y[0]), (name, t, i)
+    a, b = rec.export_state(), one.export_state()
+    for k in a:
+        assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("N,B,slices,superko,more", [
+    (9, 17001, 13, 0, {}),
+    (9, 17001, 13, 0, {"obs_pitch": 1400, "mask_pitch": 90}),
+    (9, 17001, 13, 2, {}),
+    (9, 17001, 13, 1, {"obs_pitch": 1379}),
+    (19, 5003, 10, 0, {"line_padded": True}),
+    (19, 5003, 10, 1, {}),
+    (19, 5003, 10, 2, {"mask_pitch": 363}),
+    (19, 19001, 3, 0, {}),      # more games than the machine holds at once
+    (9, 52001, 4, 0, {}),
+])
+def test_go(N, B, slices, superko, more):
+    def make():
+        env = pg.GoEnv(B, N, seed=4, auto_reset=True, **more)
+        if superko:
+            env.enable_superko(superko)
+        return env
+    check(make, slices, 11, lambda e: e.mask_pitch, lambda e: e.obs_pitch)
+
+
+@pytest.mark.parametrize("B,slices", [(45001, 12), (470003, 2)])
+def test_hex(B, slices):
+    check(lambda: pg.HexEnv(B, seed=4, auto_reset=True), slices, 11, lambda e: e.A, lambda e: e.OBS)

@@ -13,6 +13,7 @@ def build(verbose: bool = False) -> str:
     cmd = [
         HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+        "-mllvm", "-amdgpu-kernarg-preload-count=16",   # leading kernel arguments in scalar registers (wave_common.hpp)
         "-Wall", "-Wno-unused-command-line-argument",
         "-I", os.path.join(ROOT, "include"), "-o", LIB, *SRCS,
     ]

@@ -61,10 +61,7 @@ thread_local int g_last_hip = 0;
     }                                                  \
   } while (0)
 
-#ifndef PGXGO_WAVES_PER_BLOCK
-#define PGXGO_WAVES_PER_BLOCK 4
-#endif
-constexpr int kWavesPerBlock = PGXGO_WAVES_PER_BLOCK;   // wavefronts never synchronise with each other; this only shapes the launch
+constexpr int kWavesPerBlock = kBlockThreads / 64;   // wavefronts never synchronise with each other; this only shapes the launch
 
 
 // ------------------------------------------------------------------------------------------------
@@ -731,48 +728,45 @@ __device__ __forceinline__ void step_core(const Lane<N>& L, Row<N>& R, Meta& m, 
 // ------------------------------------------------------------------------------------------------
 // the step kernel: one launch = one ply of every environment
 // ------------------------------------------------------------------------------------------------
-struct StepArgs {
-  uint4* planes;
-  uint4* meta;
-  const int32_t* actions;
+struct StepArgs {            // what is not needed before the first loads
   float* rew;
   uint8_t* term;
   uint8_t* mask;
   uint8_t* obs;
   int64_t mask_pitch, obs_pitch;
-  int B;
-  int wb;                    // boards per wavefront of this launch
   int store_kind;            // kind of the output stores, by the bytes the launch writes (store_kind_for)
   int sparse_store;
   Rules rules;
   // fused sampler
   uint32_t sample_seed, sample_t;
-  const int32_t* start_t;
   int32_t* next_actions;
 };
 
 template <int N, bool SAMPLE, bool TIGHT, int ST>
-__global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(StepArgs a) {
+__global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint4* planes, uint4* meta, const int32_t* actions, const int32_t* start_t, int B,
+                                                                        int wb, uint32_t eighth, StepArgs a) {   // wb: boards per wavefront of this launch
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
   __shared__ uint64_t tally_all[kWavesPerBlock][64];
   __shared__ uint2 lut[256];
   const int wib = wave_in_block();
-  const int wave = piece_of_block() * kWavesPerBlock + wib;
-  const Lane<N> L(wave, threadIdx.x & 63, a.B, a.wb);   // in a wavefront beyond the batch no lane is valid
-  const size_t rows_total = (size_t)a.B * N;
+  const int wave = piece_of_block(eighth) * kWavesPerBlock + wib;
+  const Lane<N> L(wave, threadIdx.x & 63, B, wb);   // in a wavefront beyond the batch no lane is valid
+  const size_t rows_total = (size_t)B * N;
 
   // the loads are issued first and fly while the block fills its lookup table
   Row<N> R;
-  load_row<N>(a.planes, rows_total, L, R);
-  const uint4 meta_raw = L.boardok ? a.meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
-  const int act = L.boardok ? a.actions[L.b] : -1;
+  load_row<N>(planes, rows_total, L, R);
+  const uint4 meta_raw = L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
+  const int act = L.boardok ? actions[L.b] : -1;
   // loaded here and not where it is used: a load after the output stores would have to wait for them (one counter);
   // looked at only after the table is filled, so that no wait for a load comes before the barrier
-  const int32_t start_raw = (SAMPLE && L.boardok && a.start_t) ? a.start_t[L.b] : INT32_MIN;
+  const int32_t start_raw = (SAMPLE && L.boardok && start_t) ? start_t[L.b] : INT32_MIN;
+  in_scalar_registers(a.rew, a.term, a.mask, a.obs, a.mask_pitch, a.obs_pitch, a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset);
+  if (SAMPLE) in_scalar_registers(a.sample_seed, a.sample_t, a.next_actions);
   fill_spread_table(lut);
-  if (wave * a.wb >= a.B) return;   // whole wavefront idle; there is no block-wide barrier anywhere below
+  if (wave * wb >= B) return;   // whole wavefront idle; there is no block-wide barrier anywhere below
   const bool wait_start = (int64_t)a.sample_t < (int64_t)held_back(start_raw);
   const RowWords W_loaded = row_words<N>(R);
   Meta m = unpack_meta(meta_raw);
@@ -790,22 +784,22 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(StepArg
   apply_move<N>(L, R, m, a.rules, mv, rew0, rew1, flag, captured, reset, hdirty, tally_all[wib]);
   if (!skip && L.valid && L.r == 0) {
     *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(rew0, rew1);
-    a.term[L.b] = (uint8_t)(flag ? 1 : 0);
+    store_small<ST>(&a.term[L.b], (uint8_t)(flag ? 1 : 0));
   }
 
   // ---- a10 / a9: observation and legal mask of the player now to move ---------------------------------------
-  if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, a.B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
+  if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
   const uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
-  if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, a.B, a.mask, a.mask_pitch, lds_mask_all[wib], lut, a.wb);
+  if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, B, a.mask, a.mask_pitch, lds_mask_all[wib], lut, wb);
 
   // ---- a11: store the state --------------------------------------------------------------------------------
   if (!skip) {
     // Writing only the changed planes pays while state and outputs stay resident in the memory-side cache
     // (partial lines merge there); beyond it partial lines cost a read-modify-write in DRAM and whole rows win.
     // (whole rows written through the L2: 65536 games 87.9 -> 85.5 us per ply; with the non-temporal hint they are slower)
-    if (a.sparse_store) store_row_changed<N>(a.planes, rows_total, L, R, hdirty, W_loaded);
-    else store_row<N, kStoreThrough>(a.planes, rows_total, L, R);
-    if (L.valid && L.r == 0) a.meta[L.b] = pack_meta(m);
+    if (a.sparse_store) store_row_changed<N>(planes, rows_total, L, R, hdirty, W_loaded);
+    else store_row<N, kStoreThrough>(planes, rows_total, L, R);
+    if (L.valid && L.r == 0) meta[L.b] = pack_meta(m);
   }
   if (SAMPLE) {
     const Draw<N> d = draw_action<N>(L, legal, a.sample_seed, a.sample_t, wait_start);
@@ -1294,24 +1288,26 @@ __device__ __forceinline__ SkWin sk_window_play(const Lane<N>& L, const uint2* t
 // One ply with the repetition rule.  Same steps as go_step_kernel.
 // MODE: 1 = the rule is looked at when the move is played, 2 = honoured by the legal mask
 template <int N, bool TIGHT, int ST, int MODE>
-__global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel(StepArgs a, uint2* zt, uint4* zcur) {
+__global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel(uint4* planes, uint4* meta, const int32_t* actions, const int32_t* start_t,
+                                                                                uint4* zcur, int B, int wb, uint32_t eighth, uint2* zt, StepArgs a) {
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
   __shared__ uint64_t tally_all[kWavesPerBlock][64];
   __shared__ uint2 lut[256];
   const int wib = wave_in_block();
-  const int wave = piece_of_block() * kWavesPerBlock + wib;
-  const Lane<N> L(wave, threadIdx.x & 63, a.B, a.wb);
-  const size_t rows_total = (size_t)a.B * N;
+  const int wave = piece_of_block(eighth) * kWavesPerBlock + wib;
+  const Lane<N> L(wave, threadIdx.x & 63, B, wb);
+  const size_t rows_total = (size_t)B * N;
   Row<N> R;
-  load_row<N>(a.planes, rows_total, L, R);
-  const uint4 meta_raw = L.boardok ? a.meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
-  const int act = L.boardok ? a.actions[L.b] : -1;
+  load_row<N>(planes, rows_total, L, R);
+  const uint4 meta_raw = L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
+  const int act = L.boardok ? actions[L.b] : -1;
   const uint4 g_raw = zcur[L.boardok ? L.b : 0];   // (an unconditional load: a conditional one is waited for on the spot)
-  const int32_t start_raw = (a.next_actions && L.boardok && a.start_t) ? a.start_t[L.b] : INT32_MIN;
+  const int32_t start_raw = (a.next_actions && L.boardok && start_t) ? start_t[L.b] : INT32_MIN;
+  in_scalar_registers(a.rew, a.term, a.mask, a.obs, a.mask_pitch, a.obs_pitch, a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset);
   fill_spread_table(lut);   // (nothing loaded above is looked at before this barrier)
-  if (wave * a.wb >= a.B) return;
+  if (wave * wb >= B) return;
   const bool wait_start = (int64_t)a.sample_t < (int64_t)held_back(start_raw);
   SkGame g = L.boardok ? sk_unpack(g_raw) : sk_fresh();
   Meta m = unpack_meta(meta_raw);
@@ -1327,12 +1323,12 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   bool flag;
   auto store_state = [&]() {   // a11 (whole rows: writing only the changed planes gains nothing here)
     if (!skip) {
-      store_row<N>(a.planes, rows_total, L, R);
-      if (L.valid && L.r == 0) a.meta[L.b] = pack_meta(m);
+      store_row<N>(planes, rows_total, L, R);
+      if (L.valid && L.r == 0) meta[L.b] = pack_meta(m);
     }
   };
   auto board_final = [&](uint32_t) {   // a10, a11
-    if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, a.B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
+    if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
     if constexpr (MODE != 1) store_state();
   };
   if constexpr (MODE == 1) {
@@ -1340,7 +1336,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
     sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag, pre,
                                      board_final, [&](Row<N>& Rr, Meta& mr, bool which) {   // the state is stored below: memory still holds it as loaded
                                        Row<N> T;
-                                       load_row<N>(a.planes, rows_total, L, T);
+                                       load_row<N>(planes, rows_total, L, T);
                                        if (which) { Rr = T; mr = unpack_meta(meta_raw); }
                                      });
     store_state();
@@ -1352,11 +1348,11 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   }
   if (!skip && L.valid && L.r == 0) {
     *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(rew0, rew1);
-    a.term[L.b] = (uint8_t)(flag ? 1 : 0);
+    store_small<ST>(&a.term[L.b], (uint8_t)(flag ? 1 : 0));
   }
 
   const uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko) & ~(MODE == 2 ? forb : 0u);
-  if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, a.B, a.mask, a.mask_pitch, lds_mask_all[wib], lut, a.wb);
+  if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, B, a.mask, a.mask_pitch, lds_mask_all[wib], lut, wb);
   if (!skip && L.valid && L.r == 0) zcur[L.b] = sk_pack(g);
   if (a.next_actions) {
     const Draw<N> dr = draw_action<N>(L, legal, a.sample_seed, a.sample_t, wait_start);
@@ -1418,14 +1414,7 @@ __global__ void go_zero_kernel(uint4* p, size_t n16) {
 // the slot kernel (tree search): entry i reads the state of slot src[i], applies actions[i] (all -1 when
 // actions is null: a plain copy) and writes the result to slot dst[i]; outputs go to row i.
 // ------------------------------------------------------------------------------------------------
-struct SlotArgs {
-  uint4* planes;
-  uint4* meta;
-  int pool;             // number of state slots (the handle's batch)
-  int n;                // entries of this call
-  const int32_t* src;
-  const int32_t* dst;
-  const int32_t* actions;
+struct SlotArgs {       // what is not needed before the first loads
   float* rew;           // [n][2] or null
   uint8_t* term;        // [n] or null; 255 marks an entry whose slot index was out of range
   uint8_t* mask;        // [n][mask_pitch] or null
@@ -1439,27 +1428,30 @@ struct SlotArgs {
 
 // SK: the positional-superko rule is on; a game that moves to another slot takes its key table along.
 template <int N, bool TIGHT, int SK, int ST = kStorePlain>
-__global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots_kernel(SlotArgs a) {
+__global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots_kernel(const int32_t* src_slots, const int32_t* dst_slots, const int32_t* actions,
+                                                                                      uint4* planes, uint4* meta, int pool, int n, uint32_t eighth, SlotArgs a) {
+  // pool: number of state slots (the handle's batch), n: entries of this call
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
   __shared__ uint64_t tally_all[kWavesPerBlock][64];
   __shared__ uint2 lut[256];
   const int wib = wave_in_block();
-  const int wave = piece_of_block() * kWavesPerBlock + wib;
-  Lane<N> L(wave, threadIdx.x & 63, a.n);
-  const size_t rows_total = (size_t)a.pool * N;
-  const int src = L.boardok ? a.src[L.b] : 0, dst = L.boardok ? a.dst[L.b] : 0;
-  const bool in_pool = src >= 0 && src < a.pool && dst >= 0 && dst < a.pool;
+  const int wave = piece_of_block(eighth) * kWavesPerBlock + wib;
+  Lane<N> L(wave, threadIdx.x & 63, n);
+  const size_t rows_total = (size_t)pool * N;
+  const int src = L.boardok ? src_slots[L.b] : 0, dst = L.boardok ? dst_slots[L.b] : 0;
+  const bool in_pool = src >= 0 && src < pool && dst >= 0 && dst < pool;
   const bool bad = L.boardok && !in_pool;
   if (bad) { L.boardok = false; L.valid = false; L.full = 0u; }   // the entry becomes inert: no state access, no outputs
   L.slot = src;
   Row<N> R;
-  load_row<N>(a.planes, rows_total, L, R);
-  const uint4 meta_raw = L.boardok ? a.meta[src] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
-  const int act = (L.boardok && a.actions) ? a.actions[L.b] : -1;
+  load_row<N>(planes, rows_total, L, R);
+  const uint4 meta_raw = L.boardok ? meta[src] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
+  const int act = (L.boardok && actions) ? actions[L.b] : -1;
+  in_scalar_registers(a.rew, a.term, a.mask, a.obs, a.mask_pitch, a.obs_pitch, a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset);
   fill_spread_table(lut);
-  if (wave * G::W >= a.n) return;
+  if (wave * G::W >= n) return;
   Meta m = unpack_meta(meta_raw);
   L.slot = dst;   // from here on the board is environment dst (seat draw on reset, state store)
 
@@ -1488,7 +1480,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
     __threadfence();   // the copied tables are in place before entries are added to them or they are cleared
     SkWin none;
     none.home = ~0u; none.e = make_uint2(1u, 0u);
-    auto board_final = [&](uint32_t) { if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, a.n, a.obs, a.obs_pitch, lds_obs_all[wib], lut); };
+    auto board_final = [&](uint32_t) { if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, n, a.obs, a.obs_pitch, lds_obs_all[wib], lut); };
     if constexpr (SK == 1) {
       const SkWin pre = sk_window_play<N>(L, tab_r, g, m, !skip);
       sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag, pre,
@@ -1496,7 +1488,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
                                          Lane<N> Ls = L;
                                          Ls.slot = src;
                                          Row<N> T;
-                                         load_row<N>(a.planes, rows_total, Ls, T);
+                                         load_row<N>(planes, rows_total, Ls, T);
                                          if (which) { Rr = T; mr = unpack_meta(meta_raw); }
                                        });
     } else {
@@ -1508,19 +1500,19 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
     if (L.valid && L.r == 0) a.zcur[dslot] = sk_pack(g);
     if constexpr (SK != 2) forb = 0u;   // the mask shows the simple-ko set unless the rule proper is on
   }
-  if ((threadIdx.x & 63) == L.j * G::STRIDE + 1 && L.j < G::W && L.b < a.n) {   // row-0 lane of the entry, inert or not
-    if (bad) { if (a.term) a.term[L.b] = 255; }
+  if ((threadIdx.x & 63) == L.j * G::STRIDE + 1 && L.j < G::W && L.b < n) {   // row-0 lane of the entry, inert or not
+    if (bad) { if (a.term) store_small<ST>(&a.term[L.b], (uint8_t)255); }
     else {
       // a copied entry (action -1) reports what a skipped step reports for a fresh handle: no reward, and its terminated state
       if (a.rew) *(float2*)(a.rew + 2 * (size_t)L.b) = skip ? make_float2(0.f, 0.f) : make_float2(rew0, rew1);
-      if (a.term) a.term[L.b] = (uint8_t)(skip ? m.term : (flag ? 1 : 0));
+      if (a.term) store_small<ST>(&a.term[L.b], (uint8_t)(skip ? m.term : (flag ? 1 : 0)));
     }
   }
   const uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko) & ~forb;
-  if constexpr (!SK) { if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, a.n, a.obs, a.obs_pitch, lds_obs_all[wib], lut); }
-  if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, a.n, a.mask, a.mask_pitch, lds_mask_all[wib], lut);
-  store_row<N>(a.planes, rows_total, L, R);
-  if (L.valid && L.r == 0) a.meta[dst] = pack_meta(m);
+  if constexpr (!SK) { if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, n, a.obs, a.obs_pitch, lds_obs_all[wib], lut); }
+  if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, n, a.mask, a.mask_pitch, lds_mask_all[wib], lut);
+  store_row<N>(planes, rows_total, L, R);
+  if (L.valid && L.r == 0) meta[dst] = pack_meta(m);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1676,12 +1668,12 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_emit_kernel(const uint
 
 // k-th legal action of the current position, same row-per-lane mapping as the step kernel
 template <int N, bool SK>
-__global__ void __launch_bounds__(64 * kWavesPerBlock) go_random_actions_kernel(const uint4* planes, const uint4* meta, int B, uint32_t seed,
-                                                                                uint32_t t, const int32_t* start_t, int32_t* actions, const uint2* zt,
-                                                                                const uint4* zcur) {
+__global__ void __launch_bounds__(64 * kWavesPerBlock) go_random_actions_kernel(const uint4* planes, const uint4* meta, const int32_t* start_t,
+                                                                                int32_t* actions, int B, uint32_t seed, uint32_t t, uint32_t eighth,
+                                                                                const uint2* zt, const uint4* zcur) {
   using G = Geo<N>;
   __shared__ uint32_t sk_scratch[SK ? kWavesPerBlock : 1][64];
-  const int wave = piece_of_block() * kWavesPerBlock + wave_in_block();
+  const int wave = piece_of_block(eighth) * kWavesPerBlock + wave_in_block();
   if (wave * G::W >= B) return;
   const Lane<N> L(wave, threadIdx.x & 63, B);
   Row<N> R;
@@ -1970,10 +1962,10 @@ int launch_emit(pgxgo_ctx* h, uint8_t* mask, uint8_t* obs) {
 template <int N>
 int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed, uint32_t t, const int32_t* start_t, int32_t* next) {
   StepArgs a;
-  a.planes = h->planes; a.meta = h->meta; a.actions = actions; a.rew = h->rew_out; a.term = h->term_out;
+  a.rew = h->rew_out; a.term = h->term_out;
   a.mask = h->mask_out; a.obs = h->obs_out; a.mask_pitch = h->mask_pitch; a.obs_pitch = h->obs_pitch;
-  a.B = h->B; a.wb = h->wb; a.rules.seed = h->seed; a.rules.komi_x2 = h->komi_x2; a.rules.max_steps = h->max_steps; a.rules.auto_reset = h->auto_reset;
-  a.sample_seed = seed; a.sample_t = t; a.start_t = start_t; a.next_actions = next;
+  a.rules.seed = h->seed; a.rules.komi_x2 = h->komi_x2; a.rules.max_steps = h->max_steps; a.rules.auto_reset = h->auto_reset;
+  a.sample_seed = seed; a.sample_t = t; a.next_actions = next;
   // bytes one ply touches: state rows + outputs; 256 MB of memory-side cache on this part, keep a margin
   const size_t touched = (size_t)h->B * (Geo<N>::row_bytes * N + (h->mask_out ? (size_t)h->mask_pitch : 0) + (h->obs_out ? (size_t)h->obs_pitch : 0));
   a.sparse_store = touched < ((size_t)192 << 20) ? 1 : 0;
@@ -1987,9 +1979,9 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
     auto sk = [&](auto tight_c, auto mode_c) {
       constexpr bool T = decltype(tight_c)::value;
       constexpr int M = decltype(mode_c)::value;
-      if (a.store_kind == kStoreThrough) hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreThrough, M>), grid, block, 0, h->stream, a, h->zt, h->zcur);
-      else if (a.store_kind == kStoreThroughWhole) hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreThroughWhole, M>), grid, block, 0, h->stream, a, h->zt, h->zcur);
-      else hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreStreamWhole, M>), grid, block, 0, h->stream, a, h->zt, h->zcur);
+      if (a.store_kind == kStoreThrough) hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreThrough, M>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->zcur, h->B, h->wb, grid.x / 8, h->zt, a);
+      else if (a.store_kind == kStoreThroughWhole) hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreThroughWhole, M>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->zcur, h->B, h->wb, grid.x / 8, h->zt, a);
+      else hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreStreamWhole, M>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->zcur, h->B, h->wb, grid.x / 8, h->zt, a);
     };
     using M1 = std::integral_constant<int, 1>;
     using M2 = std::integral_constant<int, 2>;
@@ -2002,9 +1994,9 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
   }
   auto go = [&](auto sample_c, auto tight_c) {
     constexpr bool S = decltype(sample_c)::value, T = decltype(tight_c)::value;
-    if (a.store_kind == kStoreThrough) hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreThrough>), grid, block, 0, h->stream, a);
-    else if (a.store_kind == kStoreThroughWhole) hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreThroughWhole>), grid, block, 0, h->stream, a);
-    else hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreStreamWhole>), grid, block, 0, h->stream, a);
+    if (a.store_kind == kStoreThrough) hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreThrough>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->B, h->wb, grid.x / 8, a);
+    else if (a.store_kind == kStoreThroughWhole) hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreThroughWhole>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->B, h->wb, grid.x / 8, a);
+    else hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreStreamWhole>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->B, h->wb, grid.x / 8, a);
   };
   if (sample && tight) go(std::true_type{}, std::true_type{});
   else if (sample) go(std::true_type{}, std::false_type{});
@@ -2017,11 +2009,11 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
 template <int N>
 int launch_random(pgxgo_ctx* h, uint32_t seed, uint32_t t, const int32_t* start_t, int32_t* actions) {
   if (h->zt && h->sk_mode == 2)
-    hipLaunchKernelGGL((go_random_actions_kernel<N, true>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->planes, h->meta, h->B,
-                       seed, t, start_t, actions, h->zt, h->zcur);
+    hipLaunchKernelGGL((go_random_actions_kernel<N, true>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->planes, h->meta, start_t,
+                       actions, h->B, seed, t, blocks_for<N>(h->B) / 8, h->zt, h->zcur);
   else
-    hipLaunchKernelGGL((go_random_actions_kernel<N, false>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->planes, h->meta, h->B,
-                       seed, t, start_t, actions, h->zt, h->zcur);
+    hipLaunchKernelGGL((go_random_actions_kernel<N, false>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->planes, h->meta, start_t,
+                       actions, h->B, seed, t, blocks_for<N>(h->B) / 8, h->zt, h->zcur);
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
 }
@@ -2052,18 +2044,18 @@ int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
 }
 
 template <int N>
-int launch_slots(pgxgo_ctx* h, const SlotArgs& a) {
-  const dim3 grid(blocks_for<N>(a.n)), block(64 * kWavesPerBlock);
+int launch_slots(pgxgo_ctx* h, int n, const int32_t* src, const int32_t* actions, const int32_t* dst, const SlotArgs& a) {
+  const dim3 grid(blocks_for<N>(n)), block(64 * kWavesPerBlock);
   const bool tight = tight_pitches<N>(h), sk = h->zt != nullptr;
-  const size_t out_bytes = (size_t)a.n * ((a.mask ? (size_t)a.mask_pitch : 0) + (a.obs ? (size_t)a.obs_pitch : 0));
-  if (tight && sk && h->sk_mode == 1) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 1>), grid, block, 0, h->stream, a);
-  else if (tight && sk) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 2>), grid, block, 0, h->stream, a);
-  else if (tight && store_kind_for(out_bytes, true) == kStoreThrough) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreThrough>), grid, block, 0, h->stream, a);
-  else if (tight && store_kind_for(out_bytes, true) == kStoreThroughWhole) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreThroughWhole>), grid, block, 0, h->stream, a);
-  else if (tight) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreStreamWhole>), grid, block, 0, h->stream, a);
-  else if (sk && h->sk_mode == 1) hipLaunchKernelGGL((go_step_slots_kernel<N, false, 1>), grid, block, 0, h->stream, a);
-  else if (sk) hipLaunchKernelGGL((go_step_slots_kernel<N, false, 2>), grid, block, 0, h->stream, a);
-  else hipLaunchKernelGGL((go_step_slots_kernel<N, false, 0>), grid, block, 0, h->stream, a);
+  const size_t out_bytes = (size_t)n * ((a.mask ? (size_t)a.mask_pitch : 0) + (a.obs ? (size_t)a.obs_pitch : 0));
+  if (tight && sk && h->sk_mode == 1) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 1>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
+  else if (tight && sk) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 2>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
+  else if (tight && store_kind_for(out_bytes, true) == kStoreThrough) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreThrough>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
+  else if (tight && store_kind_for(out_bytes, true) == kStoreThroughWhole) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreThroughWhole>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
+  else if (tight) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreStreamWhole>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
+  else if (sk && h->sk_mode == 1) hipLaunchKernelGGL((go_step_slots_kernel<N, false, 1>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
+  else if (sk) hipLaunchKernelGGL((go_step_slots_kernel<N, false, 2>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
+  else hipLaunchKernelGGL((go_step_slots_kernel<N, false, 0>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
 }
@@ -2279,11 +2271,10 @@ int pgxgo_step_slots(pgxgo_t h, int32_t n, const int32_t* src_slots_dev, const i
   if (!h || n < 0 || n > h->B || !src_slots_dev || !dst_slots_dev) return PGXGO_EINVAL;
   if (n == 0) return PGXGO_OK;
   SlotArgs a;
-  a.planes = h->planes; a.meta = h->meta; a.pool = h->B; a.n = n; a.src = src_slots_dev; a.dst = dst_slots_dev; a.actions = actions_dev;
   a.rew = rewards_dev; a.term = terminated_dev; a.mask = mask_dev; a.obs = obs_dev; a.mask_pitch = h->mask_pitch; a.obs_pitch = h->obs_pitch;
   a.rules.seed = h->seed; a.rules.komi_x2 = h->komi_x2; a.rules.max_steps = h->max_steps; a.rules.auto_reset = h->auto_reset;
   a.zt = h->zt; a.zcur = h->zcur; a.sk_mode = h->sk_mode;
-  return DISPATCH_N(h, launch_slots<19>(h, a), launch_slots<9>(h, a));
+  return DISPATCH_N(h, launch_slots<19>(h, n, src_slots_dev, actions_dev, dst_slots_dev, a), launch_slots<9>(h, n, src_slots_dev, actions_dev, dst_slots_dev, a));
 }
 
 int pgxgo_copy_slots(pgxgo_t h, int32_t n, const int32_t* src_slots_dev, const int32_t* dst_slots_dev) {

@@ -43,7 +43,7 @@ constexpr int OBS = P * 4;                  // Table 1: 11 x 11 x 4
 constexpr int STRIDE = N + 1;               // lanes per board, one of them the zero sentinel row
 constexpr int W = 63 / STRIDE;              // boards per wavefront
 constexpr uint32_t FULL = (1u << N) - 1u;
-constexpr int kWavesPerBlock = 4;           // wavefronts never synchronise with each other after the table is filled
+constexpr int kWavesPerBlock = kBlockThreads / 64;           // wavefronts never synchronise with each other after the table is filled
 constexpr int OBS_DW = ((15 + W * OBS + 31) / 32 + 3) / 4 * 4;   // LDS dwords of a wavefront's observation bit stream
 constexpr int MASK_DW = 64;                                      // the mask stream is cleared by one store per lane
 static_assert(A == PGXHEX_ACTIONS && OBS == PGXHEX_OBS_BYTES, "header constants");
@@ -177,19 +177,14 @@ __device__ __forceinline__ int draw_action(const Lane& L, uint32_t E, bool swap,
   return pr * N + pc;
 }
 
-struct StepArgs {
-  uint32_t* rows;            // [B][N] row words
-  uint4* meta;               // [B]
-  const int32_t* actions;    // [B]
+struct StepArgs {            // what is not needed before the first loads
   float* rew;                // [B][2]
   uint8_t* term;             // [B]
   uint8_t* mask;             // [B][A] or null
   uint8_t* obs;              // [B][OBS] or null
-  int B;
   uint32_t seed;
   int auto_reset;
   uint32_t sample_seed, sample_t;
-  const int32_t* start_t;    // nullable
   int32_t* next_actions;     // SAMPLE only
 };
 
@@ -272,38 +267,41 @@ __device__ __forceinline__ Ply hex_ply(const Lane& L, uint32_t& bk, uint32_t& wt
 
 // One launch = one ply of every game, then a6 legal mask, a7 observation, a8 state store, optionally the next draw.
 template <bool SAMPLE>
-__global__ void __launch_bounds__(64 * kWavesPerBlock) hex_step_kernel(StepArgs a) {
+__global__ void __launch_bounds__(64 * kWavesPerBlock) hex_step_kernel(uint32_t* rows, uint4* meta, const int32_t* actions, const int32_t* start_t, int B, uint32_t eighth,
+                                                                      StepArgs a) {   // rows [B][N] row words; start_t nullable
   __shared__ uint2 lut[256];
   __shared__ __align__(16) uint32_t lds_obs[kWavesPerBlock][OBS_DW];
   __shared__ uint32_t lds_mask[kWavesPerBlock][MASK_DW];
   const int wib = wave_in_block(), lane = threadIdx.x & 63;
-  const int wave = piece_of_block() * kWavesPerBlock + wib;
-  const Lane L(wave, lane, a.B);
-  const uint32_t word = L.valid ? a.rows[(size_t)L.b * N + L.r] : 0u;
-  const uint4 mv = L.boardok ? a.meta[L.b] : make_uint4(0u, 0u, 0u, 0u);
-  const int act = L.boardok ? a.actions[L.b] : -1;
+  const int wave = piece_of_block(eighth) * kWavesPerBlock + wib;
+  const Lane L(wave, lane, B);
+  const uint32_t word = L.valid ? rows[(size_t)L.b * N + L.r] : 0u;
+  const uint4 mv = L.boardok ? meta[L.b] : make_uint4(0u, 0u, 0u, 0u);
+  const int act = L.boardok ? actions[L.b] : -1;
   // loaded with the state: a load issued after the output stores would have to wait for them (one counter)
-  const int32_t start_raw = (SAMPLE && a.start_t && L.boardok) ? a.start_t[L.b] : INT32_MIN;
+  const int32_t start_raw = (SAMPLE && start_t && L.boardok) ? start_t[L.b] : INT32_MIN;
+  in_scalar_registers(a.rew, a.term, a.mask, a.obs, a.seed, a.auto_reset);
+  if (SAMPLE) in_scalar_registers(a.sample_seed, a.sample_t, a.next_actions);
   fill_spread_table(lut);
-  if (wave * W >= a.B) return;
+  if (wave * W >= B) return;
   const bool wait_start = (int64_t)a.sample_t < (int64_t)held_back(start_raw);
 
   uint32_t bk = word & 0xFFFFu, wt = word >> 16;
   Meta m = unpack_meta(mv);
   const Ply ply = hex_ply(L, bk, wt, m, act, a.seed, a.auto_reset);
   if (L.valid && L.r == 0 && !ply.skip) {
-    *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(ply.rew0, ply.rew1);
-    a.term[L.b] = (ply.ended || ply.frozen) ? 1 : 0;
-    a.meta[L.b] = pack_meta(m);
+    store_small<kStoreThrough>((float2*)(a.rew + 2 * (size_t)L.b), make_float2(ply.rew0, ply.rew1));
+    store_small<kStoreThrough>(&a.term[L.b], (uint8_t)((ply.ended || ply.frozen) ? 1 : 0));
+    store_small<kStoreThrough>(&meta[L.b], pack_meta(m));
   }
   const uint32_t word_new = bk | (wt << 16);
-  if (L.valid && word_new != word) a.rows[(size_t)L.b * N + L.r] = word_new;
+  if (L.valid && word_new != word) store_small<kStoreThrough>(&rows[(size_t)L.b * N + L.r], word_new);
 
-  emit_outputs(L, bk, wt, m, wave, a.B, a.mask, a.obs, lds_mask[wib], lds_obs[wib], lut);
+  emit_outputs(L, bk, wt, m, wave, B, a.mask, a.obs, lds_mask[wib], lds_obs[wib], lut);
 
   if (SAMPLE) {
     const int next = draw_action(L, L.full & ~(bk | wt), m.steps == 1, a.sample_seed, a.sample_t, wait_start);
-    if (L.valid && L.r == 0) a.next_actions[L.b] = next;
+    if (L.valid && L.r == 0) store_small<kStoreThrough>(&a.next_actions[L.b], (int32_t)next);
   }
 }
 
@@ -356,7 +354,7 @@ __device__ __forceinline__ B128 dilate128(B128 x) {
 
 // bit i of x (x < 256) -> bit 4i, from a table in LDS
 __device__ __forceinline__ void fill_spread4_table(uint32_t* lut4) {
-  for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) lut4[x] = spread_every4(x);
+  for (uint32_t x = threadIdx.x; x < 256u; x += kBlockThreads) lut4[x] = spread_every4(x);
 }
 
 // Puts the ND-dword bit string S at bit offset o of an LDS bit stream: a left shift by 1..32 from dword (o-1)/32 on, so
@@ -530,29 +528,32 @@ __device__ __forceinline__ int lane_draw(const B128& legal, uint32_t seed, uint3
 }
 
 template <bool SAMPLE>
-__global__ void __launch_bounds__(64 * kWavesPerBlock) hex_step_lane_kernel(StepArgs a) {
+__global__ void __launch_bounds__(64 * kWavesPerBlock) hex_step_lane_kernel(uint32_t* rows, uint4* meta, const int32_t* actions, const int32_t* start_t, int B,
+                                                                           uint32_t eighth, StepArgs a) {
   __shared__ uint2 lut[256];
   __shared__ uint32_t lut4[256];
   __shared__ __align__(16) uint32_t lds_obs[kWavesPerBlock][LANE_OBS_DW];
   __shared__ __align__(16) uint32_t lds_mask[kWavesPerBlock][LANE_MASK_DW];
   const int wib = wave_in_block(), lane = threadIdx.x & 63;
-  const int wave = piece_of_block() * kWavesPerBlock + wib;
+  const int wave = piece_of_block(eighth) * kWavesPerBlock + wib;
   const int b0 = wave * 64;                 // first board of the wavefront
   const int b = b0 + lane;
-  const bool ok = b < a.B;
+  const bool ok = b < B;
   // state: 11 row words, the scalar record, the action
   uint32_t row[N];
 #pragma unroll
-  for (int r = 0; r < N; ++r) row[r] = ok ? a.rows[(size_t)b * N + r] : 0u;
-  const uint4 mv = ok ? a.meta[b] : make_uint4(0u, 0u, 0u, 0u);
-  const int act = ok ? a.actions[b] : -1;
+  for (int r = 0; r < N; ++r) row[r] = ok ? rows[(size_t)b * N + r] : 0u;
+  const uint4 mv = ok ? meta[b] : make_uint4(0u, 0u, 0u, 0u);
+  const int act = ok ? actions[b] : -1;
   // loaded with the state: a load issued after the output stores would have to wait for them (one counter)
-  const int32_t start_raw = (SAMPLE && a.start_t && ok) ? a.start_t[b] : INT32_MIN;
+  const int32_t start_raw = (SAMPLE && start_t && ok) ? start_t[b] : INT32_MIN;
+  in_scalar_registers(a.rew, a.term, a.mask, a.obs, a.seed, a.auto_reset);
+  if (SAMPLE) in_scalar_registers(a.sample_seed, a.sample_t, a.next_actions);
   fill_spread4_table(lut4);
   fill_spread_table(lut);                   // ends with the block's only barrier (nothing loaded above is looked at before it)
-  if (b0 >= a.B) return;
+  if (b0 >= B) return;
   const bool wait_start = (int64_t)a.sample_t < (int64_t)held_back(start_raw);
-  const int nb = a.B - b0 < 64 ? a.B - b0 : 64;
+  const int nb = B - b0 < 64 ? B - b0 : 64;
   Meta m = unpack_meta(mv);
   B128 bk, wt;
   rows_to_sets(row, bk, wt);
@@ -561,13 +562,13 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_step_lane_kernel(Step
   if (!ply.skip) {
     *(float2*)(a.rew + 2 * (size_t)b) = make_float2(ply.rew0, ply.rew1);
     a.term[b] = (ply.ended || ply.frozen) ? 1 : 0;
-    a.meta[b] = pack_meta(m);
+    meta[b] = pack_meta(m);
     // a8: state store.  A placed stone changes one bit of one row word; a swap or a reset rewrites the board.
     if (ply.swap_ok || ply.reset) {
-      store_sets_as_rows(a.rows + (size_t)b * N, bk, wt);
+      store_sets_as_rows(rows + (size_t)b * N, bk, wt);
     } else if (ply.point_ok) {
       const int pr = (int)(__umul24((uint32_t)act, 745u) >> 13);   // act / 11 for 0 <= act < 128
-      atomicOr(&a.rows[(size_t)b * N + pr], (1u << (act - pr * N)) << (wtm ? 16 : 0));
+      atomicOr(&rows[(size_t)b * N + pr], (1u << (act - pr * N)) << (wtm ? 16 : 0));
     }
   }
   const B128 legal = lane_legal(bk, wt, m);
@@ -698,10 +699,10 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_emit_kernel(const uin
   emit_outputs(L, word & 0xFFFFu, word >> 16, m, wave, B, mask, obs, lds_mask[wib], lds_obs[wib], lut);
 }
 
-__global__ void __launch_bounds__(64 * kWavesPerBlock) hex_random_actions_kernel(const uint32_t* rows, const uint4* meta, int B, uint32_t seed, uint32_t t,
-                                                                                const int32_t* start_t, int32_t* actions) {
+__global__ void __launch_bounds__(64 * kWavesPerBlock) hex_random_actions_kernel(const uint32_t* rows, const uint4* meta, const int32_t* start_t, int32_t* actions,
+                                                                                int B, uint32_t seed, uint32_t t, uint32_t eighth) {
   const int wib = wave_in_block(), lane = threadIdx.x & 63;
-  const int wave = piece_of_block() * kWavesPerBlock + wib;
+  const int wave = piece_of_block(eighth) * kWavesPerBlock + wib;
   if (wave * W >= B) return;
   const Lane L(wave, lane, B);
   const uint32_t word = L.valid ? rows[(size_t)L.b * N + L.r] : 0u;
@@ -841,15 +842,16 @@ int launch_reset(pgxhex_ctx* h, int first) {
 
 int launch_step(pgxhex_ctx* h, const int32_t* actions, bool sample, uint32_t seed, uint32_t t, const int32_t* start_t, int32_t* next) {
   StepArgs a;
-  a.rows = h->rows; a.meta = h->meta; a.actions = actions; a.rew = h->rew_out; a.term = h->term_out; a.mask = h->mask_out; a.obs = h->obs_out;
-  a.B = h->B; a.seed = h->seed; a.auto_reset = h->auto_reset;
-  a.sample_seed = seed; a.sample_t = t; a.start_t = start_t; a.next_actions = next;
-  if (board_per_lane(h)) {
-    const dim3 grid(lane_blocks_for(h->B));
-    if (sample) hipLaunchKernelGGL(hex_step_lane_kernel<true>, grid, dim3(64 * kWavesPerBlock), 0, h->stream, a);
-    else hipLaunchKernelGGL(hex_step_lane_kernel<false>, grid, dim3(64 * kWavesPerBlock), 0, h->stream, a);
-  } else if (sample) hipLaunchKernelGGL(hex_step_kernel<true>, dim3(blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
-  else hipLaunchKernelGGL(hex_step_kernel<false>, dim3(blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
+  a.rew = h->rew_out; a.term = h->term_out; a.mask = h->mask_out; a.obs = h->obs_out;
+  a.seed = h->seed; a.auto_reset = h->auto_reset;
+  a.sample_seed = seed; a.sample_t = t; a.next_actions = next;
+  const bool per_lane = board_per_lane(h);
+  const dim3 grid(per_lane ? lane_blocks_for(h->B) : blocks_for(h->B)), block(64 * kWavesPerBlock);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, h->rows, h->meta, actions, start_t, h->B, grid.x / 8, a); };
+  if (per_lane && sample) go(hex_step_lane_kernel<true>);
+  else if (per_lane) go(hex_step_lane_kernel<false>);
+  else if (sample) go(hex_step_kernel<true>);
+  else go(hex_step_kernel<false>);
   HIPCHK(hipGetLastError());
   return PGXHEX_OK;
 }
@@ -953,8 +955,8 @@ int pgxhex_rollout(pgxhex_t h, int32_t steps, int32_t slices, uint32_t seed, uin
 
 int pgxhex_random_actions(pgxhex_t h, uint32_t seed, uint32_t t, const int32_t* start_t_dev, int32_t* actions_dev) {
   if (!h || !actions_dev) return PGXHEX_EINVAL;
-  hipLaunchKernelGGL(hex_random_actions_kernel, dim3(blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->rows, h->meta, h->B, seed, t,
-                     start_t_dev, actions_dev);
+  hipLaunchKernelGGL(hex_random_actions_kernel, dim3(blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->rows, h->meta, start_t_dev,
+                     actions_dev, h->B, seed, t, blocks_for(h->B) / 8);
   HIPCHK(hipGetLastError());
   return PGXHEX_OK;
 }

@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace pgxwave {
 
 // counter-based hash of (seed, tag, env, t); tag 0 = action draw, tag 1 = seat draw (t = episode)
@@ -33,7 +35,17 @@ __device__ __forceinline__ int wave_in_block() { return __builtin_amdgcn_readfir
 // that each die reads and writes one contiguous eighth of the batch and such lines leave one L2 whole (65536 games of
 // 19x19: 85.5 -> 82.5 us per ply; 16384 games: 20.4 -> 20.15).  The grid must be a multiple of 8 blocks (pieces
 // beyond the batch are idle).
-__device__ __forceinline__ int piece_of_block() { return (int)(blockIdx.x & 7u) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3); }
+__device__ __forceinline__ int piece_of_block(uint32_t eighth) { return (int)(blockIdx.x & 7u) * (int)eighth + (int)(blockIdx.x >> 3); }   // eighth: blocks / 8
+__device__ __forceinline__ int piece_of_block() { return piece_of_block(gridDim.x >> 3); }
+
+// Threads of a block of the board kernels (4 wavefronts), as a constant: the launch's own block size would be another load from
+// the kernel's arguments ahead of everything else.
+constexpr int kBlockThreads = 256;
+
+// The kernels of one ply per launch take what the first loads need (pointers to state and actions, batch, boards per wavefront,
+// blocks per eighth) as plain leading arguments, which the hardware puts into scalar registers before the first instruction
+// (the build asks for it: -amdgpu-kernarg-preload-count); from the argument struct they came by four dependent loads, 1500
+// cycles before the first state load was under way.  The rest of the arguments is loaded while the state is on its way.
 
 // ------------------------------------------------------------------------------------------------
 // Pacing of recorded rollouts.  A rollout whose plies go to fresh memory writes at the rate of DRAM, and DRAM is faster when
@@ -120,6 +132,15 @@ __device__ __forceinline__ int32_t held_back(int32_t v) {
   return v;
 }
 
+// Has the wavefront-uniform values v in scalar registers from here on (the compiler would otherwise load kernel arguments one
+// by one where they are first needed, each time with a wait of its own).
+__device__ __forceinline__ void in_scalar_registers() {}
+template <class V, class... T>
+__device__ __forceinline__ void in_scalar_registers(const V& v, const T&... rest) {
+  asm volatile("" ::"s"(v));
+  in_scalar_registers(rest...);
+}
+
 // LDS traffic between the lanes of one wavefront needs no hardware barrier (a wavefront's LDS operations
 // execute in program order); this only keeps the compiler from moving accesses across the hand-over.
 __device__ __forceinline__ void wave_lds_fence() {
@@ -139,7 +160,7 @@ __device__ __forceinline__ uint32_t spread4(uint32_t nibble) { return (nibble * 
 
 // 256-entry table in LDS: entry x = the eight bytes (0/1) of the bits of x.  Filled once per block.
 __device__ __forceinline__ void fill_spread_table(uint2* lut) {
-  for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) lut[x] = make_uint2(spread4(x & 15u), spread4(x >> 4));
+  for (uint32_t x = threadIdx.x; x < 256u; x += kBlockThreads) lut[x] = make_uint2(spread4(x & 15u), spread4(x >> 4));
   __syncthreads();
 }
 
@@ -160,9 +181,9 @@ __device__ __forceinline__ void fill_spread_table(uint2* lut) {
 // followed by the two wait states this hardware needs between a store of more than 8 bytes and a write to its data
 // registers (the compiler inserts them for its own stores; with one wait state rows of the state were stored wrong).
 constexpr int kStorePlain = 0, kStoreStream = 1, kStoreThrough = 2, kStoreThroughWhole = 3, kStoreStreamThrough = 4, kStoreStreamWhole = 5;
+typedef unsigned int vec4u __attribute__((ext_vector_type(4)));
 template <int KIND>
 __device__ __forceinline__ void store16(uint4* p, uint2 lo, uint2 hi) {
-  typedef unsigned int vec4u __attribute__((ext_vector_type(4)));
   const vec4u v4 = {lo.x, lo.y, hi.x, hi.y};
   static_assert(KIND != kStoreThroughWhole && KIND != kStoreStreamWhole, "resolved by emit_bytes");
   if constexpr (KIND == kStorePlain) *p = make_uint4(lo.x, lo.y, hi.x, hi.y);
@@ -170,66 +191,100 @@ __device__ __forceinline__ void store16(uint4* p, uint2 lo, uint2 hi) {
   else if constexpr (KIND == kStoreStreamThrough) asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" ::"v"(p), "v"(v4) : "memory");
   else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v4) : "memory");
 }
+// the same to base + offset + IMM bytes, base the same in every lane (no 64-bit address arithmetic per lane)
+template <int KIND, int IMM>
+__device__ __forceinline__ void store16_at(uint8_t* base, uint32_t offset, uint2 lo, uint2 hi) {
+  static_assert(IMM >= 0 && IMM < 4096, "fits the instruction");
+  const vec4u v4 = {lo.x, lo.y, hi.x, hi.y};
+  if constexpr (KIND == kStoreThrough) asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3 sc1\n\ts_nop 1" ::"v"(offset), "v"(v4), "s"(base), "n"(IMM) : "memory");
+  else if constexpr (KIND == kStoreStreamThrough) asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3 sc1 nt\n\ts_nop 1" ::"v"(offset), "v"(v4), "s"(base), "n"(IMM) : "memory");
+  else store16<KIND>((uint4*)(base + offset + IMM), lo, hi);
+}
 
-// MAXBYTES: upper bound of nbytes (fixes the number of rounds of 64 groups).  dst and nbytes must be the same in
-// every lane.
+// A store of 1, 4, 8 or 16 bytes, written through the L2 if its launch's other stores are (KIND kStoreThrough).  A byte stored
+// the ordinary way leaves a dirty piece of a line whose other pieces have been written through, and the lines of a stream's ragged
+// ends then go to memory piece by piece: with such bytes written through as well, Hex x 16384 games 55.4 -> 44.3 us for 8 plies,
+// 19x19 x 4096 entries of a search 39.4 -> 35.0 for 4, 19x19 x 5000 with superko 57.0 -> 53.4 for 4.  The wider ones gain in Hex (a further
+// 44.2 -> 42.8) but not in Go, where rows of the state written through cost more than they save (search x 1024 35.6 -> 37.1,
+// superko x 5000 53.2 -> 66).
+template <int KIND, class T>
+__device__ __forceinline__ void store_small(T* p, T v) {
+  static_assert(sizeof(T) == 1 || sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "a store instruction's width");
+  if constexpr (KIND != kStoreThrough) *p = v;
+  else if constexpr (sizeof(T) == 1) asm volatile("global_store_byte %0, %1, off sc1" ::"v"(p), "v"((uint32_t)v) : "memory");
+  else if constexpr (sizeof(T) == 4) asm volatile("global_store_dword %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+  else if constexpr (sizeof(T) == 8) {
+    typedef unsigned int vec2u __attribute__((ext_vector_type(2)));
+    asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(__builtin_bit_cast(vec2u, v)) : "memory");
+  } else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(__builtin_bit_cast(vec4u, v)) : "memory");
+}
+
+// MAXBYTES: upper bound of nbytes.  dst and nbytes must be the same in every lane.
+// The groups go out in rounds of 64, counted from the 128-byte line dst lies in, three or four rounds at a time: their bits and
+// table entries are all read before the first of them is stored, so that a wavefront that has its SIMD to itself waits twice for
+// LDS per batch and not twice per round.  A short stream's rounds stand in a loop and keep their tests in line: a kernel of 5 us
+// runs through code it has to fetch, and every jump is another fetch.
 template <int MAXBYTES, int ST = kStorePlain>
 __device__ __forceinline__ void emit_bytes(const uint32_t* bits, const uint2* lut, uint8_t* dst, uint32_t nbytes, int lane) {
-  constexpr int ROUNDS = (((MAXBYTES + 15) >> 4) + 7 + 63) / 64;   // groups + the at most 7 skipped at the front
-  const uint32_t head = (uint32_t)((uintptr_t)dst & 15u);
-  uint8_t* base = dst - head;
-  const uint32_t q = ((uint32_t)(uintptr_t)base >> 4) & 7u;         // position of group 0 in its 128-byte line
-  const uint32_t total = head + nbytes;
-  const uint32_t m0 = head ? 1u : 0u, m1 = total >> 4;              // whole groups m0 .. m1-1
-  const int32_t mine = lane - (int32_t)q;                           // this lane's group in round 0; round i adds 64*i
-  const uint16_t* src = (const uint16_t*)bits + mine;
-  uint4* out = (uint4*)base + mine;
-  constexpr int GROUP = 6;   // rounds in flight at a time (bounds the registers held by pending LDS reads)
-  // Round 0 skips the groups before m0; rounds 1 .. ROUNDS-3 are full for a full wavefront of boards and then run
-  // without per-lane tests (the choice is the same for the whole wavefront).
-  const bool full_mid = m1 + q >= 64u * (uint32_t)(ROUNDS > 2 ? ROUNDS - 2 : 0);
-  auto active = [&](int i) { return mine + 64 * i >= (int32_t)m0 && mine + 64 * i < (int32_t)m1; };
+  constexpr int ROUNDS = (((MAXBYTES + 15) >> 4) + 7 + 63) / 64;   // groups + the at most 7 of the line before dst
+  constexpr int AT_ONCE = ROUNDS < 3 ? ROUNDS : (ROUNDS < 12 ? 3 : 4);
   constexpr int ST_WHOLE = ST == kStoreThroughWhole ? kStoreThrough : (ST == kStoreStreamWhole ? kStoreStreamThrough : ST);
   constexpr int ST_EDGE = ST == kStoreThroughWhole ? kStorePlain : (ST == kStoreStreamWhole ? kStoreStream : ST);
-  // the round before the last lies completely inside the stream when the last one is not empty (the same in every lane)
-  const bool pen_whole = m1 + q >= 64u * (uint32_t)(ROUNDS - 1);
-  if (full_mid) {
+  const uint32_t head = (uint32_t)((uintptr_t)dst & 15u);
+  const uint32_t q = ((uint32_t)(uintptr_t)dst >> 4) & 7u;          // position of dst's group in its line
+  uint8_t* line = dst - head - 16u * q;
+  const uint32_t total = head + nbytes;
+  const uint32_t first = q + (head ? 1u : 0u), last = q + (total >> 4);   // whole groups first .. last-1 of the line's count
+  const uint16_t* src = (const uint16_t*)bits - q;
+  const uint32_t offset = 16u * (uint32_t)lane;
+  // the ragged ends, one byte per lane: lanes 0-15 the bytes before the first whole group, 16-31 those after the last one
+  const uint32_t eb = (uint32_t)lane & 15u, pos = (lane & 16 ? total & ~15u : 0u) + eb;
+  const bool edge = lane < 32 && (lane & 16 ? eb < (total & 15u) : head != 0u && eb >= head);
+  const uint32_t edge_bits = edge ? bits[pos >> 5] : 0u;
+  // rounds r0 .. r0+AT_ONCE-1; INSIDE: all of them lie within the whole groups
+  auto batch = [&](uint32_t r0, auto inside) {
+    constexpr bool INSIDE = decltype(inside)::value;
+    const uint32_t g0 = 64u * r0 + (uint32_t)lane;   // this lane's group of the batch's first round
+    uint32_t v[AT_ONCE];
+    uint2 a[AT_ONCE], b[AT_ONCE];
 #pragma unroll
-    for (int g = 0; g < ROUNDS; g += GROUP) {
-      uint32_t v[GROUP];
-#pragma unroll
-      for (int i = g; i < g + GROUP && i < ROUNDS; ++i) {
-        const bool test = (i == 0 || i >= ROUNDS - 2);
-        v[i - g] = (!test || active(i)) ? (uint32_t)src[64 * i] : 0u;
-      }
-#pragma unroll
-      for (int i = g; i < g + GROUP && i < ROUNDS; ++i) {
-        const bool test = (i == 0 || i >= ROUNDS - 2);
-        if (!test) store16<ST_WHOLE>(&out[64 * i], lut[v[i - g] & 255u], lut[v[i - g] >> 8]);
-        else if (ST_WHOLE != ST_EDGE && i == ROUNDS - 2 && i > 0 && pen_whole) store16<ST_WHOLE>(&out[64 * i], lut[v[i - g] & 255u], lut[v[i - g] >> 8]);
-        else if (active(i)) store16<ST_EDGE>(&out[64 * i], lut[v[i - g] & 255u], lut[v[i - g] >> 8]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+    for (uint32_t k = 0; k < AT_ONCE; ++k) {
+      if constexpr (INSIDE) v[k] = src[g0 + 64u * k];
+      else { const uint32_t g = g0 + 64u * k; v[k] = src[g < q ? q : (g < last ? g : last - 1u)]; }   // any group of the stream does for a lane that stores nothing
     }
+#pragma unroll
+    for (int k = 0; k < AT_ONCE; ++k) { a[k] = lut[v[k] & 255u]; b[k] = lut[v[k] >> 8]; }
+    uint8_t* out = line + 1024u * r0;
+    auto store = [&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      if constexpr (k < AT_ONCE) {
+        const uint32_t g = g0 + 64u * k;
+        if constexpr (INSIDE) store16_at<ST_WHOLE, 1024 * k>(out, offset, a[k], b[k]);
+        else if (ST_WHOLE != ST_EDGE && 64u * (r0 + k) >= first && 64u * (r0 + k + 1u) <= last) store16_at<ST_WHOLE, 1024 * k>(out, offset, a[k], b[k]);   // (the same in every lane)
+        else if (__builtin_expect(g >= first && g < last, 1)) store16_at<ST_EDGE, 1024 * k>(out, offset, a[k], b[k]);
+      }
+    };
+    static_assert(AT_ONCE <= 4, "one base per batch");
+    store(std::integral_constant<int, 0>{}); store(std::integral_constant<int, 1>{}); store(std::integral_constant<int, 2>{}); store(std::integral_constant<int, 3>{});
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // A stream of the full length (a wavefront with all its boards) ends in its last or last but one round: the batches between the
+  // first and the one with these rounds need no tests.
+  constexpr int INSIDE_END = ROUNDS < 4 * AT_ONCE ? AT_ONCE : AT_ONCE + (ROUNDS - 2 - AT_ONCE) / AT_ONCE * AT_ONCE;
+  if (ROUNDS == 1) {
+    const uint32_t g = (uint32_t)lane;
+    if (g >= first && g < last) { const uint32_t v = src[g]; store16_at<ST_EDGE, 0>(line, offset, lut[v & 255u], lut[v >> 8]); }
+  } else if (INSIDE_END > AT_ONCE && __builtin_expect(last >= 64u * (uint32_t)INSIDE_END, 1)) {
+    batch(0u, std::false_type{});
+#pragma unroll
+    for (int r0 = AT_ONCE; r0 < INSIDE_END; r0 += AT_ONCE) batch((uint32_t)r0, std::true_type{});
+#pragma unroll
+    for (int r0 = INSIDE_END; r0 < ROUNDS; r0 += AT_ONCE) batch((uint32_t)r0, std::false_type{});
   } else {
-#pragma unroll
-    for (int g = 0; g < ROUNDS; g += GROUP) {
-      uint32_t v[GROUP];
-#pragma unroll
-      for (int i = g; i < g + GROUP && i < ROUNDS; ++i) v[i - g] = active(i) ? (uint32_t)src[64 * i] : 0u;
-#pragma unroll
-      for (int i = g; i < g + GROUP && i < ROUNDS; ++i)
-        if (active(i)) store16<ST_EDGE>(&out[64 * i], lut[v[i - g] & 255u], lut[v[i - g] >> 8]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+#pragma unroll 1
+    for (uint32_t r0 = 0u; 64u * r0 < last; r0 += AT_ONCE) batch(r0, std::false_type{});
   }
-  if (lane < 32) {
-    uint32_t i = lane & 15u, pos;
-    bool ok;
-    if (lane < 16) { pos = i; ok = head != 0u && i >= head; }
-    else { pos = (m1 << 4) + i; ok = i < (total & 15u); }
-    if (ok) base[pos] = (uint8_t)((bits[pos >> 5] >> (pos & 31u)) & 1u);
-  }
+  if (edge) store_small<ST_EDGE>(line + 16u * q + pos, (uint8_t)((edge_bits >> (pos & 31u)) & 1u));
 }
 
 }  // namespace pgxwave

@@ -1924,14 +1924,15 @@ size_t output_bytes_per_ply(const pgxgo_ctx* h, bool with_mask, bool with_obs) {
   return (size_t)h->B * ((with_mask ? (size_t)h->mask_pitch : 0) + (with_obs ? (size_t)h->obs_pitch : 0));
 }
 
-// One board per wavefront while every wavefront can have a SIMD to itself (1024 SIMDs), then as many boards per
-// wavefront as keep it at one wavefront per SIMD, up to W (measured per ply, one launch per ply, best / worst choice:
-// 9x9 x 2048 games 6.9 us with 2 boards against 7.5 with 1; x 4096 7.4 with 4 against 9.5 with 1; x 6144 7.7 with 6
-// against 11.6 with 1; 19x19 x 3072 8.9 with 3 against 10.3 with 1).
+// What a launch takes is decided by the SIMD (of 1024) with the most wavefronts, and by how many boards share a wavefront's floods
+// and output rounds.  So: the smallest number of wavefronts per SIMD that W boards per wavefront allow, and then the fewest boards
+// per wavefront that need no more (measured per ply, one launch per ply: 9x9 x 2048 games 5.3 us with 2 boards, 7.0 with 1, 5.9
+// with 6; x 4096 5.7 with 4, 8.9 with 1; x 8192 6.5 with 4, 6.8 with 6, 7.9 with 2; x 7001 6.1 with 4, 6.4 with 6; 19x19 x 3072
+// 7.4 with 3, 10.0 with 1; 32 plies of 9x9 x 8192 in one launch 106 us with 4, 116 with 6).
 template <int N>
 int auto_boards_per_wavefront(int B) {
-  const int want = (B + 1023) / 1024;
-  return want < 1 ? 1 : (want > Geo<N>::W ? Geo<N>::W : want);
+  const int per_simd = (int)(((int64_t)B + 1024 * Geo<N>::W - 1) / (1024 * Geo<N>::W));
+  return (int)(((int64_t)B + 1024 * (int64_t)per_simd - 1) / (1024 * (int64_t)per_simd));
 }
 
 // both output pitches are the dense or the line-padded ones: the kernels treat a wavefront's boards as one run of bytes

@@ -8,6 +8,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("PGXGO_LIB") or os.path.join(HERE, "libpgxgo.so")   # PGXGO_LIB: load another build of the same library
 
 _lib = None
+try:   # the per-ply calls' checks in native code (csrc/fastcall.cpp); without it the same checks run here
+    from . import _fastcall as _fast
+except ImportError:
+    _fast = None
+
+
+def _address(fn):
+    return C.cast(fn, C.c_void_p).value
 
 
 class PgxGoError(RuntimeError):
@@ -71,12 +79,16 @@ def _check(rc, what):
         raise PgxGoError(f"{what}: {L.pgxgo_strerror(rc).decode()} (code {rc}, hip error {L.pgxgo_last_hip_error()})")
 
 
-def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+def _ptr(t):   # an argument of type void pointer (the prototypes above convert it)
+    return None if t is None else t.data_ptr()
 
 
+# With small batches the host has to keep up with kernels of 5 us: the checks compare without building tuples and _ptr makes no object
+# (0.48 -> 0.37 us per tensor), and the calls that are made once per ply go through _fastcall, which checks the same in native code and
+# leaves every call that would be refused to the Python lines below it (step_slots with all outputs: 7.2 us in Python at first, 6.4 with
+# the cheaper checks, 3.6 natively).
 def _need(t, dtype, shape, name):
-    if t.dtype != dtype or not t.is_cuda or not t.is_contiguous() or tuple(t.shape) != tuple(shape):
+    if t.dtype is not dtype or t.shape != shape or not t.is_cuda or not t.is_contiguous():
         raise PgxGoError(f"{name}: expected contiguous cuda {dtype} tensor of shape {tuple(shape)}, got {t.dtype} {tuple(t.shape)} on {t.device}")
     return t
 
@@ -114,6 +126,8 @@ class GoEnv:
                 self._state = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
                 _check(L.pgxgo_init(C.byref(h), self.B, self.N, seed & 0xFFFFFFFF, C.byref(opts), _ptr(self._state), nbytes), "pgxgo_init")
         self._h = h
+        if _fast is not None:
+            self._calls = {n: _address(getattr(L, "pgxgo_" + n)) for n in ("step", "random_actions", "step_sample", "step_slots")}
         self.mask_out = self.obs_out = self.rewards_out = self.terminated_out = None
 
     def __del__(self):
@@ -163,24 +177,39 @@ class GoEnv:
         _check(lib().pgxgo_reset(self._h), "pgxgo_reset")
 
     def step(self, actions):
+        if _fast is not None:
+            rc = _fast.step(self._calls["step"], self._h.value, self.B, actions)
+            if rc == 0: return
+            if rc is not None: _check(rc, "pgxgo_step")
         _need(actions, torch.int32, (self.B,), "actions")
-        _check(lib().pgxgo_step(self._h, _ptr(actions)), "pgxgo_step")
+        rc = _lib.pgxgo_step(self._h, _ptr(actions))
+        if rc: _check(rc, "pgxgo_step")
 
     def random_actions(self, seed, t, start_t=None, out=None):
         if out is None:
             out = torch.empty(self.B, dtype=torch.int32, device=self.device)
+        if _fast is not None:
+            rc = _fast.random_actions(self._calls["random_actions"], self._h.value, self.B, seed & 0xFFFFFFFF, t & 0xFFFFFFFF, start_t, out)
+            if rc == 0: return out
+            if rc is not None: _check(rc, "pgxgo_random_actions")
         _need(out, torch.int32, (self.B,), "actions")
         if start_t is not None: _need(start_t, torch.int32, (self.B,), "start_t")
-        _check(lib().pgxgo_random_actions(self._h, seed & 0xFFFFFFFF, t & 0xFFFFFFFF, _ptr(start_t), _ptr(out)), "pgxgo_random_actions")
+        rc = _lib.pgxgo_random_actions(self._h, seed & 0xFFFFFFFF, t & 0xFFFFFFFF, _ptr(start_t), _ptr(out))
+        if rc: _check(rc, "pgxgo_random_actions")
         return out
 
     def step_sample(self, actions, seed, t, start_t=None, out=None):
+        if _fast is not None and out is not None:
+            rc = _fast.step_sample(self._calls["step_sample"], self._h.value, self.B, actions, seed & 0xFFFFFFFF, t & 0xFFFFFFFF, start_t, out)
+            if rc == 0: return out
+            if rc is not None: _check(rc, "pgxgo_step_sample")
         _need(actions, torch.int32, (self.B,), "actions")
         if out is None:
             out = torch.empty(self.B, dtype=torch.int32, device=self.device)
         _need(out, torch.int32, (self.B,), "next_actions")
         if start_t is not None: _need(start_t, torch.int32, (self.B,), "start_t")
-        _check(lib().pgxgo_step_sample(self._h, _ptr(actions), seed & 0xFFFFFFFF, t & 0xFFFFFFFF, _ptr(start_t), _ptr(out)), "pgxgo_step_sample")
+        rc = _lib.pgxgo_step_sample(self._h, _ptr(actions), seed & 0xFFFFFFFF, t & 0xFFFFFFFF, _ptr(start_t), _ptr(out))
+        if rc: _check(rc, "pgxgo_step_sample")
         return out
 
     def rollout(self, steps, seed, t0, start_t=None, slices=1, actions=None, rewards=None, terminated=None, mask=None, obs=None):
@@ -192,11 +221,16 @@ class GoEnv:
         if mask is not None: _need(mask, torch.uint8, (S, self.B, self.mask_pitch), "mask")
         if obs is not None: _need(obs, torch.uint8, (S, self.B, self.obs_pitch), "obs")
         if start_t is not None: _need(start_t, torch.int32, (self.B,), "start_t")
-        _check(lib().pgxgo_rollout(self._h, int(steps), S, seed & 0xFFFFFFFF, t0 & 0xFFFFFFFF, _ptr(start_t), _ptr(actions), _ptr(rewards),
-                                   _ptr(terminated), _ptr(mask), _ptr(obs)), "pgxgo_rollout")
+        rc = _lib.pgxgo_rollout(self._h, int(steps), S, seed & 0xFFFFFFFF, t0 & 0xFFFFFFFF, _ptr(start_t), _ptr(actions), _ptr(rewards),
+                                   _ptr(terminated), _ptr(mask), _ptr(obs))
+        if rc: _check(rc, "pgxgo_rollout")
 
     def step_slots(self, src, actions, dst, mask=None, obs=None, rewards=None, terminated=None):
         """state[dst[i]] = step(state[src[i]], actions[i]); outputs of entry i in row i of the optional buffers."""
+        if _fast is not None:
+            rc = _fast.step_slots(self._calls["step_slots"], self._h.value, self.mask_pitch, self.obs_pitch, src, actions, dst, mask, obs, rewards, terminated)
+            if rc == 0: return
+            if rc is not None: _check(rc, "pgxgo_step_slots")
         n = int(src.shape[0])
         _need(src, torch.int32, (n,), "src"); _need(dst, torch.int32, (n,), "dst")
         if actions is not None: _need(actions, torch.int32, (n,), "actions")
@@ -204,8 +238,8 @@ class GoEnv:
         if obs is not None: _need(obs, torch.uint8, (n, self.obs_pitch), "obs")
         if rewards is not None: _need(rewards, torch.float32, (n, 2), "rewards")
         if terminated is not None: _need(terminated, torch.uint8, (n,), "terminated")
-        _check(lib().pgxgo_step_slots(self._h, n, _ptr(src), _ptr(actions), _ptr(dst), _ptr(mask), _ptr(obs), _ptr(rewards), _ptr(terminated)),
-               "pgxgo_step_slots")
+        rc = _lib.pgxgo_step_slots(self._h, n, _ptr(src), _ptr(actions), _ptr(dst), _ptr(mask), _ptr(obs), _ptr(rewards), _ptr(terminated))
+        if rc: _check(rc, "pgxgo_step_slots")
 
     def copy_slots(self, src, dst):
         n = int(src.shape[0])

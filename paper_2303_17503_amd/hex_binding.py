@@ -3,7 +3,7 @@ import ctypes as C
 
 import torch
 
-from .binding import PgxGoError, _need, _ptr, lib as _golib
+from .binding import PgxGoError, _address, _fast, _need, _ptr, lib as _golib
 
 N, P, A, OBS = 11, 121, 122, 484
 _ready = False
@@ -70,6 +70,8 @@ class HexEnv:
             h = C.c_void_p()
             _check(L.pgxhex_init(C.byref(h), self.B, seed & 0xFFFFFFFF, C.byref(opts), _ptr(self._state), nbytes), "pgxhex_init")
         self._h = h
+        if _fast is not None:
+            self._calls = {n: _address(getattr(L, "pgxhex_" + n)) for n in ("step", "random_actions", "step_sample")}
         self.mask_out = self.obs_out = self.rewards_out = self.terminated_out = None
 
     def __del__(self):
@@ -111,18 +113,30 @@ class HexEnv:
         _check(lib().pgxhex_reset(self._h), "pgxhex_reset")
 
     def step(self, actions):
+        if _fast is not None:
+            rc = _fast.step(self._calls["step"], self._h.value, self.B, actions)
+            if rc == 0: return
+            if rc is not None: _check(rc, "pgxhex_step")
         _need(actions, torch.int32, (self.B,), "actions")
         _check(lib().pgxhex_step(self._h, _ptr(actions)), "pgxhex_step")
 
     def random_actions(self, seed, t, start_t=None, out=None):
         if out is None:
             out = torch.empty(self.B, dtype=torch.int32, device=self.device)
+        if _fast is not None:
+            rc = _fast.random_actions(self._calls["random_actions"], self._h.value, self.B, seed & 0xFFFFFFFF, t & 0xFFFFFFFF, start_t, out)
+            if rc == 0: return out
+            if rc is not None: _check(rc, "pgxhex_random_actions")
         _need(out, torch.int32, (self.B,), "actions")
         if start_t is not None: _need(start_t, torch.int32, (self.B,), "start_t")
         _check(lib().pgxhex_random_actions(self._h, seed & 0xFFFFFFFF, t & 0xFFFFFFFF, _ptr(start_t), _ptr(out)), "pgxhex_random_actions")
         return out
 
     def step_sample(self, actions, seed, t, start_t=None, out=None):
+        if _fast is not None and out is not None:
+            rc = _fast.step_sample(self._calls["step_sample"], self._h.value, self.B, actions, seed & 0xFFFFFFFF, t & 0xFFFFFFFF, start_t, out)
+            if rc == 0: return out
+            if rc is not None: _check(rc, "pgxhex_step_sample")
         _need(actions, torch.int32, (self.B,), "actions")
         if out is None:
             out = torch.empty(self.B, dtype=torch.int32, device=self.device)

@@ -11,8 +11,9 @@
 //     wave shift moves every row to its north/south neighbour and brings zeros in from off the board.
 //   * Stones are row bitboards (bit c = column c).  East/west neighbours are register shifts, north/south
 //     neighbours are DPP shifts; a flood-fill step is a handful of VALU instructions for all W boards at once.
-//   * Facts about a whole board (a move is legal, a chain has one liberty, ...) come from a ballot masked with
-//     the lane segment of the board; every lane of the board then holds the same answer.
+//   * Facts about a whole board (a move is legal, ...) come from a ballot masked with the lane segment of the board,
+//     counts (liberties of the chains a move touches) from one sum per board in LDS; every lane of the board then holds
+//     the same answer.
 //   * The state keeps, besides the stones, the set of stones whose chain has exactly one liberty
 //     ("atari sets").  With them captures, the ko test and the whole legal mask are stencils; only the
 //     chains touched by the move are re-flooded (the merged chain and at most four opposing neighbours),
@@ -37,6 +38,7 @@
 //     the kind of store -- through the L2, with the non-temporal hint, ordinary -- is chosen per launch from the
 //     bytes it writes and from whether it overwrites the previous launch's buffers (store_kind_for).  The
 //     line-padded output pitches make a wavefront's stream consist of whole lines only.
+//   * Recordings that outgrow the memory-side cache are written in time slots, in the order of their addresses (Pace).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -1900,21 +1902,18 @@ template <int N>
 unsigned blocks_for(int B) { return ((waves_for<N>(B) + kWavesPerBlock - 1) / kWavesPerBlock + 7u) & ~7u; }   // a multiple of 8: piece_of_block
 unsigned blocks_for_wb(int B, int wb) { return (((unsigned)((B + wb - 1) / wb) + kWavesPerBlock - 1) / kWavesPerBlock + 7u) & ~7u; }
 
-// Boards per wavefront for the step and rollout launches.  A wavefront can hold W boards; with few games it is
-// better to spread them over more wavefronts (shorter floods, fewer output rounds per wavefront), so the count
-// grows with the batch until about two wavefronts per SIMD exist.
-// Kind of the output stores of a one-launch-per-ply kernel by the bytes the launch writes, measured at 19x19 with the
-// observation: up to 32 MB (4096 games) everything written through the L2 is fastest (7.97 / 8.93 / 10.2 us per ply for
-// 1024 / 2048 / 4096 games against 8.5 / 10.2 / 11.4 us with plain stores); from there to the size of the memory-side
-// cache write-through for whole lines only (16384 games: 20.7 against 22.1 us); beyond it, where the hint costs
-// 20-30 % below ~50 k games and gains 9-17 % above ~57 k, the non-temporal hint on top (65536 games: 88 us against
-// 110 us plain).  The rollout kernel uses kStoreThroughWhole at every size (16384 games: 14.4 against 16.5 us per ply,
-// 65536 games: 53.8 against 60.2 us; the non-temporal hint is slower there at every size).
+// Kind of the output stores of a one-launch-per-ply kernel by the bytes the launch writes: up to 48 MB everything written
+// through the L2 (us for 4 launches, against whole lines only: 19x19 x 6001 games, 39 MB, 39.6 / 39.9, as entries of a search
+// x 5500 37.9 / 39.3; 9x9 x 24000, 35 MB, 38.0 / 40.4; above the line 19x19 x 9000, 58 MB, 50.5 / 50.0); from there to the size
+// of the memory-side cache write-through for whole lines only (16384 games: 20.7 against 22.1 us per ply with ordinary stores);
+// beyond it, where the hint costs 20-30 % below ~50 k games and gains 9-17 % above ~57 k, the non-temporal hint on top (65536
+// games: 88 us against 110 us plain).  The rollout kernel uses kStoreThroughWhole at every size unless it is paced (16384
+// games: 14.4 against 16.5 us per ply, 65536 games: 53.8 against 60.2 us; in place the non-temporal hint is slower at every size).
 // in_place: the launch overwrites the buffers the previous one wrote, whose lines are then still in the memory-side
 // cache.  In the middle range a launch into other buffers (a caller that records a trajectory) has to reach DRAM and
 // is faster with the hint as well (16384 games: 23.9 us per ply against 25.4 with ordinary stores and 25.9 with
 // write-through alone).
-constexpr size_t kWriteThroughUpTo = (size_t)32 << 20, kNonTemporalFrom = (size_t)350 << 20;
+constexpr size_t kWriteThroughUpTo = (size_t)48 << 20, kNonTemporalFrom = (size_t)350 << 20;
 int store_kind_for(size_t out_bytes, bool in_place) {
   if (out_bytes <= kWriteThroughUpTo) return kStoreThrough;
   if (out_bytes <= kNonTemporalFrom) return in_place ? kStoreThroughWhole : kStoreStreamWhole;

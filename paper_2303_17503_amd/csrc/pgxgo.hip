@@ -1927,9 +1927,11 @@ size_t output_bytes_per_ply(const pgxgo_ctx* h, bool with_mask, bool with_obs) {
 // and output rounds.  So: the smallest number of wavefronts per SIMD that W boards per wavefront allow, and then the fewest boards
 // per wavefront that need no more (measured per ply, one launch per ply: 9x9 x 2048 games 5.3 us with 2 boards, 7.0 with 1, 5.9
 // with 6; x 4096 5.7 with 4, 8.9 with 1; x 8192 6.5 with 4, 6.8 with 6, 7.9 with 2; x 7001 6.1 with 4, 6.4 with 6; 19x19 x 3072
-// 7.4 with 3, 10.0 with 1; 32 plies of 9x9 x 8192 in one launch 106 us with 4, 116 with 6).
+// 7.4 with 3, 10.0 with 1; 32 plies of 9x9 x 8192 in one launch 106 us with 4, 116 with 6).  At 19x19, where W is 3, two boards
+// against three gain nothing beyond 3072 games (x 4097 34.8 / 34.7 us for 4 plies, 4 plies of x 3237 in one launch 26.9 / 26.5).
 template <int N>
 int auto_boards_per_wavefront(int B) {
+  if (N == 19 && B > 1024 * Geo<N>::W) return Geo<N>::W;
   const int per_simd = (int)(((int64_t)B + 1024 * Geo<N>::W - 1) / (1024 * Geo<N>::W));
   return (int)(((int64_t)B + 1024 * (int64_t)per_simd - 1) / (1024 * (int64_t)per_simd));
 }

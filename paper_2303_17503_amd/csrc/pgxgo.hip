@@ -277,6 +277,7 @@ __device__ __forceinline__ void emit_mask(const Lane<N>& L, uint32_t legal, int 
   static_assert(G::W * G::MASK_DW <= 64 && (15 + G::W * G::A_PAD + 31) / 32 <= 64, "mask staging is cleared by one store per lane");
   constexpr bool tight = TIGHT;   // the caller guarantees mask_pitch == N*N+1 or A_PAD
   const uint32_t stride = (uint32_t)mask_pitch;
+  const int j = in_place(L.j), row = in_place(L.r);
   const int b0 = wave * wb;
   const int nb = B - b0 < wb ? B - b0 : wb;   // boards of this wavefront
   lds_mask[L.lane] = 0u;
@@ -284,9 +285,9 @@ __device__ __forceinline__ void emit_mask(const Lane<N>& L, uint32_t legal, int 
   if (L.valid) {
     uint32_t* reg;
     uint32_t head;
-    if constexpr (tight) { head = (uint32_t)((uintptr_t)(mask + (int64_t)b0 * mask_pitch) & 15u) + __umul24((uint32_t)L.j, stride); reg = lds_mask; }
-    else { head = (uint32_t)((uintptr_t)(mask + (int64_t)L.b * mask_pitch) & 15u); reg = lds_mask + L.j * G::MASK_DW; }
-    const uint32_t o = head + (uint32_t)(N * L.r), q = o >> 5, s = o & 31u;
+    if constexpr (tight) { head = (uint32_t)((uintptr_t)(mask + (int64_t)b0 * mask_pitch) & 15u) + __umul24((uint32_t)j, stride); reg = lds_mask; }
+    else { head = (uint32_t)((uintptr_t)(mask + (int64_t)L.b * mask_pitch) & 15u); reg = lds_mask + j * G::MASK_DW; }
+    const uint32_t o = head + (uint32_t)(N * row), q = o >> 5, s = o & 31u;
     atomicOr(&reg[q], legal << s);
     if (s + N > 32u) atomicOr(&reg[q + 1], legal >> (32u - s));
     if (L.r == 0) { const uint32_t o2 = head + G::P; atomicOr(&reg[o2 >> 5], 1u << (o2 & 31u)); }   // pass is always legal
@@ -302,14 +303,15 @@ __device__ __forceinline__ void emit_mask(const Lane<N>& L, uint32_t legal, int 
   wave_lds_fence();
 }
 
-// Observation bytes [N][N][17] of every board of the wavefront from the history words h of its rows.
-template <int N, bool TIGHT, int ST = kStorePlain>
+// Observation bytes [N][N][17] of every board of the wavefront from the history words h of its rows.  MOST: see emit_bytes.
+template <int N, bool TIGHT, int ST = kStorePlain, int MOST = 4>
 __device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[Geo<N>::HD], int wtm, int wave, int B, uint8_t* obs,
                                          int64_t obs_pitch, uint32_t* lds_obs, const uint2* lut, int wb = Geo<N>::W) {
   using G = Geo<N>;
   static_assert((15 + G::W * G::OBS_PAD + 31) / 32 <= G::W * G::OBS_DW, "one stream for all boards fits the staging area");
   constexpr bool tight = TIGHT;   // the caller guarantees obs_pitch == N*N*17 or OBS_PAD (see emit_mask)
   const uint32_t stride = (uint32_t)obs_pitch;
+  const int j = in_place(L.j), row = in_place(L.r);
   const int b0 = wave * wb;
   const int nb = B - b0 < wb ? B - b0 : wb;
   // 17 bits per point: the point's history halfword seen by the mover (pairs swapped when White moves),
@@ -333,21 +335,22 @@ __device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[G
   }
   {
     uint4* z = (uint4*)lds_obs;
+    const uint32_t zero = in_place(0u);
     constexpr int NZ = G::W * G::OBS_DW / 4;
 #pragma unroll
     for (int i = 0; i < (NZ + 63) / 64; ++i)
-      if (i * 64 + 63 < NZ || i * 64 + L.lane < NZ) z[i * 64 + L.lane] = make_uint4(0u, 0u, 0u, 0u);
+      if (i * 64 + 63 < NZ || i * 64 + L.lane < NZ) z[i * 64 + L.lane] = make_uint4(zero, zero, zero, zero);
   }
   wave_lds_fence();
   if (L.valid) {
     uint32_t* reg;
     uint32_t head;
-    if constexpr (tight) { head = (uint32_t)((uintptr_t)(obs + (int64_t)b0 * obs_pitch) & 15u) + __umul24((uint32_t)L.j, stride); reg = lds_obs; }
-    else { head = (uint32_t)((uintptr_t)(obs + (int64_t)L.b * obs_pitch) & 15u); reg = lds_obs + L.j * G::OBS_DW; }
+    if constexpr (tight) { head = (uint32_t)((uintptr_t)(obs + (int64_t)b0 * obs_pitch) & 15u) + __umul24((uint32_t)j, stride); reg = lds_obs; }
+    else { head = (uint32_t)((uintptr_t)(obs + (int64_t)L.b * obs_pitch) & 15u); reg = lds_obs + j * G::OBS_DW; }
     // The row's string goes to bit offset o of the stream.  Written as a left shift by u = 1..32 from dword (o-u)/32
     // on, every shifted dword is one funnel shift of two neighbours of S (a shift by 0 would need a special case):
     // T[i] = bits of dword q+i; T[0] and T[NI+1..NR] may share their dword with the rows next door.
-    const uint32_t o = head + (uint32_t)(G::ROWBITS * L.r);
+    const uint32_t o = head + (uint32_t)(G::ROWBITS * row);
     const uint32_t u1 = (o + 31u) & 31u;            // u - 1
     reg += (int32_t)(o - 1u - u1) >> 5;             // dword -1 only when o = 0, and then T[0] = 0 is not written
     const uint32_t sh = 31u - u1;                   // right shift of the (S[i], S[i-1]) pair that equals the left shift by u
@@ -365,11 +368,11 @@ __device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[G
   }
   wave_lds_fence();
   if constexpr (tight) {
-    emit_bytes<G::W * G::OBS_PAD, ST>(lds_obs, lut, obs + (int64_t)b0 * obs_pitch, (uint32_t)nb * stride, L.lane);
+    emit_bytes<G::W * G::OBS_PAD, ST, MOST>(lds_obs, lut, obs + (int64_t)b0 * obs_pitch, (uint32_t)nb * stride, L.lane);
   } else {
 #pragma unroll
     for (int jj = 0; jj < G::W; ++jj)
-      if (jj < nb) emit_bytes<G::OBS, ST>(lds_obs + jj * G::OBS_DW, lut, obs + (int64_t)(b0 + jj) * obs_pitch, G::OBS, L.lane);
+      if (jj < nb) emit_bytes<G::OBS, ST, MOST>(lds_obs + jj * G::OBS_DW, lut, obs + (int64_t)(b0 + jj) * obs_pitch, G::OBS, L.lane);
   }
   wave_lds_fence();
 }
@@ -493,7 +496,7 @@ __device__ __forceinline__ void reset_board(const Lane<N>& L, Row<N>& R, Meta& m
   R.bk = R.wt = R.ab = R.aw = 0u;
   m.ko = -1; m.steps = 0; m.passes = 0; m.wtm = 0; m.term = 0;
   m.episode += 1;
-  m.bp = (int)(env_hash(seed, 1u, (uint32_t)L.slot, m.episode) & 1u);
+  m.bp = (int)(env_hash(seed, 1u, (uint32_t)in_place(L.slot), m.episode) & 1u);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -537,16 +540,16 @@ struct Floods {
     if constexpr (PACKED) { w[0] = x0 | (x1 << 10) | (x2 << 20); w[1] = x3 | (x4 << 10); }
     else { w[0] = x0; w[1] = x1; w[2] = x2; w[3] = x3; w[4] = x4; }
   }
-  static __device__ __forceinline__ uint64_t count(const uint32_t (&w)[WORDS]) {
-    uint32_t lo, hi;
+  // puts the counts of word k's floods into this row's fields
+  static __device__ __forceinline__ void count(int k, uint32_t w, uint32_t& lo, uint32_t& hi) {
     if constexpr (PACKED) {
-      lo = __popc(w[0] & 0x3FFu) + (__popc(w[0] & (0x3FFu << 10)) << 10) + (__popc(w[0] >> 20) << 20);
-      hi = __popc(w[1] & 0x3FFu) + (__popc(w[1] >> 10) << 10);
+      if (k == 0) lo = __popc(w & 0x3FFu) + (__popc(w & (0x3FFu << 10)) << 10) + (__popc(w >> 20) << 20);
+      else hi = __popc(w & 0x3FFu) + (__popc(w >> 10) << 10);
     } else {
-      lo = __popc(w[0]) + (__popc(w[1]) << 10) + (__popc(w[2]) << 20);
-      hi = __popc(w[3]) + (__popc(w[4]) << 10);
+      uint32_t& half = k < 3 ? lo : hi;
+      const int at = 10 * (k < 3 ? k : k - 3);
+      half = (half & ~(0x3FFu << at)) | (__popc(w) << at);
     }
-    return (uint64_t)lo | ((uint64_t)hi << 32);
   }
   static __device__ __forceinline__ uint32_t all(uint32_t x, int bit) { return (uint32_t)((int32_t)(x << (31 - bit)) >> 31); }   // every bit = bit `bit` of x
   // bit 9 of every field whose value is at least `least` (1 or 2)
@@ -629,11 +632,12 @@ __device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m,
     FL::spread(F, pbit, nbN & opp, nbS & opp, nbW & opp, nbE & opp);
     FL::spread(S, own, opp, opp, opp, opp);
     FL::spread(EE, E, E, E, E, E);
-    uint64_t libs;   // liberties seen per flood, FL::count's fields
-    uint32_t part[FL::WORDS], open[FL::WORDS];
+    uint64_t libs;                 // liberties seen per flood, FL::count's fields
+    uint32_t lo = 0u, hi = 0u;     // this row's part of them
+    uint32_t open[FL::WORDS];
     bool run[FL::WORDS];   // a flood of this word is under way in some board of the wavefront
 #pragma unroll
-    for (int k = 0; k < FL::WORDS; ++k) { part[k] = 0u; run[k] = FL::PACKED || __ballot(F[k] != 0u) != 0ull; }
+    for (int k = 0; k < FL::WORDS; ++k) run[k] = FL::PACKED || __ballot(F[k] != 0u) != 0ull;
     for (;;) {
 #pragma unroll
       for (int k = 0; k < FL::WORDS; ++k) {
@@ -644,11 +648,11 @@ __device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m,
         const uint32_t D = dilate(F[k]);
         const uint32_t G_ = F[k] | (D & S[k]);
         open[k] = G_ ^ F[k];
-        part[k] = D & EE[k];
+        FL::count(k, D & EE[k], lo, hi);
         F[k] = G_;
       }
       if (round == kTallyRounds) { tally_clear(tally, L.lane); round = 0u; }
-      libs = tally_board(tally, round++, L, FL::count(part));
+      libs = tally_board(tally, round++, L, (uint64_t)lo | ((uint64_t)hi << 32));
       FL::undecided(open, libs);
       bool any = false;
       if constexpr (FL::PACKED) any = __ballot((open[0] | open[1]) != 0u) != 0ull;
@@ -1329,8 +1333,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
       if (L.valid && L.r == 0) meta[L.b] = pack_meta(m);
     }
   };
-  auto board_final = [&](uint32_t) {   // a10, a11
-    if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
+  auto board_final = [&](uint32_t) {   // a10, a11 (mode 1 still holds the row and the table window: a fourth round at once would spill)
+    if (a.obs) emit_obs<N, TIGHT, ST, MODE == 1 ? 3 : 4>(L, R.h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
     if constexpr (MODE != 1) store_state();
   };
   if constexpr (MODE == 1) {
@@ -1547,6 +1551,10 @@ struct RolloutArgs {
 // 6.4 / 6.6 TB/s: 294 / 285 / 281 / 279 / 299; a step below the best, since above it the gain is soon lost)
 constexpr double kPaceBytesPerSecond = 6.3e12;
 
+// The registers hold a game's state from ply to ply, and 80 of them (six wavefronts per SIMD) are just enough for it and a ply's own values.
+// What a ply derives from the lane's place alone is therefore computed anew every ply (in_place): kept from one to the next it pushed
+// 8 to 16 registers out to memory, and every one read back between the outputs waited for all output stores under way (20 plies in
+// place, 19x19 x 16384 games 307 -> 281 us, x 65536 1141 -> 1043, with pitches that are neither dense nor padded 367 -> 326).
 // SK: 0 = simple ko only, 1 / 2 = positional superko at play time / in the legal mask.  PACED: recordings that go to DRAM, see Pace;
 // their stores carry the non-temporal hint as well (16 plies of 19x19 x 16384 games at 6.2 TB/s: 286 us with it, 344 without).
 template <int N, bool TIGHT, int SK, bool PACED>
@@ -1561,32 +1569,34 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
   const int wib = wave_in_block();
   const int wave = piece_of_block() * kWavesPerBlock + wib;
   if (wave * a.wb >= a.B) return;
-  const Lane<N> L(wave, threadIdx.x & 63, a.B, a.wb);
+  const Lane<N> L0(wave, threadIdx.x & 63, a.B, a.wb);
   const size_t rows_total = (size_t)a.B * N;
 
   Row<N> R;
-  load_row<N>(a.planes, rows_total, L, R);
-  Meta m = unpack_meta(L.boardok ? a.meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
-  const int64_t start = (L.boardok && a.start_t) ? (int64_t)a.start_t[L.b] : INT64_MIN;
-  uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
+  load_row<N>(a.planes, rows_total, L0, R);
+  Meta m = unpack_meta(L0.boardok ? a.meta[L0.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
+  const int64_t start = (L0.boardok && a.start_t) ? (int64_t)a.start_t[L0.b] : INT64_MIN;
+  uint32_t legal = legal_row<N>(L0, R, m.wtm, m.ko);
   SkGame g = sk_fresh();
   uint2* tab = nullptr;
   uint32_t forb = 0u;
   if constexpr (SK) {
-    if (L.boardok) g = sk_unpack(a.zcur[L.b]);
-    tab = a.zt + (size_t)(L.boardok ? L.b : 0) * Zt<N>::SLOTS;
+    if (L0.boardok) g = sk_unpack(a.zcur[L0.b]);
+    tab = a.zt + (size_t)(L0.boardok ? L0.b : 0) * Zt<N>::SLOTS;
     SkWin none;
     none.home = ~0u; none.e = make_uint2(1u, 0u);
-    if constexpr (SK != 1) forb = sk_forb_loaded<N>(L, tab, g, R, m, none, lds_mask_all[wib]);
+    if constexpr (SK != 1) forb = sk_forb_loaded<N>(L0, tab, g, R, m, none, lds_mask_all[wib]);
     if constexpr (SK == 2) legal &= ~forb;
   }
   // mode 1: the window the next ply looks at, loaded one ply ahead
   SkWin ahead;
   ahead.home = ~0u; ahead.e = make_uint2(1u, 0u);
-  if constexpr (SK == 1) ahead = sk_window_play<N>(L, tab, g, m, L.boardok);
+  if constexpr (SK == 1) ahead = sk_window_play<N>(L0, tab, g, m, L0.boardok);
   int slice = 0;
   Pace pace(PACED, a.pace, (blockIdx.x >> 3) * kWavesPerBlock + wib, (gridDim.x >> 3) * kWavesPerBlock);
   for (int i = 0; i < a.steps; ++i) {   // the same trip count for every wavefront
+    Lane<N> L = L0;
+    if (!TIGHT) L.lane = in_place(L.lane);   // (board-by-board emission holds more)
     const uint32_t t = a.t0 + (uint32_t)i;
     const bool wait = (int64_t)t < start;
     const Draw<N> d = draw_action<N>(L, legal, a.seed, t, wait);
@@ -1628,11 +1638,11 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
     wave_lds_fence();
     slice = slice + 1 == a.slices ? 0 : slice + 1;
   }
-  store_row<N>(a.planes, rows_total, L, R);
-  if (L.valid && L.r == 0) a.meta[L.b] = pack_meta(m);
+  store_row<N>(a.planes, rows_total, L0, R);
+  if (L0.valid && L0.r == 0) a.meta[L0.b] = pack_meta(m);
   if constexpr (SK) {
-    if constexpr (SK != 1) g.fw = sk_forb_word<N>(L, forb);
-    if (L.valid && L.r == 0) a.zcur[L.b] = sk_pack(g);
+    if constexpr (SK != 1) g.fw = sk_forb_word<N>(L0, forb);
+    if (L0.valid && L0.r == 0) a.zcur[L0.b] = sk_pack(g);
   }
 }
 

@@ -66,7 +66,11 @@ struct PaceArgs {
 struct Pace {
   int64_t slot;      // when this wavefront may write its next ply, in 1/256 ticks of the constant 100 MHz clock
   uint32_t ply;      // T in the same unit
-  __device__ __forceinline__ static int64_t now() { return (int64_t)(__builtin_amdgcn_s_memrealtime() << 8); }
+  __device__ __forceinline__ static int64_t now() {   // (the same in every lane, which the compiler does not know of the clock)
+    const uint64_t t = __builtin_amdgcn_s_memrealtime() << 8;
+    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)t) |
+                     ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(t >> 32)) << 32));
+  }
   // index: this wavefront among the `eighth` wavefronts that write to the same eighth of the batch
   __device__ __forceinline__ Pace(bool on, PaceArgs a, uint32_t index, uint32_t eighth) : slot(0), ply(a.ply) {
     if (!on) return;
@@ -128,6 +132,14 @@ __device__ __forceinline__ bool board_any(bool pred, uint32_t seglo, uint32_t se
 // Returns v; keeps the compiler from evaluating anything that depends on a loaded value before this point (it
 // would otherwise move the first use, and with it the wait for the load, up to the load itself).
 __device__ __forceinline__ int32_t held_back(int32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// Returns v; what is derived from the result is computed at this place and not ahead of a loop around it (a value kept through a
+// loop costs a register in all of it).
+template <class T>
+__device__ __forceinline__ T in_place(T v) {
   asm volatile("" : "+v"(v));
   return v;
 }
@@ -219,15 +231,16 @@ __device__ __forceinline__ void store_small(T* p, T v) {
   } else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(__builtin_bit_cast(vec4u, v)) : "memory");
 }
 
-// MAXBYTES: upper bound of nbytes.  dst and nbytes must be the same in every lane.
+// MAXBYTES: upper bound of nbytes.  MOST: upper bound of the rounds that are under way at once.  dst and nbytes must be the same in every lane.
 // The groups go out in rounds of 64, counted from the 128-byte line dst lies in, three or four rounds at a time: their bits and
 // table entries are all read before the first of them is stored, so that a wavefront that has its SIMD to itself waits twice for
 // LDS per batch and not twice per round.  A short stream's rounds stand in a loop and keep their tests in line: a kernel of 5 us
 // runs through code it has to fetch, and every jump is another fetch.
-template <int MAXBYTES, int ST = kStorePlain>
+template <int MAXBYTES, int ST = kStorePlain, int MOST = 4>
 __device__ __forceinline__ void emit_bytes(const uint32_t* bits, const uint2* lut, uint8_t* dst, uint32_t nbytes, int lane) {
   constexpr int ROUNDS = (((MAXBYTES + 15) >> 4) + 7 + 63) / 64;   // groups + the at most 7 of the line before dst
-  constexpr int AT_ONCE = ROUNDS < 3 ? ROUNDS : (ROUNDS < 12 ? 3 : 4);
+  constexpr int WANTED = ROUNDS < 3 ? ROUNDS : (ROUNDS < 12 ? 3 : 4);
+  constexpr int AT_ONCE = WANTED < MOST ? WANTED : MOST;
   constexpr int ST_WHOLE = ST == kStoreThroughWhole ? kStoreThrough : (ST == kStoreStreamWhole ? kStoreStreamThrough : ST);
   constexpr int ST_EDGE = ST == kStoreThroughWhole ? kStorePlain : (ST == kStoreStreamWhole ? kStoreStream : ST);
   const uint32_t head = (uint32_t)((uintptr_t)dst & 15u);

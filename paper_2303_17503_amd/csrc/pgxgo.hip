@@ -270,7 +270,8 @@ __device__ __forceinline__ uint32_t legal_row(const Lane<N>& L, const Row<N>& R,
 // Legal mask bytes [N*N+1] of every board of the wavefront.  TIGHT: the pitch is the dense one (N*N+1) or the
 // line-padded one (A_PAD); the boards of a wavefront are then one contiguous run of bytes, pad bytes included, and
 // are staged and written as one stream (the pad bytes as zeros); otherwise board by board, pad bytes untouched.
-template <int N, bool TIGHT, int ST = kStorePlain>
+// FIRST_AS_EDGE: see emit_bytes.
+template <int N, bool TIGHT, int ST = kStorePlain, bool FIRST_AS_EDGE = false>
 __device__ __forceinline__ void emit_mask(const Lane<N>& L, uint32_t legal, int wave, int B, uint8_t* mask, int64_t mask_pitch,
                                           uint32_t* lds_mask, const uint2* lut, int wb = Geo<N>::W) {
   using G = Geo<N>;
@@ -294,17 +295,17 @@ __device__ __forceinline__ void emit_mask(const Lane<N>& L, uint32_t legal, int 
   }
   wave_lds_fence();
   if constexpr (tight) {
-    emit_bytes<G::W * G::A_PAD, ST>(lds_mask, lut, mask + (int64_t)b0 * mask_pitch, (uint32_t)nb * stride, L.lane);
+    emit_bytes<G::W * G::A_PAD, ST, 4, FIRST_AS_EDGE>(lds_mask, lut, mask + (int64_t)b0 * mask_pitch, (uint32_t)nb * stride, L.lane);
   } else {
 #pragma unroll
     for (int jj = 0; jj < G::W; ++jj)
-      if (jj < nb) emit_bytes<G::A, ST>(lds_mask + jj * G::MASK_DW, lut, mask + (int64_t)(b0 + jj) * mask_pitch, G::A, L.lane);
+      if (jj < nb) emit_bytes<G::A, ST, 4, FIRST_AS_EDGE>(lds_mask + jj * G::MASK_DW, lut, mask + (int64_t)(b0 + jj) * mask_pitch, G::A, L.lane);
   }
   wave_lds_fence();
 }
 
-// Observation bytes [N][N][17] of every board of the wavefront from the history words h of its rows.  MOST: see emit_bytes.
-template <int N, bool TIGHT, int ST = kStorePlain, int MOST = 4>
+// Observation bytes [N][N][17] of every board of the wavefront from the history words h of its rows.  MOST, FIRST_AS_EDGE: see emit_bytes.
+template <int N, bool TIGHT, int ST = kStorePlain, int MOST = 4, bool FIRST_AS_EDGE = false>
 __device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[Geo<N>::HD], int wtm, int wave, int B, uint8_t* obs,
                                          int64_t obs_pitch, uint32_t* lds_obs, const uint2* lut, int wb = Geo<N>::W) {
   using G = Geo<N>;
@@ -368,21 +369,21 @@ __device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[G
   }
   wave_lds_fence();
   if constexpr (tight) {
-    emit_bytes<G::W * G::OBS_PAD, ST, MOST>(lds_obs, lut, obs + (int64_t)b0 * obs_pitch, (uint32_t)nb * stride, L.lane);
+    emit_bytes<G::W * G::OBS_PAD, ST, MOST, FIRST_AS_EDGE>(lds_obs, lut, obs + (int64_t)b0 * obs_pitch, (uint32_t)nb * stride, L.lane);
   } else {
 #pragma unroll
     for (int jj = 0; jj < G::W; ++jj)
-      if (jj < nb) emit_bytes<G::OBS, ST, MOST>(lds_obs + jj * G::OBS_DW, lut, obs + (int64_t)(b0 + jj) * obs_pitch, G::OBS, L.lane);
+      if (jj < nb) emit_bytes<G::OBS, ST, MOST, FIRST_AS_EDGE>(lds_obs + jj * G::OBS_DW, lut, obs + (int64_t)(b0 + jj) * obs_pitch, G::OBS, L.lane);
   }
   wave_lds_fence();
 }
 
-template <int N, bool TIGHT, int ST = kStorePlain>
+template <int N, bool TIGHT, int ST = kStorePlain, bool FIRST_AS_EDGE = false>
 __device__ __forceinline__ void emit_outputs(const Lane<N>& L, const Row<N>& R, uint32_t legal, int wtm, int wave, int B,
                                              uint8_t* mask, int64_t mask_pitch, uint8_t* obs, int64_t obs_pitch,
                                              uint32_t* lds_mask, uint32_t* lds_obs, const uint2* lut, int wb = Geo<N>::W) {
-  if (mask) emit_mask<N, TIGHT, ST>(L, legal, wave, B, mask, mask_pitch, lds_mask, lut, wb);
-  if (obs) emit_obs<N, TIGHT, ST>(L, R.h, wtm, wave, B, obs, obs_pitch, lds_obs, lut, wb);
+  if (mask) emit_mask<N, TIGHT, ST, FIRST_AS_EDGE>(L, legal, wave, B, mask, mask_pitch, lds_mask, lut, wb);
+  if (obs) emit_obs<N, TIGHT, ST, 4, FIRST_AS_EDGE>(L, R.h, wtm, wave, B, obs, obs_pitch, lds_obs, lut, wb);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1561,6 +1562,11 @@ template <int N, bool TIGHT, int SK, bool PACED>
 __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_kernel(RolloutArgs a) {
   using G = Geo<N>;
   constexpr int ST = PACED ? kStoreStreamWhole : kStoreThroughWhole;
+  // In place the ends of a wavefront's streams are better left to the L2: ordinary stores to the same lines meet there from ply to ply and
+  // do not go to memory each time.  With dense pitches a stream hardly ever starts on a line; with line-padded ones every stream does,
+  // and its first 1 KB counts as an end all the same (20 plies of 16384 games: 2.14 -> 1.94 GB leave the L2, 313 -> 282 us; x 65536
+  // 1154 -> 1043 us).  9x9 x 16384, where a wavefront writes half as much, gains nothing.
+  constexpr bool FIRST_AS_EDGE = N == 19 && TIGHT && !PACED;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
   __shared__ uint64_t tally_all[kWavesPerBlock][64];
@@ -1612,7 +1618,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
       uint8_t* const obs_t = a.obs ? a.obs + (size_t)slice * a.B * a.obs_pitch : nullptr;
       auto board_final = [&](uint32_t) {
         if constexpr (PACED) pace.wait();
-        if (obs_t) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, a.B, obs_t, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
+        if (obs_t) emit_obs<N, TIGHT, ST, 4, FIRST_AS_EDGE>(L, R.h, m.wtm, wave, a.B, obs_t, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
       };
       if constexpr (SK == 1) {
         sk_step_core_play<N, false, false>(L, R, m, g, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag,
@@ -1633,7 +1639,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
       if (a.term) a.term[e] = (uint8_t)((!skip && flag) ? 1 : 0);
     }
     if constexpr (PACED && !SK) pace.wait();
-    emit_outputs<N, TIGHT, ST>(L, R, legal, m.wtm, wave, a.B, a.mask ? a.mask + sb * a.mask_pitch : nullptr, a.mask_pitch,
+    emit_outputs<N, TIGHT, ST, FIRST_AS_EDGE>(L, R, legal, m.wtm, wave, a.B, a.mask ? a.mask + sb * a.mask_pitch : nullptr, a.mask_pitch,
                     (!SK && a.obs) ? a.obs + sb * a.obs_pitch : nullptr, a.obs_pitch, lds_mask_all[wib], lds_obs_all[wib], lut, a.wb);
     wave_lds_fence();
     slice = slice + 1 == a.slices ? 0 : slice + 1;

@@ -231,12 +231,13 @@ __device__ __forceinline__ void store_small(T* p, T v) {
   } else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(__builtin_bit_cast(vec4u, v)) : "memory");
 }
 
-// MAXBYTES: upper bound of nbytes.  MOST: upper bound of the rounds that are under way at once.  dst and nbytes must be the same in every lane.
+// MAXBYTES: upper bound of nbytes.  MOST: upper bound of the rounds that are under way at once.  FIRST_AS_EDGE: the first round counts as an end of the stream
+// even if it covers whole lines.  dst and nbytes must be the same in every lane.
 // The groups go out in rounds of 64, counted from the 128-byte line dst lies in, three or four rounds at a time: their bits and
 // table entries are all read before the first of them is stored, so that a wavefront that has its SIMD to itself waits twice for
 // LDS per batch and not twice per round.  A short stream's rounds stand in a loop and keep their tests in line: a kernel of 5 us
 // runs through code it has to fetch, and every jump is another fetch.
-template <int MAXBYTES, int ST = kStorePlain, int MOST = 4>
+template <int MAXBYTES, int ST = kStorePlain, int MOST = 4, bool FIRST_AS_EDGE = false>
 __device__ __forceinline__ void emit_bytes(const uint32_t* bits, const uint2* lut, uint8_t* dst, uint32_t nbytes, int lane) {
   constexpr int ROUNDS = (((MAXBYTES + 15) >> 4) + 7 + 63) / 64;   // groups + the at most 7 of the line before dst
   constexpr int WANTED = ROUNDS < 3 ? ROUNDS : (ROUNDS < 12 ? 3 : 4);
@@ -273,7 +274,7 @@ __device__ __forceinline__ void emit_bytes(const uint32_t* bits, const uint2* lu
       if constexpr (k < AT_ONCE) {
         const uint32_t g = g0 + 64u * k;
         if constexpr (INSIDE) store16_at<ST_WHOLE, 1024 * k>(out, offset, a[k], b[k]);
-        else if (ST_WHOLE != ST_EDGE && 64u * (r0 + k) >= first && 64u * (r0 + k + 1u) <= last) store16_at<ST_WHOLE, 1024 * k>(out, offset, a[k], b[k]);   // (the same in every lane)
+        else if (ST_WHOLE != ST_EDGE && (!FIRST_AS_EDGE || r0 + k > 0u) && 64u * (r0 + k) >= first && 64u * (r0 + k + 1u) <= last) store16_at<ST_WHOLE, 1024 * k>(out, offset, a[k], b[k]);   // (the same in every lane)
         else if (__builtin_expect(g >= first && g < last, 1)) store16_at<ST_EDGE, 1024 * k>(out, offset, a[k], b[k]);
       }
     };

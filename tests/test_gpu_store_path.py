@@ -1,0 +1,28 @@
+"""The line-padded layout is the faster one for outputs that leave the caches; rewritten in place it must not be the slower one."""
+import pytest
+import torch
+
+import paper_2303_17503_amd as pg
+
+pytestmark = pytest.mark.gpu
+
+
+def test_padded_rollouts_in_place_are_as_fast_as_dense_ones():
+    B, N, plies = 16384, 19, 20
+    envs = []
+    for padded in (False, True):
+        env = pg.GoEnv(B, N, seed=3, auto_reset=True, line_padded=padded)
+        out = [torch.zeros(1, B, pitch, dtype=torch.uint8, device="cuda") for pitch in (env.mask_pitch, env.obs_pitch)]
+        env.rollout(300, 3, 0)
+        envs.append((env, *out))
+    best = [float("inf")] * 2
+    for i in range(12):   # in turn; the games are the same on both sides
+        for k, (env, mask, obs) in enumerate(envs):
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            begin.record()
+            env.rollout(plies, 3, 300 + plies * i, mask=mask, obs=obs)
+            end.record()
+            end.synchronize()
+            best[k] = min(best[k], begin.elapsed_time(end))
+    # both measured 281 us, and 313 when every whole line was written through; the best of twelve differs by 1 % from run to run
+    assert best[1] < 1.06 * best[0], best

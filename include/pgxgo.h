@@ -145,6 +145,11 @@ int pgxgo_step_sample(pgxgo_t h, const int32_t* actions_dev, uint32_t seed, uint
 int pgxgo_rollout(pgxgo_t h, int32_t steps, int32_t slices, uint32_t seed, uint32_t t0, const int32_t* start_t_dev,
                   int32_t* actions_dev, float* rewards_dev, uint8_t* terminated_dev, uint8_t* mask_dev, uint8_t* obs_dev);
 
+/* Whether pgxgo_rollout with these steps and slices, with / without mask and observation, writes its outputs in time slots (large
+ * recordings; results do not depend on it): 1 or 0, or a negative error code.  games_at_once (nullable): how many of the batch's
+ * games the machine then holds at once (0: unknown, and nothing is written in time slots). */
+int pgxgo_rollout_in_time_slots(pgxgo_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int64_t* games_at_once);
+
 /* Search-facing step (Sec. 5: tree search calls step from copies of earlier states).  The handle's `batch`
  * environments are treated as a pool of state slots; for i in 0..n-1 (n <= batch):
  *     state[dst_slots_dev[i]] = step(state[src_slots_dev[i]], actions_dev[i])

@@ -100,6 +100,9 @@ int pgxhex_step_sample(pgxhex_t h, const int32_t* actions_dev, uint32_t seed, ui
 int pgxhex_rollout(pgxhex_t h, int32_t steps, int32_t slices, uint32_t seed, uint32_t t0, const int32_t* start_t_dev,
                    int32_t* actions_dev, float* rewards_dev, uint8_t* terminated_dev, uint8_t* mask_dev, uint8_t* obs_dev);
 
+/* As pgxgo_rollout_in_time_slots (pgxgo.h).  games_at_once is 0 with a board row per lane, which is never written in time slots. */
+int pgxhex_rollout_in_time_slots(pgxhex_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int64_t* games_at_once);
+
 /* Getters for the current state; each enqueues one kernel or copy into the caller's buffer. */
 int pgxhex_legal_mask(pgxhex_t h, uint8_t* dst_dev /* [batch][122] */);
 int pgxhex_observe(pgxhex_t h, uint8_t* dst_dev /* [batch][484] */);

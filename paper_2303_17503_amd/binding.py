@@ -51,6 +51,7 @@ def lib():
         L.pgxgo_random_actions.argtypes = [vp, u32, u32, vp, vp]
         L.pgxgo_step_sample.argtypes = [vp, vp, u32, u32, vp, vp]
         L.pgxgo_rollout.argtypes = [vp, i32, i32, u32, u32, vp, vp, vp, vp, vp, vp]
+        L.pgxgo_rollout_in_time_slots.argtypes = [vp, i32, i32, i32, i32, C.POINTER(C.c_int64)]
         L.pgxgo_step_slots.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp, vp]
         L.pgxgo_copy_slots.argtypes = [vp, i32, vp, vp]
         for n in ("legal_mask", "observe", "rewards", "terminated", "current_player"):
@@ -224,6 +225,14 @@ class GoEnv:
         rc = _lib.pgxgo_rollout(self._h, int(steps), S, seed & 0xFFFFFFFF, t0 & 0xFFFFFFFF, _ptr(start_t), _ptr(actions), _ptr(rewards),
                                    _ptr(terminated), _ptr(mask), _ptr(obs))
         if rc: _check(rc, "pgxgo_rollout")
+
+    def rollout_in_time_slots(self, steps, slices=1, mask=True, obs=True):
+        """(whether such a rollout writes its outputs in time slots, how many games the machine then holds at once)"""
+        games = C.c_int64()
+        rc = lib().pgxgo_rollout_in_time_slots(self._h, int(steps), int(slices), int(bool(mask)), int(bool(obs)), C.byref(games))
+        if rc < 0:
+            _check(rc, "pgxgo_rollout_in_time_slots")
+        return bool(rc), games.value
 
     def step_slots(self, src, actions, dst, mask=None, obs=None, rewards=None, terminated=None):
         """state[dst[i]] = step(state[src[i]], actions[i]); outputs of entry i in row i of the optional buffers."""

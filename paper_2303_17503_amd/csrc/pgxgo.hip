@@ -2036,27 +2036,41 @@ int launch_random(pgxgo_ctx* h, uint32_t seed, uint32_t t, const int32_t* start_
   return PGXGO_OK;
 }
 
+// calls f with the rollout kernel's TIGHT and SK for this handle as compile-time constants
+template <int N, class F>
+void with_rollout_variant(const pgxgo_ctx* h, F&& f) {
+  auto by_mode = [&](auto tight_c) {
+    if (!h->zt) f(tight_c, std::integral_constant<int, 0>{});
+    else if (h->sk_mode == 1) f(tight_c, std::integral_constant<int, 1>{});
+    else f(tight_c, std::integral_constant<int, 2>{});
+  };
+  if (tight_pitches<N>(h)) by_mode(std::true_type{});
+  else by_mode(std::false_type{});
+}
+
+template <int N>
+PaceArgs rollout_pace(const pgxgo_ctx* h, int steps, int slices, bool with_mask, bool with_obs) {
+  PaceArgs p;
+  with_rollout_variant<N>(h, [&](auto tight_c, auto sk_c) {
+    // bytes written per game and ply: the whole record with the dense and the line-padded pitches, else without the pad
+    constexpr bool T = decltype(tight_c)::value;
+    const int64_t mask_bytes = T ? h->mask_pitch : Geo<N>::A, obs_bytes = T ? h->obs_pitch : Geo<N>::OBS;
+    const double game_bytes = (double)((with_mask ? mask_bytes : 0) + (with_obs ? obs_bytes : 0));
+    p = pace_args<go_rollout_kernel<N, T, decltype(sk_c)::value, true>>(h->B, h->wb, game_bytes, steps, slices, kPaceBytesPerSecond, kWavesPerBlock);
+  });
+  return p;
+}
+
 template <int N>
 int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
   const dim3 grid(blocks_for_wb(h->B, h->wb)), block(64 * kWavesPerBlock);
-  const bool tight = tight_pitches<N>(h), sk = h->zt != nullptr;
-  // bytes written per game and ply: the whole record with the dense and the line-padded pitches, else without the pad
-  const int64_t mask_bytes = tight ? h->mask_pitch : Geo<N>::A, obs_bytes = tight ? h->obs_pitch : Geo<N>::OBS;
-  const double game_bytes = (double)((a.mask ? mask_bytes : 0) + (a.obs ? obs_bytes : 0));
-  auto go = [&](auto tight_c, auto sk_c) {
+  a.pace = rollout_pace<N>(h, a.steps, a.slices, a.mask != nullptr, a.obs != nullptr);
+  with_rollout_variant<N>(h, [&](auto tight_c, auto sk_c) {
     constexpr bool T = decltype(tight_c)::value;
     constexpr int M = decltype(sk_c)::value;
-    a.pace = pace_args<go_rollout_kernel<N, T, M, true>>(h->B, h->wb, game_bytes, a.slices, kPaceBytesPerSecond, kWavesPerBlock);
     if (a.pace.ply) hipLaunchKernelGGL((go_rollout_kernel<N, T, M, true>), grid, block, 0, h->stream, a);
     else hipLaunchKernelGGL((go_rollout_kernel<N, T, M, false>), grid, block, 0, h->stream, a);
-  };
-  auto by_mode = [&](auto tight_c) {
-    if (!sk) go(tight_c, std::integral_constant<int, 0>{});
-    else if (h->sk_mode == 1) go(tight_c, std::integral_constant<int, 1>{});
-    else go(tight_c, std::integral_constant<int, 2>{});
-  };
-  if (tight) by_mode(std::true_type{});
-  else by_mode(std::false_type{});
+  });
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
 }
@@ -2282,6 +2296,13 @@ int pgxgo_rollout(pgxgo_t h, int32_t steps, int32_t slices, uint32_t seed, uint3
   a.mask_pitch = h->mask_pitch; a.obs_pitch = h->obs_pitch;
   a.zt = h->zt; a.zcur = h->zcur; a.sk_mode = h->sk_mode;
   return DISPATCH_N(h, launch_rollout<19>(h, a), launch_rollout<9>(h, a));
+}
+
+int pgxgo_rollout_in_time_slots(pgxgo_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int64_t* games_at_once) {
+  if (!h || steps < 0 || slices < 1) return PGXGO_EINVAL;
+  const PaceArgs p = DISPATCH_N(h, rollout_pace<19>(h, steps, slices, with_mask != 0, with_obs != 0), rollout_pace<9>(h, steps, slices, with_mask != 0, with_obs != 0));
+  if (games_at_once) *games_at_once = (int64_t)8 * p.held * h->wb;
+  return p.ply != 0u ? 1 : 0;
 }
 
 int pgxgo_step_slots(pgxgo_t h, int32_t n, const int32_t* src_slots_dev, const int32_t* actions_dev, const int32_t* dst_slots_dev,

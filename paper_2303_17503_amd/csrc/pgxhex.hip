@@ -826,6 +826,10 @@ unsigned blocks_for(int B) {
   return ((waves + kWavesPerBlock - 1) / kWavesPerBlock + 7u) & ~7u;
 }
 unsigned lane_blocks_for(int B) { return ((unsigned)((B + 64 * kWavesPerBlock - 1) / (64 * kWavesPerBlock)) + 7u) & ~7u; }
+PaceArgs rollout_pace(const pgxhex_ctx* h, int steps, int slices, bool with_mask, bool with_obs) {   // only a board per lane is paced
+  if (!board_per_lane(h, true)) return PaceArgs{0u, 0u};
+  return pace_args<hex_rollout_lane_kernel<true>>(h->B, 64, (with_mask ? A : 0) + (with_obs ? OBS : 0), steps, slices, kPaceBytesPerSecond, kWavesPerBlock);
+}
 unsigned row_blocks(int B) { return (unsigned)(((size_t)B * N + 255) / 256); }
 
 int launch_emit(pgxhex_ctx* h, uint8_t* mask, uint8_t* obs) {
@@ -944,13 +948,20 @@ int pgxhex_rollout(pgxhex_t h, int32_t steps, int32_t slices, uint32_t seed, uin
   a.steps = steps; a.slices = slices; a.seed = seed; a.t0 = t0; a.start_t = start_t_dev;
   a.actions = actions_dev; a.rew = rewards_dev; a.term = terminated_dev; a.mask = mask_dev; a.obs = obs_dev;
   if (board_per_lane(h, true)) {
-    a.pace = pace_args<hex_rollout_lane_kernel<true>>(h->B, 64, (mask_dev ? A : 0) + (obs_dev ? OBS : 0), slices, kPaceBytesPerSecond, kWavesPerBlock);
+    a.pace = rollout_pace(h, steps, slices, mask_dev != nullptr, obs_dev != nullptr);
     if (a.pace.ply) hipLaunchKernelGGL(hex_rollout_lane_kernel<true>, dim3(lane_blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
     else hipLaunchKernelGGL(hex_rollout_lane_kernel<false>, dim3(lane_blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
   }
   else hipLaunchKernelGGL(hex_rollout_kernel, dim3(blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
   HIPCHK(hipGetLastError());
   return PGXHEX_OK;
+}
+
+int pgxhex_rollout_in_time_slots(pgxhex_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int64_t* games_at_once) {
+  if (!h || steps < 0 || slices < 1) return PGXHEX_EINVAL;
+  const PaceArgs p = rollout_pace(h, steps, slices, with_mask != 0, with_obs != 0);
+  if (games_at_once) *games_at_once = (int64_t)8 * p.held * 64;
+  return p.ply != 0u ? 1 : 0;
 }
 
 int pgxhex_random_actions(pgxhex_t h, uint32_t seed, uint32_t t, const int32_t* start_t_dev, int32_t* actions_dev) {

@@ -93,7 +93,7 @@ inline uint32_t waves_held_per_eighth(int waves_per_block) {
   }();
   return (uint32_t)(blocks * 32 * waves_per_block);
 }
-// T for a rollout over `slices` output slices of which the wavefronts that are on the machine together write `ply_bytes` bytes per
+// T for a rollout that writes `slices` output slices, of which the wavefronts that are on the machine together write `ply_bytes` bytes per
 // ply; 0: no pacing.  The recording has to outgrow the 256 MB memory-side cache (19x19 x 16384 games, 107 MB per ply, without /
 // with slots: 2 slices 38.6 / 44.3 us, 3 slices 65.2 / 61.8, 16 slices 358 / 281), and a ply has to hold enough bytes for memory
 // and not the plies' own instructions to set the pace (20 MB of 19x19 x 3000 games: 271 / 284 us for 64 plies; 29 MB of
@@ -103,10 +103,12 @@ inline uint32_t pace_ticks(double ply_bytes, int slices, double bytes_per_second
   if (slices < 2 || ply_bytes * slices < 280.0 * kMB || ply_bytes < 23.0 * kMB) return 0u;
   return (uint32_t)(ply_bytes * (256.0 * 1e8 / bytes_per_second));
 }
-// game_bytes: bytes per game and ply, wb: games per wavefront
+// game_bytes: bytes per game and ply, wb: games per wavefront, slices: of the caller's buffers, of which `steps` plies write min(steps, slices)
+// (2 plies of 19x19 x 16384 into 16 slices 45.3 us with slots, 38.1 without; 1 ply of Hex x 262144 into 8 slices 35.4 / 30.1)
 template <auto KERNEL>
-inline PaceArgs pace_args(int B, int wb, double game_bytes, int slices, double bytes_per_second, int waves_per_block) {
+inline PaceArgs pace_args(int B, int wb, double game_bytes, int steps, int slices, double bytes_per_second, int waves_per_block) {
   PaceArgs p;
+  if (steps < slices) slices = steps;
   p.held = waves_held_per_eighth<KERNEL>(waves_per_block);
   const double together = 8.0 * p.held * wb;
   p.ply = pace_ticks((B < together ? B : together) * game_bytes, slices, bytes_per_second);

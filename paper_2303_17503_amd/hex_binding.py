@@ -30,6 +30,7 @@ def lib():
         L.pgxhex_random_actions.argtypes = [vp, u32, u32, vp, vp]
         L.pgxhex_step_sample.argtypes = [vp, vp, u32, u32, vp, vp]
         L.pgxhex_rollout.argtypes = [vp, i32, i32, u32, u32, vp, vp, vp, vp, vp, vp]
+        L.pgxhex_rollout_in_time_slots.argtypes = [vp, i32, i32, i32, i32, C.POINTER(C.c_int64)]
         for n in ("legal_mask", "observe", "rewards", "terminated", "current_player"):
             getattr(L, "pgxhex_" + n).argtypes = [vp, vp]
         L.pgxhex_export_state.argtypes = [vp] * 8
@@ -156,6 +157,14 @@ class HexEnv:
         if start_t is not None: _need(start_t, torch.int32, (self.B,), "start_t")
         _check(lib().pgxhex_rollout(self._h, int(steps), S, seed & 0xFFFFFFFF, t0 & 0xFFFFFFFF, _ptr(start_t), _ptr(actions), _ptr(rewards),
                                     _ptr(terminated), _ptr(mask), _ptr(obs)), "pgxhex_rollout")
+
+    def rollout_in_time_slots(self, steps, slices=1, mask=True, obs=True):
+        """(whether such a rollout writes its outputs in time slots, how many games the machine then holds at once)"""
+        games = C.c_int64()
+        rc = lib().pgxhex_rollout_in_time_slots(self._h, int(steps), int(slices), int(bool(mask)), int(bool(obs)), C.byref(games))
+        if rc < 0:
+            _check(rc, "pgxhex_rollout_in_time_slots")
+        return bool(rc), games.value
 
     def _get(self, name, shape, dtype, out):
         out = torch.empty(shape, dtype=dtype, device=self.device) if out is None else _need(out, dtype, shape, name)

@@ -53,3 +53,29 @@ def test_go(N, B, slices, superko, more):
 @pytest.mark.parametrize("B,slices", [(45001, 12), (470003, 2)])
 def test_hex(B, slices):
     check(lambda: pg.HexEnv(B, seed=4, auto_reset=True), slices, 11, lambda e: e.A, lambda e: e.OBS)
+
+
+@pytest.mark.parametrize("game,steps,slices,slots", [
+    ("go", 1, 16, False), ("go", 2, 16, False), ("go", 2, 2, False), ("go", 16, 2, False), ("go", 3, 16, True), ("go", 3, 3, True), ("go", 50, 16, True),
+    ("go", 50, 1, False), ("go", 0, 16, False), ("hex", 1, 8, False), ("hex", 2, 8, True), ("hex", 8, 8, True), ("hex", 8, 1, False)])
+def test_what_counts_is_what_a_launch_writes(game, steps, slices, slots):
+    """107 MB a ply in Go, 159 MB in Hex: two and one of them stay in the 256 MB cache, however many slices the buffers have"""
+    env = pg.GoEnv(16384, 19) if game == "go" else pg.HexEnv(262144)
+    assert env.rollout_in_time_slots(steps, slices)[0] == slots
+
+
+def test_fewer_plies_than_slices():
+    B, slices, seed = 16384, 6, 5
+    a, b = (pg.GoEnv(B, 19, seed=2, auto_reset=True) for _ in range(2))
+    new = lambda n, pitch: torch.full((n, B, pitch), 7, dtype=torch.uint8, device="cuda")  # noqa: E731
+    mask, obs, m1, o1 = new(slices, a.mask_pitch), new(slices, a.obs_pitch), new(1, a.mask_pitch), new(1, a.obs_pitch)
+    t = 0
+    for steps in (1, 4, 2):   # without slots, with them, without
+        mask.fill_(7)
+        obs.fill_(7)
+        a.rollout(steps, seed, t, slices=slices, mask=mask, obs=obs)
+        for i in range(steps):
+            b.rollout(1, seed, t + i, mask=m1, obs=o1)
+            assert torch.equal(mask[i], m1[0]) and torch.equal(obs[i], o1[0]), (steps, i)
+        assert (mask[steps:] == 7).all() and (obs[steps:] == 7).all(), steps
+        t += steps

@@ -93,14 +93,15 @@ inline uint32_t waves_held_per_eighth(int waves_per_block) {
   }();
   return (uint32_t)(blocks * 32 * waves_per_block);
 }
-// T for a rollout that writes `slices` output slices, of which the wavefronts that are on the machine together write `ply_bytes` bytes per
-// ply; 0: no pacing.  The recording has to outgrow the 256 MB memory-side cache (19x19 x 16384 games, 107 MB per ply, without /
+// T for a rollout that writes `slices` output slices, `record_bytes` in all, of which the wavefronts that are on the machine together write
+// `ply_bytes` per ply; 0: no pacing.  The recording has to outgrow the 256 MB memory-side cache (19x19 x 16384 games, 107 MB per ply, without /
 // with slots: 2 slices 38.6 / 44.3 us, 3 slices 65.2 / 61.8, 16 slices 358 / 281), and a ply has to hold enough bytes for memory
 // and not the plies' own instructions to set the pace (20 MB of 19x19 x 3000 games: 271 / 284 us for 64 plies; 29 MB of
-// 9x9 x 20000: 282 / 206 for 40; 18 MB of Hex x 30000: 359 / 349 for 64).
-inline uint32_t pace_ticks(double ply_bytes, int slices, double bytes_per_second) {
+// 9x9 x 20000: 282 / 206 for 40; 18 MB of Hex x 30000: 359 / 349 for 64).  Batches that run in generations count whole for the first of
+// these: 2 slices of 19x19 x 65536 200 / 161 us, with superko 248 / 180, 5 of 9x9 x 65536 103 / 99.
+inline uint32_t pace_ticks(double ply_bytes, double record_bytes, int slices, double bytes_per_second) {
   constexpr double kMB = 1048576.0;
-  if (slices < 2 || ply_bytes * slices < 280.0 * kMB || ply_bytes < 23.0 * kMB) return 0u;
+  if (slices < 2 || record_bytes < 280.0 * kMB || ply_bytes < 23.0 * kMB) return 0u;
   return (uint32_t)(ply_bytes * (256.0 * 1e8 / bytes_per_second));
 }
 // game_bytes: bytes per game and ply, wb: games per wavefront, slices: of the caller's buffers, of which `steps` plies write min(steps, slices)
@@ -111,7 +112,7 @@ inline PaceArgs pace_args(int B, int wb, double game_bytes, int steps, int slice
   if (steps < slices) slices = steps;
   p.held = waves_held_per_eighth<KERNEL>(waves_per_block);
   const double together = 8.0 * p.held * wb;
-  p.ply = pace_ticks((B < together ? B : together) * game_bytes, slices, bytes_per_second);
+  p.ply = pace_ticks((B < together ? B : together) * game_bytes, (double)B * slices * game_bytes, slices, bytes_per_second);
   return p;
 }
 

@@ -9,9 +9,12 @@ import paper_2303_17503_amd as pg
 pytestmark = pytest.mark.gpu
 
 
-def check(make, slices, seed, mask_of, obs_of):
+def check(make, slices, seed, mask_of, obs_of, generations):
     rec, one = make(), make()
     B = rec.B
+    slots, games = rec.rollout_in_time_slots(slices, slices)
+    assert slots and not one.rollout_in_time_slots(1, 1)[0]
+    assert (B > games) == generations, games
     new = lambda *shape, dtype=torch.uint8: torch.zeros(*shape, dtype=dtype, device="cuda")  # noqa: E731
     mask, obs = new(slices, B, mask_of(rec)), new(slices, B, obs_of(rec))
     rew, term, act = new(slices, B, 2, dtype=torch.float32), new(slices, B), new(slices, B, dtype=torch.int32)
@@ -30,7 +33,7 @@ def check(make, slices, seed, mask_of, obs_of):
         assert torch.equal(a[k], b[k]), k
 
 
-@pytest.mark.parametrize("N,B,slices,superko,more", [
+@pytest.mark.parametrize("N,B,slices,superko,more", [   # the last four: more games than the machine holds at once
     (9, 17001, 13, 0, {}),
     (9, 17001, 13, 0, {"obs_pitch": 1400, "mask_pitch": 90}),
     (9, 17001, 13, 2, {}),
@@ -38,8 +41,10 @@ def check(make, slices, seed, mask_of, obs_of):
     (19, 5003, 10, 0, {"line_padded": True}),
     (19, 5003, 10, 1, {}),
     (19, 5003, 10, 2, {"mask_pitch": 363}),
-    (19, 19001, 3, 0, {}),      # more games than the machine holds at once
+    (19, 19001, 3, 0, {}),
     (9, 52001, 4, 0, {}),
+    (9, 75001, 3, 0, {}),
+    (19, 26001, 2, 2, {}),
 ])
 def test_go(N, B, slices, superko, more):
     def make():
@@ -47,12 +52,12 @@ def test_go(N, B, slices, superko, more):
         if superko:
             env.enable_superko(superko)
         return env
-    check(make, slices, 11, lambda e: e.mask_pitch, lambda e: e.obs_pitch)
+    check(make, slices, 11, lambda e: e.mask_pitch, lambda e: e.obs_pitch, B > 19000 or (N == 9 and B > 37000))
 
 
 @pytest.mark.parametrize("B,slices", [(45001, 12), (470003, 2)])
 def test_hex(B, slices):
-    check(lambda: pg.HexEnv(B, seed=4, auto_reset=True), slices, 11, lambda e: e.A, lambda e: e.OBS)
+    check(lambda: pg.HexEnv(B, seed=4, auto_reset=True), slices, 11, lambda e: e.A, lambda e: e.OBS, B > 400000)
 
 
 @pytest.mark.parametrize("game,steps,slices,slots", [

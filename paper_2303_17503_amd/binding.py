@@ -1,6 +1,8 @@
 """ctypes binding of libpgxgo.so; names follow include/pgxgo.h (pgxgo_<name> -> GoEnv.<name>)."""
 import ctypes as C
+import importlib
 import os
+import warnings
 
 import torch
 
@@ -8,10 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("PGXGO_LIB") or os.path.join(HERE, "libpgxgo.so")   # PGXGO_LIB: load another build of the same library
 
 _lib = None
-try:   # the per-ply calls' checks in native code (csrc/fastcall.cpp); without it the same checks run here
-    from . import _fastcall as _fast
-except ImportError:
-    _fast = None
+_fast = None   # the per-ply calls' checks in native code (csrc/fastcall.cpp), loaded with the library
 
 
 def _address(fn):
@@ -27,9 +26,18 @@ class _Opts(C.Structure):
                 ("obs_pitch", C.c_int32), ("mask_pitch", C.c_int32), ("stream", C.c_void_p)]
 
 
+def _load_fast():
+    """The same checks run in Python where the extension is not there (no C++ compiler, or built for another torch)."""
+    try:
+        return importlib.import_module("._fastcall", __package__)
+    except ImportError as e:
+        warnings.warn(f"the calls made once per ply check their arguments in Python, which takes longer: {e}", RuntimeWarning, stacklevel=3)
+        return None
+
+
 def lib():
     """Loads the HIP library; raises if it has not been built (no fallback of any kind)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise PgxGoError(f"{LIB_PATH} is missing: build it with `python paper_2303_17503_amd/build.py` "
@@ -70,6 +78,7 @@ def lib():
         L.pgxgo_strerror.argtypes = [C.c_int]
         L.pgxgo_last_hip_error.restype = C.c_int
         L.pgxgo_lane_shift_probe.argtypes = [vp, vp, vp]
+        _fast = _load_fast()
         _lib = L
     return _lib
 

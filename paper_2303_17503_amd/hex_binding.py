@@ -3,10 +3,12 @@ import ctypes as C
 
 import torch
 
-from .binding import PgxGoError, _address, _fast, _need, _ptr, lib as _golib
+from . import binding
+from .binding import PgxGoError, _address, _need, _ptr, lib as _golib
 
 N, P, A, OBS = 11, 121, 122, 484
 _ready = False
+_fast = None   # as in binding.py
 
 
 class _Opts(C.Structure):
@@ -15,7 +17,7 @@ class _Opts(C.Structure):
 
 def lib():
     """The shared library with the pgxhex_* prototypes declared; raises if it has not been built (no fallback)."""
-    global _ready
+    global _ready, _fast
     L = _golib()
     if not _ready:
         vp, i32, u32 = C.c_void_p, C.c_int32, C.c_uint32
@@ -42,6 +44,7 @@ def lib():
         L.pgxhex_strerror.restype = C.c_char_p
         L.pgxhex_strerror.argtypes = [C.c_int]
         L.pgxhex_last_hip_error.restype = C.c_int
+        _fast = binding._fast
         _ready = True
     return L
 

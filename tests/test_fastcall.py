@@ -1,13 +1,51 @@
 """The native argument checks of the per-ply calls refuse what the Python checks refuse, and pass on what they pass on."""
 import ctypes as C
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
 
 import paper_2303_17503_amd as pg
-from paper_2303_17503_amd import binding
+from paper_2303_17503_amd import _fastcall as fast
+from paper_2303_17503_amd import binding, build
 
-fast = pytest.importorskip("paper_2303_17503_amd._fastcall")
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def python(code):
+    return subprocess.run([sys.executable, "-W", "always", "-c", code], cwd=ROOT, capture_output=True, text=True)
+
+
+def test_an_extension_that_does_not_load_is_reported():
+    r = python("import sys; sys.modules['paper_2303_17503_amd._fastcall'] = None\n"
+               "import paper_2303_17503_amd as pg; pg.lib(); pg.hex_binding.lib()\n"
+               "assert pg.binding._fast is None and pg.hex_binding._fast is None")
+    assert r.returncode == 0 and r.stderr.count("check their arguments in Python") == 1, r.stderr
+
+
+def test_an_extension_built_after_the_import_is_used():
+    r = python("import sys; sys.modules['paper_2303_17503_amd._fastcall'] = None\n"
+               "import paper_2303_17503_amd as pg; del sys.modules['paper_2303_17503_amd._fastcall']\n"
+               "pg.lib(); pg.hex_binding.lib(); assert pg.binding._fast is not None and pg.hex_binding._fast is pg.binding._fast")
+    assert r.returncode == 0 and "in Python" not in r.stderr, r.stderr
+
+
+def test_the_library_is_built_without_a_host_compiler(monkeypatch, tmp_path):
+    run = subprocess.run
+
+    def no_compiler(cmd, **kw):
+        if cmd[0] == "g++":
+            raise FileNotFoundError("g++")
+        return run(["true"], **kw)   # stands for hipcc
+
+    monkeypatch.setattr(build, "FAST", str(tmp_path / "_fastcall.so"))
+    (tmp_path / "_fastcall.so").write_text("an older build")
+    monkeypatch.setattr(build.subprocess, "run", no_compiler)
+    with pytest.warns(RuntimeWarning, match="not built"):
+        assert build.build() == build.LIB
+    assert not (tmp_path / "_fastcall.so").exists()
 
 
 def test_nothing_but_cuda_tensors_reaches_the_entry_point():

@@ -504,7 +504,7 @@ __device__ __forceinline__ void lane_emit(const B128& bk, const B128& wt, const 
     stream_put<16, 1, 14>(lds_obs, O, head + (uint32_t)(OBS * lane));
   }
   wave_lds_fence();
-  if (mask) emit_bytes<64 * A, ST>(lds_mask, lut, mask + (size_t)b0 * A, (uint32_t)(nb * A), lane);
+  if (mask) emit_bytes<64 * A, ST, 4, false, true>(lds_mask, lut, mask + (size_t)b0 * A, (uint32_t)(nb * A), lane);
   if (obs) emit_bytes<64 * OBS, ST>(lds_obs, lut, obs + (size_t)b0 * OBS, (uint32_t)(nb * OBS), lane);
   wave_lds_fence();
 }

@@ -1943,11 +1943,13 @@ size_t output_bytes_per_ply(const pgxgo_ctx* h, bool with_mask, bool with_obs) {
 // and output rounds.  So: the smallest number of wavefronts per SIMD that W boards per wavefront allow, and then the fewest boards
 // per wavefront that need no more (measured per ply, one launch per ply: 9x9 x 2048 games 5.3 us with 2 boards, 7.0 with 1, 5.9
 // with 6; x 4096 5.7 with 4, 8.9 with 1; x 8192 6.5 with 4, 6.8 with 6, 7.9 with 2; x 7001 6.1 with 4, 6.4 with 6; 19x19 x 3072
-// 7.4 with 3, 10.0 with 1; 32 plies of 9x9 x 8192 in one launch 106 us with 4, 116 with 6).  At 19x19, where W is 3, two boards
-// against three gain nothing beyond 3072 games (x 4097 34.8 / 34.7 us for 4 plies, 4 plies of x 3237 in one launch 26.9 / 26.5).
+// 7.4 with 3, 10.0 with 1; 32 plies of 9x9 x 8192 in one launch 106 us with 4, 116 with 6).  At 19x19 that would be two boards
+// instead of W = 3 from 3073 to 4096 games, and there three are kept: two save 2 to 4 % of a ply per launch (8 of x 3300 65.7 / 67.9 us, x 4096
+// 67.7 / 69.5) but cost 7 to 10 % of a rollout in place (20 plies of x 3300 102.0 / 94.4, x 4096 103.2 / 95.7; recorded 2 to 4 %), and a
+// handle has one count for both.
 template <int N>
 int auto_boards_per_wavefront(int B) {
-  if (N == 19 && B > 1024 * Geo<N>::W) return Geo<N>::W;
+  if (N == 19 && B > 1024 * Geo<N>::W) return Geo<N>::W;   // (beyond 4096 games the rule gives W by itself)
   const int per_simd = (int)(((int64_t)B + 1024 * Geo<N>::W - 1) / (1024 * Geo<N>::W));
   return (int)(((int64_t)B + 1024 * (int64_t)per_simd - 1) / (1024 * (int64_t)per_simd));
 }

@@ -2050,6 +2050,7 @@ void with_rollout_variant(const pgxgo_ctx* h, F&& f) {
   else by_mode(std::false_type{});
 }
 
+// (with the repetition rule a rollout is never as fast as the cache: 16384 games, 2 to 8 slices, 2 to 80 plies, 0.72 to 0.97 with slots)
 template <int N>
 PaceArgs rollout_pace(const pgxgo_ctx* h, int steps, int slices, bool with_mask, bool with_obs) {
   PaceArgs p;
@@ -2058,7 +2059,8 @@ PaceArgs rollout_pace(const pgxgo_ctx* h, int steps, int slices, bool with_mask,
     constexpr bool T = decltype(tight_c)::value;
     const int64_t mask_bytes = T ? h->mask_pitch : Geo<N>::A, obs_bytes = T ? h->obs_pitch : Geo<N>::OBS;
     const double game_bytes = (double)((with_mask ? mask_bytes : 0) + (with_obs ? obs_bytes : 0));
-    p = pace_args<go_rollout_kernel<N, T, decltype(sk_c)::value, true>>(h->B, h->wb, game_bytes, steps, slices, kPaceBytesPerSecond, kWavesPerBlock);
+    p = pace_args<go_rollout_kernel<N, T, decltype(sk_c)::value, true>>(h->B, h->wb, game_bytes, steps, slices,
+                                                                           decltype(sk_c)::value ? 0.0 : 2.0, kPaceBytesPerSecond, kWavesPerBlock);
   });
   return p;
 }

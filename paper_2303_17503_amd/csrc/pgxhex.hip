@@ -826,9 +826,11 @@ unsigned blocks_for(int B) {
   return ((waves + kWavesPerBlock - 1) / kWavesPerBlock + 7u) & ~7u;
 }
 unsigned lane_blocks_for(int B) { return ((unsigned)((B + 64 * kWavesPerBlock - 1) / (64 * kWavesPerBlock)) + 7u) & ~7u; }
+// (time with slots over time without where slices are rewritten: 3 slices of 262144 games, 477 MB, 0.98 for 6 plies, 1.07 for 9; 5 slices 0.94 for 15,
+// 1.00 for 50; 8 slices 0.84 to 0.88; 3 slices of a million, 596 MB on the machine, 0.95 for 3 plies, 1.16 for 6)
 PaceArgs rollout_pace(const pgxhex_ctx* h, int steps, int slices, bool with_mask, bool with_obs) {   // only a board per lane is paced
   if (!board_per_lane(h, true)) return PaceArgs{0u, 0u};
-  return pace_args<hex_rollout_lane_kernel<true>>(h->B, 64, (with_mask ? A : 0) + (with_obs ? OBS : 0), steps, slices, kPaceBytesPerSecond, kWavesPerBlock);
+  return pace_args<hex_rollout_lane_kernel<true>>(h->B, 64, (with_mask ? A : 0) + (with_obs ? OBS : 0), steps, slices, 2.4, kPaceBytesPerSecond, kWavesPerBlock);
 }
 unsigned row_blocks(int B) { return (unsigned)(((size_t)B * N + 255) / 256); }
 

@@ -95,26 +95,31 @@ inline uint32_t waves_held_per_eighth(int waves_per_block) {
   }();
   return (uint32_t)(blocks * 32 * waves_per_block);
 }
-// T for a rollout that writes `slices` output slices, `record_bytes` in all, of which the wavefronts that are on the machine together write
-// `ply_bytes` per ply; 0: no pacing.  The recording has to outgrow the 256 MB memory-side cache (19x19 x 16384 games, 107 MB per ply, without /
-// with slots: 2 slices 38.6 / 44.3 us, 3 slices 65.2 / 61.8, 16 slices 358 / 281), and a ply has to hold enough bytes for memory
-// and not the plies' own instructions to set the pace (20 MB of 19x19 x 3000 games: 271 / 284 us for 64 plies; 29 MB of
-// 9x9 x 20000: 282 / 206 for 40; 18 MB of Hex x 30000: 359 / 349 for 64).  Batches that run in generations count whole for the first of
-// these: 2 slices of 19x19 x 65536 200 / 161 us, with superko 248 / 180, 5 of 9x9 x 65536 103 / 99.
-inline uint32_t pace_ticks(double ply_bytes, double record_bytes, int slices, double bytes_per_second) {
-  constexpr double kMB = 1048576.0;
-  if (slices < 2 || record_bytes < 280.0 * kMB || ply_bytes < 23.0 * kMB) return 0u;
-  return (uint32_t)(ply_bytes * (256.0 * 1e8 / bytes_per_second));
-}
-// game_bytes: bytes per game and ply, wb: games per wavefront, slices: of the caller's buffers, of which `steps` plies write min(steps, slices)
-// (2 plies of 19x19 x 16384 into 16 slices 45.3 us with slots, 38.1 without; 1 ply of Hex x 262144 into 8 slices 35.4 / 30.1)
+// The pace of a rollout of `steps` plies into buffers of `slices` slices, of which min(steps, slices) are written; game_bytes: bytes
+// per game and ply, wb: games per wavefront.  A rollout is paced if memory sets its speed:
+//  * Lines that are written once have to outgrow the 256 MB memory-side cache, batches that run in generations counted whole (without
+//    / with slots: 19x19 x 16384, 107 MB per ply, 2 slices 38.1 / 44.3 us, 3 slices 65.2 / 61.8, 16 slices 358 / 281; 2 slices of 65536
+//    200 / 161).
+//  * Where the plies rewrite slices (steps > slices), much of what they rewrite is still in the cache.  So the slices of the games on the
+//    machine have to outgrow it by more, the more is rewritten: by `rewrite` times the rewritten share of the plies (time with slots over
+//    time without, 19x19: 4 slices of 16384 games, 426 MB, 0.85 for 4 plies, 1.06 for 6, 1.11 for 40; 6 slices 0.93 for 12, 0.99 for 18,
+//    1.07 for 60; 8 slices 0.84 to 0.92; 4 slices of 65536, 479 MB on the machine, 0.88 for 4 plies, 1.17 for 12, 1.28 for 40), and
+//    hardly by more if the machine is not full (8 slices of 8000, 416 MB, 0.80 for 8 plies, 0.98 for 40; 16 of 9x9 x 20000, 467 MB, 0.83
+//    to 0.86).
+//  * A ply has to hold enough bytes for memory and not its own instructions to set the pace (20 MB of 19x19 x 3000 games: 271 / 284
+//    us for 64 plies; 29 MB of 9x9 x 20000: 282 / 206 for 40; 18 MB of Hex x 30000: 359 / 349 for 64).
 template <auto KERNEL>
-inline PaceArgs pace_args(int B, int wb, double game_bytes, int steps, int slices, double bytes_per_second, int waves_per_block) {
+inline PaceArgs pace_args(int B, int wb, double game_bytes, int steps, int slices, double rewrite, double bytes_per_second, int waves_per_block) {
+  constexpr double kMB = 1048576.0;
   PaceArgs p;
-  if (steps < slices) slices = steps;
+  p.ply = 0u;
   p.held = waves_held_per_eighth<KERNEL>(waves_per_block);
-  const double together = 8.0 * p.held * wb;
-  p.ply = pace_ticks((B < together ? B : together) * game_bytes, (double)B * slices * game_bytes, slices, bytes_per_second);
+  const double together = 8.0 * p.held * wb, at_once = B < together ? B : together, written = steps < slices ? steps : slices;
+  const double rewritten = steps > slices ? 1.0 - (double)slices / steps : 0.0;
+  if (B < 0.7 * together && rewrite > 0.5) rewrite = 0.5;
+  const double footprint = (rewritten * rewrite > 0.0 ? at_once : (double)B) * game_bytes * written;
+  if (written < 2.0 || footprint < 280.0 * kMB * (1.0 + rewrite * rewritten) || at_once * game_bytes < 23.0 * kMB) return p;
+  p.ply = (uint32_t)(at_once * game_bytes * (256.0 * 1e8 / bytes_per_second));
   return p;
 }
 

@@ -84,3 +84,17 @@ def test_fewer_plies_than_slices():
             assert torch.equal(mask[i], m1[0]) and torch.equal(obs[i], o1[0]), (steps, i)
         assert (mask[steps:] == 7).all() and (obs[steps:] == 7).all(), steps
         t += steps
+
+
+@pytest.mark.parametrize("game,B,superko,steps,slices,slots", [
+    ("go", 16384, 0, 4, 4, True), ("go", 16384, 0, 6, 4, False), ("go", 16384, 0, 50, 4, False), ("go", 16384, 0, 50, 8, True),
+    ("go", 65536, 0, 2, 2, True), ("go", 65536, 0, 3, 2, False), ("go", 65536, 0, 50, 4, False), ("go", 65536, 0, 50, 8, True),
+    ("go", 8000, 0, 24, 8, True), ("go", 8000, 0, 60, 6, False), ("go", 16384, 2, 50, 3, True), ("go", 16384, 1, 50, 3, True),
+    ("hex", 262144, 0, 3, 3, True), ("hex", 262144, 0, 30, 3, False), ("hex", 262144, 0, 80, 8, True), ("hex", 1000000, 0, 6, 3, False)])
+def test_rewritten_slices_stay_in_the_cache(game, B, superko, steps, slices, slots):
+    """Plies that rewrite what the launch itself has written find much of it in the memory-side cache, which is faster than slots made for
+    DRAM: only footprints far beyond the cache are written in slots then."""
+    env = pg.GoEnv(B, 19) if game == "go" else pg.HexEnv(B)
+    if superko:
+        env.enable_superko(superko)
+    assert env.rollout_in_time_slots(steps, slices)[0] == slots

@@ -19,14 +19,12 @@
 //     chains touched by the move are re-flooded (the merged chain and at most four opposing neighbours),
 //     a flood stops as soon as two liberties have been seen, and several growth steps are taken per
 //     (comparatively expensive) look at the liberties.
-//   * History is stored point-major: 16 bits per point = 8 plies x (black, white), two points per dword,
-//     so a ply is one shift-and-insert per dword and the [N][N][17] byte observation is produced by
+//   * The emission takes the history point-major: 16 bits per point = 8 plies x (black, white), two points per
+//     dword, so a ply is one shift-and-insert per dword and the [N][N][17] byte observation is produced by
 //     building the 17-bit-per-point bit stream of a board in LDS and expanding 16 bits -> 16 bytes per
 //     lane through a 256-entry LDS table, stored as aligned 16-byte vectors.
-//   * HBM layout: struct of arrays of 16-byte vectors, plane k holds dwords 4k..4k+3 of every row record,
-//     indexed [env*N + row], so every load/store instruction of a wavefront touches one contiguous run.
-//     Only the planes of a row that changed are written back (absolute colours make unchanged points
-//     keep their history word).
+//   * HBM layout: a game's state is one run of bytes (State); at 19x19 the history lies there position by position, so
+//     that a ply writes the new position over the oldest one instead of every point's history.
 //   * Kernels: go_step_kernel (one ply per launch, optionally drawing the next random action),
 //     go_rollout_kernel (T plies per launch, state in registers), go_step_slots_kernel (tree search: step
 //     from and to arbitrary state slots), go_step_superko_kernel (one ply with the positional-superko rule:
@@ -76,9 +74,10 @@ struct Geo {
   static constexpr int STRIDE = N + 1;        // lanes per board, one of them the zero sentinel row
   static constexpr int W = 63 / STRIDE;       // boards per wavefront
   static constexpr int HD = (N + 1) / 2;      // history dwords per row, two points per dword
-  static constexpr int REC = HD + 4;          // + black, white, atari-black, atari-white
-  static constexpr int NQ = REC / 4;          // full 16-byte planes per row record
-  static constexpr int REM = REC % 4;         // dwords of the last, narrower plane
+  static constexpr bool RINGED = N > 16;      // how the history lies in memory, see State
+  static constexpr int CUR = RINGED ? 2 : 1;  // dwords of a row's stones and atari set
+  static constexpr int TAIL = RINGED ? HD - 8 : HD - 4;   // history dwords of a row beyond its first part
+  static constexpr int HIST = RINGED ? 8 : 4;             // dwords of that first part
   static constexpr uint32_t FULL = (1u << N) - 1u;
   static constexpr int OBS = P * 17;          // observation bytes per board
   static constexpr int ROWBITS = N * 17;      // observation bits contributed by one row
@@ -88,29 +87,32 @@ struct Geo {
   static constexpr int A_PAD = (A + 127) / 128 * 128;
   static constexpr int OBS_DW = ((OBS_PAD + 15 + 31) / 32 + 3) / 4 * 4;   // LDS dwords of one board's bit stream (+ up to 15 lead bits)
   static constexpr int MASK_DW = ((A + 15 + 31) / 32 + 3) / 4 * 4;
-  static constexpr size_t row_bytes = (size_t)REC * 4;
+  static constexpr int GAME = (N * (CUR + TAIL + HIST) + 3) / 4 * 4;   // dwords of a game's state, whole 16-byte groups
+  static constexpr size_t row_bytes = (size_t)(HD + 4) * 4;   // room per row in the caller's state buffer
+  static_assert(GAME * 4 <= N * row_bytes, "the state fits the size the caller was told");
   // lanes holding the rows of board slot j
   static constexpr uint64_t seg(int j) { return ((1ull << N) - 1ull) << (j * STRIDE + 1); }
 };
 
 // per-board scalars, one 16-byte record per environment
-//   x: ko point or -1     y: steps[0:16) | passes[16:18) | white_to_move[18] | terminated[19] | black_player[20]
+//   x: ko point or -1     y: steps[0:16) | passes[16:18) | white_to_move[18] | terminated[19] | black_player[20] | head[21:24) (State)
 //   z: episode            w: illegal actions received
 struct Meta {
   int ko, steps, passes, wtm, term, bp;
+  int head;              // where the ring of positions begins (State)
   uint32_t episode, illegal;
 };
 __device__ __forceinline__ Meta unpack_meta(uint4 v) {
   Meta m;
   m.ko = (int)v.x;
-  m.steps = v.y & 0xFFFF; m.passes = (v.y >> 16) & 3; m.wtm = (v.y >> 18) & 1; m.term = (v.y >> 19) & 1; m.bp = (v.y >> 20) & 1;
+  m.steps = v.y & 0xFFFF; m.passes = (v.y >> 16) & 3; m.wtm = (v.y >> 18) & 1; m.term = (v.y >> 19) & 1; m.bp = (v.y >> 20) & 1; m.head = (v.y >> 21) & 7;
   m.episode = v.z; m.illegal = v.w;
   return m;
 }
 __device__ __forceinline__ uint4 pack_meta(const Meta& m) {
   uint4 v;
   v.x = (uint32_t)m.ko;
-  v.y = (uint32_t)m.steps | ((uint32_t)m.passes << 16) | ((uint32_t)m.wtm << 18) | ((uint32_t)m.term << 19) | ((uint32_t)m.bp << 20);
+  v.y = (uint32_t)m.steps | ((uint32_t)m.passes << 16) | ((uint32_t)m.wtm << 18) | ((uint32_t)m.term << 19) | ((uint32_t)m.bp << 20) | ((uint32_t)m.head << 21);
   v.z = m.episode; v.w = m.illegal;
   return v;
 }
@@ -170,86 +172,252 @@ struct Lane {
 
 template <int N>
 struct Row {                      // per-lane registers: one row of one board
-  uint32_t h[Geo<N>::HD];         // history halfwords, bit 2i = black i plies ago, bit 2i+1 = white
   uint32_t bk, wt, ab, aw;        // stones and atari sets (stones of chains with exactly one liberty)
 };
 
-// record dword k of row idx lives in plane k/4 (16-byte planes first, then one narrower plane)
+// ------------------------------------------------------------------------------------------------
+// The state of a game in memory, GAME dwords in a row, so that a game met by itself (tree search) is a few neighbouring lines:
+//   hist   the history, HIST dwords per row, see below
+//   tail   TAIL more dwords per row of it
+//   cur    the row's stones and atari set, CUR dwords (an atari stone has its stone's colour, so one set serves both)
+// The emission wants the history point by point (Points): 16 bits per point, bit 2i = black i plies ago, bit 2i+1 = white.  Held like
+// that in memory a ply rewrites every point that changed within the last eight.
+//   9x9: it is held like that, hist is one 16-byte vector per row (columns 0 .. 7), tail column 8, and those that changed are
+//     written.
+//   19x19 (RINGED): columns 0 .. 15 are held position by position, a dword per row and position (ring_word); the position i plies
+//     ago is number (head + i) mod 8, head being kept with the game's scalars, so that a ply overwrites the oldest one and moves
+//     the head.  tail holds columns 16 .. 18 point by point.  A ply writes 20 bytes of a row; with everything point by point it was
+//     56, or the changed ones of four pieces.  Turning positions into points costs about as many instructions as pushing them did
+//     (exchange_columns_and_positions).  Bytes moved per ply of 65536 games 571 -> 516 MB; us per ply, before / since: 16384 games
+//     20.2 / 19.3, 28000 36.3 / 34.1, 65536 83.5 / 80.4, 65536 without observation 30.1 / 28.1, 16384 with superko 28.5 / 27.3.  At
+//     9x9, where hardly a byte leaves the caches, a ring is 3 to 7 % slower than this.
+// As planes over all games instead (every piece one run of all games) a search, which takes games from anywhere, is 3 to 7 % slower
+// and 40000 games 5 % faster.
+// ------------------------------------------------------------------------------------------------
 template <int N>
-__device__ __forceinline__ void load_row(const uint4* __restrict__ planes, size_t rows_total, const Lane<N>& L, Row<N>& R) {
-  using G = Geo<N>;
-  uint32_t rec[G::NQ * 4 + 4];
-#pragma unroll
-  for (int k = 0; k < G::NQ * 4 + 4; ++k) rec[k] = 0u;
-  if (L.valid) {
-    const size_t idx = (size_t)L.slot * N + L.r;
-#pragma unroll
-    for (int k = 0; k < G::NQ; ++k) {
-      uint4 v = planes[(size_t)k * rows_total + idx];
-      rec[4 * k] = v.x; rec[4 * k + 1] = v.y; rec[4 * k + 2] = v.z; rec[4 * k + 3] = v.w;
-    }
-    const uint32_t* tail = (const uint32_t*)(planes + (size_t)G::NQ * rows_total);
-    if constexpr (G::REM == 2) { uint2 v = *(const uint2*)(tail + idx * 2); rec[4 * G::NQ] = v.x; rec[4 * G::NQ + 1] = v.y; }
-    if constexpr (G::REM == 1) { rec[4 * G::NQ] = tail[idx]; }
+struct State {                    // where one row of one game lies
+  uint32_t *hist, *tail, *cur;
+  static constexpr int NEXT = N;  // dwords from one position of the ring to the next
+  __device__ __forceinline__ State(uint32_t* base, const Lane<N>& L) {
+    using G = Geo<N>;
+    uint32_t* game = base + (size_t)(uint32_t)L.slot * G::GAME;
+    hist = game + L.r * (G::RINGED ? 1 : G::HIST); tail = game + N * G::HIST + L.r * G::TAIL; cur = game + N * (G::HIST + G::TAIL) + L.r * G::CUR;
   }
-#pragma unroll
-  for (int k = 0; k < G::HD; ++k) R.h[k] = rec[k];
-  R.bk = rec[G::HD]; R.wt = rec[G::HD + 1]; R.ab = rec[G::HD + 2]; R.aw = rec[G::HD + 3];
-}
-
-// ST: kind of the 16-byte stores (wave_common.hpp)
-template <int N, int ST = kStorePlain>
-__device__ __forceinline__ void store_row(uint4* __restrict__ planes, size_t rows_total, const Lane<N>& L, const Row<N>& R) {
-  using G = Geo<N>;
-  uint32_t rec[G::NQ * 4 + 4];
-#pragma unroll
-  for (int k = 0; k < G::HD; ++k) rec[k] = R.h[k];
-  rec[G::HD] = R.bk; rec[G::HD + 1] = R.wt; rec[G::HD + 2] = R.ab; rec[G::HD + 3] = R.aw;
-  if (L.valid) {
-    const size_t idx = (size_t)L.slot * N + L.r;
-#pragma unroll
-    for (int k = 0; k < G::NQ; ++k)
-      store16<ST>(&planes[(size_t)k * rows_total + idx], make_uint2(rec[4 * k], rec[4 * k + 1]), make_uint2(rec[4 * k + 2], rec[4 * k + 3]));
-    uint32_t* tail = (uint32_t*)(planes + (size_t)G::NQ * rows_total);
-    if constexpr (G::REM == 2) *(uint2*)(tail + idx * 2) = make_uint2(rec[4 * G::NQ], rec[4 * G::NQ + 1]);
-    if constexpr (G::REM == 1) tail[idx] = rec[4 * G::NQ];
-  }
-}
-
-// The four row words as loaded, kept to tell at store time which of them changed.
-struct RowWords {
-  uint32_t bk, wt, ab, aw;
 };
 template <int N>
-__device__ __forceinline__ RowWords row_words(const Row<N>& R) { return RowWords{R.bk, R.wt, R.ab, R.aw}; }
-
-// Stores only the 16-byte planes of this row whose content differs from what the kernel loaded.  With colours
-// stored absolutely, a history word changes only while its point changed within the last 8 plies, so most
-// rows of most planes are unchanged from ply to ply.  hdirty: bit k set = a history dword of plane k changed (from
-// push_history; all ones after a reset); Old: the row words as loaded.
+struct History {                  // per-lane registers: the history of one row as it lies in memory
+  uint32_t s[Geo<N>::HIST], tail[Geo<N>::TAIL];
+  uint32_t changed;               // not RINGED: bit 0 / 1 set = hist / tail differs from what memory holds
+};
 template <int N>
-__device__ __forceinline__ void store_row_changed(uint4* __restrict__ planes, size_t rows_total, const Lane<N>& L, const Row<N>& R, uint32_t hdirty,
-                                                  const RowWords& Old) {
+struct Points {                   // column 2j in the low half of h[j], column 2j+1 in the high half
+  uint32_t h[Geo<N>::HD];
+};
+
+template <int N>
+__device__ __forceinline__ void load_row(uint32_t* state, const Lane<N>& L, Row<N>& R) {
   using G = Geo<N>;
-  uint32_t rec[G::NQ * 4 + 4], dif[G::NQ * 4 + 4];
-#pragma unroll
-  for (int k = 0; k < G::NQ * 4 + 4; ++k) { rec[k] = 0u; dif[k] = 0u; }
-#pragma unroll
-  for (int k = 0; k < G::HD; ++k) rec[k] = R.h[k];
-  rec[G::HD] = R.bk; rec[G::HD + 1] = R.wt; rec[G::HD + 2] = R.ab; rec[G::HD + 3] = R.aw;
-  dif[G::HD] = R.bk ^ Old.bk; dif[G::HD + 1] = R.wt ^ Old.wt; dif[G::HD + 2] = R.ab ^ Old.ab; dif[G::HD + 3] = R.aw ^ Old.aw;
+  uint2 v = make_uint2(0u, 0u);
   if (L.valid) {
-    const size_t idx = (size_t)L.slot * N + L.r;
+    const State<N> S(state, L);
+    if constexpr (G::CUR == 2) v = *(const uint2*)S.cur;
+    else v.x = *S.cur;
+  }
+  // black, white and atari set, N bits each, from bit 0 on
+  uint32_t at;
+  R.bk = v.x & G::FULL;
+  if constexpr (G::CUR == 2) { R.wt = __builtin_amdgcn_alignbit(v.y, v.x, N) & G::FULL; at = (v.y >> (2 * N - 32)) & G::FULL; }
+  else { R.wt = (v.x >> N) & G::FULL; at = (v.x >> (2 * N)) & G::FULL; }
+  R.ab = at & R.bk; R.aw = at & R.wt;
+}
+template <int N>
+__device__ __forceinline__ void load_history(uint32_t* state, const Lane<N>& L, History<N>& H) {
+  using G = Geo<N>;
 #pragma unroll
-    for (int k = 0; k <= G::NQ; ++k) {   // k = NQ: the narrower last plane
-      const uint32_t diff = ((hdirty >> k) & 1u) | dif[4 * k] | dif[4 * k + 1] | dif[4 * k + 2] | dif[4 * k + 3];
-      if (k < G::NQ) {
-        if (diff) planes[(size_t)k * rows_total + idx] = make_uint4(rec[4 * k], rec[4 * k + 1], rec[4 * k + 2], rec[4 * k + 3]);
-      } else {
-        uint32_t* tail = (uint32_t*)(planes + (size_t)G::NQ * rows_total);
-        if constexpr (G::REM == 2) { if (diff) *(uint2*)(tail + idx * 2) = make_uint2(rec[4 * G::NQ], rec[4 * G::NQ + 1]); }
-        if constexpr (G::REM == 1) { if (diff) tail[idx] = rec[4 * G::NQ]; }
-      }
+  for (int k = 0; k < G::HIST; ++k) H.s[k] = 0u;
+#pragma unroll
+  for (int k = 0; k < G::TAIL; ++k) H.tail[k] = 0u;
+  H.changed = 0u;
+  if (L.valid) {
+    const State<N> S(state, L);
+    if constexpr (G::RINGED) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) H.s[k] = S.hist[k * S.NEXT];
+      const uint2 v = *(const uint2*)S.tail;
+      H.tail[0] = v.x; H.tail[1] = v.y;
+    } else {
+      const uint4 v = *(const uint4*)S.hist;
+      H.s[0] = v.x; H.s[1] = v.y; H.s[2] = v.z; H.s[3] = v.w;
+      H.tail[0] = *S.tail;
+    }
+  }
+}
+// ST: kind of the stores (store_small)
+template <int N, int ST = kStorePlain>
+__device__ __forceinline__ void store_row(const State<N>& S, const Row<N>& R) {
+  const uint32_t at = R.ab | R.aw;
+  if constexpr (Geo<N>::CUR == 2) store_small<ST>((uint2*)S.cur, make_uint2(R.bk | (R.wt << N), (R.wt >> (32 - N)) | (at << (2 * N - 32))));
+  else store_small<ST>(S.cur, R.bk | (R.wt << N) | (at << (2 * N)));
+}
+template <int N, int ST = kStorePlain>
+__device__ __forceinline__ void store_tail(const State<N>& S, const History<N>& H) {
+  if constexpr (Geo<N>::TAIL == 2) store_small<ST>((uint2*)S.tail, make_uint2(H.tail[0], H.tail[1]));
+  else store_small<ST>(S.tail, H.tail[0]);
+}
+// the whole state of a row
+template <int N>
+__device__ __forceinline__ void store_all(uint32_t* state, const Lane<N>& L, const Row<N>& R, const History<N>& H) {
+  if (!L.valid) return;
+  const State<N> S(state, L);
+  store_row<N>(S, R);
+  store_tail<N>(S, H);
+  if constexpr (Geo<N>::RINGED) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) S.hist[k * S.NEXT] = H.s[k];
+  } else *(uint4*)S.hist = make_uint4(H.s[0], H.s[1], H.s[2], H.s[3]);
+}
+
+// A row's stones with the colours side by side: bits 2j / 2j+1 = black / white at column 2j (lo), at column 2j+1 (hi)
+struct Pairs {
+  uint32_t lo, hi;
+};
+__device__ __forceinline__ Pairs pairs_of(uint32_t bk, uint32_t wt) {
+  return Pairs{(bk & 0x55555555u) | ((wt & 0x55555555u) << 1), ((bk >> 1) & 0x55555555u) | (wt & 0xAAAAAAAAu)};
+}
+__device__ __forceinline__ uint32_t pair_dword(const Pairs& p, int j) { return ((p.lo >> (2 * j)) & 3u) | (((p.hi >> (2 * j)) & 3u) << 16); }   // of columns 2j, 2j+1
+// columns 0 .. 15 of a row as a dword of the ring: the even ones in the low half, the odd ones in the high half
+__device__ __forceinline__ uint32_t ring_word(const Pairs& p) { return (p.lo & 0xFFFFu) | (p.hi << 16); }
+
+// Exchanges, in eight dwords, bit k of the dword's index with bit k + 1 of the bit position within a half (k = 0, 1, 2).  Applied to
+// the ring dwords of eight positions, whose halves hold column pair j at bits 2j and 2j+1, it gives in dword j the two bits of
+// position i at 2i and 2i+1: Points.  It is its own inverse.
+__device__ __forceinline__ void exchange_columns_and_positions(uint32_t (&x)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t a = x[i], b = x[i + 4];
+    x[i] = __builtin_amdgcn_perm(b, a, 0x06020400u);        // bytes a0 b0 a2 b2
+    x[i + 4] = __builtin_amdgcn_perm(b, a, 0x07030501u);    // bytes a1 b1 a3 b3
+  }
+#pragma unroll
+  for (int d = 2; d >= 1; d >>= 1) {
+    const uint32_t mask = d == 2 ? 0x0F0F0F0Fu : 0x33333333u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (i & d) continue;
+      const uint32_t a = x[i], b = x[i + d];
+      x[i] = (a & mask) | ((b << (2 * d)) & ~mask);
+      x[i + d] = ((a >> (2 * d)) & mask) | (b & ~mask);
+    }
+  }
+}
+// both halves of x rotated right by 2 * head bits
+__device__ __forceinline__ uint32_t rotate_halves(uint32_t x, int head) {
+  typedef unsigned short halves __attribute__((ext_vector_type(2)));
+  const unsigned short right = (unsigned short)(2 * head), left = (unsigned short)((16 - 2 * head) & 15);
+  const halves v = __builtin_bit_cast(halves, x);
+  return __builtin_bit_cast(uint32_t, (halves)((v >> halves{right, right}) | (v << halves{left, left})));
+}
+template <int N>
+__device__ __forceinline__ Points<N> points_of(const History<N>& H, int head) {
+  using G = Geo<N>;
+  Points<N> Q;
+  uint32_t x[G::HIST];
+#pragma unroll
+  for (int k = 0; k < G::HIST; ++k) x[k] = H.s[k];
+  if constexpr (G::RINGED) {
+    exchange_columns_and_positions(x);
+#pragma unroll
+    for (int k = 0; k < G::HIST; ++k) x[k] = rotate_halves(x[k], head);
+  }
+#pragma unroll
+  for (int j = 0; j < G::HD; ++j) Q.h[j] = j < G::HIST ? x[j < G::HIST ? j : 0] : H.tail[j < G::HIST ? 0 : j - G::HIST];
+  return Q;
+}
+// the inverse, with the ring's head at 0
+template <int N>
+__device__ __forceinline__ History<N> history_of(const Points<N>& Q) {
+  using G = Geo<N>;
+  History<N> H;
+#pragma unroll
+  for (int k = 0; k < G::HIST; ++k) H.s[k] = Q.h[k];
+  if constexpr (G::RINGED) exchange_columns_and_positions(H.s);
+#pragma unroll
+  for (int k = 0; k < G::TAIL; ++k) H.tail[k] = Q.h[G::HIST + k];
+  H.changed = ~0u;
+  return H;
+}
+
+// a6: the position (bk, wt) becomes the newest one of a board that moved
+// (which: all ones on a board that moved, else 0.  A mask and not a condition: the compiler would make branches of it, 4 % of a rollout)
+__device__ __forceinline__ uint32_t mask_of(bool which) { return in_place(which ? ~0u : 0u); }
+__device__ __forceinline__ uint32_t pushed(uint32_t h, const Pairs& p, int j, uint32_t which) {
+  const uint32_t v = ((h << 2) & 0xFFFCFFFCu) | pair_dword(p, j);
+  return (v & which) | (h & ~which);
+}
+template <int N>
+__device__ __forceinline__ void push_points(Points<N>& Q, uint32_t bk, uint32_t wt, bool moved) {
+  const Pairs p = pairs_of(bk, wt);
+  const uint32_t which = mask_of(moved);
+#pragma unroll
+  for (int j = 0; j < Geo<N>::HD; ++j) Q.h[j] = pushed(Q.h[j], p, j, which);
+}
+template <int N>
+__device__ __forceinline__ void push_history(History<N>& H, int& head, uint32_t bk, uint32_t wt, bool moved) {
+  using G = Geo<N>;
+  const Pairs p = pairs_of(bk, wt);
+  const uint32_t which = mask_of(moved);
+  if constexpr (G::RINGED) {
+    const uint32_t word = ring_word(p);
+    if (moved) head = (head + 7) & 7;
+    const int at = moved ? head : 8;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) H.s[k] = k == at ? word : H.s[k];
+  } else {
+    uint32_t dif = 0u;
+#pragma unroll
+    for (int k = 0; k < G::HIST; ++k) { const uint32_t v = pushed(H.s[k], p, k, which); dif |= v ^ H.s[k]; H.s[k] = v; }
+    H.changed |= dif ? 1u : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < G::TAIL; ++k) { const uint32_t v = pushed(H.tail[k], p, G::HIST + k, which); H.changed |= v != H.tail[k] ? 2u : 0u; H.tail[k] = v; }
+}
+template <int N>
+__device__ __forceinline__ void clear_points(Points<N>& Q) {
+#pragma unroll
+  for (int j = 0; j < Geo<N>::HD; ++j) Q.h[j] = 0u;
+}
+template <int N>
+__device__ __forceinline__ void clear_history(History<N>& H) {
+#pragma unroll
+  for (int k = 0; k < Geo<N>::HIST; ++k) H.s[k] = 0u;
+#pragma unroll
+  for (int k = 0; k < Geo<N>::TAIL; ++k) H.tail[k] = 0u;
+  H.changed = ~0u;
+}
+// Kind of the state's stores in a launch whose outputs are stored as OUT.  A launch whose outputs go past the caches is so large that its
+// state does not stay in them either, and what it leaves dirty in the L2s (32 MB) would have to be written back at its end: written
+// through, 65536 games of 19x19 81.6 -> 79.8 us, 40000 52.6 -> 48.1.  Smaller launches lose 1 to 5 % that way.
+constexpr int state_store_kind(int out) { return out == kStoreStreamWhole ? kStoreThrough : kStorePlain; }
+
+// What a ply changes of a row in memory, after push_history and clear_history: nothing unless the board moved or was re-initialised.
+template <int N, int ST>
+__device__ __forceinline__ void store_ply(uint32_t* state, const Lane<N>& L, const Row<N>& R, const History<N>& H, int head, bool moved, bool reset) {
+  if (L.valid && (moved || reset)) {
+    const State<N> S(state, L);
+    store_row<N, ST>(S, R);
+    if constexpr (Geo<N>::RINGED) {
+      store_tail<N, ST>(S, H);
+      store_small<ST>(&S.hist[head * S.NEXT], ring_word(pairs_of(R.bk, R.wt)));   // zero after a reset, as the others are below
+    } else {
+      if (H.changed & 1u) store_small<ST>((uint4*)S.hist, make_uint4(H.s[0], H.s[1], H.s[2], H.s[3]));
+      if (H.changed & 2u) store_tail<N, ST>(S, H);
+    }
+  }
+  if constexpr (Geo<N>::RINGED) {
+    if (__ballot(reset) != 0ull && L.valid && reset) {
+      const State<N> S(state, L);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) store_small<ST>(&S.hist[k * S.NEXT], 0u);
     }
   }
 }
@@ -321,12 +489,11 @@ __device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[G
 #pragma unroll
   for (int k = 0; k < G::NR; ++k) S[k] = 0u;
   const uint32_t cb = wtm ? 0u : 1u;
-  const uint32_t swapmask = wtm ? 0x55555555u : 0u;
+  const uint32_t swap = wtm ? 1u : 0u;
 #pragma unroll
   for (int jd = 0; jd < G::HD; ++jd) {
     uint32_t w = h[jd];
-    uint32_t x = (w ^ (w >> 1)) & swapmask;
-    w ^= x | (x << 1);
+    w = ((w >> swap) & 0x55555555u) | ((w << swap) & 0xAAAAAAAAu);
     uint32_t lo17 = (w & 0xFFFFu) | (cb << 16);
     uint32_t hi17 = (2 * jd + 1 < N) ? ((w >> 16) | (cb << 16)) : 0u;
     uint32_t low32 = lo17 | (hi17 << 17), high2 = hi17 >> 15;
@@ -379,11 +546,11 @@ __device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[G
 }
 
 template <int N, bool TIGHT, int ST = kStorePlain, bool FIRST_AS_EDGE = false>
-__device__ __forceinline__ void emit_outputs(const Lane<N>& L, const Row<N>& R, uint32_t legal, int wtm, int wave, int B,
+__device__ __forceinline__ void emit_outputs(const Lane<N>& L, const Points<N>& Q, uint32_t legal, int wtm, int wave, int B,
                                              uint8_t* mask, int64_t mask_pitch, uint8_t* obs, int64_t obs_pitch,
                                              uint32_t* lds_mask, uint32_t* lds_obs, const uint2* lut, int wb = Geo<N>::W) {
   if (mask) emit_mask<N, TIGHT, ST, FIRST_AS_EDGE>(L, legal, wave, B, mask, mask_pitch, lds_mask, lut, wb);
-  if (obs) emit_obs<N, TIGHT, ST, 4, FIRST_AS_EDGE>(L, R.h, wtm, wave, B, obs, obs_pitch, lds_obs, lut, wb);
+  if (obs) emit_obs<N, TIGHT, ST, 4, FIRST_AS_EDGE>(L, Q.h, wtm, wave, B, obs, obs_pitch, lds_obs, lut, wb);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -468,32 +635,9 @@ __device__ __forceinline__ Move gate_move(const Lane<N>& L, const Row<N>& R, con
   return mv;
 }
 
-// history push: every halfword shifts by one ply and takes the position (bk, wt) in its low bits
-// hdirty: bit k is set when a history dword of the row record's 16-byte plane k changed
-template <int N>
-__device__ __forceinline__ void push_history(uint32_t (&h)[Geo<N>::HD], uint32_t bk, uint32_t wt, bool moved, uint32_t& hdirty) {
-  const uint32_t lo = (bk & 0x55555555u) | ((wt & 0x55555555u) << 1);   // bit 2j / 2j+1: black / white at column 2j
-  const uint32_t hi = ((bk >> 1) & 0x55555555u) | (wt & 0xAAAAAAAAu);   // the same for column 2j+1
-  uint32_t acc[(Geo<N>::HD + 3) / 4];
-#pragma unroll
-  for (int k = 0; k < (Geo<N>::HD + 3) / 4; ++k) acc[k] = 0u;
-#pragma unroll
-  for (int jd = 0; jd < Geo<N>::HD; ++jd) {
-    const uint32_t cur = ((lo >> (2 * jd)) & 3u) | (((hi >> (2 * jd)) & 3u) << 16);
-    const uint32_t pushed = ((h[jd] << 2) & 0xFFFCFFFCu) | cur;
-    acc[jd / 4] |= moved ? (pushed ^ h[jd]) : 0u;
-    h[jd] = moved ? pushed : h[jd];
-  }
-  hdirty = 0u;
-#pragma unroll
-  for (int k = 0; k < (Geo<N>::HD + 3) / 4; ++k) hdirty |= acc[k] ? (1u << k) : 0u;
-}
-
-// a8: back to the initial state of the next episode (Sec. 4.1); the seat is drawn anew
+// a8: back to the initial state of the next episode (Sec. 4.1); the seat is drawn anew.  The history is the caller's to clear.
 template <int N>
 __device__ __forceinline__ void reset_board(const Lane<N>& L, Row<N>& R, Meta& m, uint32_t seed) {
-#pragma unroll
-  for (int jd = 0; jd < Geo<N>::HD; ++jd) R.h[jd] = 0u;
   R.bk = R.wt = R.ab = R.aw = 0u;
   m.ko = -1; m.steps = 0; m.passes = 0; m.wtm = 0; m.term = 0;
   m.episode += 1;
@@ -578,20 +722,30 @@ struct Floods {
   }
 };
 
-// a3-a8 for every board of the wavefront; registers in, registers out.
-// Out: rewards by player id, `flag` = the terminated output (game ended in this ply, or had ended before),
-// `captured` = the stones this ply removed, `reset` = the board was re-initialised by auto-reset.
-// `hdirty` = which planes of the row record hold a changed history dword (see push_history; all ones after a reset).
-template <int N>
-__device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m, const Rules& cfg, const Move& mv, float& rew0, float& rew1,
-                                           bool& flag, uint32_t& captured, bool& reset, uint32_t& hdirty, uint64_t* tally) {
+// What one ply did to a board (the same in every lane of the board, but for `captured`)
+struct Ply {
+  float rew0, rew1;    // rewards by player id
+  bool moved;          // a stone was placed or the player passed: the history takes the new position
+  bool flag;           // the terminated output: the game ended in this ply, or had ended before
+  bool reset;          // the board was re-initialised by auto-reset
+  uint32_t captured;   // the stones this ply removed, this row's
+};
+
+// a3-a5, a7 and a8 for every board of the wavefront; registers in, registers out.  a6, the history, is the caller's: clear() is
+// called, with the lanes concerned, where a board is re-initialised (a push of the then empty board leaves a cleared history as it is).
+struct NothingToClear {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <int N, class Clear = NothingToClear>
+__device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, const Rules& cfg, const Move& mv, uint64_t* tally, Clear&& clear = Clear{}) {
+  Ply out;
   using G = Geo<N>;
   const bool playing = mv.playing, is_pass = mv.is_pass, illegal = mv.illegal, frozen = mv.frozen;
   const int pr = mv.pr, pc = mv.pc;
   const uint32_t pbit = (L.valid && L.r == pr) ? (1u << pc) : 0u;
   const int wtm0 = m.wtm;
-  rew0 = 0.f; rew1 = 0.f;
-  captured = 0u;
+  float rew0 = 0.f, rew1 = 0.f;
+  out.captured = 0u;
 
   // ---- a3-a5: place the stone, capture, update the atari sets, ko ----------------------------------------
   if (__ballot(playing) != 0ull) {
@@ -612,7 +766,7 @@ __device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m,
     tally_clear(tally, L.lane);
     if (__ballot(capseed != 0u) != 0ull) {
       const uint32_t cap = flood_plain(capseed, aopp);
-      if (playing) captured = cap;
+      if (playing) out.captured = cap;
       opp &= ~cap; aopp &= ~cap;
       released |= dilate(cap);
       // simple ko: exactly one stone taken by a stone without friends whose only liberty is the vacated point.  One tally of the
@@ -677,9 +831,6 @@ __device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m,
     m.steps += 1;
     m.wtm ^= 1;
   }
-  // ---- a6: history push ---------------------------------------------------------------------------------
-  push_history<N>(R.h, R.bk, R.wt, moved, hdirty);
-
   // ---- a7: termination and Tromp-Taylor area score ------------------------------------------------------
   const bool score = moved && (m.passes >= 2 || m.steps >= cfg.max_steps);
   if (__ballot(score) != 0ull) {
@@ -708,28 +859,14 @@ __device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m,
     m.illegal += 1;
   }
   const bool ended = score || illegal;
-  reset = ended && cfg.auto_reset != 0;
+  out.reset = ended && cfg.auto_reset != 0;
   if (ended) {
     m.term = 1;
-    // ---- a8: auto-reset (Sec. 4.1) -------------------------------------------------------------------------
-    if (cfg.auto_reset) { reset_board<N>(L, R, m, cfg.seed); hdirty = ~0u; }
+    if (cfg.auto_reset) { reset_board<N>(L, R, m, cfg.seed); clear(); }   // a8 (Sec. 4.1)
   }
-  flag = ended || frozen;
-}
-template <int N>
-__device__ __forceinline__ void apply_move(const Lane<N>& L, Row<N>& R, Meta& m, const Rules& cfg, const Move& mv, float& rew0, float& rew1,
-                                           bool& flag, uint32_t& captured, bool& reset, uint64_t* tally) {
-  uint32_t hdirty;
-  apply_move<N>(L, R, m, cfg, mv, rew0, rew1, flag, captured, reset, hdirty, tally);
-}
-
-template <int N, bool GATE>
-__device__ __forceinline__ void step_core(const Lane<N>& L, Row<N>& R, Meta& m, const Rules& cfg, bool skip, bool want_pass, bool want_point,
-                                          int pr_in, int pc_in, float& rew0, float& rew1, bool& flag, uint64_t* tally) {
-  const Move mv = gate_move<N, GATE>(L, R, m, skip, want_pass, want_point, pr_in, pc_in);
-  uint32_t captured;
-  bool reset;
-  apply_move<N>(L, R, m, cfg, mv, rew0, rew1, flag, captured, reset, tally);
+  out.rew0 = rew0; out.rew1 = rew1;
+  out.moved = moved; out.flag = ended || frozen;
+  return out;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -742,7 +879,6 @@ struct StepArgs {            // what is not needed before the first loads
   uint8_t* obs;
   int64_t mask_pitch, obs_pitch;
   int store_kind;            // kind of the output stores, by the bytes the launch writes (store_kind_for)
-  int sparse_store;
   Rules rules;
   // fused sampler
   uint32_t sample_seed, sample_t;
@@ -750,7 +886,7 @@ struct StepArgs {            // what is not needed before the first loads
 };
 
 template <int N, bool SAMPLE, bool TIGHT, int ST>
-__global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint4* planes, uint4* meta, const int32_t* actions, const int32_t* start_t, int B,
+__global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint32_t* state, uint4* meta, const int32_t* actions, const int32_t* start_t, int B,
                                                                         int wb, uint32_t eighth, StepArgs a) {   // wb: boards per wavefront of this launch
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
@@ -760,11 +896,12 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint4* 
   const int wib = wave_in_block();
   const int wave = piece_of_block(eighth) * kWavesPerBlock + wib;
   const Lane<N> L(wave, threadIdx.x & 63, B, wb);   // in a wavefront beyond the batch no lane is valid
-  const size_t rows_total = (size_t)B * N;
 
   // the loads are issued first and fly while the block fills its lookup table
   Row<N> R;
-  load_row<N>(planes, rows_total, L, R);
+  History<N> H;
+  load_row<N>(state, L, R);
+  load_history<N>(state, L, H);
   const uint4 meta_raw = L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
   const int act = L.boardok ? actions[L.b] : -1;
   // loaded here and not where it is used: a load after the output stores would have to wait for them (one counter);
@@ -775,7 +912,6 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint4* 
   fill_spread_table(lut);
   if (wave * wb >= B) return;   // whole wavefront idle; there is no block-wide barrier anywhere below
   const bool wait_start = (int64_t)a.sample_t < (int64_t)held_back(start_raw);
-  const RowWords W_loaded = row_words<N>(R);
   Meta m = unpack_meta(meta_raw);
 
   // a1/a2: decode the action and gate it
@@ -785,29 +921,21 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint4* 
   const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, pr, pc);
 
   // a3-a8
-  float rew0, rew1;
-  bool flag, reset;
-  uint32_t captured, hdirty;
-  apply_move<N>(L, R, m, a.rules, mv, rew0, rew1, flag, captured, reset, hdirty, tally_all[wib]);
+  const Ply ply = apply_move<N>(L, R, m, a.rules, mv, tally_all[wib], [&]() { clear_history<N>(H); });
+  push_history<N>(H, m.head, R.bk, R.wt, ply.moved);
   if (!skip && L.valid && L.r == 0) {
-    *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(rew0, rew1);
-    store_small<ST>(&a.term[L.b], (uint8_t)(flag ? 1 : 0));
+    *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(ply.rew0, ply.rew1);
+    store_small<ST>(&a.term[L.b], (uint8_t)(ply.flag ? 1 : 0));
   }
 
   // ---- a10 / a9: observation and legal mask of the player now to move ---------------------------------------
-  if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
+  if (a.obs) emit_obs<N, TIGHT, ST>(L, points_of<N>(H, m.head).h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
   const uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
   if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, B, a.mask, a.mask_pitch, lds_mask_all[wib], lut, wb);
 
   // ---- a11: store the state --------------------------------------------------------------------------------
-  if (!skip) {
-    // Writing only the changed planes pays while state and outputs stay resident in the memory-side cache
-    // (partial lines merge there); beyond it partial lines cost a read-modify-write in DRAM and whole rows win.
-    // (whole rows written through the L2: 65536 games 87.9 -> 85.5 us per ply; with the non-temporal hint they are slower)
-    if (a.sparse_store) store_row_changed<N>(planes, rows_total, L, R, hdirty, W_loaded);
-    else store_row<N, kStoreThrough>(planes, rows_total, L, R);
-    if (L.valid && L.r == 0) meta[L.b] = pack_meta(m);
-  }
+  store_ply<N, state_store_kind(ST)>(state, L, R, H, m.head, ply.moved, ply.reset);
+  if (!skip && L.valid && L.r == 0) store_small<state_store_kind(ST)>(&meta[L.b], pack_meta(m));
   if (SAMPLE) {
     const Draw<N> d = draw_action<N>(L, legal, a.sample_seed, a.sample_t, wait_start);
     if (L.valid && L.r == 0) a.next_actions[L.b] = d.action();
@@ -1152,15 +1280,14 @@ __device__ __forceinline__ void sk_clear_tables(const Lane<N>& L, bool flagged, 
 // legality gate only if it is not one of the position's forbidden plays (`forb`, updated to those of the new position),
 // the new position goes into the table, an auto-reset clears it.  tab_r / tab_w / game: see sk_insert, sk_clear_tables.
 // GATE as in gate_move.  Out: as apply_move.
-// board_final(hdirty) is called once the rows and scalars of the new position (an auto-reset included) are final: the
-// caller emits the observation and may store the state there.  EARLY: before the table work, so that those stores are
+// board_final(moved, reset) is called once the rows and scalars of the new position (an auto-reset included) are final: the
+// caller brings its history up to date there, emits the observation and may store the state.  EARLY: before the table work, so that those stores are
 // under way while the walks go on (measured: 25.1 -> 23.8 us per ply in the rollout kernel; in the one-launch-per-ply
 // kernel it is 1 us slower than calling it afterwards, hence the choice).
 template <int N, bool GATE, bool EARLY, class Hook>
 __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& m, SkGame& g, uint32_t& forb, const Rules& rules, bool skip, bool want_pass,
                                              bool want_point, int pr_in, int pc_in, const uint2* tab_r, uint2* tab_w, uint2* zt, int game,
-                                             uint32_t* scratch, uint64_t* tally, float& rew0, float& rew1, bool& flag, bool pre_a_loaded, const SkWin& pre_a,
-                                             Hook&& board_final) {   // board_final(hdirty): hdirty as from apply_move
+                                             uint32_t* scratch, uint64_t* tally, Ply& ply, bool pre_a_loaded, const SkWin& pre_a, Hook&& board_final) {
   const int c = m.wtm, own = c ? g.nw : g.nb, opp = c ? g.nb : g.nw;
   Move mv = gate_move<N, GATE>(L, R, m, skip, want_pass, want_point, pr_in, pc_in);
   // a play the simple rules allow but the repetition rule forbids is an illegal action
@@ -1178,19 +1305,17 @@ __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& 
   pre[2] = sk_window<N>(L, tab_r, sk_home<N>(c ^ 1, opp), mv.playing);
   Rules r0 = rules;
   r0.auto_reset = 0;   // the reset happens below, after the table work
-  bool reset;
-  uint32_t captured;
-  uint32_t hdirty;
-  apply_move<N>(L, R, m, r0, mv, rew0, rew1, flag, captured, reset, hdirty, tally);
+  ply = apply_move<N>(L, R, m, r0, mv, tally);
   const bool do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
-  if (do_reset) { reset_board<N>(L, R, m, rules.seed); hdirty = ~0u; }   // a board that is reset takes no part in the table work below
+  if (do_reset) reset_board<N>(L, R, m, rules.seed);   // a board that is reset takes no part in the table work below
+  ply.reset = do_reset;
   if constexpr (EARLY) {
     // The windows have to be in registers before the caller's stores are issued: loads and stores share one counter,
     // and a wait for these loads placed after the stores would wait for the stores as well.
     asm volatile("" ::"v"(pre[0].e.x), "v"(pre[0].e.y), "v"(pre[1].e.x), "v"(pre[1].e.y), "v"(pre[2].e.x), "v"(pre[2].e.y));
-    board_final(hdirty);
+    board_final(ply.moved, do_reset);
   }
-  const SkPly s = sk_look<N>(L, tab_r, g, c, mv, captured, pre[0], scratch);
+  const SkPly s = sk_look<N>(L, tab_r, g, c, mv, ply.captured, pre[0], scratch);
   sk_insert<N>(L, tab_r, tab_w, g, s, mv.playing && !do_reset, c, pre[2]);
   // the forbidden plays change with the position and with the player to move; otherwise they stay
   const bool moved = (mv.playing || mv.is_pass) && !do_reset;
@@ -1198,7 +1323,7 @@ __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& 
   if (moved) forb = fresh;
   if (do_reset) { g = sk_fresh(); forb = 0u; }
   sk_clear_tables<N>(L, do_reset, zt, game);
-  if constexpr (!EARLY) board_final(hdirty);
+  if constexpr (!EARLY) board_final(ply.moved, do_reset);
 }
 
 // The same for the reading in which the rule is looked at only for the move that is played (mode 1): no sets of
@@ -1210,33 +1335,32 @@ __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& 
 //     known before the rules run -- it takes exactly the opposing chains in atari next to it -- so its keys are looked
 //     up first; a hit turns the play into an illegal action.
 //   POST = true (one launch per ply, where every wavefront would wait for the window before it can do anything else):
-//     the rules run first, on the assumption that the play repeats nothing, board_final() is called (the observation is
+//     the rules run first, on the assumption that the play repeats nothing, board_final(moved, reset) is called (the observation is
 //     under way), and the look-up follows; after a hit (rare) restore(R, m, which) brings back the state as loaded for
-//     the boards flagged, the ply is applied again as an illegal action and board_final() is called once more: the
-//     same wavefront overwrites what it stored the first time.
+//     the boards flagged and the history as loaded for all, the ply is applied again as an illegal action and board_final is
+//     called once more: the same wavefront overwrites what it stored the first time.
 template <int N, bool GATE, bool POST, class Hook, class Restore>
 __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, Meta& m, SkGame& g, const Rules& rules, bool skip, bool want_pass,
                                                   bool want_point, int pr_in, int pc_in, const uint2* tab_r, uint2* tab_w, uint2* zt, int game,
-                                                  uint32_t* scratch, uint64_t* tally, float& rew0, float& rew1, bool& flag, const SkWin& pre, Hook&& board_final,
-                                                  Restore&& restore) {
+                                                  uint32_t* scratch, uint64_t* tally, Ply& ply, const SkWin& pre, Hook&& board_final, Restore&& restore) {
   const int c = m.wtm, own1 = (c ? g.nw : g.nb) + 1;
   const uint64_t seg = ((uint64_t)L.seghi << 32) | L.seglo;
   Move mv = gate_move<N, GATE>(L, R, m, skip, want_pass, want_point, pr_in, pc_in);
   Rules r0 = rules;
   r0.auto_reset = 0;   // the reset happens below, together with the table's
-  bool reset, do_reset = false;
-  uint32_t captured = 0u, hdirty = 0u;
+  bool do_reset = false;
   if constexpr (POST) {
-    apply_move<N>(L, R, m, r0, mv, rew0, rew1, flag, captured, reset, hdirty, tally);
+    ply = apply_move<N>(L, R, m, r0, mv, tally);
     do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
-    if (do_reset) { reset_board<N>(L, R, m, rules.seed); hdirty = ~0u; }
+    if (do_reset) reset_board<N>(L, R, m, rules.seed);
     // The window has to be in registers before the caller's stores are issued: loads and stores share one counter.
     asm volatile("" ::"v"(pre.e.x), "v"(pre.e.y));
-    board_final(hdirty);   // on the assumption that nothing repeats; done again below if something does
+    board_final(ply.moved, do_reset);   // on the assumption that nothing repeats; done again below if something does
   }
   // the stones the play takes: known from the rules (POST), else the opposing chains in atari next to it
-  uint32_t taken = captured;
-  if constexpr (!POST) {
+  uint32_t taken = 0u;
+  if constexpr (POST) taken = ply.captured;
+  else {
     const uint32_t pbit = (L.valid && mv.playing && L.r == mv.pr) ? (1u << mv.pc) : 0u;
     const uint32_t aopp = c ? R.ab : R.aw;
     const uint32_t seed = dilate(pbit) & aopp;
@@ -1259,25 +1383,23 @@ __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, M
   const bool repeats = mv.playing && hit;
   if (repeats) { mv.playing = false; mv.illegal = true; mv.pr = -100; mv.pc = 0; }
   if constexpr (!POST) {
-    apply_move<N>(L, R, m, r0, mv, rew0, rew1, flag, captured, reset, hdirty, tally);
+    ply = apply_move<N>(L, R, m, r0, mv, tally);
     do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
-    if (do_reset) { reset_board<N>(L, R, m, rules.seed); hdirty = ~0u; }
-    board_final(hdirty);
+    if (do_reset) reset_board<N>(L, R, m, rules.seed);
+    board_final(ply.moved, do_reset);
   } else if (__ballot(repeats) != 0ull) {
     restore(R, m, repeats);   // the boards that repeat get the state as loaded back
     Move again = mv;          // the other boards of the wavefront keep what the first pass gave them: for them, a skipped ply
     if (!repeats) { again.skip = true; again.frozen = false; again.is_pass = false; again.playing = false; again.illegal = false; again.pr = -100; again.pc = 0; }
-    float a0, a1;
-    bool f2, rs2;
-    uint32_t cap2, hd2;
-    apply_move<N>(L, R, m, r0, again, a0, a1, f2, cap2, rs2, hd2, tally);
+    const Ply second = apply_move<N>(L, R, m, r0, again, tally);
     if (repeats) {
-      rew0 = a0; rew1 = a1; flag = f2;
+      ply = second;
       do_reset = rules.auto_reset != 0;   // the illegal action has ended the game
       if (do_reset) reset_board<N>(L, R, m, rules.seed);
     }
-    board_final(~0u);
+    board_final(ply.moved, do_reset);
   }
+  ply.reset = do_reset;
   if (mv.playing && !do_reset) {
     if (L.valid && L.r == 0 && ok && sk_real(key)) tab_store(&tab_w[free_slot], key);
     g.key = key; g.nb = nb1; g.nw = nw1;
@@ -1295,7 +1417,7 @@ __device__ __forceinline__ SkWin sk_window_play(const Lane<N>& L, const uint2* t
 // One ply with the repetition rule.  Same steps as go_step_kernel.
 // MODE: 1 = the rule is looked at when the move is played, 2 = honoured by the legal mask
 template <int N, bool TIGHT, int ST, int MODE>
-__global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel(uint4* planes, uint4* meta, const int32_t* actions, const int32_t* start_t,
+__global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel(uint32_t* state, uint4* meta, const int32_t* actions, const int32_t* start_t,
                                                                                 uint4* zcur, int B, int wb, uint32_t eighth, uint2* zt, StepArgs a) {
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
@@ -1305,9 +1427,10 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   const int wib = wave_in_block();
   const int wave = piece_of_block(eighth) * kWavesPerBlock + wib;
   const Lane<N> L(wave, threadIdx.x & 63, B, wb);
-  const size_t rows_total = (size_t)B * N;
   Row<N> R;
-  load_row<N>(planes, rows_total, L, R);
+  History<N> H;
+  load_row<N>(state, L, R);
+  load_history<N>(state, L, H);
   const uint4 meta_raw = L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
   const int act = L.boardok ? actions[L.b] : -1;
   const uint4 g_raw = zcur[L.boardok ? L.b : 0];   // (an unconditional load: a conditional one is waited for on the spot)
@@ -1326,36 +1449,35 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   SkWin none;
   none.home = ~0u; none.e = make_uint2(1u, 0u);
   uint32_t forb = 0u;
-  float rew0, rew1;
-  bool flag;
-  auto store_state = [&]() {   // a11 (whole rows: writing only the changed planes gains nothing here)
-    if (!skip) {
-      store_row<N>(planes, rows_total, L, R);
-      if (L.valid && L.r == 0) meta[L.b] = pack_meta(m);
-    }
-  };
-  auto board_final = [&](uint32_t) {   // a10, a11 (mode 1 still holds the row and the table window: a fourth round at once would spill)
-    if (a.obs) emit_obs<N, TIGHT, ST, MODE == 1 ? 3 : 4>(L, R.h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
-    if constexpr (MODE != 1) store_state();
+  Ply ply;
+  // a6, a10 (mode 1 still holds the row and the table window: a fourth round at once would spill)
+  auto board_final = [&](bool moved, bool reset) {
+    push_history<N>(H, m.head, R.bk, R.wt, moved);
+    if (reset) clear_history<N>(H);
+    if (a.obs) emit_obs<N, TIGHT, ST, MODE == 1 ? 3 : 4>(L, points_of<N>(H, m.head).h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
   };
   if constexpr (MODE == 1) {
     const SkWin pre = sk_window_play<N>(L, tab, g, m, !skip);
-    sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag, pre,
+    sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], ply, pre,
                                      board_final, [&](Row<N>& Rr, Meta& mr, bool which) {   // the state is stored below: memory still holds it as loaded
                                        Row<N> T;
-                                       load_row<N>(planes, rows_total, L, T);
-                                       if (which) { Rr = T; mr = unpack_meta(meta_raw); }
+                                       load_row<N>(state, L, T);
+                                       load_history<N>(state, L, H);
+                                       const Meta as_loaded = unpack_meta(meta[L.boardok ? L.b : 0]);
+                                       mr.head = as_loaded.head;
+                                       if (which) { Rr = T; mr = as_loaded; }
                                      });
-    store_state();
   } else {
     forb = sk_forb_loaded<N>(L, tab, g, R, m, none, lds_mask_all[wib]);
-    sk_step_core<N, true, false>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag,
-                                 false, none, board_final);
+    sk_step_core<N, true, false>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], ply, false, none, board_final);
     g.fw = sk_forb_word<N>(L, forb);
   }
+  constexpr int STATE_ST = MODE == 1 && N == 9 ? kStorePlain : state_store_kind(ST);   // (mode 1 at 9x9 has no registers left for the other kind)
+  store_ply<N, STATE_ST>(state, L, R, H, m.head, ply.moved, ply.reset);   // a11
   if (!skip && L.valid && L.r == 0) {
-    *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(rew0, rew1);
-    store_small<ST>(&a.term[L.b], (uint8_t)(flag ? 1 : 0));
+    store_small<STATE_ST>(&meta[L.b], pack_meta(m));
+    *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(ply.rew0, ply.rew1);
+    store_small<ST>(&a.term[L.b], (uint8_t)(ply.flag ? 1 : 0));
   }
 
   const uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko) & ~(MODE == 2 ? forb : 0u);
@@ -1370,12 +1492,15 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
 // Fills the tables from what the state still carries: the 8 history positions and the current one (set-up, import),
 // and finds the current position's forbidden plays.  The tables must have been cleared by an earlier launch.
 template <int N>
-__global__ void __launch_bounds__(64) go_superko_rebuild_kernel(const uint4* planes, const uint4* meta, int B, uint2* zt, uint4* zcur, int mode) {
+__global__ void __launch_bounds__(64) go_superko_rebuild_kernel(uint32_t* state, const uint4* meta, int B, uint2* zt, uint4* zcur, int mode) {
   __shared__ uint32_t scratch[64];
   const Lane<N> L(blockIdx.x, threadIdx.x, B);
   Row<N> R;
-  load_row<N>(planes, (size_t)B * N, L, R);
+  History<N> H;
+  load_row<N>(state, L, R);
+  load_history<N>(state, L, H);
   const Meta m = unpack_meta(L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
+  const Points<N> Q = points_of<N>(H, m.head);
   uint2* tab = zt + (size_t)(L.boardok ? L.b : 0) * Zt<N>::SLOTS;
   SkWin none;
   none.home = ~0u; none.e = make_uint2(1u, 0u);
@@ -1386,7 +1511,7 @@ __global__ void __launch_bounds__(64) go_superko_rebuild_kernel(const uint4* pla
       black = 0u; white = 0u;
 #pragma unroll
       for (int col = 0; col < N; ++col) {
-        const uint32_t hw = (R.h[col >> 1] >> ((col & 1) * 16)) & 0xFFFFu;
+        const uint32_t hw = (Q.h[col >> 1] >> ((col & 1) * 16)) & 0xFFFFu;
         black |= ((hw >> (2 * (i - 1))) & 1u) << col;
         white |= ((hw >> (2 * (i - 1) + 1)) & 1u) << col;
       }
@@ -1436,7 +1561,7 @@ struct SlotArgs {       // what is not needed before the first loads
 // SK: the positional-superko rule is on; a game that moves to another slot takes its key table along.
 template <int N, bool TIGHT, int SK, int ST = kStorePlain>
 __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots_kernel(const int32_t* src_slots, const int32_t* dst_slots, const int32_t* actions,
-                                                                                      uint4* planes, uint4* meta, int pool, int n, uint32_t eighth, SlotArgs a) {
+                                                                                      uint32_t* state, uint4* meta, int pool, int n, uint32_t eighth, SlotArgs a) {
   // pool: number of state slots (the handle's batch), n: entries of this call
   using G = Geo<N>;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
@@ -1446,14 +1571,15 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
   const int wib = wave_in_block();
   const int wave = piece_of_block(eighth) * kWavesPerBlock + wib;
   Lane<N> L(wave, threadIdx.x & 63, n);
-  const size_t rows_total = (size_t)pool * N;
   const int src = L.boardok ? src_slots[L.b] : 0, dst = L.boardok ? dst_slots[L.b] : 0;
   const bool in_pool = src >= 0 && src < pool && dst >= 0 && dst < pool;
   const bool bad = L.boardok && !in_pool;
   if (bad) { L.boardok = false; L.valid = false; L.full = 0u; }   // the entry becomes inert: no state access, no outputs
   L.slot = src;
   Row<N> R;
-  load_row<N>(planes, rows_total, L, R);
+  History<N> H;
+  load_row<N>(state, L, R);
+  load_history<N>(state, L, H);
   const uint4 meta_raw = L.boardok ? meta[src] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
   const int act = (L.boardok && actions) ? actions[L.b] : -1;
   in_scalar_registers(a.rew, a.term, a.mask, a.obs, a.mask_pitch, a.obs_pitch, a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset);
@@ -1465,14 +1591,16 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
   const bool skip = !L.boardok || act == -1;
   const bool in_range = act >= 0 && act < G::P;
   const int pr = in_range ? act / N : 0, pc = in_range ? act - (act / N) * N : 0;
-  float rew0, rew1;
-  bool flag;
+  Ply ply;
   uint32_t forb = 0u;
+  auto board_final = [&](bool moved, bool reset) {   // a6, a10
+    push_history<N>(H, m.head, R.bk, R.wt, moved);
+    if (reset) clear_history<N>(H);
+    if (a.obs) emit_obs<N, TIGHT, ST>(L, points_of<N>(H, m.head).h, m.wtm, wave, n, a.obs, a.obs_pitch, lds_obs_all[wib], lut);
+  };
   if constexpr (!SK) {
     const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, pr, pc);
-    bool reset;
-    uint32_t captured;
-    apply_move<N>(L, R, m, a.rules, mv, rew0, rew1, flag, captured, reset, tally_all[wib]);
+    ply = apply_move<N>(L, R, m, a.rules, mv, tally_all[wib]);
   } else {
     const int sslot = L.boardok ? src : 0, dslot = L.boardok ? dst : 0;
     SkGame g = L.boardok ? sk_unpack(a.zcur[sslot]) : sk_fresh();
@@ -1487,21 +1615,22 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
     __threadfence();   // the copied tables are in place before entries are added to them or they are cleared
     SkWin none;
     none.home = ~0u; none.e = make_uint2(1u, 0u);
-    auto board_final = [&](uint32_t) { if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, n, a.obs, a.obs_pitch, lds_obs_all[wib], lut); };
     if constexpr (SK == 1) {
       const SkWin pre = sk_window_play<N>(L, tab_r, g, m, !skip);
-      sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag, pre,
+      sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], ply, pre,
                                        board_final, [&](Row<N>& Rr, Meta& mr, bool which) {   // the source slot still holds the state as loaded
                                          Lane<N> Ls = L;
                                          Ls.slot = src;
                                          Row<N> T;
-                                         load_row<N>(planes, rows_total, Ls, T);
-                                         if (which) { Rr = T; mr = unpack_meta(meta_raw); }
+                                         load_row<N>(state, Ls, T);
+                                         load_history<N>(state, Ls, H);
+                                         const Meta as_loaded = unpack_meta(meta[sslot]);
+                                         mr.head = as_loaded.head;
+                                         if (which) { Rr = T; mr = as_loaded; }
                                        });
     } else {
       forb = sk_forb_loaded<N>(L, tab_r, g, R, m, none, lds_mask_all[wib]);
-      sk_step_core<N, true, true>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag,
-                                  false, none, board_final);
+      sk_step_core<N, true, true>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], ply, false, none, board_final);
       g.fw = sk_forb_word<N>(L, forb);
     }
     if (L.valid && L.r == 0) a.zcur[dslot] = sk_pack(g);
@@ -1511,14 +1640,14 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
     if (bad) { if (a.term) store_small<ST>(&a.term[L.b], (uint8_t)255); }
     else {
       // a copied entry (action -1) reports what a skipped step reports for a fresh handle: no reward, and its terminated state
-      if (a.rew) *(float2*)(a.rew + 2 * (size_t)L.b) = skip ? make_float2(0.f, 0.f) : make_float2(rew0, rew1);
-      if (a.term) store_small<ST>(&a.term[L.b], (uint8_t)(skip ? m.term : (flag ? 1 : 0)));
+      if (a.rew) *(float2*)(a.rew + 2 * (size_t)L.b) = skip ? make_float2(0.f, 0.f) : make_float2(ply.rew0, ply.rew1);
+      if (a.term) store_small<ST>(&a.term[L.b], (uint8_t)(skip ? m.term : (ply.flag ? 1 : 0)));
     }
   }
   const uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko) & ~forb;
-  if constexpr (!SK) { if (a.obs) emit_obs<N, TIGHT, ST>(L, R.h, m.wtm, wave, n, a.obs, a.obs_pitch, lds_obs_all[wib], lut); }
+  if constexpr (!SK) board_final(ply.moved, ply.reset);
   if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, n, a.mask, a.mask_pitch, lds_mask_all[wib], lut);
-  store_row<N>(planes, rows_total, L, R);
+  store_all<N>(state, L, R, H);
   if (L.valid && L.r == 0) meta[dst] = pack_meta(m);
 }
 
@@ -1528,7 +1657,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
 // trajectory buffers.
 // ------------------------------------------------------------------------------------------------
 struct RolloutArgs {
-  uint4* planes;
+  uint32_t* state;
   uint4* meta;
   int B;
   int wb;               // boards per wavefront of this launch
@@ -1576,11 +1705,15 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
   const int wave = piece_of_block() * kWavesPerBlock + wib;
   if (wave * a.wb >= a.B) return;
   const Lane<N> L0(wave, threadIdx.x & 63, a.B, a.wb);
-  const size_t rows_total = (size_t)a.B * N;
-
   Row<N> R;
-  load_row<N>(a.planes, rows_total, L0, R);
+  Points<N> Q;
   Meta m = unpack_meta(L0.boardok ? a.meta[L0.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
+  {
+    History<N> H;
+    load_row<N>(a.state, L0, R);
+    load_history<N>(a.state, L0, H);
+    Q = points_of<N>(H, m.head);
+  }
   const int64_t start = (L0.boardok && a.start_t) ? (int64_t)a.start_t[L0.b] : INT64_MIN;
   uint32_t legal = legal_row<N>(L0, R, m.wtm, m.ko);
   SkGame g = sk_fresh();
@@ -1607,26 +1740,28 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
     const bool wait = (int64_t)t < start;
     const Draw<N> d = draw_action<N>(L, legal, a.seed, t, wait);
     const bool skip = !L.boardok || wait;
-    float rew0, rew1;
-    bool flag;
+    Ply ply;
     if constexpr (!SK) {
-      step_core<N, false>(L, R, m, a.rules, skip, d.pass, d.point, d.pr, d.pc, rew0, rew1, flag, tally_all[wib]);
+      ply = apply_move<N>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.pr, d.pc), tally_all[wib],
+                          [&]() { clear_points<N>(Q); });
+      push_points<N>(Q, R.bk, R.wt, ply.moved);
       legal = legal_row<N>(L, R, m.wtm, m.ko);
     } else {
       SkWin none;
       none.home = ~0u; none.e = make_uint2(1u, 0u);
       uint8_t* const obs_t = a.obs ? a.obs + (size_t)slice * a.B * a.obs_pitch : nullptr;
-      auto board_final = [&](uint32_t) {
+      auto board_final = [&](bool moved, bool reset) {
+        push_points<N>(Q, R.bk, R.wt, moved);
+        if (reset) clear_points<N>(Q);
         if constexpr (PACED) pace.wait();
-        if (obs_t) emit_obs<N, TIGHT, ST, 4, FIRST_AS_EDGE>(L, R.h, m.wtm, wave, a.B, obs_t, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
+        if (obs_t) emit_obs<N, TIGHT, ST, 4, FIRST_AS_EDGE>(L, Q.h, m.wtm, wave, a.B, obs_t, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
       };
       if constexpr (SK == 1) {
-        sk_step_core_play<N, false, false>(L, R, m, g, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag,
+        sk_step_core_play<N, false, false>(L, R, m, g, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], ply,
                                            ahead, board_final, [](Row<N>&, Meta&, bool) {});
         ahead = sk_window_play<N>(L, tab, g, m, L.boardok);
       } else {
-        sk_step_core<N, false, true>(L, R, m, g, forb, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], rew0, rew1, flag, false,
-                                     none, board_final);
+        sk_step_core<N, false, true>(L, R, m, g, forb, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], ply, false, none, board_final);
       }
       legal = legal_row<N>(L, R, m.wtm, m.ko) & ~(SK == 2 ? forb : 0u);
     }
@@ -1635,17 +1770,19 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
       const size_t e = sb + L.b;
       if (a.actions) a.actions[e] = d.action();
       // a waiting environment reports the values a skipped step call leaves behind at the start: zeros
-      if (a.rew) *(float2*)(a.rew + 2 * e) = skip ? make_float2(0.f, 0.f) : make_float2(rew0, rew1);
-      if (a.term) a.term[e] = (uint8_t)((!skip && flag) ? 1 : 0);
+      if (a.rew) *(float2*)(a.rew + 2 * e) = skip ? make_float2(0.f, 0.f) : make_float2(ply.rew0, ply.rew1);
+      if (a.term) a.term[e] = (uint8_t)((!skip && ply.flag) ? 1 : 0);
     }
     if constexpr (PACED && !SK) pace.wait();
-    emit_outputs<N, TIGHT, ST, FIRST_AS_EDGE>(L, R, legal, m.wtm, wave, a.B, a.mask ? a.mask + sb * a.mask_pitch : nullptr, a.mask_pitch,
+    emit_outputs<N, TIGHT, ST, FIRST_AS_EDGE>(L, Q, legal, m.wtm, wave, a.B, a.mask ? a.mask + sb * a.mask_pitch : nullptr, a.mask_pitch,
                     (!SK && a.obs) ? a.obs + sb * a.obs_pitch : nullptr, a.obs_pitch, lds_mask_all[wib], lds_obs_all[wib], lut, a.wb);
     wave_lds_fence();
     slice = slice + 1 == a.slices ? 0 : slice + 1;
   }
-  store_row<N>(a.planes, rows_total, L0, R);
-  if (L0.valid && L0.r == 0) a.meta[L0.b] = pack_meta(m);
+  const Lane<N> L1(wave, in_place(L0.lane), a.B, a.wb);   // (anew: where a game's state lies is nothing to hold through the loop)
+  store_all<N>(a.state, L1, R, history_of<N>(Q));
+  m.head = 0;
+  if (L1.valid && L1.r == 0) a.meta[L1.b] = pack_meta(m);
   if constexpr (SK) {
     if constexpr (SK != 1) g.fw = sk_forb_word<N>(L0, forb);
     if (L0.valid && L0.r == 0) a.zcur[L0.b] = sk_pack(g);
@@ -1657,7 +1794,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
 // ------------------------------------------------------------------------------------------------
 // SK: the legal mask leaves out the plays that would recreate an earlier position (positional superko, mode 2)
 template <int N, bool TIGHT, bool SK>
-__global__ void __launch_bounds__(64 * kWavesPerBlock) go_emit_kernel(const uint4* planes, const uint4* meta, int B, uint8_t* mask,
+__global__ void __launch_bounds__(64 * kWavesPerBlock) go_emit_kernel(uint32_t* state, const uint4* meta, int B, uint8_t* mask,
                                                                       int64_t mask_pitch, uint8_t* obs, int64_t obs_pitch, const uint2* zt,
                                                                       const uint4* zcur) {
   using G = Geo<N>;
@@ -1670,7 +1807,9 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_emit_kernel(const uint
   if (wave * G::W >= B) return;
   const Lane<N> L(wave, threadIdx.x & 63, B);
   Row<N> R;
-  load_row<N>(planes, (size_t)B * N, L, R);
+  History<N> H;
+  load_row<N>(state, L, R);
+  if (obs) load_history<N>(state, L, H);
   Meta m = unpack_meta(L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
   uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
   if constexpr (SK) {
@@ -1681,12 +1820,13 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_emit_kernel(const uint
       legal &= ~sk_forb_loaded<N>(L, zt + (size_t)(L.boardok ? L.b : 0) * Zt<N>::SLOTS, g, R, m, none, lds_mask_all[wib]);
     }
   }
-  emit_outputs<N, TIGHT>(L, R, legal, m.wtm, wave, B, mask, mask_pitch, obs, obs_pitch, lds_mask_all[wib], lds_obs_all[wib], lut);
+  if (mask) emit_mask<N, TIGHT>(L, legal, wave, B, mask, mask_pitch, lds_mask_all[wib], lut);
+  if (obs) emit_obs<N, TIGHT>(L, points_of<N>(H, m.head).h, m.wtm, wave, B, obs, obs_pitch, lds_obs_all[wib], lut);
 }
 
 // k-th legal action of the current position, same row-per-lane mapping as the step kernel
 template <int N, bool SK>
-__global__ void __launch_bounds__(64 * kWavesPerBlock) go_random_actions_kernel(const uint4* planes, const uint4* meta, const int32_t* start_t,
+__global__ void __launch_bounds__(64 * kWavesPerBlock) go_random_actions_kernel(uint32_t* state, const uint4* meta, const int32_t* start_t,
                                                                                 int32_t* actions, int B, uint32_t seed, uint32_t t, uint32_t eighth,
                                                                                 const uint2* zt, const uint4* zcur) {
   using G = Geo<N>;
@@ -1695,20 +1835,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_random_actions_kernel(
   if (wave * G::W >= B) return;
   const Lane<N> L(wave, threadIdx.x & 63, B);
   Row<N> R;
-#pragma unroll
-  for (int k = 0; k < G::HD; ++k) R.h[k] = 0u;
-  R.bk = R.wt = R.ab = R.aw = 0u;
-  if (L.valid) {   // stones and atari sets are the last four dwords of the row record
-    const size_t idx = (size_t)L.b * N + L.r, rows_total = (size_t)B * N;
-    uint32_t rec[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = G::HD + i;
-      if (k < 4 * G::NQ) rec[i] = ((const uint32_t*)(planes + (size_t)(k / 4) * rows_total + idx))[k & 3];
-      else rec[i] = ((const uint32_t*)(planes + (size_t)G::NQ * rows_total))[idx * G::REM + (k - 4 * G::NQ)];
-    }
-    R.bk = rec[0]; R.wt = rec[1]; R.ab = rec[2]; R.aw = rec[3];
-  }
+  load_row<N>(state, L, R);
   Meta m = unpack_meta(L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
   uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
   if constexpr (SK) {
@@ -1724,22 +1851,21 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_random_actions_kernel(
 
 // new episode for every environment: empty board, Black to move, seat from the hash
 template <int N>
-__global__ void go_reset_kernel(uint4* planes, uint4* meta, float* rew, uint8_t* term, int B, uint32_t seed, int first) {
+__global__ void go_reset_kernel(uint32_t* state, uint4* meta, float* rew, uint8_t* term, int B, uint32_t seed, int first) {
   using G = Geo<N>;
-  const size_t rows_total = (size_t)B * N;
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < rows_total) {
+  constexpr int share = (G::GAME + N - 1) / N;   // of a game's dwords for each of its N threads
+  if (i < (size_t)B * N) {
+    const int r = (int)(i % N);
 #pragma unroll
-    for (int k = 0; k < G::NQ; ++k) planes[(size_t)k * rows_total + i] = make_uint4(0u, 0u, 0u, 0u);
-    uint32_t* tail = (uint32_t*)(planes + (size_t)G::NQ * rows_total);
-#pragma unroll
-    for (int k = 0; k < G::REM; ++k) tail[i * G::REM + k] = 0u;
+    for (int k = 0; k < share; ++k)
+      if (share * r + k < G::GAME) state[i / N * G::GAME + share * r + k] = 0u;
   }
   if (i < (size_t)B) {
     Meta m;
     if (first) { m.episode = 0u; m.illegal = 0u; }
     else { Meta old = unpack_meta(meta[i]); m.episode = old.episode + 1u; m.illegal = old.illegal; }
-    m.ko = -1; m.steps = 0; m.passes = 0; m.wtm = 0; m.term = 0;
+    m.ko = -1; m.steps = 0; m.passes = 0; m.wtm = 0; m.term = 0; m.head = 0;
     m.bp = (int)(env_hash(seed, 1u, (uint32_t)i, m.episode) & 1u);
     meta[i] = pack_meta(m);
     rew[2 * i] = 0.f; rew[2 * i + 1] = 0.f; term[i] = 0;
@@ -1760,24 +1886,27 @@ struct CanonArgs {
 };
 
 template <int N>
-__global__ void __launch_bounds__(64) go_export_kernel(const uint4* planes, const uint4* meta, int B, CanonArgs c) {
+__global__ void __launch_bounds__(64) go_export_kernel(uint32_t* state, const uint4* meta, int B, CanonArgs c) {
   using G = Geo<N>;
   const Lane<N> L(blockIdx.x, threadIdx.x, B);
   Row<N> R;
-  load_row<N>(planes, (size_t)B * N, L, R);
+  History<N> H;
+  load_row<N>(state, L, R);
+  load_history<N>(state, L, H);
   if (!L.valid) return;
+  const Meta m = unpack_meta(meta[L.b]);
+  const Points<N> Q = points_of<N>(H, m.head);
   const size_t cell0 = (size_t)L.b * G::P + (size_t)L.r * N;
 #pragma unroll
   for (int col = 0; col < N; ++col) {
     if (c.board) c.board[cell0 + col] = (int8_t)((int)((R.bk >> col) & 1u) - (int)((R.wt >> col) & 1u));
     if (c.history) {
-      uint32_t hw = (R.h[col >> 1] >> ((col & 1) * 16)) & 0xFFFFu;
+      uint32_t hw = (Q.h[col >> 1] >> ((col & 1) * 16)) & 0xFFFFu;
       for (int i = 0; i < 8; ++i)
         c.history[((size_t)L.b * 8 + i) * G::P + (size_t)L.r * N + col] = (int8_t)((int)((hw >> (2 * i)) & 1u) - (int)((hw >> (2 * i + 1)) & 1u));
     }
   }
   if (L.r == 0) {
-    Meta m = unpack_meta(meta[L.b]);
     if (c.ko) c.ko[L.b] = m.ko;
     if (c.to_play) c.to_play[L.b] = (int8_t)(m.wtm ? -1 : 1);
     if (c.steps) c.steps[L.b] = m.steps;
@@ -1791,14 +1920,16 @@ __global__ void __launch_bounds__(64) go_export_kernel(const uint4* planes, cons
 
 // canonical arrays -> private state; the atari sets are rebuilt chain by chain
 template <int N>
-__global__ void __launch_bounds__(64) go_import_kernel(uint4* planes, uint4* meta, float* rew, uint8_t* term, int B, CanonArgs c) {
+__global__ void __launch_bounds__(64) go_import_kernel(uint32_t* state, uint4* meta, float* rew, uint8_t* term, int B, CanonArgs c) {
   using G = Geo<N>;
   const Lane<N> L(blockIdx.x, threadIdx.x, B);
   Row<N> R;
+  Points<N> Q;
 #pragma unroll
-  for (int k = 0; k < G::HD; ++k) R.h[k] = 0u;
+  for (int k = 0; k < G::HD; ++k) Q.h[k] = 0u;
   R.bk = R.wt = R.ab = R.aw = 0u;
   Meta m;
+  m.head = 0;
   m.ko = -1; m.steps = 0; m.passes = 0; m.wtm = 0; m.term = 0; m.bp = 0; m.episode = 0u; m.illegal = 0u;
   if (L.boardok) {
     Meta old = unpack_meta(meta[L.b]);
@@ -1817,7 +1948,7 @@ __global__ void __launch_bounds__(64) go_import_kernel(uint4* planes, uint4* met
         if (hv > 0) hw |= 1u << (2 * i); else if (hv < 0) hw |= 1u << (2 * i + 1);
       }
 #pragma unroll
-      for (int k = 0; k < G::HD; ++k) if (k == (col >> 1)) R.h[k] |= hw << ((col & 1) * 16);
+      for (int k = 0; k < G::HD; ++k) if (k == (col >> 1)) Q.h[k] |= hw << ((col & 1) * 16);
     }
   }
   const uint32_t E = L.full & ~(R.bk | R.wt);
@@ -1837,7 +1968,7 @@ __global__ void __launch_bounds__(64) go_import_kernel(uint4* planes, uint4* met
     visited |= F;
     if (one) { if (black) R.ab |= F; else R.aw |= F; }
   }
-  store_row<N>(planes, (size_t)B * N, L, R);
+  store_all<N>(state, L, R, history_of<N>(Q));
   if (L.valid && L.r == 0) {
     meta[L.b] = pack_meta(m);
     rew[2 * (size_t)L.b] = 0.f; rew[2 * (size_t)L.b + 1] = 0.f; term[L.b] = (uint8_t)m.term;
@@ -1884,7 +2015,7 @@ struct pgxgo_ctx {
   int komi_x2, max_steps, auto_reset;
   int64_t obs_pitch, mask_pitch;
   hipStream_t stream;
-  uint4* planes;
+  uint32_t* state;
   uint4* meta;
   float* rew_int;
   uint8_t* term_int;
@@ -1906,7 +2037,7 @@ int launch_reset(pgxgo_ctx* h, int first) {
   const size_t n = (size_t)h->B * N;
   const int threads = 256;
   const unsigned blocks = (unsigned)((n + threads - 1) / threads);
-  hipLaunchKernelGGL(go_reset_kernel<N>, dim3(blocks), dim3(threads), 0, h->stream, h->planes, h->meta, h->rew_out, h->term_out, h->B, h->seed,
+  hipLaunchKernelGGL(go_reset_kernel<N>, dim3(blocks), dim3(threads), 0, h->stream, h->state, h->meta, h->rew_out, h->term_out, h->B, h->seed,
                      first);
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
@@ -1922,14 +2053,16 @@ unsigned blocks_for_wb(int B, int wb) { return (((unsigned)((B + wb - 1) / wb) +
 // through the L2 (us for 4 launches, against whole lines only: 19x19 x 6001 games, 39 MB, 39.6 / 39.9, as entries of a search
 // x 5500 37.9 / 39.3; 9x9 x 24000, 35 MB, 38.0 / 40.4; above the line 19x19 x 9000, 58 MB, 50.5 / 50.0); from there to the size
 // of the memory-side cache write-through for whole lines only (16384 games: 20.7 against 22.1 us per ply with ordinary stores);
-// beyond it, where the hint costs 20-30 % below ~50 k games and gains 9-17 % above ~57 k, the non-temporal hint on top (65536
-// games: 88 us against 110 us plain).  The rollout kernel uses kStoreThroughWhole at every size unless it is paced (16384
-// games: 14.4 against 16.5 us per ply, 65536 games: 53.8 against 60.2 us; in place the non-temporal hint is slower at every size).
+// beyond what that cache holds of them beside the state the non-temporal hint on top (us per ply, whole lines written through / with the
+// hint: 19x19 x 28000 games, 182 MB, 34.1 / 38.3; x 36000, 234 MB, 47.8 / 46.1; x 40000 55 / 48; x 48000 77 / 61; x 65536 114 / 80; with
+// superko x 40000 86 / 62; 9x9 x 160000, 233 MB, 49.7 / 49.9; x 200000 67 / 62).  The rollout kernel uses kStoreThroughWhole at every size
+// unless it is paced (16384 games: 14.4 against 16.5 us per ply, 65536 games: 53.8 against 60.2 us; in place the non-temporal hint is
+// slower at every size).
 // in_place: the launch overwrites the buffers the previous one wrote, whose lines are then still in the memory-side
 // cache.  In the middle range a launch into other buffers (a caller that records a trajectory) has to reach DRAM and
 // is faster with the hint as well (16384 games: 23.9 us per ply against 25.4 with ordinary stores and 25.9 with
 // write-through alone).
-constexpr size_t kWriteThroughUpTo = (size_t)48 << 20, kNonTemporalFrom = (size_t)350 << 20;
+constexpr size_t kWriteThroughUpTo = (size_t)48 << 20, kNonTemporalFrom = (size_t)220 << 20;
 int store_kind_for(size_t out_bytes, bool in_place) {
   if (out_bytes <= kWriteThroughUpTo) return kStoreThrough;
   if (out_bytes <= kNonTemporalFrom) return in_place ? kStoreThroughWhole : kStoreStreamWhole;
@@ -1964,7 +2097,7 @@ bool tight_pitches(const pgxgo_ctx* h) {
 
 template <int N, bool TIGHT, bool SK>
 void launch_emit_as(pgxgo_ctx* h, uint8_t* mask, uint8_t* obs) {
-  hipLaunchKernelGGL((go_emit_kernel<N, TIGHT, SK>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->planes, h->meta, h->B, mask,
+  hipLaunchKernelGGL((go_emit_kernel<N, TIGHT, SK>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->state, h->meta, h->B, mask,
                      h->mask_pitch, obs, h->obs_pitch, h->zt, h->zcur);
 }
 
@@ -1986,9 +2119,6 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
   a.mask = h->mask_out; a.obs = h->obs_out; a.mask_pitch = h->mask_pitch; a.obs_pitch = h->obs_pitch;
   a.rules.seed = h->seed; a.rules.komi_x2 = h->komi_x2; a.rules.max_steps = h->max_steps; a.rules.auto_reset = h->auto_reset;
   a.sample_seed = seed; a.sample_t = t; a.next_actions = next;
-  // bytes one ply touches: state rows + outputs; 256 MB of memory-side cache on this part, keep a margin
-  const size_t touched = (size_t)h->B * (Geo<N>::row_bytes * N + (h->mask_out ? (size_t)h->mask_pitch : 0) + (h->obs_out ? (size_t)h->obs_pitch : 0));
-  a.sparse_store = touched < ((size_t)192 << 20) ? 1 : 0;
   a.store_kind = store_kind_for(output_bytes_per_ply(h, h->mask_out != nullptr, h->obs_out != nullptr),
                                 h->mask_out == h->mask_written && h->obs_out == h->obs_written);
   h->mask_written = h->mask_out; h->obs_written = h->obs_out;
@@ -1999,9 +2129,9 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
     auto sk = [&](auto tight_c, auto mode_c) {
       constexpr bool T = decltype(tight_c)::value;
       constexpr int M = decltype(mode_c)::value;
-      if (a.store_kind == kStoreThrough) hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreThrough, M>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->zcur, h->B, h->wb, grid.x / 8, h->zt, a);
-      else if (a.store_kind == kStoreThroughWhole) hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreThroughWhole, M>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->zcur, h->B, h->wb, grid.x / 8, h->zt, a);
-      else hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreStreamWhole, M>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->zcur, h->B, h->wb, grid.x / 8, h->zt, a);
+      if (a.store_kind == kStoreThrough) hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreThrough, M>), grid, block, 0, h->stream, h->state, h->meta, actions, start_t, h->zcur, h->B, h->wb, grid.x / 8, h->zt, a);
+      else if (a.store_kind == kStoreThroughWhole) hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreThroughWhole, M>), grid, block, 0, h->stream, h->state, h->meta, actions, start_t, h->zcur, h->B, h->wb, grid.x / 8, h->zt, a);
+      else hipLaunchKernelGGL((go_step_superko_kernel<N, T, kStoreStreamWhole, M>), grid, block, 0, h->stream, h->state, h->meta, actions, start_t, h->zcur, h->B, h->wb, grid.x / 8, h->zt, a);
     };
     using M1 = std::integral_constant<int, 1>;
     using M2 = std::integral_constant<int, 2>;
@@ -2014,9 +2144,9 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
   }
   auto go = [&](auto sample_c, auto tight_c) {
     constexpr bool S = decltype(sample_c)::value, T = decltype(tight_c)::value;
-    if (a.store_kind == kStoreThrough) hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreThrough>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->B, h->wb, grid.x / 8, a);
-    else if (a.store_kind == kStoreThroughWhole) hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreThroughWhole>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->B, h->wb, grid.x / 8, a);
-    else hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreStreamWhole>), grid, block, 0, h->stream, h->planes, h->meta, actions, start_t, h->B, h->wb, grid.x / 8, a);
+    if (a.store_kind == kStoreThrough) hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreThrough>), grid, block, 0, h->stream, h->state, h->meta, actions, start_t, h->B, h->wb, grid.x / 8, a);
+    else if (a.store_kind == kStoreThroughWhole) hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreThroughWhole>), grid, block, 0, h->stream, h->state, h->meta, actions, start_t, h->B, h->wb, grid.x / 8, a);
+    else hipLaunchKernelGGL((go_step_kernel<N, S, T, kStoreStreamWhole>), grid, block, 0, h->stream, h->state, h->meta, actions, start_t, h->B, h->wb, grid.x / 8, a);
   };
   if (sample && tight) go(std::true_type{}, std::true_type{});
   else if (sample) go(std::true_type{}, std::false_type{});
@@ -2029,10 +2159,10 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
 template <int N>
 int launch_random(pgxgo_ctx* h, uint32_t seed, uint32_t t, const int32_t* start_t, int32_t* actions) {
   if (h->zt && h->sk_mode == 2)
-    hipLaunchKernelGGL((go_random_actions_kernel<N, true>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->planes, h->meta, start_t,
+    hipLaunchKernelGGL((go_random_actions_kernel<N, true>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->state, h->meta, start_t,
                        actions, h->B, seed, t, blocks_for<N>(h->B) / 8, h->zt, h->zcur);
   else
-    hipLaunchKernelGGL((go_random_actions_kernel<N, false>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->planes, h->meta, start_t,
+    hipLaunchKernelGGL((go_random_actions_kernel<N, false>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->state, h->meta, start_t,
                        actions, h->B, seed, t, blocks_for<N>(h->B) / 8, h->zt, h->zcur);
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
@@ -2084,28 +2214,28 @@ int launch_slots(pgxgo_ctx* h, int n, const int32_t* src, const int32_t* actions
   const dim3 grid(blocks_for<N>(n)), block(64 * kWavesPerBlock);
   const bool tight = tight_pitches<N>(h), sk = h->zt != nullptr;
   const size_t out_bytes = (size_t)n * ((a.mask ? (size_t)a.mask_pitch : 0) + (a.obs ? (size_t)a.obs_pitch : 0));
-  if (tight && sk && h->sk_mode == 1) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 1>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
-  else if (tight && sk) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 2>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
-  else if (tight && store_kind_for(out_bytes, true) == kStoreThrough) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreThrough>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
-  else if (tight && store_kind_for(out_bytes, true) == kStoreThroughWhole) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreThroughWhole>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
-  else if (tight) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreStreamWhole>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
-  else if (sk && h->sk_mode == 1) hipLaunchKernelGGL((go_step_slots_kernel<N, false, 1>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
-  else if (sk) hipLaunchKernelGGL((go_step_slots_kernel<N, false, 2>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
-  else hipLaunchKernelGGL((go_step_slots_kernel<N, false, 0>), grid, block, 0, h->stream, src, dst, actions, h->planes, h->meta, h->B, n, grid.x / 8, a);
+  if (tight && sk && h->sk_mode == 1) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 1>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
+  else if (tight && sk) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 2>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
+  else if (tight && store_kind_for(out_bytes, true) == kStoreThrough) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreThrough>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
+  else if (tight && store_kind_for(out_bytes, true) == kStoreThroughWhole) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreThroughWhole>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
+  else if (tight) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreStreamWhole>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
+  else if (sk && h->sk_mode == 1) hipLaunchKernelGGL((go_step_slots_kernel<N, false, 1>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
+  else if (sk) hipLaunchKernelGGL((go_step_slots_kernel<N, false, 2>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
+  else hipLaunchKernelGGL((go_step_slots_kernel<N, false, 0>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
 }
 
 template <int N>
 int launch_export(pgxgo_ctx* h, const CanonArgs& c) {
-  hipLaunchKernelGGL(go_export_kernel<N>, dim3(waves_for<N>(h->B)), dim3(64), 0, h->stream, h->planes, h->meta, h->B, c);
+  hipLaunchKernelGGL(go_export_kernel<N>, dim3(waves_for<N>(h->B)), dim3(64), 0, h->stream, h->state, h->meta, h->B, c);
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
 }
 
 template <int N>
 int launch_import(pgxgo_ctx* h, const CanonArgs& c) {
-  hipLaunchKernelGGL(go_import_kernel<N>, dim3(waves_for<N>(h->B)), dim3(64), 0, h->stream, h->planes, h->meta, h->rew_out, h->term_out, h->B,
+  hipLaunchKernelGGL(go_import_kernel<N>, dim3(waves_for<N>(h->B)), dim3(64), 0, h->stream, h->state, h->meta, h->rew_out, h->term_out, h->B,
                      c);
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
@@ -2126,7 +2256,7 @@ int launch_superko_refresh(pgxgo_ctx* h, bool rebuild) {
   hipLaunchKernelGGL(go_zero_kernel, dim3(blocks), dim3(256), 0, h->stream, (uint4*)h->zt, n16);
   HIPCHK(hipGetLastError());
   if (rebuild) {
-    hipLaunchKernelGGL(go_superko_rebuild_kernel<N>, dim3(waves_for<N>(h->B)), dim3(64), 0, h->stream, h->planes, h->meta, h->B, h->zt, h->zcur, h->sk_mode);
+    hipLaunchKernelGGL(go_superko_rebuild_kernel<N>, dim3(waves_for<N>(h->B)), dim3(64), 0, h->stream, h->state, h->meta, h->B, h->zt, h->zcur, h->sk_mode);
     HIPCHK(hipGetLastError());
   }
   return PGXGO_OK;
@@ -2158,7 +2288,7 @@ int fill_ctx(pgxgo_ctx* h, int32_t batch, int32_t board_size, uint32_t seed, con
   h->obs_pitch = o.obs_pitch; h->mask_pitch = o.mask_pitch;
   h->stream = (hipStream_t)o.stream;
   uint8_t* base = (uint8_t*)state_dev;
-  h->planes = (uint4*)base;
+  h->state = (uint32_t*)base;
   h->meta = (uint4*)(base + off_meta);
   h->rew_int = (float*)(base + off_rew);
   h->term_int = base + off_term;
@@ -2293,7 +2423,7 @@ int pgxgo_rollout(pgxgo_t h, int32_t steps, int32_t slices, uint32_t seed, uint3
   if (!h || steps < 0 || slices < 1) return PGXGO_EINVAL;
   if (steps == 0) return PGXGO_OK;
   RolloutArgs a;
-  a.planes = h->planes; a.meta = h->meta; a.B = h->B; a.wb = h->wb;
+  a.state = h->state; a.meta = h->meta; a.B = h->B; a.wb = h->wb;
   a.rules.seed = h->seed; a.rules.komi_x2 = h->komi_x2; a.rules.max_steps = h->max_steps; a.rules.auto_reset = h->auto_reset;
   a.steps = steps; a.slices = slices; a.seed = seed; a.t0 = t0; a.start_t = start_t_dev;
   a.actions = actions_dev; a.rew = rewards_dev; a.term = terminated_dev; a.mask = mask_dev; a.obs = obs_dev;

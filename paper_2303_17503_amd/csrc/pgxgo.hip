@@ -29,6 +29,7 @@
 //     go_rollout_kernel (T plies per launch, state in registers), go_step_slots_kernel (tree search: step
 //     from and to arbitrary state slots), go_step_superko_kernel (one ply with the positional-superko rule:
 //     Zobrist keys in per-game open-addressing tables), plus small set-up / export / import kernels.
+//   * Small batches are stepped by teams of four wavefronts per group of boards (go_step_team_kernel).
 //   * How many boards a launch puts into a wavefront (1 .. W) is chosen per launch: W for throughput at large
 //     batches, fewer at small batches where the slowest board of a wavefront and its serial output rounds
 //     decide the latency.
@@ -149,6 +150,7 @@ template <int N>
 struct Lane {
   int lane, j, r, b;     // lane id, board slot in the wavefront, row, index of the board in the call (outputs, actions)
   int slot;              // index of the environment whose state this board is (= b except in the slot kernels)
+  int some;              // an environment that exists, near this one's: what a lane without a board loads in its place
   bool valid;            // this lane holds a real row of a real board
   bool boardok;          // slot j holds a real board (also true for its sentinel lane)
   uint32_t seglo, seghi; // lanes of the rows of this lane's board
@@ -162,6 +164,7 @@ struct Lane {
     r = rr - 1;
     b = wave * wb + j;
     slot = b;
+    some = wave * wb < B ? wave * wb : 0;
     boardok = (j < wb) && (b < B);
     valid = boardok && rr >= 1;
     uint64_t seg = (j < wb) ? (((1ull << N) - 1ull) << (j * G::STRIDE + 1)) : 0ull;
@@ -200,8 +203,11 @@ struct State {                    // where one row of one game lies
   static constexpr int NEXT = N;  // dwords from one position of the ring to the next
   __device__ __forceinline__ State(uint32_t* base, const Lane<N>& L) {
     using G = Geo<N>;
-    uint32_t* game = base + (size_t)(uint32_t)L.slot * G::GAME;
-    hist = game + L.r * (G::RINGED ? 1 : G::HIST); tail = game + N * G::HIST + L.r * G::TAIL; cur = game + N * (G::HIST + G::TAIL) + L.r * G::CUR;
+    // a lane without a row of its own gets some row of the state: its loads need no branch, and it stores nothing.  (A row near
+    // by: with the same one for all wavefronts 256 games of 9x9 took 0.1 us more.)
+    uint32_t* game = base + (size_t)(uint32_t)(L.boardok ? L.slot : L.some) * G::GAME;
+    const int r = L.r > 0 ? L.r : 0;
+    hist = game + r * (G::RINGED ? 1 : G::HIST); tail = game + N * G::HIST + r * G::TAIL; cur = game + N * (G::HIST + G::TAIL) + r * G::CUR;
   }
 };
 template <int N>
@@ -217,41 +223,36 @@ struct Points {                   // column 2j in the low half of h[j], column 2
 template <int N>
 __device__ __forceinline__ void load_row(uint32_t* state, const Lane<N>& L, Row<N>& R) {
   using G = Geo<N>;
+  const State<N> S(state, L);
   uint2 v = make_uint2(0u, 0u);
-  if (L.valid) {
-    const State<N> S(state, L);
-    if constexpr (G::CUR == 2) v = *(const uint2*)S.cur;
-    else v.x = *S.cur;
-  }
-  // black, white and atari set, N bits each, from bit 0 on
-  uint32_t at;
-  R.bk = v.x & G::FULL;
-  if constexpr (G::CUR == 2) { R.wt = __builtin_amdgcn_alignbit(v.y, v.x, N) & G::FULL; at = (v.y >> (2 * N - 32)) & G::FULL; }
-  else { R.wt = (v.x >> N) & G::FULL; at = (v.x >> (2 * N)) & G::FULL; }
+  if constexpr (G::CUR == 2) v = *(const uint2*)S.cur;
+  else v.x = *S.cur;
+  // black, white and atari set, N bits each, from bit 0 on (a lane without a row: empty)
+  const uint32_t at = G::CUR == 2 ? v.y >> (2 * N - 32) : v.x >> (2 * N);
+  R.bk = v.x & L.full;
+  R.wt = (G::CUR == 2 ? __builtin_amdgcn_alignbit(v.y, v.x, N) : v.x >> N) & L.full;
   R.ab = at & R.bk; R.aw = at & R.wt;
 }
+// (what a lane without a row gets is some other row's history: nothing is done with it)
 template <int N>
 __device__ __forceinline__ void load_history(uint32_t* state, const Lane<N>& L, History<N>& H) {
   using G = Geo<N>;
+  const State<N> S(state, L);
+  if constexpr (G::RINGED) {
 #pragma unroll
-  for (int k = 0; k < G::HIST; ++k) H.s[k] = 0u;
-#pragma unroll
-  for (int k = 0; k < G::TAIL; ++k) H.tail[k] = 0u;
-  H.changed = 0u;
-  if (L.valid) {
-    const State<N> S(state, L);
-    if constexpr (G::RINGED) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) H.s[k] = S.hist[k * S.NEXT];
-      const uint2 v = *(const uint2*)S.tail;
-      H.tail[0] = v.x; H.tail[1] = v.y;
-    } else {
-      const uint4 v = *(const uint4*)S.hist;
-      H.s[0] = v.x; H.s[1] = v.y; H.s[2] = v.z; H.s[3] = v.w;
-      H.tail[0] = *S.tail;
-    }
+    for (int k = 0; k < 8; ++k) H.s[k] = S.hist[k * S.NEXT];
+    const uint2 v = *(const uint2*)S.tail;
+    H.tail[0] = v.x; H.tail[1] = v.y;
+  } else {
+    const uint4 v = *(const uint4*)S.hist;
+    H.s[0] = v.x; H.s[1] = v.y; H.s[2] = v.z; H.s[3] = v.w;
+    H.tail[0] = *S.tail;
   }
+  H.changed = 0u;
 }
+// The scalars of this lane's game (of some game in a lane without one: every use of them asks for a real board first)
+template <int N>
+__device__ __forceinline__ uint4 load_meta(const uint4* meta, const Lane<N>& L) { return meta[L.boardok ? L.slot : L.some]; }
 // ST: kind of the stores (store_small)
 template <int N, int ST = kStorePlain>
 __device__ __forceinline__ void store_row(const State<N>& S, const Row<N>& R) {
@@ -401,7 +402,9 @@ constexpr int state_store_kind(int out) { return out == kStoreStreamWhole ? kSto
 
 // What a ply changes of a row in memory, after push_history and clear_history: nothing unless the board moved or was re-initialised.
 template <int N, int ST>
-__device__ __forceinline__ void store_ply(uint32_t* state, const Lane<N>& L, const Row<N>& R, const History<N>& H, int head, bool moved, bool reset) {
+__device__ __forceinline__ void store_ply(uint32_t* state, const Lane<N>& L_, const Row<N>& R, const History<N>& H, int head, bool moved, bool reset) {
+  Lane<N> L = L_;
+  L.slot = in_place(L.slot); L.r = in_place(L.r);   // (the addresses anew: kept from the loads on they cost the superko kernels registers they do not have)
   if (L.valid && (moved || reset)) {
     const State<N> S(state, L);
     store_row<N, ST>(S, R);
@@ -472,20 +475,11 @@ __device__ __forceinline__ void emit_mask(const Lane<N>& L, uint32_t legal, int 
   wave_lds_fence();
 }
 
-// Observation bytes [N][N][17] of every board of the wavefront from the history words h of its rows.  MOST, FIRST_AS_EDGE: see emit_bytes.
-template <int N, bool TIGHT, int ST = kStorePlain, int MOST = 4, bool FIRST_AS_EDGE = false>
-__device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[Geo<N>::HD], int wtm, int wave, int B, uint8_t* obs,
-                                         int64_t obs_pitch, uint32_t* lds_obs, const uint2* lut, int wb = Geo<N>::W) {
+// The observation's bits of one row: 17 bits per point, the point's history halfword seen by the mover (pairs swapped when White
+// moves), then the colour bit (Appendix C "Go", Observation); a row is N such pieces back to back.
+template <int N>
+__device__ __forceinline__ void obs_string(uint32_t (&S)[Geo<N>::NR], const uint32_t (&h)[Geo<N>::HD], int wtm) {
   using G = Geo<N>;
-  static_assert((15 + G::W * G::OBS_PAD + 31) / 32 <= G::W * G::OBS_DW, "one stream for all boards fits the staging area");
-  constexpr bool tight = TIGHT;   // the caller guarantees obs_pitch == N*N*17 or OBS_PAD (see emit_mask)
-  const uint32_t stride = (uint32_t)obs_pitch;
-  const int j = in_place(L.j), row = in_place(L.r);
-  const int b0 = wave * wb;
-  const int nb = B - b0 < wb ? B - b0 : wb;
-  // 17 bits per point: the point's history halfword seen by the mover (pairs swapped when White moves),
-  // then the colour bit (Appendix C "Go", Observation); a row is N such pieces back to back.
-  uint32_t S[G::NR];
 #pragma unroll
   for (int k = 0; k < G::NR; ++k) S[k] = 0u;
   const uint32_t cb = wtm ? 0u : 1u;
@@ -501,38 +495,60 @@ __device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[G
     S[k] |= low32 << sh;
     if (k + 1 < G::NR) S[k + 1] |= sh ? ((low32 >> (32 - sh)) | (high2 << sh)) : high2;
   }
-  {
-    uint4* z = (uint4*)lds_obs;
-    const uint32_t zero = in_place(0u);
-    constexpr int NZ = G::W * G::OBS_DW / 4;
+}
+template <int N>
+__device__ __forceinline__ void clear_obs_stream(uint32_t* lds_obs, int lane) {
+  using G = Geo<N>;
+  uint4* z = (uint4*)lds_obs;
+  const uint32_t zero = in_place(0u);
+  constexpr int NZ = G::W * G::OBS_DW / 4;
 #pragma unroll
-    for (int i = 0; i < (NZ + 63) / 64; ++i)
-      if (i * 64 + 63 < NZ || i * 64 + L.lane < NZ) z[i * 64 + L.lane] = make_uint4(zero, zero, zero, zero);
+  for (int i = 0; i < (NZ + 63) / 64; ++i)
+    if (i * 64 + 63 < NZ || i * 64 + lane < NZ) z[i * 64 + lane] = make_uint4(zero, zero, zero, zero);
+}
+// Puts a row's bits at bit offset o of the (cleared) stream.  Written as a left shift by u = 1..32 from dword (o-u)/32 on, every
+// shifted dword is one funnel shift of two neighbours of S (a shift by 0 would need a special case): T[i] = bits of dword q+i;
+// T[0] and T[NI+1..NR] may share their dword with the rows next door.
+template <int N>
+__device__ __forceinline__ void put_obs_string(uint32_t* reg, const uint32_t (&S)[Geo<N>::NR], uint32_t o) {
+  using G = Geo<N>;
+  const uint32_t u1 = (o + 31u) & 31u;            // u - 1
+  reg += (int32_t)(o - 1u - u1) >> 5;             // dword -1 only when o = 0, and then T[0] = 0 is not written
+  const uint32_t sh = 31u - u1;                   // right shift of the (S[i], S[i-1]) pair that equals the left shift by u
+  {
+    const uint32_t t0 = __builtin_amdgcn_alignbit(S[0], 0u, sh);
+    if (t0) atomicOr(&reg[0], t0);
   }
+#pragma unroll
+  for (int i = 1; i <= G::NR; ++i) {
+    const uint32_t hi = (i < G::NR) ? S[i] : 0u;
+    const uint32_t t = __builtin_amdgcn_alignbit(hi, S[i - 1], sh);
+    if (i <= G::NI) reg[i] = t;
+    else if (t) atomicOr(&reg[i], t);
+  }
+}
+
+// Observation bytes [N][N][17] of every board of the wavefront from the history words h of its rows.  MOST, FIRST_AS_EDGE: see emit_bytes.
+template <int N, bool TIGHT, int ST = kStorePlain, int MOST = 4, bool FIRST_AS_EDGE = false>
+__device__ __forceinline__ void emit_obs(const Lane<N>& L, const uint32_t (&h)[Geo<N>::HD], int wtm, int wave, int B, uint8_t* obs,
+                                         int64_t obs_pitch, uint32_t* lds_obs, const uint2* lut, int wb = Geo<N>::W) {
+  using G = Geo<N>;
+  static_assert((15 + G::W * G::OBS_PAD + 31) / 32 <= G::W * G::OBS_DW, "one stream for all boards fits the staging area");
+  constexpr bool tight = TIGHT;   // the caller guarantees obs_pitch == N*N*17 or OBS_PAD (see emit_mask)
+  const uint32_t stride = (uint32_t)obs_pitch;
+  const int j = in_place(L.j), row = in_place(L.r);
+  const int b0 = wave * wb;
+  const int nb = B - b0 < wb ? B - b0 : wb;
+  uint32_t S[G::NR];
+  obs_string<N>(S, h, wtm);
+  clear_obs_stream<N>(lds_obs, L.lane);
   wave_lds_fence();
   if (L.valid) {
     uint32_t* reg;
     uint32_t head;
     if constexpr (tight) { head = (uint32_t)((uintptr_t)(obs + (int64_t)b0 * obs_pitch) & 15u) + __umul24((uint32_t)j, stride); reg = lds_obs; }
     else { head = (uint32_t)((uintptr_t)(obs + (int64_t)L.b * obs_pitch) & 15u); reg = lds_obs + j * G::OBS_DW; }
-    // The row's string goes to bit offset o of the stream.  Written as a left shift by u = 1..32 from dword (o-u)/32
-    // on, every shifted dword is one funnel shift of two neighbours of S (a shift by 0 would need a special case):
-    // T[i] = bits of dword q+i; T[0] and T[NI+1..NR] may share their dword with the rows next door.
-    const uint32_t o = head + (uint32_t)(G::ROWBITS * row);
-    const uint32_t u1 = (o + 31u) & 31u;            // u - 1
-    reg += (int32_t)(o - 1u - u1) >> 5;             // dword -1 only when o = 0, and then T[0] = 0 is not written
-    const uint32_t sh = 31u - u1;                   // right shift of the (S[i], S[i-1]) pair that equals the left shift by u
-    {
-      const uint32_t t0 = __builtin_amdgcn_alignbit(S[0], 0u, sh);
-      if (t0) atomicOr(&reg[0], t0);
-    }
-#pragma unroll
-    for (int i = 1; i <= G::NR; ++i) {
-      const uint32_t hi = (i < G::NR) ? S[i] : 0u;
-      const uint32_t t = __builtin_amdgcn_alignbit(hi, S[i - 1], sh);
-      if (i <= G::NI) reg[i] = t;
-      else if (t) atomicOr(&reg[i], t);
-    }
+    put_obs_string<N>(reg, S, head + (uint32_t)(G::ROWBITS * row));
   }
   wave_lds_fence();
   if constexpr (tight) {
@@ -564,7 +580,7 @@ struct Draw {          // the drawn action as every lane of the board sees it
 };
 
 template <int N>
-__device__ __forceinline__ Draw<N> draw_action(const Lane<N>& L, uint32_t legal, uint32_t seed, uint32_t t, bool wait) {
+__device__ __forceinline__ Draw<N> draw_action(const Lane<N>& L, uint32_t legal, uint32_t hash, bool wait) {   // hash: env_hash(seed, 0, L.b, t)
   using G = Geo<N>;
   const uint32_t cnt = __popc(legal);
   // legal points in the rows above this one, and on the whole board, from ballots of the bits of cnt
@@ -576,7 +592,7 @@ __device__ __forceinline__ Draw<N> draw_action(const Lane<N>& L, uint32_t legal,
     before += __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)) << k;
     total += (uint32_t)(__popc(lo) + __popc(hi)) << k;
   }
-  const uint32_t k = env_hash(seed, 0u, (uint32_t)L.b, t) % total;
+  const uint32_t k = hash % total;
   // position of the (n+1)-th set bit of the row word by halving (meaningful in the row that holds it)
   uint32_t n = k - before, w = legal, pos = 0u;
 #pragma unroll
@@ -594,6 +610,10 @@ __device__ __forceinline__ Draw<N> draw_action(const Lane<N>& L, uint32_t legal,
   d.pr = (src & 63) - (L.j * G::STRIDE + 1);
   d.pc = (int)__shfl((int)pos, src & 63);
   return d;
+}
+template <int N>
+__device__ __forceinline__ Draw<N> draw_action(const Lane<N>& L, uint32_t legal, uint32_t seed, uint32_t t, bool wait) {
+  return draw_action<N>(L, legal, env_hash(seed, 0u, (uint32_t)L.b, t), wait);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -902,8 +922,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint32_
   History<N> H;
   load_row<N>(state, L, R);
   load_history<N>(state, L, H);
-  const uint4 meta_raw = L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
-  const int act = L.boardok ? actions[L.b] : -1;
+  const uint4 meta_raw = load_meta<N>(meta, L);
+  const int act_raw = actions[L.boardok ? L.b : L.some], act = L.boardok ? act_raw : -1;
   // loaded here and not where it is used: a load after the output stores would have to wait for them (one counter);
   // looked at only after the table is filled, so that no wait for a load comes before the barrier
   const int32_t start_raw = (SAMPLE && L.boardok && start_t) ? start_t[L.b] : INT32_MIN;
@@ -939,6 +959,152 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint32_
   if (SAMPLE) {
     const Draw<N> d = draw_action<N>(L, legal, a.sample_seed, a.sample_t, wait_start);
     if (L.valid && L.r == 0) a.next_actions[L.b] = d.action();
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The same ply by TEAMS, for batches that leave most of the machine empty.  A block is a team: four wavefronts that share one
+// group of boards.  One applies the rules; the others load what they need meanwhile and, once it has left the new position in LDS,
+// one of them writes the mask, one the observation, one draws the next action, and the first stores the state.
+// A ply of few games is bound by the chain of instructions of a wavefront that has its SIMD to itself (one every four to five cycles, some
+// 1000 of them at 9x9 and 1200 at 19x19): a team's chain is the state's load, the gate and the rules, and then the longest of
+// four shorter ones (9x9 x 256 games: a wavefront lives 6600 instead of 9150 cycles).  What the observation's wavefront can do ahead it
+// does while the rules run.  Figures, and where the line to the other kernel lies: auto_boards_per_team.
+// ------------------------------------------------------------------------------------------------
+// What the wavefront that applies the rules leaves for the other three: every lane its row, the board's facts in the bits beyond
+// column N-1.
+template <int N>
+struct HandOver {
+  static_assert(N * N + 1 < 512 && N <= 20, "ko point and flags fit beside a row");
+  uint4 v;
+  static __device__ __forceinline__ HandOver of(const Row<N>& R, const Meta& m, const Ply& ply) {
+    return HandOver{make_uint4(R.bk | (ply.moved ? 1u << 29 : 0u) | (ply.reset ? 1u << 30 : 0u), R.wt | ((uint32_t)(m.ko + 1) << 20) | ((uint32_t)m.wtm << 31), R.ab, R.aw)};
+  }
+  __device__ __forceinline__ Row<N> row() const { return Row<N>{v.x & Geo<N>::FULL, v.y & Geo<N>::FULL, v.z, v.w}; }
+  __device__ __forceinline__ bool moved() const { return (v.x >> 29) & 1u; }
+  __device__ __forceinline__ bool reset() const { return (v.x >> 30) & 1u; }
+  __device__ __forceinline__ int wtm() const { return (int)(v.y >> 31); }
+  __device__ __forceinline__ int ko() const { return (int)((v.y >> 20) & 511u) - 1; }
+  __device__ __forceinline__ uint32_t legal(const Lane<N>& L) const { return legal_row<N>(L, row(), wtm(), ko()); }
+};
+enum TeamRole { kTeamRules = 0, kTeamMask = 1, kTeamDraw = 2, kTeamObs = 3, kTeamWaves = 4 };
+
+// The observation of a team: everything but the ply's own changes is put into the stream beforehand, as if the position were to
+// stay as it is (a pass), and the points that do change are corrected in it.  A board for which that was wrong (skipped, illegal, ended)
+// has the wavefront build its stream anew.
+template <int N, int ST, class Wait>
+__device__ __forceinline__ void team_obs(const Lane<N>& L, const Row<N>& before, Points<N> Q, const Meta& m, const uint4* hand, int group, int B, uint8_t* obs,
+                                         int64_t obs_pitch, uint32_t* lds_obs, const uint2* lut, int wb, Wait&& wait_for_hand_over) {
+  using G = Geo<N>;
+  const uint32_t stride = (uint32_t)obs_pitch;
+  const int b0 = group * wb, nb = B - b0 < wb ? B - b0 : wb;
+  uint8_t* const dst = obs + (int64_t)b0 * obs_pitch;
+  const uint32_t at = (uint32_t)((uintptr_t)dst & 15u) + __umul24((uint32_t)L.j, stride) + (uint32_t)(G::ROWBITS * L.r);
+  auto build = [&](const Points<N>& P, int wtm) {
+    uint32_t S[G::NR];
+    obs_string<N>(S, P.h, wtm);
+    clear_obs_stream<N>(lds_obs, L.lane);
+    wave_lds_fence();
+    if (L.valid) put_obs_string<N>(lds_obs, S, at);
+    wave_lds_fence();
+  };
+  Points<N> next = Q;
+  push_points<N>(next, before.bk, before.wt, true);
+  build(next, m.wtm ^ 1);
+  wait_for_hand_over();
+  const HandOver<N> in{hand[L.lane]};
+  const Row<N> R = in.row();
+  const bool as_expected = in.moved() && !in.reset();   // then the other player is to move
+  if (__ballot(L.valid && !as_expected) != 0ull) {
+    if (in.reset()) clear_points<N>(Q);
+    push_points<N>(Q, R.bk, R.wt, in.moved());
+    build(Q, in.wtm());
+  } else {
+    const uint32_t db = R.bk ^ before.bk, dw = R.wt ^ before.wt;
+    uint32_t d = db | dw;
+    while (__ballot(d != 0u) != 0ull) {   // the stone played, and those it took
+      if (d) {
+        const int c = __ffs(d) - 1;
+        const uint32_t black = (db >> c) & 1u, white = (dw >> c) & 1u;
+        const uint32_t bits = in.wtm() ? white | (black << 1) : black | (white << 1);   // mover's stone, opponent's stone
+        const uint32_t o = at + 17u * (uint32_t)c, q = o >> 5, sh = o & 31u;
+        atomicXor(&lds_obs[q], bits << sh);
+        if (sh == 31u) atomicXor(&lds_obs[q + 1], bits >> 1);
+        d &= d - 1u;
+      }
+    }
+    wave_lds_fence();
+  }
+  emit_bytes<G::W * G::OBS_PAD, ST>(lds_obs, lut, dst, (uint32_t)nb * stride, L.lane);
+}
+
+template <int N, bool SAMPLE, int ST>
+__global__ void __launch_bounds__(64 * kTeamWaves) go_step_team_kernel(uint32_t* state, uint4* meta, const int32_t* actions, const int32_t* start_t, int B,
+                                                                       int wb, uint32_t eighth, StepArgs a) {   // wb: boards per team
+  using G = Geo<N>;
+  static_assert(64 * kTeamWaves == kBlockThreads, "the table is filled by one entry per thread");
+  __shared__ __attribute__((aligned(16))) uint32_t lds_obs[G::W * G::OBS_DW];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_mask[64];
+  __shared__ uint64_t tally[64];
+  __shared__ uint2 lut[256];
+  __shared__ uint4 hand[64];
+  const int group = piece_of_block(eighth);
+  if (group * wb >= B) return;   // the whole block
+  const int role = wave_in_block();
+  const Lane<N> L(group, threadIdx.x & 63, B, wb);
+  auto fill_table = [&]() { const uint32_t x = threadIdx.x; lut[x] = make_uint2(spread4(x & 15u), spread4(x >> 4)); };
+
+  if (role == kTeamRules) {
+    Row<N> R;
+    History<N> H;
+    load_row<N>(state, L, R);
+    const uint4 meta_raw = load_meta<N>(meta, L);
+    const int act_raw = actions[L.boardok ? L.b : L.some], act = L.boardok ? act_raw : -1;
+    load_history<N>(state, L, H);
+    in_scalar_registers(a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset, a.rew, a.term);
+    fill_table();
+    Meta m = unpack_meta(meta_raw);
+    const bool skip = !L.boardok || act == -1;
+    const bool in_range = act >= 0 && act < G::P;
+    const int pr = in_range ? act / N : 0, pc = in_range ? act - (act / N) * N : 0;
+    const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, pr, pc);
+    const Ply ply = apply_move<N>(L, R, m, a.rules, mv, tally, [&]() { clear_history<N>(H); });
+    hand[L.lane] = HandOver<N>::of(R, m, ply).v;
+    __syncthreads();
+    push_history<N>(H, m.head, R.bk, R.wt, ply.moved);
+    store_ply<N, kStorePlain>(state, L, R, H, m.head, ply.moved, ply.reset);
+    if (!skip && L.valid && L.r == 0) {
+      meta[L.b] = pack_meta(m);
+      *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(ply.rew0, ply.rew1);
+      a.term[L.b] = (uint8_t)(ply.flag ? 1 : 0);   // (neighbouring teams write bytes of one line: through the L2 it goes to memory with each of them)
+    }
+  } else if (role == kTeamMask) {
+    in_scalar_registers(a.mask, a.mask_pitch);
+    fill_table();
+    __syncthreads();
+    if (a.mask) emit_mask<N, true, ST>(L, HandOver<N>{hand[L.lane]}.legal(L), group, B, a.mask, a.mask_pitch, lds_mask, lut, wb);
+  } else if (role == kTeamDraw) {
+    const int32_t start_raw = (SAMPLE && L.boardok && start_t) ? start_t[L.b] : INT32_MIN;
+    in_scalar_registers(a.sample_seed, a.sample_t, a.next_actions);
+    fill_table();
+    const uint32_t hash = in_place(env_hash(a.sample_seed, 0u, (uint32_t)L.b, a.sample_t));
+    __syncthreads();
+    if (SAMPLE) {
+      const Draw<N> d = draw_action<N>(L, HandOver<N>{hand[L.lane]}.legal(L), hash, (int64_t)a.sample_t < (int64_t)start_raw);
+      if (L.valid && L.r == 0) a.next_actions[L.b] = d.action();
+    }
+  } else if (a.obs) {
+    Row<N> R;
+    History<N> H;
+    load_row<N>(state, L, R);
+    load_history<N>(state, L, H);
+    const Meta m = unpack_meta(load_meta<N>(meta, L));
+    in_scalar_registers(a.obs, a.obs_pitch);
+    fill_table();
+    team_obs<N, ST>(L, R, points_of<N>(H, m.head), m, hand, group, B, a.obs, a.obs_pitch, lds_obs, lut, wb, [] { __syncthreads(); });
+  } else {
+    fill_table();
+    __syncthreads();
   }
 }
 
@@ -1431,9 +1597,9 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   History<N> H;
   load_row<N>(state, L, R);
   load_history<N>(state, L, H);
-  const uint4 meta_raw = L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
-  const int act = L.boardok ? actions[L.b] : -1;
-  const uint4 g_raw = zcur[L.boardok ? L.b : 0];   // (an unconditional load: a conditional one is waited for on the spot)
+  const uint4 meta_raw = load_meta<N>(meta, L);
+  const int act_raw = actions[L.boardok ? L.b : L.some], act = L.boardok ? act_raw : -1;
+  const uint4 g_raw = zcur[L.boardok ? L.b : L.some];
   const int32_t start_raw = (a.next_actions && L.boardok && start_t) ? start_t[L.b] : INT32_MIN;
   in_scalar_registers(a.rew, a.term, a.mask, a.obs, a.mask_pitch, a.obs_pitch, a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset);
   fill_spread_table(lut);   // (nothing loaded above is looked at before this barrier)
@@ -1450,11 +1616,11 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   none.home = ~0u; none.e = make_uint2(1u, 0u);
   uint32_t forb = 0u;
   Ply ply;
-  // a6, a10 (mode 1 still holds the row and the table window: a fourth round at once would spill)
+  // a6, a10 (mode 1 still holds the row and the table window: a fourth round at once, at 9x9 a third, would spill)
   auto board_final = [&](bool moved, bool reset) {
     push_history<N>(H, m.head, R.bk, R.wt, moved);
     if (reset) clear_history<N>(H);
-    if (a.obs) emit_obs<N, TIGHT, ST, MODE == 1 ? 3 : 4>(L, points_of<N>(H, m.head).h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
+    if (a.obs) emit_obs<N, TIGHT, ST, MODE == 1 ? (N == 9 ? 2 : 3) : 4>(L, points_of<N>(H, m.head).h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
   };
   if constexpr (MODE == 1) {
     const SkWin pre = sk_window_play<N>(L, tab, g, m, !skip);
@@ -1463,7 +1629,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
                                        Row<N> T;
                                        load_row<N>(state, L, T);
                                        load_history<N>(state, L, H);
-                                       const Meta as_loaded = unpack_meta(meta[L.boardok ? L.b : 0]);
+                                       const Meta as_loaded = unpack_meta(load_meta<N>(meta, L));
                                        mr.head = as_loaded.head;
                                        if (which) { Rr = T; mr = as_loaded; }
                                      });
@@ -1499,7 +1665,7 @@ __global__ void __launch_bounds__(64) go_superko_rebuild_kernel(uint32_t* state,
   History<N> H;
   load_row<N>(state, L, R);
   load_history<N>(state, L, H);
-  const Meta m = unpack_meta(L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
+  const Meta m = unpack_meta(load_meta<N>(meta, L));
   const Points<N> Q = points_of<N>(H, m.head);
   uint2* tab = zt + (size_t)(L.boardok ? L.b : 0) * Zt<N>::SLOTS;
   SkWin none;
@@ -1575,12 +1741,12 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
   const bool in_pool = src >= 0 && src < pool && dst >= 0 && dst < pool;
   const bool bad = L.boardok && !in_pool;
   if (bad) { L.boardok = false; L.valid = false; L.full = 0u; }   // the entry becomes inert: no state access, no outputs
-  L.slot = src;
+  L.slot = src; L.some = 0;
   Row<N> R;
   History<N> H;
   load_row<N>(state, L, R);
   load_history<N>(state, L, H);
-  const uint4 meta_raw = L.boardok ? meta[src] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
+  const uint4 meta_raw = load_meta<N>(meta, L);
   const int act = (L.boardok && actions) ? actions[L.b] : -1;
   in_scalar_registers(a.rew, a.term, a.mask, a.obs, a.mask_pitch, a.obs_pitch, a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset);
   fill_spread_table(lut);
@@ -1707,7 +1873,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
   const Lane<N> L0(wave, threadIdx.x & 63, a.B, a.wb);
   Row<N> R;
   Points<N> Q;
-  Meta m = unpack_meta(L0.boardok ? a.meta[L0.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
+  Meta m = unpack_meta(load_meta<N>(a.meta, L0));
   {
     History<N> H;
     load_row<N>(a.state, L0, R);
@@ -1810,7 +1976,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_emit_kernel(uint32_t* 
   History<N> H;
   load_row<N>(state, L, R);
   if (obs) load_history<N>(state, L, H);
-  Meta m = unpack_meta(L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
+  Meta m = unpack_meta(load_meta<N>(meta, L));
   uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
   if constexpr (SK) {
     if (mask) {
@@ -1836,7 +2002,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_random_actions_kernel(
   const Lane<N> L(wave, threadIdx.x & 63, B);
   Row<N> R;
   load_row<N>(state, L, R);
-  Meta m = unpack_meta(L.boardok ? meta[L.b] : make_uint4(0xFFFFFFFFu, 0u, 0u, 0u));
+  Meta m = unpack_meta(load_meta<N>(meta, L));
   uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
   if constexpr (SK) {
     const SkGame g = L.boardok ? sk_unpack(zcur[L.b]) : sk_fresh();
@@ -2011,6 +2177,7 @@ size_t state_bytes_for(int B, size_t* off_meta, size_t* off_rew, size_t* off_ter
 struct pgxgo_ctx {
   int B, N;
   int wb;        // boards per wavefront used by the step and rollout launches (1 .. W)
+  int team;      // boards per team of the step launches that teams take (auto_boards_per_team), or 0
   uint32_t seed;
   int komi_x2, max_steps, auto_reset;
   int64_t obs_pitch, mask_pitch;
@@ -2087,6 +2254,23 @@ int auto_boards_per_wavefront(int B) {
   return (int)(((int64_t)B + 1024 * (int64_t)per_simd - 1) / (1024 * (int64_t)per_simd));
 }
 
+// Boards per team of four wavefronts (go_step_team_kernel) for batches that are faster that way, else 0.  A team is worth while as long as
+// the machine has wavefront slots to spare: up to four teams per compute unit at 9x9 (us per ply, one wavefront for all / teams: 256
+// games 4.60 / 3.72, 1024 4.94 / 4.16, 2048 4.95 / 4.55, 4096 5.29 / 5.20, 5000 5.58 / 5.46, 8192 6.15 / 6.31) and eight at 19x19, where the
+// observation is four times as long (256 games 5.96 / 4.63, 1000 6.47 / 5.66, 2048 7.18 / 6.08, 4096 8.79 / 7.50, 5500 9.57 / 8.57, 8192
+// 12.0 / 12.4; without observation 1000 5.34 / 4.79, 4096 6.27 / 6.05, 5500 6.48 / 6.54).  Boards: as few as keep the teams at one to two per
+// compute unit (9x9 x 256 with 1 / 2 / 4 boards 3.72 / 3.77 / 3.97, x 1024 4.63 / 4.16 / 4.30, x 2048 5.8 / 4.78 / 4.55; 19x19 x 400 with 1 / 3
+// 5.09 / 5.33, x 700 5.46 / 5.42, x 2048 7.52 / 6.08).
+template <int N>
+int auto_boards_per_team(int B) {
+  if (N == 9) return B <= 384 ? 1 : B <= 1024 ? 2 : B <= 4096 ? 4 : 0;
+  return B <= 512 ? 1 : B <= 2048 * Geo<N>::W ? Geo<N>::W : 0;
+}
+constexpr int kTeamsWithoutObservation = 1366;   // 19x19: more teams only pay with the observation
+// Outputs of a team launch up to this many bytes are stored the ordinary way (9x9 x 256 games 3.72 us against 3.83 written through, 19x19 x 400, 2.6
+// MB, 5.09 / 5.13, without observation x 2048 5.24 / 5.36), beyond it through the L2 (9x9 x 2048, 3 MB, 4.63 / 4.55; 19x19 x 1000 6.10 / 5.66).
+constexpr size_t kTeamPlainUpTo = (size_t)5 << 19;
+
 // both output pitches are the dense or the line-padded ones: the kernels treat a wavefront's boards as one run of bytes
 // (with the line-padded pitch the pad bytes belong to that run and are written as zeros)
 template <int N>
@@ -2124,6 +2308,23 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
   h->mask_written = h->mask_out; h->obs_written = h->obs_out;
   const dim3 grid(blocks_for_wb(h->B, h->wb)), block(64 * kWavesPerBlock);
   const bool tight = tight_pitches<N>(h);
+  const int teams = h->team ? (h->B + h->team - 1) / h->team : 0;
+  if (tight && !h->zt && teams && (h->obs_out || teams <= kTeamsWithoutObservation)) {
+    const dim3 tgrid((unsigned)(teams + 7) & ~7u);
+    const bool plain = output_bytes_per_ply(h, h->mask_out != nullptr, h->obs_out != nullptr) <= kTeamPlainUpTo;
+    auto team = [&](auto sample_c, auto st_c) {
+      hipLaunchKernelGGL((go_step_team_kernel<N, decltype(sample_c)::value, decltype(st_c)::value>), tgrid, block, 0, h->stream, h->state, h->meta, actions, start_t,
+                         h->B, h->team, tgrid.x / 8, a);
+    };
+    using Plain = std::integral_constant<int, kStorePlain>;
+    using Through = std::integral_constant<int, kStoreThrough>;
+    if (sample && plain) team(std::true_type{}, Plain{});
+    else if (sample) team(std::true_type{}, Through{});
+    else if (plain) team(std::false_type{}, Plain{});
+    else team(std::false_type{}, Through{});
+    HIPCHK(hipGetLastError());
+    return PGXGO_OK;
+  }
   if (h->zt) {
     if (!sample) a.next_actions = nullptr;
     auto sk = [&](auto tight_c, auto mode_c) {
@@ -2284,6 +2485,7 @@ int fill_ctx(pgxgo_ctx* h, int32_t batch, int32_t board_size, uint32_t seed, con
   *h = pgxgo_ctx{};
   h->B = batch; h->N = board_size; h->seed = seed;
   h->wb = board_size == 19 ? auto_boards_per_wavefront<19>(batch) : auto_boards_per_wavefront<9>(batch);
+  h->team = board_size == 19 ? auto_boards_per_team<19>(batch) : auto_boards_per_team<9>(batch);
   h->komi_x2 = o.komi_x2; h->max_steps = o.max_steps; h->auto_reset = o.auto_reset ? 1 : 0;
   h->obs_pitch = o.obs_pitch; h->mask_pitch = o.mask_pitch;
   h->stream = (hipStream_t)o.stream;
@@ -2520,6 +2722,7 @@ int pgxgo_set_boards_per_wavefront(pgxgo_t h, int32_t boards) {
   const int wmax = h->N == 19 ? Geo<19>::W : Geo<9>::W;
   if (boards < 0 || boards > wmax) return PGXGO_EINVAL;
   h->wb = boards ? boards : (h->N == 19 ? auto_boards_per_wavefront<19>(h->B) : auto_boards_per_wavefront<9>(h->B));
+  h->team = boards ? 0 : (h->N == 19 ? auto_boards_per_team<19>(h->B) : auto_boards_per_team<9>(h->B));   // a number that is asked for is had
   return h->wb;
 }
 

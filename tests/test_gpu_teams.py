@@ -1,0 +1,46 @@
+"""Small batches are stepped by teams of four wavefronts.  At the sizes where the number of boards per team changes, and in the last
+team of a batch, their outputs and state are those of the kernel in which one wavefront does everything (set_boards_per_wavefront asks
+for it), through skipped, illegal and passed plies, captures, endings and restarts in one team."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2303_17503_amd as pg
+
+pytestmark = pytest.mark.gpu
+
+
+def bound(env, obs):
+    B = env.B
+    out = [env.new_mask(), env.new_obs() if obs else None, torch.zeros((B, 2), dtype=torch.float32, device="cuda"), torch.zeros(B, dtype=torch.uint8, device="cuda")]
+    env.bind_outputs(*out)
+    return [t for t in out if t is not None]
+
+
+@pytest.mark.parametrize("N,B,auto_reset,obs,line_padded", [
+    (9, 1, True, True, False), (9, 384, True, True, False), (9, 385, False, True, True), (9, 1025, True, True, False), (9, 4095, True, False, False),
+    (19, 1, True, True, True), (19, 512, True, True, False), (19, 513, False, True, False), (19, 4097, True, False, False), (19, 6143, True, True, False)])
+def test_teams_and_single_wavefronts_agree(N, B, auto_reset, obs, line_padded):
+    kw = dict(seed=9, auto_reset=auto_reset, line_padded=line_padded, max_steps=60 if auto_reset else 0)
+    a, b = pg.GoEnv(B, N, **kw), pg.GoEnv(B, N, **kw)
+    b.set_boards_per_wavefront(2)
+    for e in (a, b):
+        e.rollout(40 if auto_reset else 150, 9, 0)
+    oa, ob = bound(a, obs), bound(b, obs)
+    rng = np.random.default_rng(B)
+    nxt = a.random_actions(9, 500)
+    for t in range(24):
+        odd = torch.as_tensor(rng.choice([-1, 0, N * N, N * N + 5], size=B).astype(np.int32), device="cuda")   # skip, a corner, pass, out of range
+        use = torch.as_tensor(rng.random(B) < (0.1 if t % 2 else 0.0), device="cuda")                          # every other ply all boards play
+        act = torch.where(use, odd, nxt).contiguous()
+        if t % 3 == 0:
+            a.step(act); b.step(act)
+            nxt, nb = a.random_actions(9, 501 + t), b.random_actions(9, 501 + t)
+        else:
+            nxt, nb = a.step_sample(act, 9, 501 + t), b.step_sample(act, 9, 501 + t)
+        assert torch.equal(nxt, nb), t
+        for x, y in zip(oa, ob):
+            assert torch.equal(x, y), t
+    sa, sb = a.export_state(), b.export_state()
+    for k in sa:
+        assert torch.equal(sa[k], sb[k]), k

@@ -265,17 +265,21 @@ __device__ __forceinline__ void store_tail(const State<N>& S, const History<N>& 
   if constexpr (Geo<N>::TAIL == 2) store_small<ST>((uint2*)S.tail, make_uint2(H.tail[0], H.tail[1]));
   else store_small<ST>(S.tail, H.tail[0]);
 }
-// the whole state of a row
+// the whole history, the whole state of a row
 template <int N>
-__device__ __forceinline__ void store_all(uint32_t* state, const Lane<N>& L, const Row<N>& R, const History<N>& H) {
+__device__ __forceinline__ void store_history(uint32_t* state, const Lane<N>& L, const History<N>& H) {
   if (!L.valid) return;
   const State<N> S(state, L);
-  store_row<N>(S, R);
   store_tail<N>(S, H);
   if constexpr (Geo<N>::RINGED) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) S.hist[k * S.NEXT] = H.s[k];
   } else *(uint4*)S.hist = make_uint4(H.s[0], H.s[1], H.s[2], H.s[3]);
+}
+template <int N>
+__device__ __forceinline__ void store_all(uint32_t* state, const Lane<N>& L, const Row<N>& R, const History<N>& H) {
+  if (L.valid) store_row<N>(State<N>(state, L), R);
+  store_history<N>(state, L, H);
 }
 
 // A row's stones with the colours side by side: bits 2j / 2j+1 = black / white at column 2j (lo), at column 2j+1 (hi)
@@ -969,7 +973,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint32_
 // A ply of few games is bound by the chain of instructions of a wavefront that has its SIMD to itself (one every four to five cycles, some
 // 1000 of them at 9x9 and 1200 at 19x19): a team's chain is the state's load, the gate and the rules, and then the longest of
 // four shorter ones (9x9 x 256 games: a wavefront lives 6600 instead of 9150 cycles).  What the observation's wavefront can do ahead it
-// does while the rules run.  Figures, and where the line to the other kernel lies: auto_boards_per_team.
+// does while the rules run.  Figures, and where the line to the other kernel lies: boards_per_step_team.
 // ------------------------------------------------------------------------------------------------
 // What the wavefront that applies the rules leaves for the other three: every lane its row, the board's facts in the bits beyond
 // column N-1.
@@ -1956,6 +1960,97 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
 }
 
 // ------------------------------------------------------------------------------------------------
+// The same plies by teams (go_step_team_kernel): one wavefront draws and applies the rules, ply after ply; it leaves each position in
+// LDS, in one of two places in turn, and goes on with the next ply while the others write the outputs of this one.
+// A ply's chain is then a draw and the rules alone: of the 5200 cycles that a wavefront by itself takes for a ply of one 9x9 board, with its
+// observation, 3200 are left.  Figures, and which rollouts go this way: boards_per_rollout_team.
+// ------------------------------------------------------------------------------------------------
+// Everything the wavefronts of a block wrote to LDS is there for all of them.  (Unlike __syncthreads this does not wait for their output
+// stores as well.)
+__device__ __forceinline__ void team_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+template <int N, bool OBS>
+__global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_rollout_team_kernel(RolloutArgs a) {   // a.wb: boards per team
+  using G = Geo<N>;
+  constexpr int WAVES = OBS ? 3 : 2, ST = kStoreThroughWhole;
+  constexpr bool FIRST_AS_EDGE = N == 19;   // as in go_rollout_kernel
+  __shared__ __attribute__((aligned(16))) uint32_t lds_obs[OBS ? G::W * G::OBS_DW : 4];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_mask[64];
+  __shared__ uint64_t tally[64];
+  __shared__ uint2 lut[256];
+  __shared__ uint4 hand[2][64];
+  __shared__ uint4 scalars[2][G::W];   // per board: action, rewards, terminated
+  const int group = piece_of_block();
+  if (group * a.wb >= a.B) return;   // the whole block
+  const int role = wave_in_block();
+  const Lane<N> L(group, threadIdx.x & 63, a.B, a.wb);
+  for (uint32_t x = threadIdx.x; x < 256u; x += 64u * WAVES) lut[x] = make_uint2(spread4(x & 15u), spread4(x >> 4));
+
+  if (role == 0) {   // the draws and the rules
+    Row<N> R;
+    load_row<N>(a.state, L, R);
+    Meta m = unpack_meta(load_meta<N>(a.meta, L));
+    const int64_t start = (L.boardok && a.start_t) ? (int64_t)a.start_t[L.b] : INT64_MIN;
+    uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
+    for (int i = 0; i < a.steps; ++i) {
+      const uint32_t t = a.t0 + (uint32_t)i;
+      const bool wait = (int64_t)t < start;
+      const Draw<N> d = draw_action<N>(L, legal, a.seed, t, wait);
+      const bool skip = !L.boardok || wait;
+      const Ply ply = apply_move<N>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.pr, d.pc), tally);
+      hand[i & 1][L.lane] = HandOver<N>::of(R, m, ply).v;
+      // a waiting environment reports the values a skipped step call leaves behind at the start: zeros
+      if (L.valid && L.r == 0)
+        scalars[i & 1][L.j] = make_uint4((uint32_t)d.action(), skip ? 0u : __float_as_uint(ply.rew0), skip ? 0u : __float_as_uint(ply.rew1), !skip && ply.flag ? 1u : 0u);
+      legal = legal_row<N>(L, R, m.wtm, m.ko);
+      team_barrier();
+    }
+    if (L.valid) {
+      store_row<N>(State<N>(a.state, L), R);
+      m.head = 0;
+      if (L.r == 0) a.meta[L.b] = pack_meta(m);
+    }
+  } else {   // 1: the mask and the scalars; 2: the observation; the last of them keeps the history
+    const bool history = role == WAVES - 1, observe = OBS && role == 2;
+    Points<N> Q;
+    if (history) {
+      History<N> H;
+      load_history<N>(a.state, L, H);
+      Q = points_of<N>(H, unpack_meta(load_meta<N>(a.meta, L)).head);
+    }
+    int slice = 0;
+    for (int i = 0; i < a.steps; ++i) {
+      team_barrier();
+      const HandOver<N> in{hand[i & 1][L.lane]};
+      const size_t sb = (size_t)slice * a.B;
+      if (role == 1) {
+        if (L.valid && L.r == 0) {
+          const size_t e = sb + L.b;
+          const uint4 v = scalars[i & 1][L.j];
+          if (a.actions) a.actions[e] = (int32_t)v.x;
+          if (a.rew) *(float2*)(a.rew + 2 * e) = make_float2(__uint_as_float(v.y), __uint_as_float(v.z));
+          if (a.term) a.term[e] = (uint8_t)v.w;
+        }
+        if (a.mask) emit_mask<N, true, ST, FIRST_AS_EDGE>(L, in.legal(L), group, a.B, a.mask + sb * a.mask_pitch, a.mask_pitch, lds_mask, lut, a.wb);
+      }
+      if (history) {
+        const Row<N> R = in.row();
+        if (in.reset()) clear_points<N>(Q);
+        push_points<N>(Q, R.bk, R.wt, in.moved());
+      }
+      if constexpr (OBS) {
+        if (observe) emit_obs<N, true, ST, 4, FIRST_AS_EDGE>(L, Q.h, in.wtm(), group, a.B, a.obs + sb * a.obs_pitch, a.obs_pitch, lds_obs, lut, a.wb);
+      }
+      slice = slice + 1 == a.slices ? 0 : slice + 1;
+    }
+    if (history) store_history<N>(a.state, L, history_of<N>(Q));
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 // auxiliary kernels
 // ------------------------------------------------------------------------------------------------
 // SK: the legal mask leaves out the plays that would recreate an earlier position (positional superko, mode 2)
@@ -2177,7 +2272,7 @@ size_t state_bytes_for(int B, size_t* off_meta, size_t* off_rew, size_t* off_ter
 struct pgxgo_ctx {
   int B, N;
   int wb;        // boards per wavefront used by the step and rollout launches (1 .. W)
-  int team;      // boards per team of the step launches that teams take (auto_boards_per_team), or 0
+  bool automatic;   // wb is this library's choice; then teams take the batches that suit them (boards_per_step_team, boards_per_rollout_team)
   uint32_t seed;
   int komi_x2, max_steps, auto_reset;
   int64_t obs_pitch, mask_pitch;
@@ -2262,7 +2357,7 @@ int auto_boards_per_wavefront(int B) {
 // compute unit (9x9 x 256 with 1 / 2 / 4 boards 3.72 / 3.77 / 3.97, x 1024 4.63 / 4.16 / 4.30, x 2048 5.8 / 4.78 / 4.55; 19x19 x 400 with 1 / 3
 // 5.09 / 5.33, x 700 5.46 / 5.42, x 2048 7.52 / 6.08).
 template <int N>
-int auto_boards_per_team(int B) {
+int boards_per_step_team(int B) {
   if (N == 9) return B <= 384 ? 1 : B <= 1024 ? 2 : B <= 4096 ? 4 : 0;
   return B <= 512 ? 1 : B <= 2048 * Geo<N>::W ? Geo<N>::W : 0;
 }
@@ -2308,13 +2403,13 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
   h->mask_written = h->mask_out; h->obs_written = h->obs_out;
   const dim3 grid(blocks_for_wb(h->B, h->wb)), block(64 * kWavesPerBlock);
   const bool tight = tight_pitches<N>(h);
-  const int teams = h->team ? (h->B + h->team - 1) / h->team : 0;
+  const int wb = h->automatic ? boards_per_step_team<N>(h->B) : 0, teams = wb ? (h->B + wb - 1) / wb : 0;
   if (tight && !h->zt && teams && (h->obs_out || teams <= kTeamsWithoutObservation)) {
     const dim3 tgrid((unsigned)(teams + 7) & ~7u);
     const bool plain = output_bytes_per_ply(h, h->mask_out != nullptr, h->obs_out != nullptr) <= kTeamPlainUpTo;
     auto team = [&](auto sample_c, auto st_c) {
       hipLaunchKernelGGL((go_step_team_kernel<N, decltype(sample_c)::value, decltype(st_c)::value>), tgrid, block, 0, h->stream, h->state, h->meta, actions, start_t,
-                         h->B, h->team, tgrid.x / 8, a);
+                         h->B, wb, tgrid.x / 8, a);
     };
     using Plain = std::integral_constant<int, kStorePlain>;
     using Through = std::integral_constant<int, kStoreThrough>;
@@ -2396,10 +2491,34 @@ PaceArgs rollout_pace(const pgxgo_ctx* h, int steps, int slices, bool with_mask,
   return p;
 }
 
+// Boards per team of a rollout (go_rollout_team_kernel), or 0 where one wavefront for everything is faster.  us for 16 plies in place, one
+// wavefront / teams: 9x9 x 256 games 42.2 / 25.1, 1000 43.5 / 28.3, 5001 53.4 / 35.9, 12000 64.5 / 55.5, 20000 92.6 / 88.2, 24000 93.4 / 99.1,
+// without observation x 1000 32.6 / 27.6, 5001 35.9 / 31.5, 20000 65.5 / 62.3, 24000 66.6 / 77.1; 19x19 x 400 60.3 / 34.0, 1500 72 / 39,
+// 4000 81 / 66, 8192 121 / 114, 16384 227 / 212, 28000 377 / 353, 65536 836 / 797, without observation x 400 41.5 / 33.7, 8192 67 / 63, 11000
+// 81.2 / 80.3, 12000 81.5 / 87.5.  A single ply gains too little (19x19 x 8192 14.4 / 15.8).  Batches of more teams than the machine
+// holds at once start anew several times and need plies to make up for it (65536 games, 4 plies 252 / 297; 28000 106 / 99).
+// Boards as in boards_per_step_team; 19x19 without observation, where the mask is short, spreads further (1000 games with 1 / 3 37.5 / 40.4).
+template <int N>
+int boards_per_rollout_team(int B, int steps, bool with_obs) {
+  if (steps < 2) return 0;
+  if (N == 9) return B <= 384 ? 1 : B <= 1024 ? 2 : B <= 4096 ? 4 : B <= 20480 ? 6 : 0;
+  if (!with_obs) return B <= 1024 ? 1 : B <= 2048 ? 2 : B <= 11000 ? 3 : 0;
+  return B <= 512 ? 1 : B <= 30720 || steps >= 16 ? 3 : 0;
+}
+
 template <int N>
 int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
   const dim3 grid(blocks_for_wb(h->B, h->wb)), block(64 * kWavesPerBlock);
   a.pace = rollout_pace<N>(h, a.steps, a.slices, a.mask != nullptr, a.obs != nullptr);
+  const int team = h->automatic && !h->zt && !a.pace.ply && tight_pitches<N>(h) ? boards_per_rollout_team<N>(h->B, a.steps, a.obs != nullptr) : 0;
+  if (team) {
+    a.wb = team;
+    const dim3 teams((unsigned)(((int64_t)h->B + team - 1) / team + 7) & ~7u);
+    if (a.obs) hipLaunchKernelGGL((go_rollout_team_kernel<N, true>), teams, dim3(64 * 3), 0, h->stream, a);
+    else hipLaunchKernelGGL((go_rollout_team_kernel<N, false>), teams, dim3(64 * 2), 0, h->stream, a);
+    HIPCHK(hipGetLastError());
+    return PGXGO_OK;
+  }
   with_rollout_variant<N>(h, [&](auto tight_c, auto sk_c) {
     constexpr bool T = decltype(tight_c)::value;
     constexpr int M = decltype(sk_c)::value;
@@ -2485,7 +2604,7 @@ int fill_ctx(pgxgo_ctx* h, int32_t batch, int32_t board_size, uint32_t seed, con
   *h = pgxgo_ctx{};
   h->B = batch; h->N = board_size; h->seed = seed;
   h->wb = board_size == 19 ? auto_boards_per_wavefront<19>(batch) : auto_boards_per_wavefront<9>(batch);
-  h->team = board_size == 19 ? auto_boards_per_team<19>(batch) : auto_boards_per_team<9>(batch);
+  h->automatic = true;
   h->komi_x2 = o.komi_x2; h->max_steps = o.max_steps; h->auto_reset = o.auto_reset ? 1 : 0;
   h->obs_pitch = o.obs_pitch; h->mask_pitch = o.mask_pitch;
   h->stream = (hipStream_t)o.stream;
@@ -2722,7 +2841,7 @@ int pgxgo_set_boards_per_wavefront(pgxgo_t h, int32_t boards) {
   const int wmax = h->N == 19 ? Geo<19>::W : Geo<9>::W;
   if (boards < 0 || boards > wmax) return PGXGO_EINVAL;
   h->wb = boards ? boards : (h->N == 19 ? auto_boards_per_wavefront<19>(h->B) : auto_boards_per_wavefront<9>(h->B));
-  h->team = boards ? 0 : (h->N == 19 ? auto_boards_per_team<19>(h->B) : auto_boards_per_team<9>(h->B));   // a number that is asked for is had
+  h->automatic = boards == 0;   // a number that is asked for is had
   return h->wb;
 }
 

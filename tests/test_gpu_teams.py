@@ -44,3 +44,27 @@ def test_teams_and_single_wavefronts_agree(N, B, auto_reset, obs, line_padded):
     sa, sb = a.export_state(), b.export_state()
     for k in sa:
         assert torch.equal(sa[k], sb[k]), k
+
+
+@pytest.mark.parametrize("N,B,steps,slices,obs,auto_reset", [
+    (9, 1, 5, 1, True, True), (9, 385, 9, 4, True, True), (9, 1023, 2, 2, False, False), (9, 20480, 6, 3, True, True), (9, 4097, 11, 11, False, True),
+    (19, 1, 4, 1, False, True), (19, 511, 7, 7, True, False), (19, 1025, 5, 2, False, True), (19, 9001, 3, 1, True, True), (19, 11000, 2, 1, False, True)])
+def test_rollouts_by_teams_and_by_single_wavefronts_agree(N, B, steps, slices, obs, auto_reset):
+    kw = dict(seed=4, auto_reset=auto_reset, max_steps=45 if auto_reset else 0)
+    envs = [pg.GoEnv(B, N, **kw), pg.GoEnv(B, N, **kw)]
+    envs[1].set_boards_per_wavefront(3)
+    start = torch.as_tensor(np.random.default_rng(B).integers(0, 44, size=B).astype(np.int32), device="cuda")   # some wait through a whole launch
+    got = []
+    for e in envs:
+        assert not e.rollout_in_time_slots(steps, slices, True, obs)[0]
+        m, o = torch.full((slices, B, e.mask_pitch), 7, dtype=torch.uint8, device="cuda"), torch.full((slices, B, e.obs_pitch), 7, dtype=torch.uint8, device="cuda")
+        r, t = torch.full((slices, B, 2), 7.0, dtype=torch.float32, device="cuda"), torch.full((slices, B), 7, dtype=torch.uint8, device="cuda")
+        a = torch.full((slices, B), 7, dtype=torch.int32, device="cuda")
+        seen = []
+        for k in range(4):
+            e.rollout(steps, 4, 36 + k * steps, start_t=start, slices=slices, actions=a, rewards=r, terminated=t, mask=m, obs=o if obs else None)
+            seen += [x.clone() for x in (m, o, r, t, a)]
+        seen += list(e.export_state().values())
+        got.append(seen)
+    for i, (x, y) in enumerate(zip(*got)):
+        assert torch.equal(x, y), i

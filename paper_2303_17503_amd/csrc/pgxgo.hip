@@ -119,7 +119,26 @@ __device__ __forceinline__ uint4 pack_meta(const Meta& m) {
 }
 
 // all 4-neighbours of the set x (bits beyond column N-1 may be set; callers intersect with on-board sets)
-__device__ __forceinline__ uint32_t dilate(uint32_t x) { return (x << 1) | (x >> 1) | from_lane_below(x) | from_lane_above(x); }
+// (kept(v): v is wanted by itself.  The ORs of a dilation are built as two halves, each of which ends in one that takes the neighbouring
+// lane's row as an operand; as one expression the compiler moves the two rows into registers first and ORs three at a time, two
+// instructions more.)
+__device__ __forceinline__ uint32_t kept(uint32_t v) {
+  asm volatile("" ::"v"(v));
+  return v;
+}
+struct Halves {
+  uint32_t a, b;
+};
+__device__ __forceinline__ uint32_t dilate(uint32_t x) {
+  const uint32_t a = kept(from_lane_below(x) | (x << 1)), b = kept(from_lane_above(x) | (x >> 1));
+  return a | b;
+}
+// the set and all its 4-neighbours, as two halves
+__device__ __forceinline__ Halves grown(uint32_t x) {
+  const uint32_t sideways = kept((x << 1) | x);
+  return Halves{kept(from_lane_below(x) | sideways), kept(from_lane_above(x) | (x >> 1))};
+}
+__device__ __forceinline__ uint32_t grown_in(uint32_t x, uint32_t S) { const Halves h = grown(x); return (h.a | h.b) & S; }
 
 // Size class of a board-wide set given by its row words: exactly one element / two or more.
 __device__ __forceinline__ void board_count(uint32_t w, uint32_t seglo, uint32_t seghi, bool& one, bool& two) {
@@ -129,13 +148,13 @@ __device__ __forceinline__ void board_count(uint32_t w, uint32_t seglo, uint32_t
   one = !two && c == 1;
 }
 
-// connected component(s) of `seed` inside S
+// connected component(s) of `seed`, a part of S, inside S
 __device__ __forceinline__ uint32_t flood_plain(uint32_t seed, uint32_t S) {
   uint32_t F = seed;
   for (;;) {   // three growth steps per convergence test: the test (ballot, scalar branch) costs as much as a step
-    F |= dilate(F) & S;
-    F |= dilate(F) & S;
-    uint32_t G = F | (dilate(F) & S);
+    F = grown_in(F, S);
+    F = grown_in(F, S);
+    uint32_t G = grown_in(F, S);
     bool ch = G != F;
     F = G;
     if (__ballot(ch) == 0ull) break;
@@ -176,6 +195,7 @@ struct Lane {
 template <int N>
 struct Row {                      // per-lane registers: one row of one board
   uint32_t bk, wt, ab, aw;        // stones and atari sets (stones of chains with exactly one liberty)
+  uint32_t ko;                    // the ko point, if it is in this row (place_ko)
 };
 
 // ------------------------------------------------------------------------------------------------
@@ -232,6 +252,7 @@ __device__ __forceinline__ void load_row(uint32_t* state, const Lane<N>& L, Row<
   R.bk = v.x & L.full;
   R.wt = (G::CUR == 2 ? __builtin_amdgcn_alignbit(v.y, v.x, N) : v.x >> N) & L.full;
   R.ab = at & R.bk; R.aw = at & R.wt;
+  R.ko = 0u;
 }
 // (what a lane without a row gets is some other row's history: nothing is done with it)
 template <int N>
@@ -429,17 +450,22 @@ __device__ __forceinline__ void store_ply(uint32_t* state, const Lane<N>& L_, co
   }
 }
 
+// the ko point of the loaded scalars as a row word
+template <int N>
+__device__ __forceinline__ void place_ko(const Lane<N>& L, Row<N>& R, const Meta& m) {
+  const int kr = m.ko / N, kc = m.ko - kr * N;
+  R.ko = (m.ko >= 0 && L.valid && L.r == kr) ? (1u << kc) : 0u;
+}
+
 // legal points of the player to move (Fig. 2 legal_action_mask, pass excluded): empty, not the ko point, and
 // next to an empty point, or to an own chain that is not in atari, or to an opposing chain that is
 template <int N>
-__device__ __forceinline__ uint32_t legal_row(const Lane<N>& L, const Row<N>& R, int wtm, int ko) {
+__device__ __forceinline__ uint32_t legal_row(const Lane<N>& L, const Row<N>& R, int wtm) {
   uint32_t E = L.full & ~(R.bk | R.wt);
   uint32_t own = wtm ? R.wt : R.bk, opp = wtm ? R.bk : R.wt;
   uint32_t aown = wtm ? R.aw : R.ab, aopp = wtm ? R.ab : R.aw;
   uint32_t support = E | (own & ~aown) | (opp & aopp);
-  int kr = ko / N, kc = ko - kr * N;
-  uint32_t kobit = (ko >= 0 && L.r == kr) ? (1u << kc) : 0u;
-  return E & ~kobit & dilate(support);
+  return E & ~R.ko & dilate(support);
 }
 
 // Legal mask bytes [N*N+1] of every board of the wavefront.  TIGHT: the pitch is the dense one (N*N+1) or the
@@ -577,15 +603,20 @@ __device__ __forceinline__ void emit_outputs(const Lane<N>& L, const Points<N>& 
 // uniform random legal action: the k-th legal action in ascending order, k = hash mod legal_count
 // ------------------------------------------------------------------------------------------------
 template <int N>
-struct Draw {          // the drawn action as every lane of the board sees it
-  bool pass, point;    // neither = the environment is still waiting for its start time (action -1)
-  int pr, pc;          // row and column when `point`
-  __device__ __forceinline__ int action() const { return pass ? Geo<N>::P : point ? pr * N + pc : -1; }
+struct Draw {
+  bool pass, point;    // the same in every lane of the board; neither = the environment is still waiting for its start time (action -1)
+  uint32_t bit;        // the drawn point in the lane of its row, else 0
+  int pos, src;        // its column, in that lane; that lane
+  // the action is known to one lane of the board: that of the drawn point, else that of the first row
+  __device__ __forceinline__ bool known(const Lane<N>& L) const { return point ? bit != 0u : L.valid && L.r == 0; }
+  __device__ __forceinline__ int action(const Lane<N>& L) const { return pass ? Geo<N>::P : point ? L.r * N + pos : -1; }
+  // row and column for every lane of the board when `point` (called by all lanes of the wavefront)
+  __device__ __forceinline__ int row(const Lane<N>& L) const { return src - (L.j * Geo<N>::STRIDE + 1); }
+  __device__ __forceinline__ int column() const { return __shfl(pos, src); }
 };
 
 template <int N>
 __device__ __forceinline__ Draw<N> draw_action(const Lane<N>& L, uint32_t legal, uint32_t hash, bool wait) {   // hash: env_hash(seed, 0, L.b, t)
-  using G = Geo<N>;
   const uint32_t cnt = __popc(legal);
   // legal points in the rows above this one, and on the whole board, from ballots of the bits of cnt
   uint32_t before = 0u, total = 1u;   // pass is always legal
@@ -600,7 +631,7 @@ __device__ __forceinline__ Draw<N> draw_action(const Lane<N>& L, uint32_t legal,
   // position of the (n+1)-th set bit of the row word by halving (meaningful in the row that holds it)
   uint32_t n = k - before, w = legal, pos = 0u;
 #pragma unroll
-  for (int width = 16; width >= 1; width >>= 1) {
+  for (int width = N > 16 ? 16 : 8; width >= 1; width >>= 1) {
     const uint32_t c = __popc(w & ((1u << width) - 1u));
     if (n >= c) { n -= c; w >>= width; pos += width; }
   }
@@ -611,8 +642,8 @@ __device__ __forceinline__ Draw<N> draw_action(const Lane<N>& L, uint32_t legal,
   Draw<N> d;
   d.pass = !wait && k == total - 1u;
   d.point = !wait && k != total - 1u;
-  d.pr = (src & 63) - (L.j * G::STRIDE + 1);
-  d.pc = (int)__shfl((int)pos, src & 63);
+  d.bit = mine && d.point ? 1u << pos : 0u;
+  d.pos = (int)pos; d.src = src & 63;
   return d;
 }
 template <int N>
@@ -634,13 +665,17 @@ struct Move {
   bool frozen;    // the game had ended before (no auto-reset): nothing changes, terminated is reported
   bool is_pass, playing, illegal;
   int pr, pc;     // the point when `playing`
+  uint32_t bit;   // the same as a row word: in the lane of its row, else 0
+  __device__ __forceinline__ void forbid() { playing = false; illegal = true; pr = -100; pc = 0; bit = 0u; }
 };
+template <int N>
+__device__ __forceinline__ uint32_t bit_of(const Lane<N>& L, bool on, int pr, int pc) { return L.valid && on && L.r == pr ? 1u << pc : 0u; }
 
-// a1/a2.  want_pass / want_point(pr,pc): the requested action; anything else is illegal.
+// a1/a2.  want_pass / want_point(pr,pc), bit_in = that point as a row word: the requested action; anything else is illegal.
 // GATE: check the point against the mover's legal set (not needed for actions drawn from that set).
 template <int N, bool GATE>
 __device__ __forceinline__ Move gate_move(const Lane<N>& L, const Row<N>& R, const Meta& m, bool skip, bool want_pass, bool want_point,
-                                          int pr_in, int pc_in) {
+                                          uint32_t bit_in, int pr_in, int pc_in) {
   Move mv;
   mv.skip = skip;
   mv.frozen = !skip && m.term;
@@ -649,20 +684,20 @@ __device__ __forceinline__ Move gate_move(const Lane<N>& L, const Row<N>& R, con
   const bool on_board = live && want_point;
   mv.playing = on_board;
   if (GATE) {
-    const uint32_t pbit = (L.valid && on_board && L.r == pr_in) ? (1u << pc_in) : 0u;
-    const uint32_t legal_now = legal_row<N>(L, R, m.wtm, m.ko);
-    mv.playing = on_board && board_any((legal_now & pbit) != 0u, L.seglo, L.seghi);
+    const uint32_t legal_now = legal_row<N>(L, R, m.wtm);
+    mv.playing = on_board && board_any((legal_now & bit_in) != 0u, L.seglo, L.seghi);
   }
   mv.illegal = live && !mv.is_pass && !mv.playing;
   mv.pr = mv.playing ? pr_in : -100;
   mv.pc = mv.playing ? pc_in : 0;
+  mv.bit = mv.playing ? bit_in : 0u;
   return mv;
 }
 
 // a8: back to the initial state of the next episode (Sec. 4.1); the seat is drawn anew.  The history is the caller's to clear.
 template <int N>
 __device__ __forceinline__ void reset_board(const Lane<N>& L, Row<N>& R, Meta& m, uint32_t seed) {
-  R.bk = R.wt = R.ab = R.aw = 0u;
+  R.bk = R.wt = R.ab = R.aw = R.ko = 0u;
   m.ko = -1; m.steps = 0; m.passes = 0; m.wtm = 0; m.term = 0;
   m.episode += 1;
   m.bp = (int)(env_hash(seed, 1u, (uint32_t)in_place(L.slot), m.episode) & 1u);
@@ -765,8 +800,7 @@ __device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, 
   Ply out;
   using G = Geo<N>;
   const bool playing = mv.playing, is_pass = mv.is_pass, illegal = mv.illegal, frozen = mv.frozen;
-  const int pr = mv.pr, pc = mv.pc;
-  const uint32_t pbit = (L.valid && L.r == pr) ? (1u << pc) : 0u;
+  const uint32_t pbit = mv.bit;
   const int wtm0 = m.wtm;
   float rew0 = 0.f, rew1 = 0.f;
   out.captured = 0u;
@@ -775,15 +809,14 @@ __device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, 
   if (__ballot(playing) != 0ull) {
     uint32_t own = wtm0 ? R.wt : R.bk, opp = wtm0 ? R.bk : R.wt;
     uint32_t aown = wtm0 ? R.aw : R.ab, aopp = wtm0 ? R.ab : R.aw;
-    const uint32_t nbN = (L.valid && L.r == pr - 1) ? (1u << pc) : 0u;
-    const uint32_t nbS = (L.valid && L.r == pr + 1) ? (1u << pc) : 0u;
-    const uint32_t nbW = (L.valid && L.r == pr) ? ((1u << pc) >> 1) : 0u;
-    const uint32_t nbE = (L.valid && L.r == pr) ? ((2u << pc) & G::FULL) : 0u;
+    // (a sentinel lane may get a bit too: none of the sets they are intersected with has stones there)
+    const uint32_t nbN = from_lane_above(pbit), nbS = from_lane_below(pbit), nbW = pbit >> 1, nbE = (pbit << 1) & G::FULL;
     const uint32_t nb = nbN | nbS | nbW | nbE;
     const uint32_t friends = nb & own;   // own stones next to the new one
     own |= pbit;
     // opposing chains in atari that touch the new stone lose their last liberty
     int ko_new = -1;
+    uint32_t ko_bit = 0u;
     const uint32_t capseed = nb & aopp;
     uint32_t released = nb;   // own chains in atari next to these points stop being that: the new stone joins them, or they gain a liberty
     unsigned round = 0u;      // tally round in use
@@ -798,7 +831,7 @@ __device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, 
       const uint32_t around = (friends | (nb & ~(own | opp))) & L.full;
       const uint32_t where = capseed ? (uint32_t)(L.r * N + __ffs(capseed) - 1) : 0u;
       const uint64_t sum = tally_board(tally, round++, L, (uint64_t)(__popc(cap) | (__popc(around) << 16)) | ((uint64_t)where << 32));
-      if ((uint32_t)sum == 0x10001u) ko_new = (int)(sum >> 32);
+      if ((uint32_t)sum == 0x10001u) { ko_new = (int)(sum >> 32); ko_bit = cap; }
     }
     const uint32_t E = L.full & ~(own | opp);
     const uint32_t clrseed = released & aown;
@@ -823,11 +856,11 @@ __device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, 
         open[k] = 0u;
         if (!run[k]) continue;
 #pragma unroll
-        for (int i = 0; i < kBlindSteps; ++i) F[k] |= dilate(F[k]) & S[k];
-        const uint32_t D = dilate(F[k]);
-        const uint32_t G_ = F[k] | (D & S[k]);
+        for (int i = 0; i < kBlindSteps; ++i) F[k] = grown_in(F[k], S[k]);
+        const Halves D = grown(F[k]);   // (every flood lies in its S, and S has no point of EE)
+        const uint32_t G_ = (D.a | D.b) & S[k];
         open[k] = G_ ^ F[k];
-        FL::count(k, D & EE[k], lo, hi);
+        FL::count(k, (D.a | D.b) & EE[k], lo, hi);
         F[k] = G_;
       }
       if (round == kTallyRounds) { tally_clear(tally, L.lane); round = 0u; }
@@ -843,13 +876,13 @@ __device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, 
     }
     FL::atari(F, libs, aown, aopp);
     if (playing) {
-      m.ko = ko_new;
+      m.ko = ko_new; R.ko = ko_bit;
       R.bk = wtm0 ? opp : own; R.wt = wtm0 ? own : opp;
       R.ab = wtm0 ? aopp : aown; R.aw = wtm0 ? aown : aopp;
     }
   }
   const bool moved = playing || is_pass;
-  if (is_pass) { m.ko = -1; m.passes += 1; }
+  if (is_pass) { m.ko = -1; R.ko = 0u; m.passes += 1; }
   if (playing) m.passes = 0;
   if (moved) {
     m.steps += 1;
@@ -937,12 +970,13 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint32_
   if (wave * wb >= B) return;   // whole wavefront idle; there is no block-wide barrier anywhere below
   const bool wait_start = (int64_t)a.sample_t < (int64_t)held_back(start_raw);
   Meta m = unpack_meta(meta_raw);
+  place_ko<N>(L, R, m);
 
   // a1/a2: decode the action and gate it
   const bool skip = !L.boardok || act == -1;
   const bool in_range = act >= 0 && act < G::P;
   const int pr = in_range ? act / N : 0, pc = in_range ? act - (act / N) * N : 0;
-  const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, pr, pc);
+  const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc);
 
   // a3-a8
   const Ply ply = apply_move<N>(L, R, m, a.rules, mv, tally_all[wib], [&]() { clear_history<N>(H); });
@@ -954,7 +988,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint32_
 
   // ---- a10 / a9: observation and legal mask of the player now to move ---------------------------------------
   if (a.obs) emit_obs<N, TIGHT, ST>(L, points_of<N>(H, m.head).h, m.wtm, wave, B, a.obs, a.obs_pitch, lds_obs_all[wib], lut, wb);
-  const uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
+  const uint32_t legal = legal_row<N>(L, R, m.wtm);
   if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, B, a.mask, a.mask_pitch, lds_mask_all[wib], lut, wb);
 
   // ---- a11: store the state --------------------------------------------------------------------------------
@@ -962,7 +996,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint32_
   if (!skip && L.valid && L.r == 0) store_small<state_store_kind(ST)>(&meta[L.b], pack_meta(m));
   if (SAMPLE) {
     const Draw<N> d = draw_action<N>(L, legal, a.sample_seed, a.sample_t, wait_start);
-    if (L.valid && L.r == 0) a.next_actions[L.b] = d.action();
+    if (d.known(L)) a.next_actions[L.b] = d.action(L);
   }
 }
 
@@ -979,17 +1013,19 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_kernel(uint32_
 // column N-1.
 template <int N>
 struct HandOver {
-  static_assert(N * N + 1 < 512 && N <= 20, "ko point and flags fit beside a row");
+  static_assert(N <= 20, "flags fit beside a row");
   uint4 v;
   static __device__ __forceinline__ HandOver of(const Row<N>& R, const Meta& m, const Ply& ply) {
-    return HandOver{make_uint4(R.bk | (ply.moved ? 1u << 29 : 0u) | (ply.reset ? 1u << 30 : 0u), R.wt | ((uint32_t)(m.ko + 1) << 20) | ((uint32_t)m.wtm << 31), R.ab, R.aw)};
+    return HandOver{make_uint4(R.bk | (ply.moved ? 1u << 29 : 0u) | (ply.reset ? 1u << 30 : 0u) | ((uint32_t)m.wtm << 31), R.wt, R.ab | R.aw, R.ko)};
   }
-  __device__ __forceinline__ Row<N> row() const { return Row<N>{v.x & Geo<N>::FULL, v.y & Geo<N>::FULL, v.z, v.w}; }
+  __device__ __forceinline__ Row<N> row() const {
+    const uint32_t bk = v.x & Geo<N>::FULL;
+    return Row<N>{bk, v.y, v.z & bk, v.z & v.y, v.w};
+  }
   __device__ __forceinline__ bool moved() const { return (v.x >> 29) & 1u; }
   __device__ __forceinline__ bool reset() const { return (v.x >> 30) & 1u; }
-  __device__ __forceinline__ int wtm() const { return (int)(v.y >> 31); }
-  __device__ __forceinline__ int ko() const { return (int)((v.y >> 20) & 511u) - 1; }
-  __device__ __forceinline__ uint32_t legal(const Lane<N>& L) const { return legal_row<N>(L, row(), wtm(), ko()); }
+  __device__ __forceinline__ int wtm() const { return (int)(v.x >> 31); }
+  __device__ __forceinline__ uint32_t legal(const Lane<N>& L) const { return legal_row<N>(L, row(), wtm()); }
 };
 enum TeamRole { kTeamRules = 0, kTeamMask = 1, kTeamDraw = 2, kTeamObs = 3, kTeamWaves = 4 };
 
@@ -1068,10 +1104,11 @@ __global__ void __launch_bounds__(64 * kTeamWaves) go_step_team_kernel(uint32_t*
     in_scalar_registers(a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset, a.rew, a.term);
     fill_table();
     Meta m = unpack_meta(meta_raw);
+    place_ko<N>(L, R, m);
     const bool skip = !L.boardok || act == -1;
     const bool in_range = act >= 0 && act < G::P;
     const int pr = in_range ? act / N : 0, pc = in_range ? act - (act / N) * N : 0;
-    const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, pr, pc);
+    const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc);
     const Ply ply = apply_move<N>(L, R, m, a.rules, mv, tally, [&]() { clear_history<N>(H); });
     hand[L.lane] = HandOver<N>::of(R, m, ply).v;
     __syncthreads();
@@ -1095,7 +1132,7 @@ __global__ void __launch_bounds__(64 * kTeamWaves) go_step_team_kernel(uint32_t*
     __syncthreads();
     if (SAMPLE) {
       const Draw<N> d = draw_action<N>(L, HandOver<N>{hand[L.lane]}.legal(L), hash, (int64_t)a.sample_t < (int64_t)start_raw);
-      if (L.valid && L.r == 0) a.next_actions[L.b] = d.action();
+      if (d.known(L)) a.next_actions[L.b] = d.action(L);
     }
   } else if (a.obs) {
     Row<N> R;
@@ -1375,7 +1412,9 @@ __device__ __forceinline__ uint32_t sk_forbidden(const Lane<N>& L, const uint2* 
                const uint32_t d_other = c2 ? e.x ^ g.key.x : e.y ^ g.key.y;
                uint64_t pend = __ballot(look && sk_real(e) && u < 2u * N * N && (int)(u & 1u) == c2);
                if (pend == 0ull) return;          // nearly always: no earlier position is one stone of the mover's away
-               const uint32_t legal_s = legal_row<N>(L, R, m.wtm, m.ko);
+               Row<N> now = R;   // (its ko bit from the scalars: not held through the table work, which needs the registers)
+               place_ko<N>(L, now, m);
+               const uint32_t legal_s = legal_row<N>(L, now, m.wtm);
                while (pend != 0ull) {             // one candidate per board per turn
                  const uint64_t mine = pend & seg;
                  const bool on = mine != 0ull;
@@ -1456,14 +1495,13 @@ __device__ __forceinline__ void sk_clear_tables(const Lane<N>& L, bool flagged, 
 // kernel it is 1 us slower than calling it afterwards, hence the choice).
 template <int N, bool GATE, bool EARLY, class Hook>
 __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& m, SkGame& g, uint32_t& forb, const Rules& rules, bool skip, bool want_pass,
-                                             bool want_point, int pr_in, int pc_in, const uint2* tab_r, uint2* tab_w, uint2* zt, int game,
+                                             bool want_point, uint32_t bit_in, int pr_in, int pc_in, const uint2* tab_r, uint2* tab_w, uint2* zt, int game,
                                              uint32_t* scratch, uint64_t* tally, Ply& ply, bool pre_a_loaded, const SkWin& pre_a, Hook&& board_final) {
   const int c = m.wtm, own = c ? g.nw : g.nb, opp = c ? g.nb : g.nw;
-  Move mv = gate_move<N, GATE>(L, R, m, skip, want_pass, want_point, pr_in, pc_in);
+  Move mv = gate_move<N, GATE>(L, R, m, skip, want_pass, want_point, bit_in, pr_in, pc_in);
   // a play the simple rules allow but the repetition rule forbids is an illegal action
-  const uint32_t pbit = (L.valid && mv.playing && L.r == mv.pr) ? (1u << mv.pc) : 0u;
-  const bool repeats = mv.playing && board_any((pbit & forb) != 0u, L.seglo, L.seghi);
-  if (repeats) { mv.playing = false; mv.illegal = true; mv.pr = -100; mv.pc = 0; }
+  const bool repeats = mv.playing && board_any((mv.bit & forb) != 0u, L.seglo, L.seghi);
+  if (repeats) mv.forbid();
   // The chains this ply needs start at slots known before the rules run when the move takes nothing (most do): the
   // loads fly while the rules run.  pre[0]: one more stone of the mover's colour (where the new position goes);
   // pre[1]: one more stone of the other colour (the next mover's forbidden plays); pre[2]: as many stones of the
@@ -1511,11 +1549,11 @@ __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& 
 //     called once more: the same wavefront overwrites what it stored the first time.
 template <int N, bool GATE, bool POST, class Hook, class Restore>
 __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, Meta& m, SkGame& g, const Rules& rules, bool skip, bool want_pass,
-                                                  bool want_point, int pr_in, int pc_in, const uint2* tab_r, uint2* tab_w, uint2* zt, int game,
+                                                  bool want_point, uint32_t bit_in, int pr_in, int pc_in, const uint2* tab_r, uint2* tab_w, uint2* zt, int game,
                                                   uint32_t* scratch, uint64_t* tally, Ply& ply, const SkWin& pre, Hook&& board_final, Restore&& restore) {
   const int c = m.wtm, own1 = (c ? g.nw : g.nb) + 1;
   const uint64_t seg = ((uint64_t)L.seghi << 32) | L.seglo;
-  Move mv = gate_move<N, GATE>(L, R, m, skip, want_pass, want_point, pr_in, pc_in);
+  Move mv = gate_move<N, GATE>(L, R, m, skip, want_pass, want_point, bit_in, pr_in, pc_in);
   Rules r0 = rules;
   r0.auto_reset = 0;   // the reset happens below, together with the table's
   bool do_reset = false;
@@ -1531,9 +1569,8 @@ __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, M
   uint32_t taken = 0u;
   if constexpr (POST) taken = ply.captured;
   else {
-    const uint32_t pbit = (L.valid && mv.playing && L.r == mv.pr) ? (1u << mv.pc) : 0u;
     const uint32_t aopp = c ? R.ab : R.aw;
-    const uint32_t seed = dilate(pbit) & aopp;
+    const uint32_t seed = dilate(mv.bit) & aopp;
     if (__ballot(seed != 0u) != 0ull) taken = flood_plain(seed, aopp);
   }
   int ncap = 0;
@@ -1551,7 +1588,7 @@ __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, M
   sk_walk<N>(L, tab_r, sk_home_counts<N>(nb1, nw1), mv.playing, pre, ~0u,
              [&](uint2 e, bool look) { if ((__ballot(look && e.x == key.x && e.y == key.y) & seg) != 0ull) hit = true; }, ok, free_slot);
   const bool repeats = mv.playing && hit;
-  if (repeats) { mv.playing = false; mv.illegal = true; mv.pr = -100; mv.pc = 0; }
+  if (repeats) mv.forbid();
   if constexpr (!POST) {
     ply = apply_move<N>(L, R, m, r0, mv, tally);
     do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
@@ -1560,7 +1597,7 @@ __device__ __forceinline__ void sk_step_core_play(const Lane<N>& L, Row<N>& R, M
   } else if (__ballot(repeats) != 0ull) {
     restore(R, m, repeats);   // the boards that repeat get the state as loaded back
     Move again = mv;          // the other boards of the wavefront keep what the first pass gave them: for them, a skipped ply
-    if (!repeats) { again.skip = true; again.frozen = false; again.is_pass = false; again.playing = false; again.illegal = false; again.pr = -100; again.pc = 0; }
+    if (!repeats) { again.skip = true; again.frozen = false; again.is_pass = false; again.playing = false; again.illegal = false; again.pr = -100; again.pc = 0; again.bit = 0u; }
     const Ply second = apply_move<N>(L, R, m, r0, again, tally);
     if (repeats) {
       ply = second;
@@ -1611,6 +1648,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   const bool wait_start = (int64_t)a.sample_t < (int64_t)held_back(start_raw);
   SkGame g = L.boardok ? sk_unpack(g_raw) : sk_fresh();
   Meta m = unpack_meta(meta_raw);
+  place_ko<N>(L, R, m);
   uint2* tab = zt + (size_t)(L.boardok ? L.b : 0) * Zt<N>::SLOTS;
 
   const bool skip = !L.boardok || act == -1;
@@ -1628,18 +1666,19 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   };
   if constexpr (MODE == 1) {
     const SkWin pre = sk_window_play<N>(L, tab, g, m, !skip);
-    sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], ply, pre,
+    sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], ply, pre,
                                      board_final, [&](Row<N>& Rr, Meta& mr, bool which) {   // the state is stored below: memory still holds it as loaded
                                        Row<N> T;
                                        load_row<N>(state, L, T);
                                        load_history<N>(state, L, H);
                                        const Meta as_loaded = unpack_meta(load_meta<N>(meta, L));
                                        mr.head = as_loaded.head;
+                                       place_ko<N>(L, T, as_loaded);
                                        if (which) { Rr = T; mr = as_loaded; }
                                      });
   } else {
     forb = sk_forb_loaded<N>(L, tab, g, R, m, none, lds_mask_all[wib]);
-    sk_step_core<N, true, false>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], ply, false, none, board_final);
+    sk_step_core<N, true, false>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally_all[wib], ply, false, none, board_final);
     g.fw = sk_forb_word<N>(L, forb);
   }
   constexpr int STATE_ST = MODE == 1 && N == 9 ? kStorePlain : state_store_kind(ST);   // (mode 1 at 9x9 has no registers left for the other kind)
@@ -1650,12 +1689,13 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
     store_small<ST>(&a.term[L.b], (uint8_t)(ply.flag ? 1 : 0));
   }
 
-  const uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko) & ~(MODE == 2 ? forb : 0u);
+  place_ko<N>(L, R, m);
+  const uint32_t legal = legal_row<N>(L, R, m.wtm) & ~(MODE == 2 ? forb : 0u);
   if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, B, a.mask, a.mask_pitch, lds_mask_all[wib], lut, wb);
   if (!skip && L.valid && L.r == 0) zcur[L.b] = sk_pack(g);
   if (a.next_actions) {
     const Draw<N> dr = draw_action<N>(L, legal, a.sample_seed, a.sample_t, wait_start);
-    if (L.valid && L.r == 0) a.next_actions[L.b] = dr.action();
+    if (dr.known(L)) a.next_actions[L.b] = dr.action(L);
   }
 }
 
@@ -1670,6 +1710,7 @@ __global__ void __launch_bounds__(64) go_superko_rebuild_kernel(uint32_t* state,
   load_row<N>(state, L, R);
   load_history<N>(state, L, H);
   const Meta m = unpack_meta(load_meta<N>(meta, L));
+  place_ko<N>(L, R, m);
   const Points<N> Q = points_of<N>(H, m.head);
   uint2* tab = zt + (size_t)(L.boardok ? L.b : 0) * Zt<N>::SLOTS;
   SkWin none;
@@ -1756,6 +1797,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
   fill_spread_table(lut);
   if (wave * G::W >= n) return;
   Meta m = unpack_meta(meta_raw);
+  place_ko<N>(L, R, m);
   L.slot = dst;   // from here on the board is environment dst (seat draw on reset, state store)
 
   const bool skip = !L.boardok || act == -1;
@@ -1769,7 +1811,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
     if (a.obs) emit_obs<N, TIGHT, ST>(L, points_of<N>(H, m.head).h, m.wtm, wave, n, a.obs, a.obs_pitch, lds_obs_all[wib], lut);
   };
   if constexpr (!SK) {
-    const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, pr, pc);
+    const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc);
     ply = apply_move<N>(L, R, m, a.rules, mv, tally_all[wib]);
   } else {
     const int sslot = L.boardok ? src : 0, dslot = L.boardok ? dst : 0;
@@ -1787,7 +1829,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
     none.home = ~0u; none.e = make_uint2(1u, 0u);
     if constexpr (SK == 1) {
       const SkWin pre = sk_window_play<N>(L, tab_r, g, m, !skip);
-      sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], ply, pre,
+      sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], ply, pre,
                                        board_final, [&](Row<N>& Rr, Meta& mr, bool which) {   // the source slot still holds the state as loaded
                                          Lane<N> Ls = L;
                                          Ls.slot = src;
@@ -1796,11 +1838,12 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
                                          load_history<N>(state, Ls, H);
                                          const Meta as_loaded = unpack_meta(meta[sslot]);
                                          mr.head = as_loaded.head;
-                                         if (which) { Rr = T; mr = as_loaded; }
+                                         place_ko<N>(L, T, as_loaded);
+                                       if (which) { Rr = T; mr = as_loaded; }
                                        });
     } else {
       forb = sk_forb_loaded<N>(L, tab_r, g, R, m, none, lds_mask_all[wib]);
-      sk_step_core<N, true, true>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], ply, false, none, board_final);
+      sk_step_core<N, true, true>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc, tab_r, tab_w, a.zt, dslot, lds_mask_all[wib], tally_all[wib], ply, false, none, board_final);
       g.fw = sk_forb_word<N>(L, forb);
     }
     if (L.valid && L.r == 0) a.zcur[dslot] = sk_pack(g);
@@ -1814,7 +1857,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
       if (a.term) store_small<ST>(&a.term[L.b], (uint8_t)(skip ? m.term : (ply.flag ? 1 : 0)));
     }
   }
-  const uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko) & ~forb;
+  const uint32_t legal = legal_row<N>(L, R, m.wtm) & ~forb;
   if constexpr (!SK) board_final(ply.moved, ply.reset);
   if (a.mask) emit_mask<N, TIGHT, ST>(L, legal, wave, n, a.mask, a.mask_pitch, lds_mask_all[wib], lut);
   store_all<N>(state, L, R, H);
@@ -1883,9 +1926,10 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
     load_row<N>(a.state, L0, R);
     load_history<N>(a.state, L0, H);
     Q = points_of<N>(H, m.head);
+    place_ko<N>(L0, R, m);
   }
   const int64_t start = (L0.boardok && a.start_t) ? (int64_t)a.start_t[L0.b] : INT64_MIN;
-  uint32_t legal = legal_row<N>(L0, R, m.wtm, m.ko);
+  uint32_t legal = legal_row<N>(L0, R, m.wtm);
   SkGame g = sk_fresh();
   uint2* tab = nullptr;
   uint32_t forb = 0u;
@@ -1910,12 +1954,15 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
     const bool wait = (int64_t)t < start;
     const Draw<N> d = draw_action<N>(L, legal, a.seed, t, wait);
     const bool skip = !L.boardok || wait;
+    const size_t sb = (size_t)slice * a.B;
+    if (a.actions && d.known(L)) a.actions[sb + L.b] = d.action(L);
     Ply ply;
+    const int dr = d.row(L), dc = SK ? d.column() : 0;
     if constexpr (!SK) {
-      ply = apply_move<N>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.pr, d.pc), tally_all[wib],
+      ply = apply_move<N>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.bit, 0, 0), tally_all[wib],
                           [&]() { clear_points<N>(Q); });
       push_points<N>(Q, R.bk, R.wt, ply.moved);
-      legal = legal_row<N>(L, R, m.wtm, m.ko);
+      legal = legal_row<N>(L, R, m.wtm);
     } else {
       SkWin none;
       none.home = ~0u; none.e = make_uint2(1u, 0u);
@@ -1927,18 +1974,16 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
         if (obs_t) emit_obs<N, TIGHT, ST, 4, FIRST_AS_EDGE>(L, Q.h, m.wtm, wave, a.B, obs_t, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
       };
       if constexpr (SK == 1) {
-        sk_step_core_play<N, false, false>(L, R, m, g, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], ply,
+        sk_step_core_play<N, false, false>(L, R, m, g, a.rules, skip, d.pass, d.point, d.bit, dr, dc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], ply,
                                            ahead, board_final, [](Row<N>&, Meta&, bool) {});
         ahead = sk_window_play<N>(L, tab, g, m, L.boardok);
       } else {
-        sk_step_core<N, false, true>(L, R, m, g, forb, a.rules, skip, d.pass, d.point, d.pr, d.pc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], ply, false, none, board_final);
+        sk_step_core<N, false, true>(L, R, m, g, forb, a.rules, skip, d.pass, d.point, d.bit, dr, dc, tab, tab, a.zt, L.b, lds_mask_all[wib], tally_all[wib], ply, false, none, board_final);
       }
-      legal = legal_row<N>(L, R, m.wtm, m.ko) & ~(SK == 2 ? forb : 0u);
+      legal = legal_row<N>(L, R, m.wtm) & ~(SK == 2 ? forb : 0u);
     }
-    const size_t sb = (size_t)slice * a.B;
     if (L.valid && L.r == 0) {
       const size_t e = sb + L.b;
-      if (a.actions) a.actions[e] = d.action();
       // a waiting environment reports the values a skipped step call leaves behind at the start: zeros
       if (a.rew) *(float2*)(a.rew + 2 * e) = skip ? make_float2(0.f, 0.f) : make_float2(ply.rew0, ply.rew1);
       if (a.term) a.term[e] = (uint8_t)((!skip && ply.flag) ? 1 : 0);
@@ -1982,7 +2027,8 @@ __global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_rollout_team_kernel(Rol
   __shared__ uint64_t tally[64];
   __shared__ uint2 lut[256];
   __shared__ uint4 hand[2][64];
-  __shared__ uint4 scalars[2][G::W];   // per board: action, rewards, terminated
+  __shared__ uint4 scalars[2][G::W];   // per board: rewards, terminated
+  __shared__ int32_t drawn[2][G::W];
   const int group = piece_of_block();
   if (group * a.wb >= a.B) return;   // the whole block
   const int role = wave_in_block();
@@ -1993,19 +2039,20 @@ __global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_rollout_team_kernel(Rol
     Row<N> R;
     load_row<N>(a.state, L, R);
     Meta m = unpack_meta(load_meta<N>(a.meta, L));
+    place_ko<N>(L, R, m);
     const int64_t start = (L.boardok && a.start_t) ? (int64_t)a.start_t[L.b] : INT64_MIN;
-    uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
+    uint32_t legal = legal_row<N>(L, R, m.wtm);
     for (int i = 0; i < a.steps; ++i) {
       const uint32_t t = a.t0 + (uint32_t)i;
       const bool wait = (int64_t)t < start;
       const Draw<N> d = draw_action<N>(L, legal, a.seed, t, wait);
       const bool skip = !L.boardok || wait;
-      const Ply ply = apply_move<N>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.pr, d.pc), tally);
+      if (d.known(L)) drawn[i & 1][L.j] = d.action(L);
+      const Ply ply = apply_move<N>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.bit, 0, 0), tally);
       hand[i & 1][L.lane] = HandOver<N>::of(R, m, ply).v;
       // a waiting environment reports the values a skipped step call leaves behind at the start: zeros
-      if (L.valid && L.r == 0)
-        scalars[i & 1][L.j] = make_uint4((uint32_t)d.action(), skip ? 0u : __float_as_uint(ply.rew0), skip ? 0u : __float_as_uint(ply.rew1), !skip && ply.flag ? 1u : 0u);
-      legal = legal_row<N>(L, R, m.wtm, m.ko);
+      if (L.valid && L.r == 0) scalars[i & 1][L.j] = make_uint4(skip ? 0u : __float_as_uint(ply.rew0), skip ? 0u : __float_as_uint(ply.rew1), !skip && ply.flag ? 1u : 0u, 0u);
+      legal = legal_row<N>(L, R, m.wtm);
       team_barrier();
     }
     if (L.valid) {
@@ -2030,9 +2077,9 @@ __global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_rollout_team_kernel(Rol
         if (L.valid && L.r == 0) {
           const size_t e = sb + L.b;
           const uint4 v = scalars[i & 1][L.j];
-          if (a.actions) a.actions[e] = (int32_t)v.x;
-          if (a.rew) *(float2*)(a.rew + 2 * e) = make_float2(__uint_as_float(v.y), __uint_as_float(v.z));
-          if (a.term) a.term[e] = (uint8_t)v.w;
+          if (a.actions) a.actions[e] = drawn[i & 1][L.j];
+          if (a.rew) *(float2*)(a.rew + 2 * e) = make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+          if (a.term) a.term[e] = (uint8_t)v.z;
         }
         if (a.mask) emit_mask<N, true, ST, FIRST_AS_EDGE>(L, in.legal(L), group, a.B, a.mask + sb * a.mask_pitch, a.mask_pitch, lds_mask, lut, a.wb);
       }
@@ -2072,7 +2119,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_emit_kernel(uint32_t* 
   load_row<N>(state, L, R);
   if (obs) load_history<N>(state, L, H);
   Meta m = unpack_meta(load_meta<N>(meta, L));
-  uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
+  place_ko<N>(L, R, m);
+  uint32_t legal = legal_row<N>(L, R, m.wtm);
   if constexpr (SK) {
     if (mask) {
       const SkGame g = L.boardok ? sk_unpack(zcur[L.b]) : sk_fresh();
@@ -2098,7 +2146,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_random_actions_kernel(
   Row<N> R;
   load_row<N>(state, L, R);
   Meta m = unpack_meta(load_meta<N>(meta, L));
-  uint32_t legal = legal_row<N>(L, R, m.wtm, m.ko);
+  place_ko<N>(L, R, m);
+  uint32_t legal = legal_row<N>(L, R, m.wtm);
   if constexpr (SK) {
     const SkGame g = L.boardok ? sk_unpack(zcur[L.b]) : sk_fresh();
     SkWin none;
@@ -2107,7 +2156,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) go_random_actions_kernel(
   }
   const bool wait = L.boardok && start_t && (int64_t)t < (int64_t)start_t[L.b];
   const Draw<N> d = draw_action<N>(L, legal, seed, t, wait);
-  if (L.valid && L.r == 0) actions[L.b] = d.action();
+  if (d.known(L)) actions[L.b] = d.action(L);
 }
 
 // new episode for every environment: empty board, Black to move, seat from the hash
@@ -2188,7 +2237,7 @@ __global__ void __launch_bounds__(64) go_import_kernel(uint32_t* state, uint4* m
   Points<N> Q;
 #pragma unroll
   for (int k = 0; k < G::HD; ++k) Q.h[k] = 0u;
-  R.bk = R.wt = R.ab = R.aw = 0u;
+  R.bk = R.wt = R.ab = R.aw = R.ko = 0u;
   Meta m;
   m.head = 0;
   m.ko = -1; m.steps = 0; m.passes = 0; m.wtm = 0; m.term = 0; m.bp = 0; m.episode = 0u; m.illegal = 0u;

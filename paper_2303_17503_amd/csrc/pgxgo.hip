@@ -1865,6 +1865,83 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
 }
 
 // ------------------------------------------------------------------------------------------------
+// The same by teams (go_step_team_kernel): one wavefront applies the rules and stores the new state, one writes the mask, one the
+// observation.  Figures, and which calls go this way: boards_per_slot_team.
+// ------------------------------------------------------------------------------------------------
+template <int N, bool OBS, int ST>
+__global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_step_slots_team_kernel(const int32_t* src_slots, const int32_t* dst_slots, const int32_t* actions, uint32_t* state,
+                                                                                uint4* meta, int pool, int n, int wb, uint32_t eighth, SlotArgs a) {   // wb: boards per team
+  using G = Geo<N>;
+  constexpr uint32_t THREADS = 64u * (OBS ? 3u : 2u);
+  __shared__ __attribute__((aligned(16))) uint32_t lds_obs[OBS ? G::W * G::OBS_DW : 4];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_mask[64];
+  __shared__ uint64_t tally[64];
+  __shared__ uint2 lut[256];
+  __shared__ uint4 hand[64];
+  const int group = piece_of_block(eighth);
+  if (group * wb >= n) return;   // the whole block
+  const int role = wave_in_block();
+  Lane<N> L(group, threadIdx.x & 63, n, wb);
+  const int entry = L.boardok ? L.b : L.some;   // (a lane without an entry loads the team's first one: no branch around a load)
+  const int src = src_slots[entry], dst = dst_slots[entry];
+  auto fill_table = [&]() {
+#pragma unroll
+    for (uint32_t x = threadIdx.x; x < 256u; x += THREADS) lut[x] = make_uint2(spread4(x & 15u), spread4(x >> 4));
+  };
+  const bool in_pool = src >= 0 && src < pool && dst >= 0 && dst < pool;
+  const bool bad = L.boardok && !in_pool;
+  if (bad) { L.boardok = false; L.valid = false; L.full = 0u; }   // the entry becomes inert: no state access, no outputs
+  L.slot = src; L.some = 0;
+
+  if (role == 0) {
+    const int act_raw = actions[entry];
+    Row<N> R;
+    History<N> H;
+    load_row<N>(state, L, R);
+    const uint4 meta_raw = load_meta<N>(meta, L);
+    load_history<N>(state, L, H);
+    in_scalar_registers(a.rew, a.term, a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset);
+    fill_table();
+    const int act = L.boardok ? act_raw : -1;
+    Meta m = unpack_meta(meta_raw);
+    place_ko<N>(L, R, m);
+    L.slot = dst;   // from here on the board is environment dst (seat draw on reset, state store)
+    const bool skip = !L.boardok || act == -1;
+    const bool in_range = act >= 0 && act < G::P;
+    const int pr = in_range ? act / N : 0, pc = in_range ? act - (act / N) * N : 0;
+    const Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc);
+    const Ply ply = apply_move<N>(L, R, m, a.rules, mv, tally, [&]() { clear_history<N>(H); });
+    hand[L.lane] = HandOver<N>::of(R, m, ply).v;
+    __syncthreads();
+    push_history<N>(H, m.head, R.bk, R.wt, ply.moved);
+    store_all<N>(state, L, R, H);
+    if (L.valid && L.r == 0) meta[dst] = pack_meta(m);
+    if (L.lane == L.j * G::STRIDE + 1 && L.j < wb && L.b < n) {   // row-0 lane of the entry, inert or not
+      if (bad) { if (a.term) a.term[L.b] = (uint8_t)255; }
+      else {
+        // a copied entry (action -1) reports what a skipped step reports for a fresh handle: no reward, and its terminated state
+        if (a.rew) *(float2*)(a.rew + 2 * (size_t)L.b) = skip ? make_float2(0.f, 0.f) : make_float2(ply.rew0, ply.rew1);
+        if (a.term) a.term[L.b] = (uint8_t)(skip ? m.term : (ply.flag ? 1 : 0));
+      }
+    }
+  } else if (role == 1) {
+    in_scalar_registers(a.mask, a.mask_pitch);
+    fill_table();
+    __syncthreads();
+    if (a.mask) emit_mask<N, true, ST>(L, HandOver<N>{hand[L.lane]}.legal(L), group, n, a.mask, a.mask_pitch, lds_mask, lut, wb);
+  } else if constexpr (OBS) {
+    Row<N> R;
+    History<N> H;
+    load_row<N>(state, L, R);
+    load_history<N>(state, L, H);
+    const Meta m = unpack_meta(load_meta<N>(meta, L));
+    in_scalar_registers(a.obs, a.obs_pitch);
+    fill_table();
+    team_obs<N, ST>(L, R, points_of<N>(H, m.head), m, hand, group, n, a.obs, a.obs_pitch, lds_obs, lut, wb, [] { __syncthreads(); });
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 // the rollout kernel: one launch = `steps` plies of uniform random legal play of every environment.  The
 // state stays in registers between plies; each ply's outputs go to slice (i mod slices) of the caller's
 // trajectory buffers.
@@ -2578,11 +2655,38 @@ int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
   return PGXGO_OK;
 }
 
+// Boards per team of a search call of n entries (go_step_slots_team_kernel), 0 where one wavefront for everything is as fast.  The chain is
+// that of a ply with two more loads ahead of it, and the lines lie where they lie for plies; without observation teams win up to there
+// too (us per call, one wavefront / teams: 9x9 x 256 entries 4.38 / 3.26, 1024 4.51 / 3.47, 4096 4.66 / 4.11, without observation 256 3.38 /
+// 3.11, 4096 3.63 / 3.36; 19x19 x 256 5.40 / 3.76, 1000 5.60 / 4.28, 4096 8.61 / 7.47, 5500 9.50 / 8.83, without observation 256 3.86 /
+// 3.24, 4096 5.14 / 4.78, 5500 5.37 / 5.18).  What bounds such a call now is the loads' chain (slot, state) and the rules.  Mere copies
+// have no chain to shorten and stay with the other kernel, calls with the repetition rule too.
+template <int N>
+int boards_per_slot_team(int n) { return boards_per_step_team<N>(n); }
+
 template <int N>
 int launch_slots(pgxgo_ctx* h, int n, const int32_t* src, const int32_t* actions, const int32_t* dst, const SlotArgs& a) {
   const dim3 grid(blocks_for<N>(n)), block(64 * kWavesPerBlock);
   const bool tight = tight_pitches<N>(h), sk = h->zt != nullptr;
   const size_t out_bytes = (size_t)n * ((a.mask ? (size_t)a.mask_pitch : 0) + (a.obs ? (size_t)a.obs_pitch : 0));
+  const int wb = tight && !sk && h->automatic && actions ? boards_per_slot_team<N>(n) : 0;
+  if (wb) {
+    const dim3 teams((unsigned)((n + wb - 1) / wb + 7) & ~7u);
+    auto team = [&](auto obs_c, auto st_c) {
+      constexpr bool O = decltype(obs_c)::value;
+      hipLaunchKernelGGL((go_step_slots_team_kernel<N, O, decltype(st_c)::value>), teams, dim3(64 * (O ? 3 : 2)), 0, h->stream, src, dst, actions, h->state, h->meta, h->B,
+                         n, wb, teams.x / 8, a);
+    };
+    using Plain = std::integral_constant<int, kStorePlain>;
+    using Through = std::integral_constant<int, kStoreThrough>;
+    const bool plain = out_bytes <= kTeamPlainUpTo;
+    if (a.obs && plain) team(std::true_type{}, Plain{});
+    else if (a.obs) team(std::true_type{}, Through{});
+    else if (plain) team(std::false_type{}, Plain{});
+    else team(std::false_type{}, Through{});
+    HIPCHK(hipGetLastError());
+    return PGXGO_OK;
+  }
   if (tight && sk && h->sk_mode == 1) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 1>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
   else if (tight && sk) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 2>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);
   else if (tight && store_kind_for(out_bytes, true) == kStoreThrough) hipLaunchKernelGGL((go_step_slots_kernel<N, true, 0, kStoreThrough>), grid, block, 0, h->stream, src, dst, actions, h->state, h->meta, h->B, n, grid.x / 8, a);

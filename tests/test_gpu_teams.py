@@ -1,4 +1,4 @@
-"""Small batches are stepped by teams of four wavefronts.  At the sizes where the number of boards per team changes, and in the last
+"""Small batches are stepped by teams of wavefronts.  At the sizes where the number of boards per team changes, and in the last
 team of a batch, their outputs and state are those of the kernel in which one wavefront does everything (set_boards_per_wavefront asks
 for it), through skipped, illegal and passed plies, captures, endings and restarts in one team."""
 import numpy as np
@@ -68,3 +68,39 @@ def test_rollouts_by_teams_and_by_single_wavefronts_agree(N, B, steps, slices, o
         got.append(seen)
     for i, (x, y) in enumerate(zip(*got)):
         assert torch.equal(x, y), i
+
+
+@pytest.mark.parametrize("N,n,auto_reset,obs,line_padded", [
+    (9, 1, False, True, False), (9, 385, True, True, True), (9, 1023, False, False, False), (9, 1025, False, True, False), (9, 4095, False, True, False),
+    (19, 2, False, True, True), (19, 512, True, True, False), (19, 514, False, False, False), (19, 4097, False, True, False)])
+def test_search_entries_by_teams_and_by_single_wavefronts_agree(N, n, auto_reset, obs, line_padded):
+    pool = 3 * n + 1
+    kw = dict(seed=3, auto_reset=auto_reset, line_padded=line_padded, max_steps=50)
+    envs = [pg.GoEnv(pool, N, **kw), pg.GoEnv(pool, N, **kw)]
+    envs[1].set_boards_per_wavefront(3)
+    for e in envs:
+        e.rollout(46, 3, 0)
+    rng = np.random.default_rng(n)
+    dev = lambda x: torch.as_tensor(x.astype(np.int32), device="cuda")  # noqa: E731
+    for t in range(8):
+        order = rng.permutation(pool)
+        src = rng.choice(order[:pool - n], size=n)                  # several entries may come from one slot
+        dst = np.where(rng.random(n) < 0.2, -1, order[pool - n:])   # (-1: filled in below)
+        own = np.unique(src, return_index=True)[1]                  # an entry whose source nobody else reads may go back to it
+        alone = np.array([i for i in own if (src == src[i]).sum() == 1 and dst[i] < 0], dtype=int)
+        dst[alone] = src[alone]
+        dst[dst < 0] = order[pool - n:][dst < 0]
+        act = envs[0].random_actions(3, 60 + t).cpu().numpy()[src]
+        if t % 2:
+            act = np.where(rng.random(n) < 0.15, rng.choice([-1, 0, N * N, N * N + 7], size=n), act)   # a copy, a corner, pass, out of range
+            outside = rng.random(n) < 0.03
+            src = np.where(outside, rng.choice([-1, pool], size=n), src)
+        out = []
+        for e in envs:
+            m, r, z = torch.full((n, e.mask_pitch), 7, dtype=torch.uint8, device="cuda"), torch.full((n, 2), 7.0, device="cuda"), torch.full((n,), 7, dtype=torch.uint8, device="cuda")
+            o = torch.full((n, e.obs_pitch), 7, dtype=torch.uint8, device="cuda")
+            some = t != 6   # once without rewards and terminated
+            e.step_slots(dev(src), dev(act), dev(dst), mask=m if t != 4 else None, obs=o if obs else None, rewards=r if some else None, terminated=z if some else None)
+            out.append([m, o, r, z, *e.export_state().values()])
+        for i, (x, y) in enumerate(zip(*out)):
+            assert torch.equal(x, y), (t, i)

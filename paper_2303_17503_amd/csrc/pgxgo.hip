@@ -1967,9 +1967,13 @@ struct RolloutArgs {
   PaceArgs pace;
 };
 
-// The rate that the slots of a paced rollout are laid out for (us for 16 plies of 19x19 x 16384 games, recorded, with 6.0 / 6.2 / 6.3 /
-// 6.4 / 6.6 TB/s: 294 / 285 / 281 / 279 / 299; a step below the best, since above it the gain is soon lost)
-constexpr double kPaceBytesPerSecond = 6.3e12;
+// The rate that the slots of a paced rollout are laid out for (us for plies of 19x19 x 16384 games, recorded, with 6.3 / 6.35 / 6.4 / 6.45 /
+// 6.5 / 6.6 TB/s: 16 plies 281.2 / 280.4 / 277.8 / 276.1 / 275.3 / 276.0, 64 plies 1092 / 1084 / 1076 / 1069 / 1061 / 1145; two steps below
+// the best, since above it the gain is soon lost)
+constexpr double kPaceBytesPerSecond = 6.4e12;
+// Ticks until the first slot with the repetition rule, whose first ply looks at the tables beforehand (with 0 / 2 us: 8 plies of 30001 games, which
+// run in generations, 327 / 324; 16 of 16384 351 / 346)
+constexpr uint32_t kPaceFirstSuperko = 200u;
 
 // The registers hold a game's state from ply to ply, and 80 of them (six wavefronts per SIMD) are just enough for it and a ply's own values.
 // What a ply derives from the lane's place alone is therefore computed anew every ply (in_place): kept from one to the next it pushed
@@ -1990,8 +1994,9 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
   __shared__ uint64_t tally_all[kWavesPerBlock][64];
   __shared__ uint2 lut[256];
-  fill_spread_table(lut);
   const int wib = wave_in_block();
+  Pace pace(PACED, a.pace, (blockIdx.x >> 3) * kWavesPerBlock + wib, (gridDim.x >> 3) * kWavesPerBlock, SK ? kPaceFirstSuperko : 0u);
+  fill_spread_table(lut);
   const int wave = piece_of_block() * kWavesPerBlock + wib;
   if (wave * a.wb >= a.B) return;
   const Lane<N> L0(wave, threadIdx.x & 63, a.B, a.wb);
@@ -2023,7 +2028,6 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
   ahead.home = ~0u; ahead.e = make_uint2(1u, 0u);
   if constexpr (SK == 1) ahead = sk_window_play<N>(L0, tab, g, m, L0.boardok);
   int slice = 0;
-  Pace pace(PACED, a.pace, (blockIdx.x >> 3) * kWavesPerBlock + wib, (gridDim.x >> 3) * kWavesPerBlock);
   for (int i = 0; i < a.steps; ++i) {   // the same trip count for every wavefront
     Lane<N> L = L0;
     if (!TIGHT) L.lane = in_place(L.lane);   // (board-by-board emission holds more)

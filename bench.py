@@ -355,7 +355,7 @@ def bench_go(args, cfg):
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
         kern_ms = ev0.elapsed_time(ev1) / K       # per ply: the launch covers rollout_len plies
-        kname = "go_rollout_kernel<%d>" % N
+        kname = "go_rollout_kernel<%d> or, where it is faster, go_rollout_team_kernel" % N
         if S == 1:
             bufs_r = go_rollout_buffers(torch, S_rot, B, pitches, with_obs)
             ms = timed(lambda i: env.rollout(Lr, seed, pre + Wm + K + i * Lr, start_t=start_dev, slices=S_rot, **bufs_r), max(1, K // Lr)) / Lr
@@ -395,7 +395,7 @@ def bench_go(args, cfg):
                 st.t = t + 1
             torch.cuda.synchronize()
             kern_ms = sum(a.elapsed_time(b) for a, b in pairs) / n_ev
-        kname = "go_step_superko_kernel<%d>" % N if args.superko else "go_step_kernel<%d,%s>" % (N, "true" if args.mode == "fused" else "false")
+        kname = "go_step_superko_kernel<%d>" % N if args.superko else "go_step_kernel<%d,%s> or, for small batches, go_step_team_kernel" % (N, "true" if args.mode == "fused" else "false")
         # the same path, the next K plies, with mask and observation rotating over S_rot slices
         masks = [st.env.new_mask() for _ in range(S_rot)]
         obss = [st.env.new_obs() for _ in range(S_rot)] if with_obs else None
@@ -481,7 +481,7 @@ def bench_go(args, cfg):
         ms_r = timed(lambda i: env2.rollout(Lr, seed, pre + Wm + i * Lr, start_t=st.start, **bufs), Kr // Lr) / Lr
         wall_r = time.perf_counter() - tr0
         a_r = bytes_ply * B / (ms_r * 1e-3) / 1e9
-        out["rollout"] = {"value": B * Kr / wall_r, "unit": "env steps/s", "steps": Kr, "rollout_len": Lr, "kernel": "go_rollout_kernel<%d>" % N,
+        out["rollout"] = {"value": B * Kr / wall_r, "unit": "env steps/s", "steps": Kr, "rollout_len": Lr, "kernel": "go_rollout_kernel<%d> or, where it is faster, go_rollout_team_kernel" % N,
                           "kernel_ms_per_ply": ms_r, "achieved": a_r, "frac": a_r / HBM_PEAK_GBS, "frac_of_fill": fill["in_place_ms"] / ms_r,
                           "timed_ply_window": [pre + Wm, pre + Wm + Kr],
                           "note": "pgxgo_rollout: the same plies and outputs (in place) with rollout_len plies per launch; not the headline value"}

@@ -2092,7 +2092,9 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
 // observation, 3200 are left.  Figures, and which rollouts go this way: boards_per_rollout_team.
 // ------------------------------------------------------------------------------------------------
 // Everything the wavefronts of a block wrote to LDS is there for all of them.  (Unlike __syncthreads this does not wait for their output
-// stores as well.)
+// stores as well.  It orders nothing in memory.  So rows and history are written by the wavefront that has read them itself.  The
+// scalars are read by two; the one with the history writes them, when the other, which has needed all of them for its first ply, has handed
+// over the new ones in LDS.)
 __device__ __forceinline__ void team_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
@@ -2110,6 +2112,7 @@ __global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_rollout_team_kernel(Rol
   __shared__ uint4 hand[2][64];
   __shared__ uint4 scalars[2][G::W];   // per board: rewards, terminated
   __shared__ int32_t drawn[2][G::W];
+  __shared__ uint4 scalars_after[G::W];   // the game's record as the launch leaves it
   const int group = piece_of_block();
   if (group * a.wb >= a.B) return;   // the whole block
   const int role = wave_in_block();
@@ -2139,8 +2142,9 @@ __global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_rollout_team_kernel(Rol
     if (L.valid) {
       store_row<N>(State<N>(a.state, L), R);
       m.head = 0;
-      if (L.r == 0) a.meta[L.b] = pack_meta(m);
+      if (L.r == 0) scalars_after[L.j] = pack_meta(m);
     }
+    team_barrier();
   } else {   // 1: the mask and the scalars; 2: the observation; the last of them keeps the history
     const bool history = role == WAVES - 1, observe = OBS && role == 2;
     Points<N> Q;
@@ -2174,7 +2178,11 @@ __global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_rollout_team_kernel(Rol
       }
       slice = slice + 1 == a.slices ? 0 : slice + 1;
     }
-    if (history) store_history<N>(a.state, L, history_of<N>(Q));
+    team_barrier();
+    if (history) {
+      store_history<N>(a.state, L, history_of<N>(Q));
+      if (L.valid && L.r == 0) a.meta[L.b] = scalars_after[L.j];   // (this wavefront has taken the ring's beginning from there)
+    }
   }
 }
 

@@ -70,6 +70,33 @@ def test_rollouts_by_teams_and_by_single_wavefronts_agree(N, B, steps, slices, o
         assert torch.equal(x, y), i
 
 
+@pytest.mark.parametrize("N,B,obs", [(9, 7, True), (9, 1500, False), (19, 2, False), (19, 517, True)])
+def test_the_shortest_rollouts_by_teams_of_games_whose_rings_begin_anywhere(N, B, obs):
+    """One wavefront of a team reads where a game's ring of positions begins, which the launch itself sets back to its start."""
+    envs = [pg.GoEnv(B, N, seed=6, auto_reset=True, max_steps=30) for _ in range(2)]
+    envs[1].set_boards_per_wavefront(2)
+    outs = [bound(e, True) for e in envs]
+    rng = np.random.default_rng(B)
+    for t in range(0, 40, 4):
+        for k in range(2):
+            a = envs[0].random_actions(6, t + k)
+            a[torch.as_tensor(rng.random(B) < 0.4, device="cuda")] = -1   # a game that sits out keeps its ring where it is
+            for e in envs:
+                e.step(a)
+        got = []
+        for e in envs:
+            m, o = torch.full((2, B, e.mask_pitch), 7, dtype=torch.uint8, device="cuda"), torch.full((2, B, e.obs_pitch), 7, dtype=torch.uint8, device="cuda")
+            e.rollout(2, 6, t + 2, slices=2, mask=m, obs=o if obs else None)
+            got.append([m, o, *e.export_state().values()])
+        for i, (x, y) in enumerate(zip(*got)):
+            assert torch.equal(x, y), (t, i)
+        a = envs[0].random_actions(6, t + 4)
+        for e in envs:
+            e.step(a)
+        for i, (x, y) in enumerate(zip(*outs)):
+            assert torch.equal(x, y), (t, i)
+
+
 @pytest.mark.parametrize("N,n,auto_reset,obs,line_padded", [
     (9, 1, False, True, False), (9, 385, True, True, True), (9, 1023, False, False, False), (9, 1025, False, True, False), (9, 4095, False, True, False),
     (19, 2, False, True, True), (19, 512, True, True, False), (19, 514, False, False, False), (19, 4097, False, True, False)])

@@ -184,15 +184,42 @@ def cpu_baseline(cfg, pre, plies, n_threads, envs_per_thread, superko=False, min
 
 def bound_statement(kern_us, floor_us, fill_us, waves_per_simd):
     """Which limit binds, by a stated rule on quantities measured in this run (the counters are in profiles/)."""
-    rule = ("latency if kernel <= 1.5 x the ply of ONE wavefront (launch gap + load -> rules -> emit -> store of a single "
-            "wavefront); else hbm if a plain fill of the same output bytes takes >= 0.6 of the kernel; else valu issue")
+    rule = ("latency if kernel <= 1.5 x the ply of ONE group of boards (launch gap + load -> rules -> emit -> store of a single wavefront, "
+            "or team of wavefronts, of the same kernel); else hbm if a plain fill of the same output bytes takes 0.6 to 1 of the kernel (a "
+            "fill that takes longer than the kernel that wrote as much is a launch, not memory); else valu issue")
     if kern_us <= 1.5 * floor_us:
-        b = "launch gap + serial latency of one wavefront"
-    elif fill_us / kern_us >= 0.6:
+        b = "launch gap + serial latency of one group"
+    elif 0.6 <= fill_us / kern_us <= 1.0:
         b = "hbm (output stores)"
     else:
         b = "valu issue"
-    return {"bound_by": b, "rule": rule, "one_wavefront_ply_us": floor_us, "fill_of_outputs_us": fill_us, "wavefronts_per_simd": waves_per_simd}
+    return {"bound_by": b, "rule": rule, "one_group_ply_us": floor_us, "fill_of_outputs_us": fill_us, "wavefronts_per_simd": waves_per_simd}
+
+
+def go_kernel(env, B, with_obs, steps=0, slices=1, fused=True, superko=0):
+    """(name of the kernel that runs such a step call (steps = 0) or rollout, its wavefronts per SIMD)"""
+    N = env.N
+    wb, waves = env.boards_per_team(steps, slices, obs=with_obs)
+    if steps:
+        name = "go_rollout_team_kernel<%d>" % N if wb else "go_rollout_kernel<%d>" % N
+    elif superko:
+        name = "go_step_superko_kernel<%d>" % N
+    else:
+        name = "%s<%d,%s>" % ("go_step_team_kernel" if wb else "go_step_kernel", N, "true" if fused else "false")
+    return name, math.ceil(B / (wb or env.set_boards_per_wavefront(0))) * waves / 1024.0
+
+
+def one_group(cfg, env, with_obs, fused=True, superko=0, line_padded=False):
+    """A stepper whose plies are those of one group of boards of the kernel that steps `env`: a team with one board where that kernel is
+    run by teams, else one wavefront full of boards."""
+    import paper_2303_17503_amd as pg
+
+    W = pg.lib().pgxgo_boards_per_wavefront(cfg.board_size)
+    team = env.boards_per_team(0, obs=with_obs)[0] > 0
+    one = GoStepper(cfg, 1 if team else W, with_obs, fused=fused, superko=superko, line_padded=line_padded)
+    if not team:
+        one.env.set_boards_per_wavefront(W)
+    return one
 
 
 def main():
@@ -355,7 +382,7 @@ def bench_go(args, cfg):
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
         kern_ms = ev0.elapsed_time(ev1) / K       # per ply: the launch covers rollout_len plies
-        kname = "go_rollout_kernel<%d> or, where it is faster, go_rollout_team_kernel" % N
+        kname, _ = go_kernel(env, B, with_obs, Lr, S)
         if S == 1:
             bufs_r = go_rollout_buffers(torch, S_rot, B, pitches, with_obs)
             ms = timed(lambda i: env.rollout(Lr, seed, pre + Wm + K + i * Lr, start_t=start_dev, slices=S_rot, **bufs_r), max(1, K // Lr)) / Lr
@@ -395,7 +422,7 @@ def bench_go(args, cfg):
                 st.t = t + 1
             torch.cuda.synchronize()
             kern_ms = sum(a.elapsed_time(b) for a, b in pairs) / n_ev
-        kname = "go_step_superko_kernel<%d>" % N if args.superko else "go_step_kernel<%d,%s> or, for small batches, go_step_team_kernel" % (N, "true" if args.mode == "fused" else "false")
+        kname, waves_per_simd = go_kernel(st.env, B, with_obs, fused=args.mode == "fused", superko=args.superko)
         # the same path, the next K plies, with mask and observation rotating over S_rot slices
         masks = [st.env.new_mask() for _ in range(S_rot)]
         obss = [st.env.new_obs() for _ in range(S_rot)] if with_obs else None
@@ -412,7 +439,7 @@ def bench_go(args, cfg):
     fill = fill_ceiling(out_bytes, S_rot)
     gap_us = launch_gap_us()
     copy_gbs = device_copy_gbs(out_bytes)
-    pmc_file = os.path.join("profiles", f"{'go_rollout_kernel' if args.mode == 'rollout' else 'go_step_kernel'}_{cfg.name}.txt")
+    pmc_file = os.path.join("profiles", f"{kname.split('<')[0]}_{cfg.name}.txt")
     traffic = read_traffic(os.path.join(ROOT, pmc_file)) if with_obs and args.mode != "separate" and not args.superko and not args.line_padded else None
     if dram is not None:
         a = bytes_ply * B / (dram["kernel_ms"] * 1e-3) / 1e9
@@ -460,14 +487,11 @@ def bench_go(args, cfg):
         out["roofline"]["kernel_ms_median"] = sorted(seg_ms)[2]
         out["roofline"]["kernel_ms_best"] = min(seg_ms)
     if args.mode != "rollout":
-        # the ply of ONE wavefront of the same kernel (W boards), launch gap included: the latency floor of a launch
-        W = pg.lib().pgxgo_boards_per_wavefront(N)
-        tiny = GoStepper(cfg, W, with_obs, fused=(args.mode == "fused"), line_padded=args.line_padded)
-        tiny.env.set_boards_per_wavefront(W)
+        # the ply of ONE group of boards of the same kernel, launch gap included: the latency floor of a launch
+        tiny = one_group(cfg, st.env, with_obs, fused=(args.mode == "fused"), superko=args.superko, line_padded=args.line_padded)
         tiny.preroll(min(pre, 60)); tiny.run(20)
         floor_us = timed(lambda i: tiny.step_once(), 200) * 1e3
-        wb = st.env.set_boards_per_wavefront(0)
-        out["roofline"]["binding"] = bound_statement(kern_ms * 1e3, floor_us, fill["in_place_ms"] * 1e3, math.ceil(B / wb) / 1024.0)
+        out["roofline"]["binding"] = bound_statement(kern_ms * 1e3, floor_us, fill["in_place_ms"] * 1e3, waves_per_simd)
     if args.mode == "fused" and not args.superko and not args.line_padded and K >= args.rollout_len:
         # for information: the same workload and ply window through the rollout kernel (rollout_len plies per launch, state in registers)
         Lr = args.rollout_len
@@ -481,7 +505,7 @@ def bench_go(args, cfg):
         ms_r = timed(lambda i: env2.rollout(Lr, seed, pre + Wm + i * Lr, start_t=st.start, **bufs), Kr // Lr) / Lr
         wall_r = time.perf_counter() - tr0
         a_r = bytes_ply * B / (ms_r * 1e-3) / 1e9
-        out["rollout"] = {"value": B * Kr / wall_r, "unit": "env steps/s", "steps": Kr, "rollout_len": Lr, "kernel": "go_rollout_kernel<%d> or, where it is faster, go_rollout_team_kernel" % N,
+        out["rollout"] = {"value": B * Kr / wall_r, "unit": "env steps/s", "steps": Kr, "rollout_len": Lr, "kernel": go_kernel(env2, B, with_obs, Lr)[0],
                           "kernel_ms_per_ply": ms_r, "achieved": a_r, "frac": a_r / HBM_PEAK_GBS, "frac_of_fill": fill["in_place_ms"] / ms_r,
                           "timed_ply_window": [pre + Wm, pre + Wm + Kr],
                           "note": "pgxgo_rollout: the same plies and outputs (in place) with rollout_len plies per launch; not the headline value"}
@@ -535,7 +559,7 @@ def bench_hex(args, cfg):
             env.rollout(Lr, seed, pre + Wm + i * Lr, **bufs)
         ev1.record()
         torch.cuda.synchronize()
-        kname = "hex_rollout_kernel"
+        kname = "hex_rollout_lane_kernel" if env.rollout_in_time_slots(Lr)[1] else "hex_rollout_kernel"   # (games at once: 0 with a row per lane)
     else:
         acts = [torch.empty(B, dtype=torch.int32, device="cuda") for _ in range(2)]
         env.random_actions(seed, pre, out=acts[pre & 1])
@@ -549,7 +573,7 @@ def bench_hex(args, cfg):
             env.step_sample(acts[t & 1], seed, t + 1, out=acts[(t + 1) & 1])
         ev1.record()
         torch.cuda.synchronize()
-        kname = "hex_step_kernel<true>"
+        kname = "hex_step_lane_kernel<true>" if env.set_mapping(0) == 2 else "hex_step_kernel<true>"
     wall = time.perf_counter() - t0
     kern_ms = ev0.elapsed_time(ev1) / K       # per ply (a rollout launch covers rollout_len plies)
     if args.mode == "fused":
@@ -573,7 +597,7 @@ def bench_hex(args, cfg):
     if dram is not None:
         a = bytes_ply * B / (dram["kernel_ms"] * 1e-3) / 1e9
         dram.update({"achieved": a, "frac": a / HBM_PEAK_GBS, "frac_of_fill": fill["rotating_ms"] / dram["kernel_ms"]})
-    pmc_file = os.path.join("profiles", f"{'hex_step_lane_kernel' if B >= 196608 else 'hex_step_kernel'}_{cfg.name}.txt")
+    pmc_file = os.path.join("profiles", f"{kname.split('<')[0]}_{cfg.name}.txt")
     traffic = read_traffic(os.path.join(ROOT, pmc_file)) if with_obs and args.mode == "fused" else None
     out = {
         "metric": "Hex env steps/sec on 1 MI355X (11x11, random legal play); HBM GB/s % peak",
@@ -592,13 +616,16 @@ def bench_hex(args, cfg):
     if traffic:   # the fill's time scaled from the output bytes to the bytes the counters saw this kernel move
         out["roofline"]["frac_of_fill_at_traffic"] = fill["in_place_ms"] * traffic / out_bytes / kern_ms
     if args.mode == "fused":
-        tiny = pg.HexEnv(5, seed=seed, auto_reset=cfg.auto_reset)
+        mapping = env.set_mapping(0)
+        W = 64 if mapping == 2 else pg.lib().pgxhex_boards_per_wavefront()
+        tiny = pg.HexEnv(W, seed=seed, auto_reset=cfg.auto_reset)
+        tiny.set_mapping(mapping)
         tm, to = tiny.new_mask(), tiny.new_obs() if with_obs else None
         tiny.bind_outputs(tm, to, None, None)
-        ta = [torch.empty(5, dtype=torch.int32, device="cuda") for _ in range(2)]
+        ta = [torch.empty(W, dtype=torch.int32, device="cuda") for _ in range(2)]
         tiny.random_actions(seed, 0, out=ta[0])
         floor_us = timed(lambda t: tiny.step_sample(ta[t & 1], seed, t + 1, out=ta[(t + 1) & 1]), 200) * 1e3
-        out["roofline"]["binding"] = bound_statement(kern_ms * 1e3, floor_us, fill["in_place_ms"] * 1e3, math.ceil(B / 5) / 1024.0)
+        out["roofline"]["binding"] = bound_statement(kern_ms * 1e3, floor_us, fill["in_place_ms"] * 1e3, math.ceil(B / W) / 1024.0)
     if not args.no_cpu_baseline:
         n_threads = max(1, min(16, os.cpu_count() or 1))
         per = max(1, min(1024, B // n_threads))                      # enough work per call that the C code, not the interpreter, is timed

@@ -150,6 +150,12 @@ int pgxgo_rollout(pgxgo_t h, int32_t steps, int32_t slices, uint32_t seed, uint3
  * games the machine then holds at once (0: unknown, and nothing is written in time slots). */
 int pgxgo_rollout_in_time_slots(pgxgo_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int64_t* games_at_once);
 
+/* How the plies are launched (results do not depend on it): boards per team where blocks of several wavefronts share a group of boards
+ * (pgxgo_step / pgxgo_step_sample of small batches, most rollouts that are not written in time slots), or 0 where one wavefront does
+ * everything for its boards (as many as pgxgo_set_boards_per_wavefront says), or a negative error code.  steps = 0 asks about a step call
+ * with / without a bound observation, else about pgxgo_rollout with these arguments.  wavefronts (nullable): those of a team, or 1. */
+int pgxgo_boards_per_team(pgxgo_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int32_t* wavefronts);
+
 /* Search-facing step (Sec. 5: tree search calls step from copies of earlier states).  The handle's `batch`
  * environments are treated as a pool of state slots; for i in 0..n-1 (n <= batch):
  *     state[dst_slots_dev[i]] = step(state[src_slots_dev[i]], actions_dev[i])
@@ -187,10 +193,12 @@ int pgxgo_import_state(pgxgo_t h, const int8_t* board_dev, const int8_t* history
                        const int8_t* to_play_dev, const int32_t* steps_dev, const int8_t* passes_dev,
                        const uint8_t* terminated_dev, const uint8_t* black_player_dev, const uint32_t* episode_dev);
 
-/* Launch-shape knob: how many boards the step and rollout kernels put into one 64-lane wavefront, 1 up to
- * pgxgo_boards_per_wavefront(board_size).  0 restores the automatic choice made by pgxgo_init (fewer boards per
- * wavefront for small batches, where latency rather than throughput decides).  Results do not depend on it.
- * Returns the value now in use (> 0), or a negative error code. */
+/* Launch-shape knob.  1 up to pgxgo_boards_per_wavefront(board_size): step and rollout calls run by the kernels in which one wavefront
+ * does everything, with this many boards in each 64-lane wavefront, and search calls by the kernel of that kind as well (its boards per
+ * wavefront are fixed).  0 restores the automatic choice made by pgxgo_init: teams of wavefronts where they are faster
+ * (pgxgo_boards_per_team), and elsewhere fewer boards per wavefront for small batches, where latency rather than throughput decides.  So
+ * asking for the number that 0 returned is not the same as 0.  Results do not depend on it.  Returns the boards per wavefront that kernels
+ * without teams now use (> 0), or a negative error code. */
 int pgxgo_set_boards_per_wavefront(pgxgo_t h, int32_t boards);
 
 /* Positional superko (Appendix C "Go": Tromp-Taylor rules, whose repetition rule forbids a play that recreates an

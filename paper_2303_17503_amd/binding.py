@@ -60,6 +60,7 @@ def lib():
         L.pgxgo_step_sample.argtypes = [vp, vp, u32, u32, vp, vp]
         L.pgxgo_rollout.argtypes = [vp, i32, i32, u32, u32, vp, vp, vp, vp, vp, vp]
         L.pgxgo_rollout_in_time_slots.argtypes = [vp, i32, i32, i32, i32, C.POINTER(C.c_int64)]
+        L.pgxgo_boards_per_team.argtypes = [vp, i32, i32, i32, i32, C.POINTER(i32)]
         L.pgxgo_step_slots.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp, vp]
         L.pgxgo_copy_slots.argtypes = [vp, i32, vp, vp]
         for n in ("legal_mask", "observe", "rewards", "terminated", "current_player"):
@@ -243,6 +244,14 @@ class GoEnv:
             _check(rc, "pgxgo_rollout_in_time_slots")
         return bool(rc), games.value
 
+    def boards_per_team(self, steps=0, slices=1, mask=True, obs=True):
+        """(boards per team, wavefronts of a team) of a step call (steps = 0) or such a rollout; (0, 1) where one wavefront does everything"""
+        waves = C.c_int32()
+        rc = lib().pgxgo_boards_per_team(self._h, int(steps), int(slices), int(bool(mask)), int(bool(obs)), C.byref(waves))
+        if rc < 0:
+            _check(rc, "pgxgo_boards_per_team")
+        return rc, waves.value
+
     def step_slots(self, src, actions, dst, mask=None, obs=None, rewards=None, terminated=None):
         """state[dst[i]] = step(state[src[i]], actions[i]); outputs of entry i in row i of the optional buffers."""
         if _fast is not None:
@@ -293,7 +302,9 @@ class GoEnv:
         _check(lib().pgxgo_sync(self._h), "pgxgo_sync")
 
     def set_boards_per_wavefront(self, boards=0):
-        """Launch-shape knob of the step and rollout kernels (0 = automatic); returns the value in use."""
+        """Launch-shape knob.  0 = automatic: teams of wavefronts for small batches (boards_per_team), elsewhere a number chosen by the batch.
+        Any other number is had in step and rollout calls, and turns teams off, also in search calls.  Returns the number that kernels
+        without teams use."""
         rc = lib().pgxgo_set_boards_per_wavefront(self._h, int(boards))
         if rc <= 0:
             _check(rc if rc < 0 else -1, "pgxgo_set_boards_per_wavefront")

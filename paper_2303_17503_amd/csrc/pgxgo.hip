@@ -2100,10 +2100,11 @@ __device__ __forceinline__ void team_barrier() {
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
+constexpr int rollout_team_waves(bool with_obs) { return with_obs ? 3 : 2; }
 template <int N, bool OBS>
-__global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_rollout_team_kernel(RolloutArgs a) {   // a.wb: boards per team
+__global__ void __launch_bounds__(64 * rollout_team_waves(OBS)) go_rollout_team_kernel(RolloutArgs a) {   // a.wb: boards per team
   using G = Geo<N>;
-  constexpr int WAVES = OBS ? 3 : 2, ST = kStoreThroughWhole;
+  constexpr int WAVES = rollout_team_waves(OBS), ST = kStoreThroughWhole;
   constexpr bool FIRST_AS_EDGE = N == 19;   // as in go_rollout_kernel
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs[OBS ? G::W * G::OBS_DW : 4];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask[64];
@@ -2487,6 +2488,14 @@ int auto_boards_per_wavefront(int B) {
   return (int)(((int64_t)B + 1024 * (int64_t)per_simd - 1) / (1024 * (int64_t)per_simd));
 }
 
+// both output pitches are the dense or the line-padded ones: the kernels treat a wavefront's boards as one run of bytes
+// (with the line-padded pitch the pad bytes belong to that run and are written as zeros)
+template <int N>
+bool tight_pitches(const pgxgo_ctx* h) {
+  using G = Geo<N>;
+  return (h->mask_pitch == G::A || h->mask_pitch == G::A_PAD) && (h->obs_pitch == G::OBS || h->obs_pitch == G::OBS_PAD);
+}
+
 // Boards per team of four wavefronts (go_step_team_kernel) for batches that are faster that way, else 0.  A team is worth while as long as
 // the machine has wavefront slots to spare: up to four teams per compute unit at 9x9 (us per ply, one wavefront for all / teams: 256
 // games 4.60 / 3.72, 1024 4.94 / 4.16, 2048 4.95 / 4.55, 4096 5.29 / 5.20, 5000 5.58 / 5.46, 8192 6.15 / 6.31) and eight at 19x19, where the
@@ -2500,17 +2509,16 @@ int boards_per_step_team(int B) {
   return B <= 512 ? 1 : B <= 2048 * Geo<N>::W ? Geo<N>::W : 0;
 }
 constexpr int kTeamsWithoutObservation = 1366;   // 19x19: more teams only pay with the observation
+// boards per team of a step of this handle, or 0: one wavefront for everything
+template <int N>
+int step_team(const pgxgo_ctx* h, bool with_obs) {
+  if (!h->automatic || h->zt || !tight_pitches<N>(h)) return 0;
+  const int wb = boards_per_step_team<N>(h->B);
+  return wb && (with_obs || (h->B + wb - 1) / wb <= kTeamsWithoutObservation) ? wb : 0;
+}
 // Outputs of a team launch up to this many bytes are stored the ordinary way (9x9 x 256 games 3.72 us against 3.83 written through, 19x19 x 400, 2.6
 // MB, 5.09 / 5.13, without observation x 2048 5.24 / 5.36), beyond it through the L2 (9x9 x 2048, 3 MB, 4.63 / 4.55; 19x19 x 1000 6.10 / 5.66).
 constexpr size_t kTeamPlainUpTo = (size_t)5 << 19;
-
-// both output pitches are the dense or the line-padded ones: the kernels treat a wavefront's boards as one run of bytes
-// (with the line-padded pitch the pad bytes belong to that run and are written as zeros)
-template <int N>
-bool tight_pitches(const pgxgo_ctx* h) {
-  using G = Geo<N>;
-  return (h->mask_pitch == G::A || h->mask_pitch == G::A_PAD) && (h->obs_pitch == G::OBS || h->obs_pitch == G::OBS_PAD);
-}
 
 template <int N, bool TIGHT, bool SK>
 void launch_emit_as(pgxgo_ctx* h, uint8_t* mask, uint8_t* obs) {
@@ -2541,9 +2549,9 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
   h->mask_written = h->mask_out; h->obs_written = h->obs_out;
   const dim3 grid(blocks_for_wb(h->B, h->wb)), block(64 * kWavesPerBlock);
   const bool tight = tight_pitches<N>(h);
-  const int wb = h->automatic ? boards_per_step_team<N>(h->B) : 0, teams = wb ? (h->B + wb - 1) / wb : 0;
-  if (tight && !h->zt && teams && (h->obs_out || teams <= kTeamsWithoutObservation)) {
-    const dim3 tgrid((unsigned)(teams + 7) & ~7u);
+  const int wb = step_team<N>(h, h->obs_out != nullptr);
+  if (wb) {
+    const dim3 tgrid((unsigned)((h->B + wb - 1) / wb + 7) & ~7u);
     const bool plain = output_bytes_per_ply(h, h->mask_out != nullptr, h->obs_out != nullptr) <= kTeamPlainUpTo;
     auto team = [&](auto sample_c, auto st_c) {
       hipLaunchKernelGGL((go_step_team_kernel<N, decltype(sample_c)::value, decltype(st_c)::value>), tgrid, block, 0, h->stream, h->state, h->meta, actions, start_t,
@@ -2644,16 +2652,26 @@ int boards_per_rollout_team(int B, int steps, bool with_obs) {
   return B <= 512 ? 1 : B <= 30720 || steps >= 16 ? 3 : 0;
 }
 
+// boards per team of such a rollout of this handle, or 0: one wavefront for everything
+template <int N>
+int rollout_team(const pgxgo_ctx* h, int steps, bool with_obs, const PaceArgs& pace) {
+  return h->automatic && !h->zt && !pace.ply && tight_pitches<N>(h) ? boards_per_rollout_team<N>(h->B, steps, with_obs) : 0;
+}
+template <int N>
+int team_of(const pgxgo_ctx* h, int steps, int slices, bool with_mask, bool with_obs) {   // steps = 0: of a step
+  return steps ? rollout_team<N>(h, steps, with_obs, rollout_pace<N>(h, steps, slices, with_mask, with_obs)) : step_team<N>(h, with_obs);
+}
+
 template <int N>
 int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
   const dim3 grid(blocks_for_wb(h->B, h->wb)), block(64 * kWavesPerBlock);
   a.pace = rollout_pace<N>(h, a.steps, a.slices, a.mask != nullptr, a.obs != nullptr);
-  const int team = h->automatic && !h->zt && !a.pace.ply && tight_pitches<N>(h) ? boards_per_rollout_team<N>(h->B, a.steps, a.obs != nullptr) : 0;
+  const int team = rollout_team<N>(h, a.steps, a.obs != nullptr, a.pace);
   if (team) {
     a.wb = team;
     const dim3 teams((unsigned)(((int64_t)h->B + team - 1) / team + 7) & ~7u);
-    if (a.obs) hipLaunchKernelGGL((go_rollout_team_kernel<N, true>), teams, dim3(64 * 3), 0, h->stream, a);
-    else hipLaunchKernelGGL((go_rollout_team_kernel<N, false>), teams, dim3(64 * 2), 0, h->stream, a);
+    if (a.obs) hipLaunchKernelGGL((go_rollout_team_kernel<N, true>), teams, dim3(64 * rollout_team_waves(true)), 0, h->stream, a);
+    else hipLaunchKernelGGL((go_rollout_team_kernel<N, false>), teams, dim3(64 * rollout_team_waves(false)), 0, h->stream, a);
     HIPCHK(hipGetLastError());
     return PGXGO_OK;
   }
@@ -2923,6 +2941,13 @@ int pgxgo_rollout_in_time_slots(pgxgo_t h, int32_t steps, int32_t slices, int32_
   const PaceArgs p = DISPATCH_N(h, rollout_pace<19>(h, steps, slices, with_mask != 0, with_obs != 0), rollout_pace<9>(h, steps, slices, with_mask != 0, with_obs != 0));
   if (games_at_once) *games_at_once = (int64_t)8 * p.held * h->wb;
   return p.ply != 0u ? 1 : 0;
+}
+
+int pgxgo_boards_per_team(pgxgo_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int32_t* wavefronts) {
+  if (!h || steps < 0 || slices < 1) return PGXGO_EINVAL;
+  const int wb = DISPATCH_N(h, team_of<19>(h, steps, slices, with_mask != 0, with_obs != 0), team_of<9>(h, steps, slices, with_mask != 0, with_obs != 0));
+  if (wavefronts) *wavefronts = !wb ? 1 : steps ? rollout_team_waves(with_obs != 0) : (int)kTeamWaves;
+  return wb;
 }
 
 int pgxgo_step_slots(pgxgo_t h, int32_t n, const int32_t* src_slots_dev, const int32_t* actions_dev, const int32_t* dst_slots_dev,

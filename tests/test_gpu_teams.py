@@ -5,7 +5,9 @@ import numpy as np
 import pytest
 import torch
 
+import bench
 import paper_2303_17503_amd as pg
+import workloads
 
 pytestmark = pytest.mark.gpu
 
@@ -15,6 +17,33 @@ def bound(env, obs):
     out = [env.new_mask(), env.new_obs() if obs else None, torch.zeros((B, 2), dtype=torch.float32, device="cuda"), torch.zeros(B, dtype=torch.uint8, device="cuda")]
     env.bind_outputs(*out)
     return [t for t in out if t is not None]
+
+
+@pytest.mark.parametrize("N,B,obs,steps,slices,team", [   # on both sides of every line; steps = 0: a step call
+    (9, 256, True, 0, 1, (1, 4)), (9, 384, True, 0, 1, (1, 4)), (9, 385, False, 0, 1, (2, 4)), (9, 4096, True, 0, 1, (4, 4)), (9, 4097, True, 0, 1, (0, 1)),
+    (19, 512, True, 0, 1, (1, 4)), (19, 6144, True, 0, 1, (3, 4)), (19, 6145, True, 0, 1, (0, 1)), (19, 4098, False, 0, 1, (3, 4)), (19, 4099, False, 0, 1, (0, 1)),
+    (9, 5001, True, 1, 1, (0, 1)), (9, 5001, True, 2, 1, (6, 3)), (9, 5001, False, 64, 64, (6, 2)), (9, 20480, True, 9, 1, (6, 3)), (9, 20481, True, 9, 1, (0, 1)),
+    (19, 1024, False, 2, 1, (1, 2)), (19, 11000, False, 2, 1, (3, 2)), (19, 11001, False, 2, 1, (0, 1)), (19, 30720, True, 2, 1, (3, 3)),
+    (19, 30721, True, 15, 1, (0, 1)), (19, 30721, True, 16, 1, (3, 3)), (19, 16384, True, 16, 1, (3, 3)), (19, 16384, True, 16, 16, (0, 1))])
+def test_which_calls_go_by_teams(N, B, obs, steps, slices, team):
+    env = pg.GoEnv(B, N)
+    assert env.boards_per_team(steps, slices, obs=obs) == team
+    env.set_boards_per_wavefront(2)
+    assert env.boards_per_team(steps, slices, obs=obs) == (0, 1)
+    env.set_boards_per_wavefront(0)
+    assert env.boards_per_team(steps, slices, obs=obs) == team
+    assert pg.GoEnv(B, N, mask_pitch=N * N + 2).boards_per_team(steps, slices, obs=obs) == (0, 1)
+
+
+@pytest.mark.parametrize("config", [0, 2, 3])
+def test_the_benchmark_compares_a_ply_with_one_group_of_the_same_kernel(config):
+    cfg = workloads.CONFIGS[config]
+    env = pg.GoEnv(cfg.batch, cfg.board_size)
+    one = bench.one_group(cfg, env, True)
+    kernel, waves = bench.go_kernel(env, cfg.batch, True)
+    assert kernel.startswith("go_step_team_kernel" if config < 3 else "go_step_kernel")
+    assert bench.go_kernel(one.env, one.B, True)[0] == kernel
+    assert waves == {0: 256 * 4 / 1024, 2: 342 * 4 / 1024, 3: 5462 / 1024}[config]
 
 
 @pytest.mark.parametrize("N,B,auto_reset,obs,line_padded", [

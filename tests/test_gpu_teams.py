@@ -8,6 +8,7 @@ import torch
 import bench
 import paper_2303_17503_amd as pg
 import workloads
+from gpu_common import Pair
 
 pytestmark = pytest.mark.gpu
 
@@ -97,6 +98,40 @@ def test_rollouts_by_teams_and_by_single_wavefronts_agree(N, B, steps, slices, o
         got.append(seen)
     for i, (x, y) in enumerate(zip(*got)):
         assert torch.equal(x, y), i
+
+
+@pytest.mark.parametrize("B,steps,slices,team", [(30720, 2, 1, 3), (30721, 15, 1, 0), (30721, 16, 1, 3), (40001, 17, 2, 3)])
+def test_large_rollouts_by_teams_and_by_single_wavefronts_agree(B, steps, slices, team):
+    assert pg.GoEnv(B, 19).boards_per_team(steps, slices)[0] == team
+    test_rollouts_by_teams_and_by_single_wavefronts_agree(19, B, steps, slices, True, True)
+
+
+def test_rollouts_by_teams_with_slices_beyond_four_gibibytes():
+    """720001 games of 19x19, two slices of 4.4 GB, some 90 times the games that the machine holds at once: the oracle replays the first games,
+    those on both sides of the 4 GiB offset and the last ones."""
+    B, N, seed, before, plies = 720001, 19, 21, 60, 17
+    cross = (1 << 32) // (N * N * 17)
+    ids = np.concatenate([np.arange(384), np.arange(cross - 192, cross + 192), np.arange(B - 384, B)]).astype(np.int32)
+    p = Pair(B, N, seed, True, ids=ids, bind=False)
+    assert p.env.boards_per_team(plies, 2) == (3, 3) and not p.env.rollout_in_time_slots(plies, 2)[0]
+    p.env.rollout(before, seed, 0)
+    for t in range(before):
+        p.orc.step(p.orc.random_actions(seed, t))
+    new = lambda *shape, dtype=torch.uint8: torch.full(shape, 7, dtype=dtype, device="cuda")  # noqa: E731
+    mask, obs = new(2, B, N * N + 1), new(2, B, N * N * 17)
+    act, rew, term = new(2, B, dtype=torch.int32), new(2, B, 2, dtype=torch.float32), new(2, B)
+    p.env.rollout(plies, seed, before, slices=2, actions=act, rewards=rew, terminated=term, mask=mask, obs=obs)
+    for i in range(plies):
+        a = p.orc.random_actions(seed, before + i)
+        p.orc.step(a)
+        if i >= plies - 2:
+            k = i & 1
+            for name, x, y in (("actions", act, a), ("mask", mask, p.orc.legal_mask()), ("obs", obs, p.orc.observe()), ("rewards", rew, p.orc.rewards()),
+                               ("terminated", term, p.orc.terminated())):
+                assert (p.pick(x[k]).reshape(y.shape) == y).all(), (name, i)
+    g, c = p.env.export_state(), p.orc.export_state()
+    for name in ("board", "history", "ko", "to_play", "steps", "passes", "episode"):
+        assert (p.pick(g[name]).astype(np.int64) == getattr(c, name).astype(np.int64)).all(), name
 
 
 @pytest.mark.parametrize("N,B,obs", [(9, 7, True), (9, 1500, False), (19, 2, False), (19, 517, True)])

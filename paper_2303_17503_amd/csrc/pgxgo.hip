@@ -42,6 +42,7 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "pgxgo.h"
@@ -2638,35 +2639,54 @@ PaceArgs rollout_pace(const pgxgo_ctx* h, int steps, int slices, bool with_mask,
 }
 
 // Boards per team of a rollout (go_rollout_team_kernel), or 0 where one wavefront for everything is faster.  us for 16 plies in place, one
-// wavefront / teams: 9x9 x 256 games 42.2 / 25.1, 1000 43.5 / 28.3, 5001 53.4 / 35.9, 12000 64.5 / 55.5, 20000 92.6 / 88.2, 24000 93.4 / 99.1,
-// without observation x 1000 32.6 / 27.6, 5001 35.9 / 31.5, 20000 65.5 / 62.3, 24000 66.6 / 77.1; 19x19 x 400 60.3 / 34.0, 1500 72 / 39,
-// 4000 81 / 66, 8192 121 / 114, 16384 227 / 212, 28000 377 / 353, 65536 836 / 797, without observation x 400 41.5 / 33.7, 8192 67 / 63, 11000
-// 81.2 / 80.3, 12000 81.5 / 87.5.  A single ply gains too little (19x19 x 8192 14.4 / 15.8).  Batches of more teams than the machine
-// holds at once start anew several times and need plies to make up for it (65536 games, 4 plies 252 / 297; 28000 106 / 99).
+// wavefront / teams: 9x9 x 256 games 42.2 / 25.1, 1000 43.5 / 28.3, 5001 53.4 / 35.9, 12000 64.5 / 55.5, without observation x 1000 32.6 /
+// 27.6, 5001 35.9 / 31.5; 19x19 x 400 60.3 / 34.0, 1500 72 / 39, 4000 81 / 66, 8192 121 / 114, 16384 227 / 212, 28000 377 / 353, 65536
+// 836 / 797, without observation x 400 41.5 / 33.7, 8192 67 / 63.  A single ply gains too little (19x19 x 8192 14.4 / 15.8).
+// A launch of teams takes longer to get going, the more of them a compute unit has to hold and the more generations of them there are, and
+// needs plies to make up for it.  Time of teams over time of one wavefront, outputs that are not in the caches:
+//  * 9x9, whose teams of six the machine holds up to 15360 games of: 2 plies 0.95 x 12288, 1.03 x 13312, 1.09 x 15360; 3 plies 0.96 x 13312, 0.99
+//    x 14336, 1.02 x 15360; 4 plies 0.96 x 14336; 5 plies 0.99 x 15360; so 1024 games more for every ply.  Beyond, 8 plies 0.975 x 15616, 1.00 x
+//    16384, 1.02 x 17408, 1.07 x 18432 (12 to 64 plies are the same), and again ahead where one wavefront for everything needs a fourth on
+//    every SIMD: 8 plies 0.91 x 18433, 0.99 x 20480, 6 plies 0.98 x 19456, 1.006 x 20480, 4 plies 1.03 x 20480.
+//  * 9x9 without observation: 2 plies 1.00 x 8000, 1.02 x 9000, 1.04 x 10000, 1.03 x 20480; 3 plies 0.98 x 13000, 1.02 x 14336; 16 plies 0.97 x 16384.
+//  * 19x19 without observation: 2 plies 1.00 x 5120, 1.03 x 6000, 1.04 x 11000; otherwise up to 3584 teams (3 / 32 plies 0.95 / 0.91 x 10240,
+//    1.03 / 1.02 x 11000).
+//  * 19x19: 2 plies 0.98 x 26000, 1.04 x 27648, 1.08 x 30720 (outputs in the cache 0.97, 1.00, 1.00), 3 plies 0.97 x 26000, 1.015 x 27648, 1.04 x
+//    30720 (0.96, 0.99, 0.99), 4 plies 1.01 x 30720 (0.98); from 16 plies on teams win at every size.  Two slices written in turn, together more
+//    than the memory-side cache, are slower by teams up to 6 plies (3 / 4 / 6 plies 0.94 / 0.98 / 0.94 x 22000, 0.95 / 1.03 / 1.00 x 23000, 1.06 /
+//    1.07 / 1.015 x 27000; three slices 0.96 x 27000).
 // Boards as in boards_per_step_team; 19x19 without observation, where the mask is short, spreads further (1000 games with 1 / 3 37.5 / 40.4).
 template <int N>
-int boards_per_rollout_team(int B, int steps, bool with_obs) {
+int boards_per_rollout_team(int B, int steps, int slices, bool with_obs) {
   if (steps < 2) return 0;
-  if (N == 9) return B <= 384 ? 1 : B <= 1024 ? 2 : B <= 4096 ? 4 : B <= 20480 ? 6 : 0;
-  if (!with_obs) return B <= 1024 ? 1 : B <= 2048 ? 2 : B <= 11000 ? 3 : 0;
-  return B <= 512 ? 1 : B <= 30720 || steps >= 16 ? 3 : 0;
+  constexpr int K = 1024;
+  int most;   // games
+  if (N == 9 && with_obs) most = steps < 8 ? std::min(10 + steps, 15) * K : 16 * K;
+  else if (N == 9) most = steps == 2 ? 8 * K : steps == 3 ? 13 * K : 20 * K;
+  else if (!with_obs) most = steps == 2 ? 5 * K : 3584 * Geo<N>::W;
+  else if (steps >= 16) most = B;
+  else most = slices == 2 && steps < 7 ? 22 * K : steps < 4 ? (24 + steps) * K : 30 * K;
+  const bool ahead_again = N == 9 && with_obs && steps >= 6 && B > 18 * K && B <= 20 * K;
+  if (B > most && !ahead_again) return 0;
+  if (N == 9) return B <= 384 ? 1 : B <= K ? 2 : B <= 4 * K ? 4 : 6;
+  return with_obs ? (B <= 512 ? 1 : 3) : B <= K ? 1 : B <= 2 * K ? 2 : 3;
 }
 
 // boards per team of such a rollout of this handle, or 0: one wavefront for everything
 template <int N>
-int rollout_team(const pgxgo_ctx* h, int steps, bool with_obs, const PaceArgs& pace) {
-  return h->automatic && !h->zt && !pace.ply && tight_pitches<N>(h) ? boards_per_rollout_team<N>(h->B, steps, with_obs) : 0;
+int rollout_team(const pgxgo_ctx* h, int steps, int slices, bool with_obs, const PaceArgs& pace) {
+  return h->automatic && !h->zt && !pace.ply && tight_pitches<N>(h) ? boards_per_rollout_team<N>(h->B, steps, slices, with_obs) : 0;
 }
 template <int N>
 int team_of(const pgxgo_ctx* h, int steps, int slices, bool with_mask, bool with_obs) {   // steps = 0: of a step
-  return steps ? rollout_team<N>(h, steps, with_obs, rollout_pace<N>(h, steps, slices, with_mask, with_obs)) : step_team<N>(h, with_obs);
+  return steps ? rollout_team<N>(h, steps, slices, with_obs, rollout_pace<N>(h, steps, slices, with_mask, with_obs)) : step_team<N>(h, with_obs);
 }
 
 template <int N>
 int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
   const dim3 grid(blocks_for_wb(h->B, h->wb)), block(64 * kWavesPerBlock);
   a.pace = rollout_pace<N>(h, a.steps, a.slices, a.mask != nullptr, a.obs != nullptr);
-  const int team = rollout_team<N>(h, a.steps, a.obs != nullptr, a.pace);
+  const int team = rollout_team<N>(h, a.steps, a.slices, a.obs != nullptr, a.pace);
   if (team) {
     a.wb = team;
     const dim3 teams((unsigned)(((int64_t)h->B + team - 1) / team + 7) & ~7u);

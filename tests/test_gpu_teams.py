@@ -23,9 +23,13 @@ def bound(env, obs):
 @pytest.mark.parametrize("N,B,obs,steps,slices,team", [   # on both sides of every line; steps = 0: a step call
     (9, 256, True, 0, 1, (1, 4)), (9, 384, True, 0, 1, (1, 4)), (9, 385, False, 0, 1, (2, 4)), (9, 4096, True, 0, 1, (4, 4)), (9, 4097, True, 0, 1, (0, 1)),
     (19, 512, True, 0, 1, (1, 4)), (19, 6144, True, 0, 1, (3, 4)), (19, 6145, True, 0, 1, (0, 1)), (19, 4098, False, 0, 1, (3, 4)), (19, 4099, False, 0, 1, (0, 1)),
-    (9, 5001, True, 1, 1, (0, 1)), (9, 5001, True, 2, 1, (6, 3)), (9, 5001, False, 64, 64, (6, 2)), (9, 20480, True, 9, 1, (6, 3)), (9, 20481, True, 9, 1, (0, 1)),
-    (19, 1024, False, 2, 1, (1, 2)), (19, 11000, False, 2, 1, (3, 2)), (19, 11001, False, 2, 1, (0, 1)), (19, 30720, True, 2, 1, (3, 3)),
-    (19, 30721, True, 15, 1, (0, 1)), (19, 30721, True, 16, 1, (3, 3)), (19, 16384, True, 16, 1, (3, 3)), (19, 16384, True, 16, 16, (0, 1))])
+    (9, 5001, True, 1, 1, (0, 1)), (9, 5001, False, 64, 64, (6, 2)), (9, 12288, True, 2, 1, (6, 3)), (9, 12289, True, 2, 1, (0, 1)), (9, 13312, True, 3, 1, (6, 3)),
+    (9, 15360, True, 7, 1, (6, 3)), (9, 15361, True, 7, 1, (0, 1)), (9, 16384, True, 8, 1, (6, 3)), (9, 16385, True, 64, 1, (0, 1)), (9, 18432, True, 9, 1, (0, 1)),
+    (9, 18433, True, 9, 1, (6, 3)), (9, 18433, True, 5, 1, (0, 1)), (9, 20480, True, 6, 1, (6, 3)), (9, 20481, True, 9, 1, (0, 1)),
+    (9, 8192, False, 2, 1, (6, 2)), (9, 8193, False, 2, 1, (0, 1)), (9, 13313, False, 3, 1, (0, 1)), (9, 20480, False, 4, 1, (6, 2)), (9, 20481, False, 4, 1, (0, 1)),
+    (19, 1024, False, 2, 1, (1, 2)), (19, 5120, False, 2, 1, (3, 2)), (19, 5121, False, 2, 1, (0, 1)), (19, 10752, False, 3, 1, (3, 2)), (19, 10753, False, 99, 1, (0, 1)),
+    (19, 26624, True, 2, 1, (3, 3)), (19, 26625, True, 2, 1, (0, 1)), (19, 30720, True, 4, 1, (3, 3)), (19, 30721, True, 15, 1, (0, 1)), (19, 30721, True, 16, 1, (3, 3)),
+    (19, 22528, True, 3, 2, (3, 3)), (19, 22529, True, 6, 2, (0, 1)), (19, 22529, True, 7, 2, (3, 3)), (19, 16384, True, 16, 1, (3, 3)), (19, 16384, True, 16, 16, (0, 1))])
 def test_which_calls_go_by_teams(N, B, obs, steps, slices, team):
     env = pg.GoEnv(B, N)
     assert env.boards_per_team(steps, slices, obs=obs) == team
@@ -100,7 +104,7 @@ def test_rollouts_by_teams_and_by_single_wavefronts_agree(N, B, steps, slices, o
         assert torch.equal(x, y), i
 
 
-@pytest.mark.parametrize("B,steps,slices,team", [(30720, 2, 1, 3), (30721, 15, 1, 0), (30721, 16, 1, 3), (40001, 17, 2, 3)])
+@pytest.mark.parametrize("B,steps,slices,team", [(30720, 5, 1, 3), (30720, 2, 1, 0), (30721, 15, 1, 0), (30721, 16, 1, 3), (40001, 17, 2, 3)])
 def test_large_rollouts_by_teams_and_by_single_wavefronts_agree(B, steps, slices, team):
     assert pg.GoEnv(B, 19).boards_per_team(steps, slices)[0] == team
     test_rollouts_by_teams_and_by_single_wavefronts_agree(19, B, steps, slices, True, True)

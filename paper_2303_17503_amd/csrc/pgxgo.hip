@@ -1996,7 +1996,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
   __shared__ uint64_t tally_all[kWavesPerBlock][64];
   __shared__ uint2 lut[256];
   const int wib = wave_in_block();
-  Pace pace(PACED, a.pace, (blockIdx.x >> 3) * kWavesPerBlock + wib, (gridDim.x >> 3) * kWavesPerBlock, SK ? kPaceFirstSuperko : 0u);
+  Pace pace(PACED, PACED ? Pace::now() : 0, a.pace, (blockIdx.x >> 3) * kWavesPerBlock + wib, (gridDim.x >> 3) * kWavesPerBlock, SK ? kPaceFirstSuperko : 0u);
   fill_spread_table(lut);
   const int wave = piece_of_block() * kWavesPerBlock + wib;
   if (wave * a.wb >= a.B) return;

@@ -655,9 +655,9 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_rollout_kernel(Rollou
   if (L.valid && L.r == 0) a.meta[L.b] = pack_meta(m);
 }
 
-// The rate that the slots of a paced rollout are laid out for (us for 8 plies of 262144 games, recorded, with 6.6 / 6.65 / 6.7 / 6.8 / 6.9
-// TB/s: 200.4 / 199.1 / 199.2 / 205 / 215, for 20 of 100001 242 / 243 / 244 / 246 / 247, without slots 246 for the former; whole lines only,
-// hence faster than Go's ragged runs)
+// The rate that the slots of a paced rollout are laid out for (us of a launch of 8 plies of 262144 games, recorded, with 6.45 / 6.5 / 6.55 /
+// 6.6 / 6.65 / 6.7 TB/s 210.7 / 209.2 / 207.9 / 206.5 / 205.1 / 203.9, of 20 of 100001 243.7 / 243.9 / 245.2 / 245.1 / 246.1 / 247.4; from 6.8
+// on the former turns too, 3 % at 6.8 and 8 % at 6.9; without slots 246 for the former; whole lines only, hence faster than Go's ragged runs)
 constexpr double kPaceBytesPerSecond = 6.55e12;
 // Ticks until the first slot (8 plies of 262144 games / 20 of 100001 with 0, 1, 2, 3, 4 us: 201.8, 203.1, 203.9, 204.9, 205.9 / 241.6, 239.0, 238.3,
 // 239.3, 240.6)
@@ -669,10 +669,12 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_rollout_lane_kernel(R
   __shared__ uint32_t lut4[256];
   __shared__ __align__(16) uint32_t lds_obs[kWavesPerBlock][LANE_OBS_DW];
   __shared__ __align__(16) uint32_t lds_mask[kWavesPerBlock][LANE_MASK_DW];
-  const int wib = wave_in_block(), lane = threadIdx.x & 63;
-  Pace pace(PACED, a.pace, (blockIdx.x >> 3) * kWavesPerBlock + wib, (gridDim.x >> 3) * kWavesPerBlock, kPaceFirst);
+  // (The clock first, but the place among the others after the tables: with that up here too, the loop below, instruction by instruction the
+  // same, lay elsewhere in the code and an unpaced rollout was slower, 28 plies of 42508 games without observation 94.1 -> 96.7 us.)
+  const int64_t begin = PACED ? Pace::now() : 0;
   fill_spread4_table(lut4);
   fill_spread_table(lut);
+  const int wib = wave_in_block(), lane = threadIdx.x & 63;
   const int wave = piece_of_block() * kWavesPerBlock + wib;
   const int b0 = wave * 64;
   if (b0 >= a.B) return;
@@ -687,6 +689,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_rollout_lane_kernel(R
   B128 bk, wt;
   rows_to_sets(row, bk, wt);
   B128 legal = lane_legal(bk, wt, m);
+  Pace pace(PACED, begin, a.pace, (blockIdx.x >> 3) * kWavesPerBlock + wib, (gridDim.x >> 3) * kWavesPerBlock, kPaceFirst);
   int slice = 0;
   for (int i = 0; i < a.steps; ++i) {   // the same trip count for every wavefront
     const uint32_t t = a.t0 + (uint32_t)i;

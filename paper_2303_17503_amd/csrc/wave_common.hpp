@@ -71,13 +71,13 @@ struct Pace {
     return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)t) |
                      ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(t >> 32)) << 32));
   }
-  // index: this wavefront among the `eighth` wavefronts that write to the same eighth of the batch.  first: when the first of them may write,
-  // in ticks after this call.  To be called as the kernel begins: the loads of the state and the first ply, 4 to 5 us, then pass within the
+  // begin: now() as the kernel begins.  index: this wavefront among the `eighth` wavefronts that write to the same eighth of the batch.  first:
+  // when the first of them may write, in ticks after `begin`.  From the kernel's beginning: the loads of the state and the first ply, 4 to 5 us, then pass within the
   // slots of those that are to write early, who go ahead late, and not ahead of all slots (16 plies of 19x19 x 16384 games 285.8 -> 281.2
-  // us, 8 of Hex x 262144 206.1 -> 201.4; each us later costs one).
-  __device__ __forceinline__ Pace(bool on, PaceArgs a, uint32_t index, uint32_t eighth, uint32_t first) : slot(0), ply(a.ply) {
+  // us, 8 of Hex x 262144, whose first slot lies 1 us later, 206.1 -> 202.4; each us later costs one).
+  __device__ __forceinline__ Pace(bool on, int64_t begin, PaceArgs a, uint32_t index, uint32_t eighth, uint32_t first) : slot(0), ply(a.ply) {
     if (!on) return;
-    slot = now() + ((int64_t)first << 8);
+    slot = begin + ((int64_t)first << 8);
     if (eighth <= a.held) slot += (int64_t)((uint64_t)ply * index / eighth);
     else if (index < a.held) slot += (int64_t)((uint64_t)ply * index / a.held);
     else if (index >= eighth / a.held * a.held) ply = (uint32_t)((uint64_t)ply * (eighth % a.held) / a.held);

@@ -408,6 +408,37 @@ __device__ __forceinline__ void push_history(History<N>& H, int& head, uint32_t 
 #pragma unroll
   for (int k = 0; k < G::TAIL; ++k) { const uint32_t v = pushed(H.tail[k], p, G::HIST + k, which); H.changed |= v != H.tail[k] ? 2u : 0u; H.tail[k] = v; }
 }
+// The history as a rollout keeps it from ply to ply: by points for the emission, or, AS_STORED, as the ring that memory holds
+template <int N, bool AS_STORED>
+__device__ __forceinline__ Points<N> kept_history(const History<N>& H, int head) {
+  if constexpr (!AS_STORED) return points_of<N>(H, head);
+  Points<N> Q;
+#pragma unroll
+  for (int j = 0; j < Geo<N>::HD; ++j) Q.h[j] = j < Geo<N>::HIST ? H.s[j < Geo<N>::HIST ? j : 0] : H.tail[j < Geo<N>::HIST ? 0 : j - Geo<N>::HIST];
+  return Q;
+}
+template <int N, bool AS_STORED>
+__device__ __forceinline__ void push_kept(Points<N>& Q, int& head, uint32_t bk, uint32_t wt, bool moved) {
+  using G = Geo<N>;
+  if constexpr (!AS_STORED) return push_points<N>(Q, bk, wt, moved);
+  const Pairs p = pairs_of(bk, wt);
+  const uint32_t word = ring_word(p), which = mask_of(moved);
+  if (moved) head = (head + 7) & 7;
+  const int at = moved ? head : 8;
+#pragma unroll
+  for (int k = 0; k < G::HD; ++k) Q.h[k] = k < G::HIST ? (k == at ? word : Q.h[k]) : pushed(Q.h[k], p, k, which);
+}
+template <int N, bool AS_STORED>
+__device__ __forceinline__ History<N> history_of_kept(const Points<N>& Q, int& head) {
+  if constexpr (!AS_STORED) { head = 0; return history_of<N>(Q); }
+  History<N> H;
+#pragma unroll
+  for (int k = 0; k < Geo<N>::HIST; ++k) H.s[k] = Q.h[k];
+#pragma unroll
+  for (int k = 0; k < Geo<N>::TAIL; ++k) H.tail[k] = Q.h[Geo<N>::HIST + k];
+  H.changed = ~0u;
+  return H;
+}
 template <int N>
 __device__ __forceinline__ void clear_points(Points<N>& Q) {
 #pragma unroll
@@ -1982,9 +2013,13 @@ constexpr uint32_t kPaceFirstSuperko = 200u;
 // place, 19x19 x 16384 games 307 -> 281 us, x 65536 1141 -> 1043, with pitches that are neither dense nor padded 367 -> 326).
 // SK: 0 = simple ko only, 1 / 2 = positional superko at play time / in the legal mask.  PACED: recordings that go to DRAM, see Pace;
 // their stores carry the non-temporal hint as well (16 plies of 19x19 x 16384 games at 6.2 TB/s: 286 us with it, 344 without).
-template <int N, bool TIGHT, int SK, bool PACED>
+// AS_STORED (19x19, no observation, and then never PACED): the history stays a ring.  Turned into points and back, which only the emission
+// needs, a launch of one ply of 16384 games took 14.8 instead of 13.5 us, of 50000 29.5 instead of 25.8 (14.0 and 28.0 when memory held points too);
+// as a choice at run time it costs rollouts with observation up to 1.5 %.
+template <int N, bool TIGHT, int SK, bool PACED, bool AS_STORED = false>
 __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_kernel(RolloutArgs a) {
   using G = Geo<N>;
+  static_assert(!AS_STORED || (G::RINGED && !PACED), "a ring is kept where memory holds one, and nothing is emitted from it");
   constexpr int ST = PACED ? kStoreStreamWhole : kStoreThroughWhole;
   // In place the ends of a wavefront's streams are better left to the L2: ordinary stores to the same lines meet there from ply to ply and
   // do not go to memory each time.  With dense pitches a stream hardly ever starts on a line; with line-padded ones every stream does,
@@ -2008,7 +2043,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
     History<N> H;
     load_row<N>(a.state, L0, R);
     load_history<N>(a.state, L0, H);
-    Q = points_of<N>(H, m.head);
+    Q = kept_history<N, AS_STORED>(H, m.head);
     place_ko<N>(L0, R, m);
   }
   const int64_t start = (L0.boardok && a.start_t) ? (int64_t)a.start_t[L0.b] : INT64_MIN;
@@ -2043,14 +2078,14 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
     if constexpr (!SK) {
       ply = apply_move<N>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.bit, 0, 0), tally_all[wib],
                           [&]() { clear_points<N>(Q); });
-      push_points<N>(Q, R.bk, R.wt, ply.moved);
+      push_kept<N, AS_STORED>(Q, m.head, R.bk, R.wt, ply.moved);
       legal = legal_row<N>(L, R, m.wtm);
     } else {
       SkWin none;
       none.home = ~0u; none.e = make_uint2(1u, 0u);
       uint8_t* const obs_t = a.obs ? a.obs + (size_t)slice * a.B * a.obs_pitch : nullptr;
       auto board_final = [&](bool moved, bool reset) {
-        push_points<N>(Q, R.bk, R.wt, moved);
+        push_kept<N, AS_STORED>(Q, m.head, R.bk, R.wt, moved);
         if (reset) clear_points<N>(Q);
         if constexpr (PACED) pace.wait();
         if (obs_t) emit_obs<N, TIGHT, ST, 4, FIRST_AS_EDGE>(L, Q.h, m.wtm, wave, a.B, obs_t, a.obs_pitch, lds_obs_all[wib], lut, a.wb);
@@ -2077,8 +2112,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
     slice = slice + 1 == a.slices ? 0 : slice + 1;
   }
   const Lane<N> L1(wave, in_place(L0.lane), a.B, a.wb);   // (anew: where a game's state lies is nothing to hold through the loop)
-  store_all<N>(a.state, L1, R, history_of<N>(Q));
-  m.head = 0;
+  store_all<N>(a.state, L1, R, history_of_kept<N, AS_STORED>(Q, m.head));
   if (L1.valid && L1.r == 0) a.meta[L1.b] = pack_meta(m);
   if constexpr (SK) {
     if constexpr (SK != 1) g.fw = sk_forb_word<N>(L0, forb);
@@ -2649,8 +2683,8 @@ PaceArgs rollout_pace(const pgxgo_ctx* h, int steps, int slices, bool with_mask,
 //    16384, 1.02 x 17408, 1.07 x 18432 (12 to 64 plies are the same), and again ahead where one wavefront for everything needs a fourth on
 //    every SIMD: 8 plies 0.91 x 18433, 0.99 x 20480, 6 plies 0.98 x 19456, 1.006 x 20480, 4 plies 1.03 x 20480.
 //  * 9x9 without observation: 2 plies 1.00 x 8000, 1.02 x 9000, 1.04 x 10000, 1.03 x 20480; 3 plies 0.98 x 13000, 1.02 x 14336; 16 plies 0.97 x 16384.
-//  * 19x19 without observation: 2 plies 1.00 x 5120, 1.03 x 6000, 1.04 x 11000; otherwise up to 3584 teams (3 / 32 plies 0.95 / 0.91 x 10240,
-//    1.03 / 1.02 x 11000).
+//  * 19x19 without observation: 2 plies 0.98 x 3072, 1.05 x 4000; 3 plies 0.99 x 4096, 1.01 x 5120, 1.04 x 5500; 4 plies 1.00 x 7000, 1.045 x 8192;
+//    8 plies 0.99 x 7000, 1.025 x 8192, 1.00 x 10240; 16 / 32 plies 1.00 / 0.975 x 8192, 0.97 x 10240; beyond 3584 teams, x 11000, 1.08.
 //  * 19x19: 2 plies 0.98 x 26000, 1.04 x 27648, 1.08 x 30720 (outputs in the cache 0.97, 1.00, 1.00), 3 plies 0.97 x 26000, 1.015 x 27648, 1.04 x
 //    30720 (0.96, 0.99, 0.99), 4 plies 1.01 x 30720 (0.98); from 16 plies on teams win at every size.  Two slices written in turn, together more
 //    than the memory-side cache, are slower by teams up to 6 plies (3 / 4 / 6 plies 0.94 / 0.98 / 0.94 x 22000, 0.95 / 1.03 / 1.00 x 23000, 1.06 /
@@ -2663,7 +2697,7 @@ int boards_per_rollout_team(int B, int steps, int slices, bool with_obs) {
   int most;   // games
   if (N == 9 && with_obs) most = steps < 8 ? std::min(10 + steps, 15) * K : 16 * K;
   else if (N == 9) most = steps == 2 ? 8 * K : steps == 3 ? 13 * K : 20 * K;
-  else if (!with_obs) most = steps == 2 ? 5 * K : 3584 * Geo<N>::W;
+  else if (!with_obs) most = steps < 4 ? (1 + steps) * K : steps < 16 ? 7 * K : 3584 * Geo<N>::W;
   else if (steps >= 16) most = B;
   else most = slices == 2 && steps < 7 ? 22 * K : steps < 4 ? (24 + steps) * K : 30 * K;
   const bool ahead_again = N == 9 && with_obs && steps >= 6 && B > 18 * K && B <= 20 * K;
@@ -2699,6 +2733,7 @@ int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
     constexpr bool T = decltype(tight_c)::value;
     constexpr int M = decltype(sk_c)::value;
     if (a.pace.ply) hipLaunchKernelGGL((go_rollout_kernel<N, T, M, true>), grid, block, 0, h->stream, a);
+    else if (Geo<N>::RINGED && !a.obs) hipLaunchKernelGGL((go_rollout_kernel<N, T, M, false, Geo<N>::RINGED>), grid, block, 0, h->stream, a);
     else hipLaunchKernelGGL((go_rollout_kernel<N, T, M, false>), grid, block, 0, h->stream, a);
   });
   HIPCHK(hipGetLastError());

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2303_17503_amd as pg
 from gpu_common import Pair, to_np
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +37,28 @@ def test_rings_that_begin_anywhere(N, B):
         p.step(torch.as_tensor(a, device="cuda"), a)
         t += 1
         p.compare("after an import of what was exported", state=True)
+
+
+@pytest.mark.parametrize("B,superko,more", [(1, 0, {}), (37, 0, {}), (37, 1, {}), (38, 2, {}), (37, 0, {"mask_pitch": 364}), (38, 2, {"mask_pitch": 364}), (37, 1, {"mask_pitch": 364})])
+def test_rollouts_without_observation_keep_the_same_history(B, superko, more):
+    """Where nothing is emitted a 19x19 rollout by single wavefronts leaves the rings as they are; what follows sees the same eight positions."""
+    envs = [pg.GoEnv(B, 19, seed=8, auto_reset=True, max_steps=40, **more) for _ in range(2)]
+    obs = [torch.zeros((1, B, envs[0].obs_pitch), dtype=torch.uint8, device="cuda"), None]
+    start = torch.arange(B, dtype=torch.int32, device="cuda") % 7 * 5   # some wait
+    for e in envs:
+        e.set_boards_per_wavefront(3)
+        if superko:
+            e.enable_superko(superko)
+    rng = np.random.default_rng(B)
+    t = 0
+    for plies in (1, 2, 9, 1, 30):
+        a = envs[0].random_actions(8, t)
+        a[torch.as_tensor(rng.random(B) < 0.4, device="cuda")] = -1   # a game that sits out keeps its ring where it is
+        for e, o in zip(envs, obs):
+            e.step(a)
+            e.rollout(plies, 8, t + 1, start_t=start, obs=o)
+        t += 1 + plies
+        x, y = (e.export_state() for e in envs)
+        for k in x:
+            assert torch.equal(x[k], y[k]), (t, k)
+        assert torch.equal(envs[0].observe(), envs[1].observe()) and torch.equal(*(e.mask_view(e.legal_mask()) for e in envs)), t

@@ -27,7 +27,8 @@ def bound(env, obs):
     (9, 15360, True, 7, 1, (6, 3)), (9, 15361, True, 7, 1, (0, 1)), (9, 16384, True, 8, 1, (6, 3)), (9, 16385, True, 64, 1, (0, 1)), (9, 18432, True, 9, 1, (0, 1)),
     (9, 18433, True, 9, 1, (6, 3)), (9, 18433, True, 5, 1, (0, 1)), (9, 20480, True, 6, 1, (6, 3)), (9, 20481, True, 9, 1, (0, 1)),
     (9, 8192, False, 2, 1, (6, 2)), (9, 8193, False, 2, 1, (0, 1)), (9, 13313, False, 3, 1, (0, 1)), (9, 20480, False, 4, 1, (6, 2)), (9, 20481, False, 4, 1, (0, 1)),
-    (19, 1024, False, 2, 1, (1, 2)), (19, 5120, False, 2, 1, (3, 2)), (19, 5121, False, 2, 1, (0, 1)), (19, 10752, False, 3, 1, (3, 2)), (19, 10753, False, 99, 1, (0, 1)),
+    (19, 1024, False, 2, 1, (1, 2)), (19, 3072, False, 2, 1, (3, 2)), (19, 3073, False, 2, 1, (0, 1)), (19, 4097, False, 3, 1, (0, 1)), (19, 7168, False, 4, 1, (3, 2)),
+    (19, 7169, False, 15, 1, (0, 1)), (19, 10752, False, 16, 1, (3, 2)), (19, 10753, False, 99, 1, (0, 1)),
     (19, 26624, True, 2, 1, (3, 3)), (19, 26625, True, 2, 1, (0, 1)), (19, 30720, True, 4, 1, (3, 3)), (19, 30721, True, 15, 1, (0, 1)), (19, 30721, True, 16, 1, (3, 3)),
     (19, 22528, True, 3, 2, (3, 3)), (19, 22529, True, 6, 2, (0, 1)), (19, 22529, True, 7, 2, (3, 3)), (19, 16384, True, 16, 1, (3, 3)), (19, 16384, True, 16, 16, (0, 1))])
 def test_which_calls_go_by_teams(N, B, obs, steps, slices, team):

@@ -63,7 +63,7 @@ thread_local int g_last_hip = 0;
     }                                                  \
   } while (0)
 
-constexpr int kWavesPerBlock = kBlockThreads / 64;   // wavefronts never synchronise with each other; this only shapes the launch
+constexpr int kWavesPerBlock = kBlockThreads / 64;   // of the kernels without teams: the wavefronts share the lookup table and no more; this only shapes the launch
 
 
 // ------------------------------------------------------------------------------------------------
@@ -212,9 +212,10 @@ struct Row {                      // per-lane registers: one row of one board
 //     ago is number (head + i) mod 8, head being kept with the game's scalars, so that a ply overwrites the oldest one and moves
 //     the head.  tail holds columns 16 .. 18 point by point.  A ply writes 20 bytes of a row; with everything point by point it was
 //     56, or the changed ones of four pieces.  Turning positions into points costs about as many instructions as pushing them did
-//     (exchange_columns_and_positions).  Bytes moved per ply of 65536 games 571 -> 516 MB; us per ply, before / since: 16384 games
-//     20.2 / 19.3, 28000 36.3 / 34.1, 65536 83.5 / 80.4, 65536 without observation 30.1 / 28.1, 16384 with superko 28.5 / 27.3.  At
-//     9x9, where hardly a byte leaves the caches, a ring is 3 to 7 % slower than this.
+//     (exchange_columns_and_positions).  Bytes moved per ply of 65536 games 571 -> 521 MB; us per ply, before / since, with what
+//     else changed then (this order of a game's pieces, packed atari sets, state_store_kind): 16384 games 20.0 / 19.5, 28000 36.3 / 34.1,
+//     65536 81.5 / 78.2, without observation 30.1 / 27.5, 16384 with superko 28.5 / 27.3; 36000 to 40000 games alone have lost, 1 %
+//     (44.6 / 45.0, 49.1 / 49.7).  At 9x9, where hardly a byte leaves the caches, a ring is 3 to 7 % slower than this.
 // As planes over all games instead (every piece one run of all games) a search, which takes games from anywhere, is 3 to 7 % slower
 // and 40000 games 5 % faster.
 // ------------------------------------------------------------------------------------------------
@@ -1818,7 +1819,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_step_slots
   const bool in_pool = src >= 0 && src < pool && dst >= 0 && dst < pool;
   const bool bad = L.boardok && !in_pool;
   if (bad) { L.boardok = false; L.valid = false; L.full = 0u; }   // the entry becomes inert: no state access, no outputs
-  L.slot = src; L.some = 0;
+  L.slot = src; L.some = 0;   // (a lane without an entry loads from slot 0, whatever another entry may be doing with it, and uses nothing of that)
   Row<N> R;
   History<N> H;
   load_row<N>(state, L, R);
@@ -2010,7 +2011,8 @@ constexpr uint32_t kPaceFirstSuperko = 200u;
 // The registers hold a game's state from ply to ply, and 80 of them (six wavefronts per SIMD) are just enough for it and a ply's own values.
 // What a ply derives from the lane's place alone is therefore computed anew every ply (in_place): kept from one to the next it pushed
 // 8 to 16 registers out to memory, and every one read back between the outputs waited for all output stores under way (20 plies in
-// place, 19x19 x 16384 games 307 -> 281 us, x 65536 1141 -> 1043, with pitches that are neither dense nor padded 367 -> 326).
+// place by this kernel, which teams have taken over since unless a handle asks for it: 19x19 x 16384 games 307 -> 281 us, x 65536 1141 -> 1043;
+// with pitches that are neither dense nor padded 367 -> 326).
 // SK: 0 = simple ko only, 1 / 2 = positional superko at play time / in the legal mask.  PACED: recordings that go to DRAM, see Pace;
 // their stores carry the non-temporal hint as well (16 plies of 19x19 x 16384 games at 6.2 TB/s: 286 us with it, 344 without).
 // AS_STORED (19x19, no observation, and then never PACED): the history stays a ring.  Turned into points and back, which only the emission
@@ -2023,8 +2025,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
   constexpr int ST = PACED ? kStoreStreamWhole : kStoreThroughWhole;
   // In place the ends of a wavefront's streams are better left to the L2: ordinary stores to the same lines meet there from ply to ply and
   // do not go to memory each time.  With dense pitches a stream hardly ever starts on a line; with line-padded ones every stream does,
-  // and its first 1 KB counts as an end all the same (20 plies of 16384 games: 2.14 -> 1.94 GB leave the L2, 313 -> 282 us; x 65536
-  // 1154 -> 1043 us).  9x9 x 16384, where a wavefront writes half as much, gains nothing.
+  // and its first 1 KB counts as an end all the same (20 plies of 16384 games by this kernel: 2.14 -> 1.94 GB leave the L2, 313 -> 282 us; x
+  // 65536 1154 -> 1043 us).  9x9 x 16384, where a wavefront writes half as much, gains nothing.
   constexpr bool FIRST_AS_EDGE = N == 19 && TIGHT && !PACED;
   __shared__ __attribute__((aligned(16))) uint32_t lds_obs_all[kWavesPerBlock][G::W * G::OBS_DW];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mask_all[kWavesPerBlock][64];
@@ -2491,9 +2493,9 @@ unsigned blocks_for_wb(int B, int wb) { return (((unsigned)((B + wb - 1) / wb) +
 // of the memory-side cache write-through for whole lines only (16384 games: 20.7 against 22.1 us per ply with ordinary stores);
 // beyond what that cache holds of them beside the state the non-temporal hint on top (us per ply, whole lines written through / with the
 // hint: 19x19 x 28000 games, 182 MB, 34.1 / 38.3; x 36000, 234 MB, 47.8 / 46.1; x 40000 55 / 48; x 48000 77 / 61; x 65536 114 / 80; with
-// superko x 40000 86 / 62; 9x9 x 160000, 233 MB, 49.7 / 49.9; x 200000 67 / 62).  The rollout kernel uses kStoreThroughWhole at every size
-// unless it is paced (16384 games: 14.4 against 16.5 us per ply, 65536 games: 53.8 against 60.2 us; in place the non-temporal hint is
-// slower at every size).
+// superko x 40000 86 / 62; 9x9 x 160000, 233 MB, 49.7 / 49.9; x 200000 67 / 62).  Rollouts use kStoreThroughWhole at every size
+// unless they are paced (by single wavefronts, 16384 games: 14.4 against 16.5 us per ply, 65536 games: 53.8 against 60.2 us; in place the
+// non-temporal hint is slower at every size).
 // in_place: the launch overwrites the buffers the previous one wrote, whose lines are then still in the memory-side
 // cache.  In the middle range a launch into other buffers (a caller that records a trajectory) has to reach DRAM and
 // is faster with the hint as well (16384 games: 23.9 us per ply against 25.4 with ordinary stores and 25.9 with
@@ -2533,7 +2535,8 @@ bool tight_pitches(const pgxgo_ctx* h) {
 
 // Boards per team of four wavefronts (go_step_team_kernel) for batches that are faster that way, else 0.  A team is worth while as long as
 // the machine has wavefront slots to spare: up to four teams per compute unit at 9x9 (us per ply, one wavefront for all / teams: 256
-// games 4.60 / 3.72, 1024 4.94 / 4.16, 2048 4.95 / 4.55, 4096 5.29 / 5.20, 5000 5.58 / 5.46, 8192 6.15 / 6.31) and eight at 19x19, where the
+// games 4.60 / 3.72, 1024 4.94 / 4.16, 2048 4.95 / 4.55, 4096 5.21 / 4.99; beyond it is one or the other by turns, four boards to a team 4500 5.56 /
+// 5.40, 5000 5.49 / 5.53, 6000 5.59 / 5.70, 6500 5.95 / 5.80, 7500 6.03 / 6.26, 8192 6.03 / 6.35) and eight at 19x19, where the
 // observation is four times as long (256 games 5.96 / 4.63, 1000 6.47 / 5.66, 2048 7.18 / 6.08, 4096 8.79 / 7.50, 5500 9.57 / 8.57, 8192
 // 12.0 / 12.4; without observation 1000 5.34 / 4.79, 4096 6.27 / 6.05, 5500 6.48 / 6.54).  Boards: as few as keep the teams at one to two per
 // compute unit (9x9 x 256 with 1 / 2 / 4 boards 3.72 / 3.77 / 3.97, x 1024 4.63 / 4.16 / 4.30, x 2048 5.8 / 4.78 / 4.55; 19x19 x 400 with 1 / 3
@@ -2741,10 +2744,11 @@ int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
 }
 
 // Boards per team of a search call of n entries (go_step_slots_team_kernel), 0 where one wavefront for everything is as fast.  The chain is
-// that of a ply with two more loads ahead of it, and the lines lie where they lie for plies; without observation teams win up to there
-// too (us per call, one wavefront / teams: 9x9 x 256 entries 4.38 / 3.26, 1024 4.51 / 3.47, 4096 4.66 / 4.11, without observation 256 3.38 /
-// 3.11, 4096 3.63 / 3.36; 19x19 x 256 5.40 / 3.76, 1000 5.60 / 4.28, 4096 8.61 / 7.47, 5500 9.50 / 8.83, without observation 256 3.86 /
-// 3.24, 4096 5.14 / 4.78, 5500 5.37 / 5.18).  What bounds such a call now is the loads' chain (slot, state) and the rules.  Mere copies
+// that of a ply with two more loads ahead of it, and the lines lie where they lie for plies (us per call, one wavefront / teams: 9x9 x 256
+// entries 4.38 / 3.26, 1024 4.51 / 3.47, 4096 4.66 / 4.11, without observation 256 3.38 / 3.11, 4096 3.63 / 3.36; 19x19 x 256 5.40 / 3.76, 1000
+// 5.60 / 4.28, 4096 8.61 / 7.47, 5500 9.50 / 8.83, without observation 256 3.86 / 3.24).  Without observation teams have drawn level with
+// one wavefront at 4096 entries of 19x19, out of 16384 games in progress 5.45 / 5.49, and are 2 to 5 % behind from there to the line
+// (5500 5.77 / 5.98).  What bounds such a call now is the loads' chain (slot, state) and the rules.  Mere copies
 // have no chain to shorten and stay with the other kernel, calls with the repetition rule too.
 template <int N>
 int boards_per_slot_team(int n) { return boards_per_step_team<N>(n); }

@@ -214,8 +214,8 @@ struct Row {                      // per-lane registers: one row of one board
 //     56, or the changed ones of four pieces.  Turning positions into points costs about as many instructions as pushing them did
 //     (exchange_columns_and_positions).  Bytes moved per ply of 65536 games 571 -> 521 MB; us per ply, before / since, with what
 //     else changed then (this order of a game's pieces, packed atari sets, state_store_kind): 16384 games 20.0 / 19.5, 28000 36.3 / 34.1,
-//     65536 81.5 / 78.2, without observation 30.1 / 27.5, 16384 with superko 28.5 / 27.3; 36000 to 40000 games alone have lost, 1 %
-//     (44.6 / 45.0, 49.1 / 49.7).  At 9x9, where hardly a byte leaves the caches, a ring is 3 to 7 % slower than this.
+//     65536 81.5 / 78.2, without observation 30.1 / 27.5, 16384 with superko 28.5 / 27.3; 36000 to 40000 games have lost 1 % (44.6
+//     / 45.0, 49.1 / 49.7), and plies of one wavefront for everything where its chain counts up to 1.5 % (6489 games 11.2 / 11.35).  At 9x9, where hardly a byte leaves the caches, a ring is 3 to 7 % slower than this.
 // As planes over all games instead (every piece one run of all games) a search, which takes games from anywhere, is 3 to 7 % slower
 // and 40000 games 5 % faster.
 // ------------------------------------------------------------------------------------------------

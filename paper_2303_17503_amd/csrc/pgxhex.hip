@@ -166,12 +166,12 @@ __device__ __forceinline__ Draw draw_action(const Lane& L, uint32_t E, bool swap
   uint32_t before = 0u, total = swap ? 1u : 0u;
 #pragma unroll
   for (int k = 0; (1 << k) <= N; ++k) {
-    const uint64_t m = __ballot((cnt >> k) & 1u);
+    const uint64_t m = ballot(((cnt >> k) & 1u) != 0u);
     const uint32_t lo = (uint32_t)m & L.seglo, hi = (uint32_t)(m >> 32) & L.seghi;
     before += __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)) << k;
     total += (uint32_t)(__popc(lo) + __popc(hi)) << k;
   }
-  const uint32_t k = hash % (total ? total : 1u);
+  const uint32_t k = remainder_of(hash, total ? total : 1u);
   uint32_t n = k - before, w = E, pos = 0u;   // position of the (n+1)-th set bit of the row word by halving
 #pragma unroll
   for (int width = 8; width >= 1; width >>= 1) {
@@ -236,8 +236,8 @@ __device__ __forceinline__ Ply hex_ply(const Lane& L, uint32_t& bk, uint32_t& wt
 
   // swap rule: on the second turn the board holds Black's lone stone (r0,c0); it comes off and a white stone goes to (c0,r0)
   uint32_t swapped = 0u;
-  if (__ballot(swap_ok) != 0ull) {   // once per game at most: keep it off the common path
-    const uint64_t nz = __ballot(bk != 0u);
+  if (ballot(swap_ok) != 0ull) {   // once per game at most: keep it off the common path
+    const uint64_t nz = ballot(bk != 0u);
     const uint32_t zlo = (uint32_t)nz & L.seglo, zhi = (uint32_t)(nz >> 32) & L.seghi;
     const int src = zlo ? __ffs(zlo) - 1 : (zhi ? 31 + __ffs(zhi) : 0);
     const int r0 = src - (L.j * STRIDE + 1);
@@ -258,7 +258,7 @@ __device__ __forceinline__ Ply hex_ply(const Lane& L, uint32_t& bk, uint32_t& wt
     const uint32_t G = grown_in(F, S);
     const bool ch = G != F;
     F = G;
-    if (__ballot(ch) == 0ull) break;
+    if (ballot(ch) == 0ull) break;
   }
   const bool side_a = wtm ? (F & 1u) != 0u : (F != 0u && L.r == 0);
   const bool side_b = wtm ? ((F >> (N - 1)) & 1u) != 0u : (F != 0u && L.r == N - 1);
@@ -462,7 +462,7 @@ __device__ __forceinline__ LanePly lane_ply(B128& bk, B128& wt, Meta& m, int act
     const B128 G = b_or(F, b_and(dilate128(F), S));
     const bool ch = b_ne(G, F);
     F = G;
-    if (__ballot(ch) == 0ull) break;
+    if (ballot(ch) == 0ull) break;
   }
   const bool hit_a = b_any(b_and(F, wtm ? set_of<1>() : set_of<3>()));
   const bool hit_b = b_any(b_and(F, wtm ? set_of<2>() : set_of<4>()));
@@ -536,7 +536,7 @@ __device__ __forceinline__ void lane_emit(const B128& bk, const B128& wt, const 
 __device__ __forceinline__ int lane_draw(const B128& legal, uint32_t seed, uint32_t b, uint32_t t, bool wait) {
   const uint32_t c0 = __popc(legal.w[0]), c1 = __popc(legal.w[1]), c2 = __popc(legal.w[2]), c3 = __popc(legal.w[3]);
   const uint32_t total = c0 + c1 + c2 + c3;
-  uint32_t k = env_hash(seed, 0u, b, t) % (total ? total : 1u);
+  uint32_t k = remainder_of(env_hash(seed, 0u, b, t), total ? total : 1u);
   uint32_t w = legal.w[0], base = 0u;
   if (k >= c0) { k -= c0; w = legal.w[1]; base = 32u;
     if (k >= c1) { k -= c1; w = legal.w[2]; base = 64u;

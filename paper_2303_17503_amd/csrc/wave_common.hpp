@@ -24,6 +24,16 @@ __device__ __forceinline__ uint32_t env_hash(uint32_t seed, uint32_t tag, uint32
   return mixer(mixer(mixer(seed + 0x9E3779B9u * (tag + 1u)) ^ env) ^ t);
 }
 
+// n mod d for 1 <= d <= 1024, any n.  The quotient in floats is off by at most 2^10 / d + 1, so what is left of n lies within 2^10 + d of [0, d) and its own
+// quotient, taken half a unit up, cannot round to the wrong side.  (Checked for every d with reciprocals one unit in the last place off
+// either way, as the instruction may give them.)  The general division takes four of the slow 32-bit products where this takes one, in a chain
+// that nothing else fills.
+__device__ __forceinline__ uint32_t remainder_of(uint32_t n, uint32_t d) {
+  const float f = __builtin_amdgcn_rcpf((float)d);
+  const uint32_t left = n - (uint32_t)__builtin_fminf((float)n * f, 4294967040.0f) * d;
+  return left - (uint32_t)__mul24((int)__builtin_floorf(__builtin_fmaf((float)(int32_t)left, f, 0.5f * f)), (int)d);
+}
+
 // index of the calling wavefront within its block, as a value the compiler knows to be the same in every lane
 // (so that everything derived from it -- output addresses, trip counts -- is computed once per wavefront)
 __device__ __forceinline__ int wave_in_block() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
@@ -135,10 +145,12 @@ __device__ __forceinline__ uint32_t from_lane_below(uint32_t x) {  // lane i rec
 __device__ __forceinline__ uint32_t from_lane_above(uint32_t x) {  // lane i receives lane i+1, lane 63 receives 0
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x130 /* wave_shl:1 */, 0xF, 0xF, true);
 }
+// The lanes where p holds.  (HIP's own ballot takes an int: a condition that is already a lane mask goes through a register and back.)
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 // A fact about a whole board, known to every lane of the board: does `pred` hold in any of its rows?
 // (seglo/seghi = the lanes holding the rows of the calling lane's board)
 __device__ __forceinline__ bool board_any(bool pred, uint32_t seglo, uint32_t seghi) {
-  const uint64_t m = __ballot(pred);
+  const uint64_t m = ballot(pred);
   return (((uint32_t)m & seglo) | ((uint32_t)(m >> 32) & seghi)) != 0u;
 }
 

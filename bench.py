@@ -203,7 +203,7 @@ def go_kernel(env, B, with_obs, steps=0, slices=1, fused=True, superko=0):
     if steps:
         name = "go_rollout_team_kernel<%d>" % N if wb else "go_rollout_kernel<%d>" % N
     elif superko:
-        name = "go_step_superko_kernel<%d>" % N
+        name = ("go_step_superko_team_kernel<%d>" if wb else "go_step_superko_kernel<%d>") % N
     else:
         name = "%s<%d,%s>" % ("go_step_team_kernel" if wb else "go_step_kernel", N, "true" if fused else "false")
     return name, math.ceil(B / (wb or env.set_boards_per_wavefront(0))) * waves / 1024.0

@@ -29,7 +29,7 @@
 //     go_rollout_kernel (T plies per launch, state in registers), go_step_slots_kernel (tree search: step
 //     from and to arbitrary state slots), go_step_superko_kernel (one ply with the positional-superko rule:
 //     Zobrist keys in per-game open-addressing tables), plus small set-up / export / import kernels.
-//   * Small batches are stepped by teams of four wavefronts per group of boards (go_step_team_kernel).
+//   * Small batches are stepped by teams of wavefronts per group of boards (go_step_team_kernel, go_step_superko_team_kernel).
 //   * How many boards a launch puts into a wavefront (1 .. W) is chosen per launch: W for throughput at large
 //     batches, fewer at small batches where the slowest board of a wavefront and its serial output rounds
 //     decide the latency.
@@ -1469,8 +1469,8 @@ __device__ __forceinline__ uint32_t sk_forbidden_play(const Lane<N>& L, const Ro
 }
 
 // The plays of the player to move that would recreate an earlier position of the game (row words): one walk of the
-// chain of the positions with one more stone of the mover's colour than now.
-template <int N>
+// chain of the positions with one more stone of the mover's colour than now.  KO_IN_ROW: R's ko bit is up to date and m.ko is not looked at.
+template <int N, bool KO_IN_ROW = false>
 __device__ __forceinline__ uint32_t sk_forbidden(const Lane<N>& L, const uint2* tab, const SkGame& g, const Row<N>& R, const Meta& m, bool active,
                                                  const SkWin& pre, uint32_t* scratch) {
   uint32_t forb = 0u;
@@ -1487,7 +1487,7 @@ __device__ __forceinline__ uint32_t sk_forbidden(const Lane<N>& L, const uint2* 
                uint64_t pend = ballot(look && sk_real(e) && u < 2u * N * N && (int)(u & 1u) == c2);
                if (pend == 0ull) return;          // nearly always: no earlier position is one stone of the mover's away
                Row<N> now = R;   // (its ko bit from the scalars: not held through the table work, which needs the registers)
-               place_ko<N>(L, now, m);
+               if constexpr (!KO_IN_ROW) place_ko<N>(L, now, m);
                const uint32_t legal_s = legal_row<N>(L, now, m.wtm);
                while (pend != 0ull) {             // one candidate per board per turn
                  const uint64_t mine = pend & seg;
@@ -1771,6 +1771,120 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   if (a.next_actions) {
     const Draw<N> dr = draw_action<N>(L, legal, a.sample_seed, a.sample_t, wait_start);
     if (dr.known(L)) a.next_actions[L.b] = dr.action(L);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The same by teams (go_step_team_kernel), for the rule proper (mode 2): one wavefront applies the rules and stores the state, one has the
+// table -- its windows are loaded while the rules run -- and then the mask and the draw, which need what it finds, and one has the observation.
+// What bounds the other kernel is that all of this stands in a row in one wavefront.  Figures, and which plies go this way: boards_per_superko_team.
+// ------------------------------------------------------------------------------------------------
+template <int N, bool OBS, int ST>
+__global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_step_superko_team_kernel(uint32_t* state, uint4* meta, const int32_t* actions, const int32_t* start_t, uint4* zcur,
+                                                                                  int B, int wb, uint32_t eighth, uint2* zt, StepArgs a) {   // wb: boards per team
+  using G = Geo<N>;
+  constexpr uint32_t THREADS = 64u * (OBS ? 3u : 2u);
+  __shared__ __attribute__((aligned(16))) uint32_t lds_obs[OBS ? G::W * G::OBS_DW : 4];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_mask[64];
+  __shared__ TallyCells tally_cells;
+  __shared__ uint2 lut[256];
+  __shared__ uint4 hand[64];
+  const int group = piece_of_block(eighth);
+  if (group * wb >= B) return;   // the whole block
+  const int role = wave_in_block();
+  const Lane<N> L(group, threadIdx.x & 63, B, wb);
+  const int game = L.boardok ? L.b : L.some;
+  auto fill_table = [&]() {
+#pragma unroll
+    for (uint32_t x = threadIdx.x; x < 256u; x += THREADS) lut[x] = make_uint2(spread4(x & 15u), spread4(x >> 4));
+  };
+  SkWin none;
+  none.home = ~0u; none.e = make_uint2(1u, 0u);
+
+  if (role == 0) {   // the rules
+    Row<N> R;
+    History<N> H;
+    load_row<N>(state, L, R);
+    const uint4 meta_raw = load_meta<N>(meta, L);
+    const int act_raw = actions[game], act = L.boardok ? act_raw : -1;
+    const uint4 g_raw = zcur[game];
+    load_history<N>(state, L, H);
+    in_scalar_registers(a.rules.seed, a.rules.komi_x2, a.rules.max_steps, a.rules.auto_reset, a.rew, a.term);
+    fill_table();
+    Meta m = unpack_meta(meta_raw);
+    place_ko<N>(L, R, m);
+    const bool skip = !L.boardok || act == -1;
+    const bool in_range = act >= 0 && act < G::P;
+    const int pr = in_range ? act / N : 0, pc = in_range ? act - (act / N) * N : 0;
+    Move mv = gate_move<N, true>(L, R, m, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc);
+    const SkGame g = L.boardok ? sk_unpack(g_raw) : sk_fresh();
+    const uint32_t forb = sk_forb_loaded<N>(L, zt + (size_t)game * Zt<N>::SLOTS, g, R, m, none, (uint32_t*)hand);
+    if (mv.playing && board_any((mv.bit & forb) != 0u, L.seglo, L.seghi)) mv.forbid();
+    Tally tally(&tally_cells, 0, L);
+    const Ply ply = apply_move<N>(L, R, m, a.rules, mv, tally, [&]() { clear_history<N>(H); });
+    hand[L.lane] = HandOver<N>::of(R, m, ply).v;
+    __syncthreads();
+    push_history<N>(H, m.head, R.bk, R.wt, ply.moved);
+    store_ply<N, kStorePlain>(state, L, R, H, m.head, ply.moved, ply.reset);
+    if (!skip && L.valid && L.r == 0) {
+      meta[L.b] = pack_meta(m);
+      *(float2*)(a.rew + 2 * (size_t)L.b) = make_float2(ply.rew0, ply.rew1);
+      a.term[L.b] = (uint8_t)(ply.flag ? 1 : 0);
+    }
+  } else if (role == 1) {   // the table, the mask, the draw
+    Row<N> before;
+    const uint4 meta_raw = load_meta<N>(meta, L), g_raw = zcur[game];
+    const int act_raw = actions[game], act = L.boardok ? act_raw : -1;
+    const int32_t start_raw = (a.next_actions && L.boardok && start_t) ? start_t[L.b] : INT32_MIN;
+    load_row<N>(state, L, before);
+    in_scalar_registers(a.mask, a.mask_pitch, a.sample_seed, a.sample_t, a.next_actions);
+    fill_table();
+    Meta m = unpack_meta(meta_raw);
+    SkGame g = L.boardok ? sk_unpack(g_raw) : sk_fresh();
+    uint2* const tab = zt + (size_t)game * Zt<N>::SLOTS;
+    // the windows of sk_step_core, for a play that is legal and takes nothing
+    const int c = m.wtm, own = c ? g.nw : g.nb, opp = c ? g.nb : g.nw;
+    const bool may_play = act >= 0 && act < G::P && !m.term;
+    const SkWin pre_a = sk_window<N>(L, tab, sk_home<N>(c, own + 1), may_play);
+    const SkWin pre_forb = sk_window<N>(L, tab, sk_home<N>(c ^ 1, opp + 1), may_play || (act == G::P && !m.term));
+    const SkWin pre_b = sk_window<N>(L, tab, sk_home<N>(c ^ 1, opp), may_play);
+    const uint32_t hash = in_place(env_hash(a.sample_seed, 0u, (uint32_t)L.b, a.sample_t));
+    // here before the other wavefront stores the next position, which it does once it has handed it over
+    asm volatile("" ::"v"(before.bk), "v"(before.wt));
+    __syncthreads();
+    const HandOver<N> in{hand[L.lane]};
+    const Row<N> R = in.row();
+    const bool moved = in.moved() && !in.reset(), played = moved && act != G::P;
+    Move mv;
+    mv.playing = played;
+    mv.pr = played ? act / N : -100; mv.pc = played ? act - (act / N) * N : 0;
+    const uint32_t captured = !played ? 0u : c ? before.bk & ~R.bk : before.wt & ~R.wt;
+    const SkPly s = sk_look<N>(L, tab, g, c, mv, captured, pre_a, lds_mask);
+    sk_insert<N>(L, tab, tab, g, s, played, c, pre_b);
+    // the forbidden plays change with the position and with the player to move; otherwise they stay, where they fit the record, and are found anew where not
+    m.wtm = in.wtm();
+    const bool find = moved || (L.boardok && !in.reset() && (g.fw & 0xFFFFu) == kLookAgain);
+    const uint32_t found = sk_forbidden<N, true>(L, tab, g, R, m, find, pre_forb, lds_mask);
+    const uint32_t forb = in.reset() ? 0u : find ? found : sk_forb_rows<N>(L, g.fw);
+    if (in.reset()) g = sk_fresh();
+    sk_clear_tables<N>(L, in.reset(), zt, L.b);
+    g.fw = sk_forb_word<N>(L, forb);
+    const uint32_t legal = legal_row<N>(L, R, in.wtm()) & ~forb;
+    if (a.mask) emit_mask<N, true, ST>(L, legal, group, B, a.mask, a.mask_pitch, lds_mask, lut, wb);
+    if (act != -1 && L.valid && L.r == 0) zcur[L.b] = sk_pack(g);
+    if (a.next_actions) {
+      const Draw<N> d = draw_action<N>(L, legal, hash, (int64_t)a.sample_t < (int64_t)start_raw);
+      if (d.known(L)) a.next_actions[L.b] = d.action(L);
+    }
+  } else if constexpr (OBS) {
+    Row<N> R;
+    History<N> H;
+    load_row<N>(state, L, R);
+    load_history<N>(state, L, H);
+    const Meta m = unpack_meta(load_meta<N>(meta, L));
+    in_scalar_registers(a.obs, a.obs_pitch);
+    fill_table();
+    team_obs<N, ST>(L, R, points_of<N>(H, m.head), m, hand, group, B, a.obs, a.obs_pitch, lds_obs, lut, wb, [] { __syncthreads(); });
   }
 }
 
@@ -2610,6 +2724,21 @@ int step_team(const pgxgo_ctx* h, bool with_obs) {
 // MB, 5.09 / 5.13, without observation x 2048 5.24 / 5.36), beyond it through the L2 (9x9 x 2048, 3 MB, 4.63 / 4.55; 19x19 x 1000 6.10 / 5.66).
 constexpr size_t kTeamPlainUpTo = (size_t)5 << 19;
 
+// Boards per team of three wavefronts of a ply with the repetition rule in the mask (go_step_superko_team_kernel), or 0: one wavefront for
+// everything.  us per ply, one wavefront / teams: 19x19 x 256 games 8.36 / 6.2, 1000 9.33 / 7.14, 3000 10.4 / 8.6, 5000 12.3 / 10.2, 8000 15.1 / 13.6, 10000 17.2 / 15.5,
+// 12000 18.8 / 19.6, 16384 26.1 / 29.7; without observation 256 7.9 / 6.0, 5000 9.1 / 8.8, 10000 11.4 / 11.0, 12000 11.8 / 11.9; 9x9 x 256 8.0 / 6.05, 1000 9.0 /
+// 7.05, 4096 9.6 / 8.2, 8192 10.6 / 9.5, 16384 12.8 / 12.2, 24000 14.7 / 15.1; without observation 4096 8.6 / 7.8, 16384 11.1 / 11.05.  The line lies farther out
+// than without the rule (boards_per_step_team), as there is more to do beside the outputs.  Boards: 9x9 with 1 / 4 / 6 256 6.05 / 6.34 / 6.77, 1000 7.29 /
+// 7.05 / 7.37, 5001 13.8 / 8.65 / 8.53; 19x19 with 1 / 3 256 6.24 / 6.57, 512 6.74 / 6.73, 1000 7.46 / 7.14.
+template <int N>
+int boards_per_superko_team(int B) {
+  if (N == 9) return B <= 384 ? 1 : B <= 4096 ? 4 : B <= 16384 ? 6 : 0;
+  return B <= 384 ? 1 : B <= 10240 ? Geo<N>::W : 0;
+}
+constexpr int superko_team_waves(bool with_obs) { return with_obs ? 3 : 2; }
+template <int N>
+int superko_team(const pgxgo_ctx* h) { return h->automatic && h->zt && h->sk_mode == 2 && tight_pitches<N>(h) ? boards_per_superko_team<N>(h->B) : 0; }
+
 template <int N, bool TIGHT, bool SK>
 void launch_emit_as(pgxgo_ctx* h, uint8_t* mask, uint8_t* obs) {
   hipLaunchKernelGGL((go_emit_kernel<N, TIGHT, SK>), dim3(blocks_for<N>(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, h->state, h->meta, h->B, mask,
@@ -2656,8 +2785,26 @@ int launch_step(pgxgo_ctx* h, const int32_t* actions, bool sample, uint32_t seed
     HIPCHK(hipGetLastError());
     return PGXGO_OK;
   }
+  if (h->zt && !sample) a.next_actions = nullptr;
+  const int sk_wb = superko_team<N>(h);
+  if (sk_wb) {
+    const dim3 teams((unsigned)((h->B + sk_wb - 1) / sk_wb + 7) & ~7u);
+    auto team = [&](auto obs_c, auto st_c) {
+      constexpr bool O = decltype(obs_c)::value;
+      hipLaunchKernelGGL((go_step_superko_team_kernel<N, O, decltype(st_c)::value>), teams, dim3(64 * superko_team_waves(O)), 0, h->stream, h->state, h->meta, actions, start_t, h->zcur, h->B, sk_wb,
+                         teams.x / 8, h->zt, a);
+    };
+    using Plain = std::integral_constant<int, kStorePlain>;
+    using Through = std::integral_constant<int, kStoreThrough>;
+    const bool plain = output_bytes_per_ply(h, a.mask != nullptr, a.obs != nullptr) <= kTeamPlainUpTo;
+    if (a.obs && plain) team(std::true_type{}, Plain{});
+    else if (a.obs) team(std::true_type{}, Through{});
+    else if (plain) team(std::false_type{}, Plain{});
+    else team(std::false_type{}, Through{});
+    HIPCHK(hipGetLastError());
+    return PGXGO_OK;
+  }
   if (h->zt) {
-    if (!sample) a.next_actions = nullptr;
     auto sk = [&](auto tight_c, auto mode_c) {
       constexpr bool T = decltype(tight_c)::value;
       constexpr int M = decltype(mode_c)::value;
@@ -2768,7 +2915,7 @@ int rollout_team(const pgxgo_ctx* h, int steps, int slices, bool with_obs, const
 }
 template <int N>
 int team_of(const pgxgo_ctx* h, int steps, int slices, bool with_mask, bool with_obs) {   // steps = 0: of a step
-  return steps ? rollout_team<N>(h, steps, slices, with_obs, rollout_pace<N>(h, steps, slices, with_mask, with_obs)) : step_team<N>(h, with_obs);
+  return steps ? rollout_team<N>(h, steps, slices, with_obs, rollout_pace<N>(h, steps, slices, with_mask, with_obs)) : h->zt ? superko_team<N>(h) : step_team<N>(h, with_obs);
 }
 
 template <int N>
@@ -3057,7 +3204,7 @@ int pgxgo_rollout_in_time_slots(pgxgo_t h, int32_t steps, int32_t slices, int32_
 int pgxgo_boards_per_team(pgxgo_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int32_t* wavefronts) {
   if (!h || steps < 0 || slices < 1) return PGXGO_EINVAL;
   const int wb = DISPATCH_N(h, team_of<19>(h, steps, slices, with_mask != 0, with_obs != 0), team_of<9>(h, steps, slices, with_mask != 0, with_obs != 0));
-  if (wavefronts) *wavefronts = !wb ? 1 : steps ? rollout_team_waves(with_obs != 0) : (int)kTeamWaves;
+  if (wavefronts) *wavefronts = !wb ? 1 : steps ? rollout_team_waves(with_obs != 0) : h->zt ? superko_team_waves(with_obs != 0) : (int)kTeamWaves;
   return wb;
 }
 

@@ -1100,6 +1100,15 @@ struct HandOver {
   __device__ __forceinline__ int wtm() const { return (int)(v.x >> 31); }
   __device__ __forceinline__ uint32_t legal(const Lane<N>& L) const { return legal_row<N>(L, row(), wtm()); }
 };
+// The wavefront with the rules goes first where its SIMD has a team's other wavefront to issue from as well (more than one team per compute unit,
+// 256) and no second one with rules (up to one team per SIMD, 1024): the team waits for it.  eighth: teams / 8.  us, without / with: a ply of 9x9 x 4096
+// 4.88 / 4.49, x 3000 4.67 / 4.51; 32 plies of 9x9 in one launch without observation x 1000 38.4 / 36.2, x 5001 43.5 / 40.8, x 6000 43.9 / 41.0, with it x 1000 37.9 / 36.1,
+// x 4096 53.0 / 52.1; 16 plies of 19x19 x 1500 without observation 29.5 / 27.1, with it 32.6 / 32.0; search x 4096 of 9x9 4.18 / 4.04; superko 9x9 x 4096 8.2 / 8.1.
+// Beyond 1024 teams the outputs, which start later, lose what the rules gain or more: 32 plies of 9x9 x 8000 61.1 / 64.3, x 15000 119 / 140; search of 19x19 x 6144
+// 9.2 / 9.8.  With one team per compute unit nothing is gained (16 plies of 19x19 x 256 23.0 / 23.4).
+__device__ __forceinline__ void rules_first(uint32_t eighth) {
+  if (eighth > 32u && eighth <= 128u) __builtin_amdgcn_s_setprio(3);
+}
 enum TeamRole { kTeamRules = 0, kTeamMask = 1, kTeamDraw = 2, kTeamObs = 3, kTeamWaves = 4 };
 
 // The observation of a team: everything but the ply's own changes is put into the stream beforehand, as if the position were to
@@ -1168,6 +1177,7 @@ __global__ void __launch_bounds__(64 * kTeamWaves) go_step_team_kernel(uint32_t*
   auto fill_table = [&]() { const uint32_t x = threadIdx.x; lut[x] = make_uint2(spread4(x & 15u), spread4(x >> 4)); };
 
   if (role == kTeamRules) {
+    rules_first(eighth);
     Row<N> R;
     History<N> H;
     load_row<N>(state, L, R);
@@ -1802,6 +1812,7 @@ __global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_step_superko_team_kerne
   none.home = ~0u; none.e = make_uint2(1u, 0u);
 
   if (role == 0) {   // the rules
+    rules_first(eighth);
     Row<N> R;
     History<N> H;
     load_row<N>(state, L, R);
@@ -2084,6 +2095,7 @@ __global__ void __launch_bounds__(64 * (OBS ? 3 : 2)) go_step_slots_team_kernel(
   L.slot = src; L.some = 0;
 
   if (role == 0) {
+    rules_first(eighth);
     const int act_raw = actions[entry];
     Row<N> R;
     History<N> H;
@@ -2319,6 +2331,7 @@ __global__ void __launch_bounds__(64 * rollout_team_waves(OBS)) go_rollout_team_
   for (uint32_t x = threadIdx.x; x < 256u; x += 64u * WAVES) lut[x] = make_uint2(spread4(x & 15u), spread4(x >> 4));
 
   if (role == 0) {   // the draws and the rules
+    rules_first(gridDim.x >> 3);
     Row<N> R;
     load_row<N>(a.state, L, R);
     Meta m = unpack_meta(load_meta<N>(a.meta, L));

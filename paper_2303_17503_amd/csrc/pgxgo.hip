@@ -2310,7 +2310,8 @@ __device__ __forceinline__ void team_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 constexpr int rollout_team_waves(bool with_obs) { return with_obs ? 3 : 2; }
-template <int N, bool OBS>
+// SK: 0 = simple ko only, 1 / 2 = positional superko at play time / in the legal mask, whose table is the business of the wavefront with the rules
+template <int N, bool OBS, int SK>
 __global__ void __launch_bounds__(64 * rollout_team_waves(OBS)) go_rollout_team_kernel(RolloutArgs a) {   // a.wb: boards per team
   using G = Geo<N>;
   constexpr int WAVES = rollout_team_waves(OBS), ST = kStoreThroughWhole;
@@ -2324,6 +2325,8 @@ __global__ void __launch_bounds__(64 * rollout_team_waves(OBS)) go_rollout_team_
   __shared__ int32_t drawn[2][8];
   __shared__ uint32_t hashes[4][64];      // of the draws, computed by the wavefront with the mask three plies ahead
   __shared__ uint4 scalars_after[G::W];   // the game's record as the launch leaves it
+  __shared__ uint32_t legal_of[SK == 2 ? 2 : 1][64];   // SK = 2: what the position alone does not say
+  __shared__ uint32_t sk_scratch[SK ? 64 : 1];
   const int group = piece_of_block();
   if (group * a.wb >= a.B) return;   // the whole block
   const int role = wave_in_block();
@@ -2340,6 +2343,17 @@ __global__ void __launch_bounds__(64 * rollout_team_waves(OBS)) go_rollout_team_
     uint32_t legal = legal_row<N>(L, R, m.wtm);
     for (uint32_t k = 0; k < 2u; ++k) hashes[k][L.lane] = env_hash(a.seed, 0u, (uint32_t)L.b, a.t0 + k);   // (plies 0 and 1 are drawn before the other's come)
     Tally tally(&tally_cells, 0, L);
+    SkGame g = sk_fresh();
+    uint2* tab = nullptr;
+    uint32_t forb = 0u;
+    SkWin none, ahead;
+    none.home = ~0u; none.e = make_uint2(1u, 0u);
+    if constexpr (SK) {
+      if (L.boardok) g = sk_unpack(a.zcur[L.b]);
+      tab = a.zt + (size_t)(L.boardok ? L.b : 0) * Zt<N>::SLOTS;
+      if constexpr (SK == 1) ahead = sk_window_play<N>(L, tab, g, m, L.boardok);
+      else { forb = sk_forb_loaded<N>(L, tab, g, R, m, none, sk_scratch); legal &= ~forb; }
+    }
     for (int i = 0; i < a.steps; ++i) {
       const uint32_t t = a.t0 + (uint32_t)i;
       const bool wait = (int64_t)t < start;
@@ -2347,13 +2361,28 @@ __global__ void __launch_bounds__(64 * rollout_team_waves(OBS)) go_rollout_team_
       if (i) team_barrier();   // hands over the ply before: what it left in LDS is there by now, and nobody waits for that
       const bool skip = !L.boardok || wait;
       if (d.known(L)) drawn[i & 1][L.j] = d.action(L);
-      const Ply ply = apply_move<N>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.bit, 0, 0), tally);
+      Ply ply;
+      if constexpr (!SK) ply = apply_move<N>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.bit, 0, 0), tally);
+      else {
+        const int dr = d.row(L), dc = d.column();
+        auto nothing = [](bool, bool) {};   // (history and observation are the others')
+        if constexpr (SK == 1) {
+          sk_step_core_play<N, false, false>(L, R, m, g, a.rules, skip, d.pass, d.point, d.bit, dr, dc, tab, tab, a.zt, L.b, sk_scratch, tally, ply, ahead, nothing, [](Row<N>&, Meta&, bool) {});
+          ahead = sk_window_play<N>(L, tab, g, m, L.boardok);
+        } else
+          sk_step_core<N, false, false>(L, R, m, g, forb, a.rules, skip, d.pass, d.point, d.bit, dr, dc, tab, tab, a.zt, L.b, sk_scratch, tally, ply, false, none, nothing);
+      }
       hand[i & 1][L.lane] = HandOver<N>::of(R, m, ply).v;
       // a waiting environment reports the values a skipped step call leaves behind at the start: zeros
       if (L.valid && L.r == 0) scalars[i & 1][L.j] = make_uint4(skip ? 0u : __float_as_uint(ply.rew0), skip ? 0u : __float_as_uint(ply.rew1), !skip && ply.flag ? 1u : 0u, 0u);
-      legal = legal_row<N>(L, R, m.wtm);
+      legal = legal_row<N>(L, R, m.wtm) & ~(SK == 2 ? forb : 0u);
+      if constexpr (SK == 2) legal_of[i & 1][L.lane] = legal;
     }
     team_barrier();
+    if constexpr (SK) {
+      if constexpr (SK == 2) g.fw = sk_forb_word<N>(L, forb);
+      if (L.valid && L.r == 0) a.zcur[L.b] = sk_pack(g);
+    }
     if (L.valid) {
       store_row<N>(State<N>(a.state, L), R);
       m.head = 0;
@@ -2383,7 +2412,7 @@ __global__ void __launch_bounds__(64 * rollout_team_waves(OBS)) go_rollout_team_
           if (a.rew) *(float2*)(a.rew + 2 * e) = make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
           if (a.term) a.term[e] = (uint8_t)v.z;
         }
-        if (a.mask) emit_mask<N, true, ST, FIRST_AS_EDGE>(L, in.legal(L), group, a.B, a.mask + sb * a.mask_pitch, a.mask_pitch, lds_mask, lut, a.wb);
+        if (a.mask) emit_mask<N, true, ST, FIRST_AS_EDGE>(L, SK == 2 ? legal_of[SK == 2 ? i & 1 : 0][L.lane] : in.legal(L), group, a.B, a.mask + sb * a.mask_pitch, a.mask_pitch, lds_mask, lut, a.wb);
       }
       if (history) {
         const Row<N> R = in.row();
@@ -2921,26 +2950,52 @@ int boards_per_rollout_team(int B, int steps, int slices, bool with_obs) {
   return with_obs ? (B <= 512 ? 1 : 3) : B <= K ? 1 : B <= 2 * K ? 2 : 3;
 }
 
+// The same with the repetition rule, whose table work stays with the rules and so weighs against teams.  us, one wavefront / teams: mode 1, 16 plies,
+// 9x9 x 256 games 50.7 / 31.6, 5001 66.4 / 42.5, 19x19 x 1000 69.2 / 43.5, 4000 91.7 / 66.3; mode 2 9x9 x 256 68.6 / 51.2, 5001 97.4 / 77.8, 19x19 x 1000 85.3 /
+// 64.0, 2000 99.5 / 68.8; without observation mode 1 9x9 x 5001 47.7 / 41.1, 19x19 x 1000 48.5 / 42.0, mode 2 75.8 / 71.0 x 4096 and 64.8 / 62.2.  Time of teams over
+// time of one wavefront at the lines: with observation, where the machine holds the teams at once, mode 1 2 / 6 plies 0.90 / 0.80 x 9216, 1.16 / 1.05 x 10240
+// (19x19 0.86 / 0.79 x 4608, 1.13 / 1.02 x 5120), mode 2 0.94 / 0.89 x 7000, 4 plies 1.16 x 8000 (19x19 0.89 / 0.78 x 3500, 1.04 x 4000).  Without it a launch of few
+// plies does not make up for the teams' start: mode 1 2 plies 1.00 x 8192, 3 plies 0.97 x 12288 (19x19 0.96 x 4096, 1.01 x 6144), 6 plies 0.97 x 6144;
+// mode 2 2 to 6 plies 0.93 to 1.04, 16 plies 0.94 x 4096, 0.99 x 8000 (19x19 0.96 x 4000, 0.97 x 6000).
+template <int N>
+int boards_per_superko_rollout_team(int B, int steps, bool with_obs, int mode) {
+  constexpr int K = 1024;
+  int most;   // games
+  if (with_obs) most = steps < 2 ? 0 : (mode == 1 ? 1536 : 1152) * Geo<N>::W;
+  else if (mode == 1) most = steps < 3 ? 0 : N == 9 ? 12 * K : steps < 4 ? 4 * K : 6 * K;
+  else most = steps < 8 ? 0 : 6 * K;
+  if (B > most) return 0;
+  if (N == 9) return B <= 384 ? 1 : B <= K ? 2 : B <= 4 * K ? 4 : 6;
+  return B <= 512 ? 1 : 3;
+}
 // boards per team of such a rollout of this handle, or 0: one wavefront for everything
 template <int N>
-int rollout_team(const pgxgo_ctx* h, int steps, int slices, bool with_obs, const PaceArgs& pace) {
-  return h->automatic && !h->zt && !pace.ply && tight_pitches<N>(h) ? boards_per_rollout_team<N>(h->B, steps, slices, with_obs) : 0;
+int rollout_team(const pgxgo_ctx* h, int steps, int slices, bool with_mask, bool with_obs, const PaceArgs& pace) {
+  if (!h->automatic || pace.ply || !tight_pitches<N>(h)) return 0;
+  if (h->zt && !with_mask && !with_obs) return 0;   // (nothing to take off the wavefront with the rules: 300 plies of 9x9 x 5001, mode 2, 1.17 / 1.34 ms)
+  return h->zt ? boards_per_superko_rollout_team<N>(h->B, steps, with_obs, h->sk_mode) : boards_per_rollout_team<N>(h->B, steps, slices, with_obs);
 }
 template <int N>
 int team_of(const pgxgo_ctx* h, int steps, int slices, bool with_mask, bool with_obs) {   // steps = 0: of a step
-  return steps ? rollout_team<N>(h, steps, slices, with_obs, rollout_pace<N>(h, steps, slices, with_mask, with_obs)) : h->zt ? superko_team<N>(h) : step_team<N>(h, with_obs);
+  return steps ? rollout_team<N>(h, steps, slices, with_mask, with_obs, rollout_pace<N>(h, steps, slices, with_mask, with_obs)) : h->zt ? superko_team<N>(h) : step_team<N>(h, with_obs);
 }
 
 template <int N>
 int launch_rollout(pgxgo_ctx* h, RolloutArgs& a) {
   const dim3 grid(blocks_for_wb(h->B, h->wb)), block(64 * kWavesPerBlock);
   a.pace = rollout_pace<N>(h, a.steps, a.slices, a.mask != nullptr, a.obs != nullptr);
-  const int team = rollout_team<N>(h, a.steps, a.slices, a.obs != nullptr, a.pace);
+  const int team = rollout_team<N>(h, a.steps, a.slices, a.mask != nullptr, a.obs != nullptr, a.pace);
   if (team) {
     a.wb = team;
     const dim3 teams((unsigned)(((int64_t)h->B + team - 1) / team + 7) & ~7u);
-    if (a.obs) hipLaunchKernelGGL((go_rollout_team_kernel<N, true>), teams, dim3(64 * rollout_team_waves(true)), 0, h->stream, a);
-    else hipLaunchKernelGGL((go_rollout_team_kernel<N, false>), teams, dim3(64 * rollout_team_waves(false)), 0, h->stream, a);
+    auto go = [&](auto sk_c) {
+      constexpr int M = decltype(sk_c)::value;
+      if (a.obs) hipLaunchKernelGGL((go_rollout_team_kernel<N, true, M>), teams, dim3(64 * rollout_team_waves(true)), 0, h->stream, a);
+      else hipLaunchKernelGGL((go_rollout_team_kernel<N, false, M>), teams, dim3(64 * rollout_team_waves(false)), 0, h->stream, a);
+    };
+    if (!h->zt) go(std::integral_constant<int, 0>{});
+    else if (h->sk_mode == 1) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 2>{});
     HIPCHK(hipGetLastError());
     return PGXGO_OK;
   }

@@ -1,4 +1,4 @@
-"""Plies with the repetition rule in the mask are run by teams of wavefronts up to a line.  At the sizes where the boards per team change,
+"""Plies with the repetition rule in the mask, and rollouts with the rule in either reading, are run by teams of wavefronts up to a line.  At the sizes where the boards per team change,
 and in ragged last teams, outputs and state are those of the kernel in which one wavefront does everything; the oracle checks positions
 with more forbidden plays than a game's record holds."""
 import numpy as np
@@ -21,7 +21,6 @@ def test_which_plies_go_by_teams(N, B, obs, mode, team):
     env = pg.GoEnv(B, N)
     env.enable_superko(mode)
     assert env.boards_per_team(0, obs=obs) == team
-    assert env.boards_per_team(16, obs=obs) == (0, 1)
     assert bench.go_kernel(env, B, obs, superko=mode)[0].startswith("go_step_superko_team" if team[0] else "go_step_superko_kernel")
     env.set_boards_per_wavefront(2)
     assert env.boards_per_team(0, obs=obs) == (0, 1)
@@ -77,3 +76,43 @@ def test_more_forbidden_plays_than_a_record_holds(forbidden):
         a = np.roll(acts, turn)
         pair.step(torch.as_tensor(a, device="cuda"), a)
         pair.compare(f"turn {turn}", state=True)
+
+
+@pytest.mark.parametrize("N,B,obs,mode,steps,team", [
+    (9, 9216, True, 1, 2, (6, 3)), (9, 9217, True, 1, 16, (0, 1)), (9, 6912, True, 2, 16, (6, 3)), (9, 6913, True, 2, 16, (0, 1)), (9, 12288, False, 1, 3, (6, 2)),
+    (9, 12289, False, 1, 16, (0, 1)), (9, 1000, False, 1, 2, (0, 1)), (9, 6144, False, 2, 8, (6, 2)), (9, 6144, False, 2, 7, (0, 1)), (9, 6145, False, 2, 16, (0, 1)),
+    (19, 4608, True, 1, 2, (3, 3)), (19, 4609, True, 1, 8, (0, 1)), (19, 3456, True, 2, 2, (3, 3)), (19, 3457, True, 2, 8, (0, 1)), (19, 4096, False, 1, 3, (3, 2)),
+    (19, 4097, False, 1, 3, (0, 1)), (19, 6144, False, 1, 4, (3, 2)), (19, 6145, False, 1, 4, (0, 1)), (19, 512, True, 2, 2, (1, 3)), (19, 512, True, 2, 1, (0, 1))])
+def test_which_rollouts_go_by_teams(N, B, obs, mode, steps, team):
+    env = pg.GoEnv(B, N)
+    env.enable_superko(mode)
+    assert env.boards_per_team(steps, 1, obs=obs) == team
+    assert env.boards_per_team(steps, 1, mask=False, obs=False) == (0, 1)
+    env.set_boards_per_wavefront(3)
+    assert env.boards_per_team(steps, 1, obs=obs) == (0, 1)
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("N,B,steps,slices,obs,auto_reset", [
+    (9, 1, 9, 1, True, True), (9, 385, 9, 4, True, False), (9, 1023, 8, 8, False, True), (9, 6143, 8, 2, True, True), (9, 2, 2, 1, True, False),
+    (19, 1, 8, 1, False, True), (19, 511, 7, 7, True, False), (19, 1025, 8, 2, False, True), (19, 3455, 3, 1, True, True)])
+def test_rollouts_by_teams_and_by_single_wavefronts_agree(N, B, steps, slices, obs, auto_reset, mode):
+    kw = dict(seed=4, auto_reset=auto_reset, max_steps=45 if auto_reset else 0)
+    envs = [pg.GoEnv(B, N, **kw), pg.GoEnv(B, N, **kw)]
+    envs[1].set_boards_per_wavefront(3)
+    start = torch.as_tensor(np.random.default_rng(B).integers(0, 44, size=B).astype(np.int32), device="cuda")   # some wait through a whole launch
+    got = []
+    for e in envs:
+        e.enable_superko(mode)
+        assert (e.boards_per_team(steps, slices, obs=obs)[0] > 0) == (e is envs[0])
+        m, o = torch.full((slices, B, e.mask_pitch), 7, dtype=torch.uint8, device="cuda"), torch.full((slices, B, e.obs_pitch), 7, dtype=torch.uint8, device="cuda")
+        r, t = torch.full((slices, B, 2), 7.0, dtype=torch.float32, device="cuda"), torch.full((slices, B), 7, dtype=torch.uint8, device="cuda")
+        a = torch.full((slices, B), 7, dtype=torch.int32, device="cuda")
+        seen = []
+        for k in range(20 if N == 9 else 6):
+            e.rollout(steps, 4, 36 + k * steps, start_t=start, slices=slices, actions=a, rewards=r, terminated=t, mask=m, obs=o if obs else None)
+            seen += [x.clone() for x in (m, o, r, t, a)]
+        seen += [e.legal_mask().clone()] + list(e.export_state().values())   # the mask by the record that the launch leaves
+        got.append(seen)
+    for i, (x, y) in enumerate(zip(*got)):
+        assert torch.equal(x, y), i

@@ -122,7 +122,7 @@ int pgxhex_import_state(pgxhex_t h, const int8_t* board_dev, const int8_t* to_pl
 
 /* Launch-shape knob of pgxhex_step / pgxhex_step_sample / pgxhex_rollout: 1 = a board row per lane (5 boards per wavefront), 2 = a whole
  * board per lane (64 boards per wavefront; pays from about 28 k games on, in the rollout kernel from about 20 k), 0 = the
- * automatic choice by batch size.  Results do not depend on it.  Returns the mapping the step calls now use (1 or 2), or
+ * automatic choice by batch size, which runs rollouts of small batches by teams of wavefronts with a board row per lane as well.  Results do not depend on it.  Returns the mapping the step calls now use (1 or 2), or
  * a negative error code. */
 int pgxhex_set_mapping(pgxhex_t h, int32_t mapping);
 

@@ -1100,15 +1100,6 @@ struct HandOver {
   __device__ __forceinline__ int wtm() const { return (int)(v.x >> 31); }
   __device__ __forceinline__ uint32_t legal(const Lane<N>& L) const { return legal_row<N>(L, row(), wtm()); }
 };
-// The wavefront with the rules goes first where its SIMD has a team's other wavefront to issue from as well (more than one team per compute unit,
-// 256) and no second one with rules (up to one team per SIMD, 1024): the team waits for it.  eighth: teams / 8.  us, without / with: a ply of 9x9 x 4096
-// 4.88 / 4.49, x 3000 4.67 / 4.51; 32 plies of 9x9 in one launch without observation x 1000 38.4 / 36.2, x 5001 43.5 / 40.8, x 6000 43.9 / 41.0, with it x 1000 37.9 / 36.1,
-// x 4096 53.0 / 52.1; 16 plies of 19x19 x 1500 without observation 29.5 / 27.1, with it 32.6 / 32.0; search x 4096 of 9x9 4.18 / 4.04; superko 9x9 x 4096 8.2 / 8.1.
-// Beyond 1024 teams the outputs, which start later, lose what the rules gain or more: 32 plies of 9x9 x 8000 61.1 / 64.3, x 15000 119 / 140; search of 19x19 x 6144
-// 9.2 / 9.8.  With one team per compute unit nothing is gained (16 plies of 19x19 x 256 23.0 / 23.4).
-__device__ __forceinline__ void rules_first(uint32_t eighth) {
-  if (eighth > 32u && eighth <= 128u) __builtin_amdgcn_s_setprio(3);
-}
 enum TeamRole { kTeamRules = 0, kTeamMask = 1, kTeamDraw = 2, kTeamObs = 3, kTeamWaves = 4 };
 
 // The observation of a team: everything but the ply's own changes is put into the stream beforehand, as if the position were to
@@ -2300,15 +2291,9 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
 // observation, 3200 are left.  The hand-over waits for the next draw, by when the writes to LDS are done, and the other wavefronts hash for the draws: 64 plies
 // of 9x9 x 5001 games without observation 82.6 -> 81.8 us.  Figures, and which rollouts go this way: boards_per_rollout_team.
 // ------------------------------------------------------------------------------------------------
-// Everything the wavefronts of a block wrote to LDS is there for all of them.  (Unlike __syncthreads this does not wait for their output
-// stores as well.  It orders nothing in memory.  So rows and history are written by the wavefront that has read them itself.  The
+// (team_barrier orders nothing in memory.  So rows and history are written by the wavefront that has read them itself.  The
 // scalars are read by two; the one with the history writes them, when the other, which has needed all of them for its first ply, has handed
 // over the new ones in LDS.)
-__device__ __forceinline__ void team_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 constexpr int rollout_team_waves(bool with_obs) { return with_obs ? 3 : 2; }
 // SK: 0 = simple ko only, 1 / 2 = positional superko at play time / in the legal mask, whose table is the business of the wavefront with the rules
 template <int N, bool OBS, int SK>

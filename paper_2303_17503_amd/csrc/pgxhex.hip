@@ -655,6 +655,79 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) hex_rollout_kernel(Rollou
   if (L.valid && L.r == 0) a.meta[L.b] = pack_meta(m);
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same plies by teams of wavefronts, for batches that leave most of the machine empty: one draws and applies the rules, ply after ply; it leaves each
+// position in LDS, in one of two places in turn, and goes on while another writes mask, scalars and action of this ply and a third the observation.
+// What bounds the other kernel there is the chain of all of this in one wavefront.  Figures, and which rollouts go this way: teams_for_rollout.
+// ------------------------------------------------------------------------------------------------
+constexpr int rollout_team_waves(bool with_obs) { return with_obs ? 3 : 2; }
+template <bool OBSERVE>
+__global__ void __launch_bounds__(64 * rollout_team_waves(OBSERVE)) hex_rollout_team_kernel(RolloutArgs a) {
+  constexpr uint32_t THREADS = 64u * rollout_team_waves(OBSERVE);
+  __shared__ uint2 lut[256];
+  __shared__ __align__(16) uint32_t lds_obs[OBSERVE ? OBS_DW : 4];
+  __shared__ uint32_t lds_mask[MASK_DW];
+  __shared__ uint32_t hand[2][64];     // a row's stones; bit 15: White to move, bit 31: the swap is on offer
+  __shared__ uint4 scalars[2][8];      // per board: rewards, terminated, the action
+  __shared__ uint32_t hashes[4][64];   // of the draws, computed by the wavefront with the mask three plies ahead
+  const int group = piece_of_block();
+  if (group * W >= a.B) return;   // the whole block
+  const int role = wave_in_block();
+  const Lane L(group, threadIdx.x & 63, a.B);
+  for (uint32_t x = threadIdx.x; x < 256u; x += THREADS) lut[x] = make_uint2(spread4(x & 15u), spread4(x >> 4));
+  auto hash_of = [&](uint32_t t) { return env_hash(a.seed, 0u, (uint32_t)L.b, t); };
+
+  if (role == 0) {   // the draws and the rules
+    rules_first(gridDim.x >> 3);
+    const uint32_t word = L.valid ? a.rows[(size_t)L.b * N + L.r] : 0u;
+    uint32_t bk = word & 0xFFFFu, wt = word >> 16;
+    Meta m = unpack_meta(L.boardok ? a.meta[L.b] : make_uint4(0u, 0u, 0u, 0u));
+    const int64_t start = (L.boardok && a.start_t) ? (int64_t)a.start_t[L.b] : INT64_MIN;
+    for (uint32_t k = 0; k < 2u; ++k) hashes[k][L.lane] = hash_of(a.t0 + k);   // (plies 0 and 1 are drawn before the other's come)
+    for (int i = 0; i < a.steps; ++i) {
+      const bool wait = (int64_t)(a.t0 + (uint32_t)i) < start;
+      const Draw d = draw_action(L, L.full & ~(bk | wt), m.steps == 1, hashes[i & 3][L.lane], wait);
+      if (i) team_barrier();   // hands over the ply before: what it left in LDS is there by now, and nobody waits for that
+      if (d.known) scalars[i & 1][L.j].w = (uint32_t)d.action;
+      const Ply ply = hex_ply<false>(L, bk, wt, m, Move{wait || !L.boardok, d.cell, d.swap, d.bit}, a.seed_env, a.auto_reset);
+      hand[i & 1][L.lane] = bk | (wt << 16) | ((uint32_t)m.wtm << 15) | (m.steps == 1 ? 1u << 31 : 0u);
+      if (L.valid && L.r == 0) {
+        uint4& s = scalars[i & 1][L.j];
+        // a waiting environment reports what a skipped step leaves behind at the start: zeros
+        s.x = ply.skip ? 0u : __float_as_uint(ply.rew0); s.y = ply.skip ? 0u : __float_as_uint(ply.rew1);
+        s.z = !ply.skip && (ply.ended || ply.frozen) ? 1u : 0u;
+      }
+    }
+    team_barrier();
+    if (L.valid) a.rows[(size_t)L.b * N + L.r] = bk | (wt << 16);
+    if (L.valid && L.r == 0) a.meta[L.b] = pack_meta(m);
+  } else {   // 1: the mask, the scalars and the action; 2: the observation
+    if (role == 1) hashes[2][L.lane] = hash_of(a.t0 + 2u);
+    int slice = 0;
+    for (int i = 0; i < a.steps; ++i) {
+      team_barrier();
+      const uint32_t in = hand[i & 1][L.lane];
+      const size_t sb = (size_t)slice * a.B;
+      const uint32_t bk = in & FULL, wt = (in >> 16) & FULL;
+      // a board's flags are those of its row lanes
+      Meta m{};
+      m.wtm = (int)((in >> 15) & 1u); m.steps = (int)(in >> 31);
+      if (role == 1) {
+        hashes[(i + 3) & 3][L.lane] = hash_of(a.t0 + (uint32_t)i + 3u);   // (in the place of ply i - 1's; the other may be drawing ply i + 2)
+        if (L.valid && L.r == 0) {
+          const size_t e = sb + L.b;
+          const uint4 v = scalars[i & 1][L.j];
+          if (a.actions) a.actions[e] = (int32_t)v.w;
+          if (a.rew) *(float2*)(a.rew + 2 * e) = make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+          if (a.term) a.term[e] = (uint8_t)v.z;
+        }
+        emit_outputs(L, bk, wt, m, group, a.B, a.mask ? a.mask + sb * A : nullptr, nullptr, lds_mask, lds_obs, lut);
+      } else if constexpr (OBSERVE) emit_outputs(L, bk, wt, m, group, a.B, nullptr, a.obs + sb * OBS, lds_mask, lds_obs, lut);
+      slice = slice + 1 == a.slices ? 0 : slice + 1;
+    }
+  }
+}
+
 // The rate that the slots of a paced rollout are laid out for (us of a launch of 8 plies of 262144 games, recorded, with 6.45 / 6.5 / 6.55 /
 // 6.6 / 6.65 / 6.7 TB/s 210.7 / 209.2 / 207.9 / 206.5 / 205.1 / 203.9, of 20 of 100001 243.7 / 243.9 / 245.2 / 245.1 / 246.1 / 247.4; from 6.8
 // on the former turns too, 3 % at 6.8 and 8 % at 6.9; without slots 246 for the former; whole lines only, hence faster than Go's ragged runs)
@@ -862,6 +935,16 @@ PaceArgs rollout_pace(const pgxhex_ctx* h, int steps, int slices, bool with_mask
   if (!board_per_lane(h, true)) return PaceArgs{0u, 0u};
   return pace_args<hex_rollout_lane_kernel<true>>(h->B, 64, (with_mask ? A : 0) + (with_obs ? OBS : 0), steps, slices, 2.4, kPaceBytesPerSecond, kWavesPerBlock);
 }
+// Is such a rollout run by teams (hex_rollout_team_kernel)?  us for 16 plies, one wavefront / teams: 256 games 29.5 / 16.5, 1000 30.0 / 17.0, 5120 30.9 / 18.2, 8192
+// 35.7 / 27.7, 16384 50.0 / 45.1, without observation 21.4 / 16.1, 22.6 / 17.3 x 5120, 26.3 / 23.3 x 8192, 37.6 / 34.6 x 16384; recorded the same.  Beyond the lines the
+// machine's wavefronts are all busy and a team's start and hand-overs are lost.  Time of teams over time of one wavefront: 2 plies 0.95 x 10000, 1.01 x 12000;
+// 4 plies 0.95 x 16384, 1.13 x 20000; 16 plies 0.90 x 16384, 1.08 x 20000; without observation 2 plies 0.92 x 5120, 0.98 x 6000, 1.02 x 8192; 4 plies 0.92 x
+// 12000, 1.04 x 16384; 16 plies 0.92 x 16384.
+bool teams_for_rollout(const pgxhex_ctx* h, int steps, bool with_mask, bool with_obs) {
+  if (h->mapping != 0 || steps < 2 || !(with_mask || with_obs)) return false;   // (nothing to take off the wavefront with the rules)
+  constexpr int K = 1024;
+  return h->B <= (with_obs ? (steps < 4 ? 10 * K : 16 * K) : steps < 4 ? 5 * K : steps < 16 ? 12 * K : 16 * K);
+}
 unsigned row_blocks(int B) { return (unsigned)(((size_t)B * N + 255) / 256); }
 
 int launch_emit(pgxhex_ctx* h, uint8_t* mask, uint8_t* obs) {
@@ -984,7 +1067,11 @@ int pgxhex_rollout(pgxhex_t h, int32_t steps, int32_t slices, uint32_t seed, uin
     if (a.pace.ply) hipLaunchKernelGGL(hex_rollout_lane_kernel<true>, dim3(lane_blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
     else hipLaunchKernelGGL(hex_rollout_lane_kernel<false>, dim3(lane_blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
   }
-  else hipLaunchKernelGGL(hex_rollout_kernel, dim3(blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
+  else if (teams_for_rollout(h, steps, mask_dev != nullptr, obs_dev != nullptr)) {
+    const dim3 teams(((unsigned)((h->B + W - 1) / W) + 7u) & ~7u);
+    if (obs_dev) hipLaunchKernelGGL(hex_rollout_team_kernel<true>, teams, dim3(64 * rollout_team_waves(true)), 0, h->stream, a);
+    else hipLaunchKernelGGL(hex_rollout_team_kernel<false>, teams, dim3(64 * rollout_team_waves(false)), 0, h->stream, a);
+  } else hipLaunchKernelGGL(hex_rollout_kernel, dim3(blocks_for(h->B)), dim3(64 * kWavesPerBlock), 0, h->stream, a);
   HIPCHK(hipGetLastError());
   return PGXHEX_OK;
 }

@@ -186,6 +186,24 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Teams: a block whose wavefronts share one group of boards, one for the rules, the others for the outputs.
+// Everything the wavefronts of a block wrote to LDS is there for all of them.  (Unlike __syncthreads this does not wait for their output
+// stores as well, and it orders nothing in memory.)
+__device__ __forceinline__ void team_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// The wavefront with the rules goes first where its SIMD has a team's other wavefront to issue from as well (more than one team per compute unit,
+// 256) and no second one with rules (up to one team per SIMD, 1024): the team waits for it.  eighth: teams / 8.  us, without / with: a ply of 9x9 x 4096
+// 4.88 / 4.49, x 3000 4.67 / 4.51; 32 plies of 9x9 in one launch without observation x 1000 38.4 / 36.2, x 5001 43.5 / 40.8, x 6000 43.9 / 41.0, with it x 1000 37.9 / 36.1,
+// x 4096 53.0 / 52.1; 16 plies of 19x19 x 1500 without observation 29.5 / 27.1, with it 32.6 / 32.0; search x 4096 of 9x9 4.18 / 4.04; superko 9x9 x 4096 8.2 / 8.1.
+// Beyond 1024 teams the outputs, which start later, lose what the rules gain or more: 32 plies of 9x9 x 8000 61.1 / 64.3, x 15000 119 / 140; search of 19x19 x 6144
+// 9.2 / 9.8.  With one team per compute unit nothing is gained (16 plies of 19x19 x 256 23.0 / 23.4).
+__device__ __forceinline__ void rules_first(uint32_t eighth) {
+  if (eighth > 32u && eighth <= 128u) __builtin_amdgcn_s_setprio(3);
+}
+
 // ------------------------------------------------------------------------------------------------
 // bit stream -> byte stream.  `bits` (LDS) holds bit (head+i) = byte i of the destination, head = the
 // destination's offset from the previous 16-byte boundary.  Whole aligned 16-byte groups are written as

@@ -559,7 +559,8 @@ def bench_hex(args, cfg):
             env.rollout(Lr, seed, pre + Wm + i * Lr, **bufs)
         ev1.record()
         torch.cuda.synchronize()
-        kname = "hex_rollout_lane_kernel" if env.rollout_in_time_slots(Lr)[1] else "hex_rollout_team_kernel" if B <= 10240 else "hex_rollout_kernel"   # (games at once: 0 with a row per lane)
+        most = (10240 if Lr < 4 else 16384) if obs is not None else 5120 if Lr < 4 else 12288 if Lr < 16 else 16384   # games that are run by teams
+        kname = "hex_rollout_lane_kernel" if env.rollout_in_time_slots(Lr)[1] else "hex_rollout_team_kernel" if B <= most and Lr > 1 else "hex_rollout_kernel"   # (games at once: 0 with a row per lane)
     else:
         acts = [torch.empty(B, dtype=torch.int32, device="cuda") for _ in range(2)]
         env.random_actions(seed, pre, out=acts[pre & 1])

@@ -862,8 +862,10 @@ struct NothingToClear {
   __device__ __forceinline__ void operator()() const {}
 };
 // RARE_IN_LINE: the end of a game stands among the rest.  Out of the way it saves the usual ply its jumps, each of them a fetch, but go_rollout_kernel at 19x19
-// then needs two registers more than it has.
-template <int N, bool RARE_IN_LINE = false, class Clear = NothingToClear>
+// then needs two registers more than it has.  SIXTH: the flood that clears the mover's atari set runs in the sixth field where there is one.  Plies with the
+// rule in the mask by single wavefronts, which are run beyond 16384 games where the instructions of several wavefronts count and not one's chain, are 1.5 % slower that way (9x9 x
+// 30001 16.2 / 16.4 us).
+template <int N, bool RARE_IN_LINE = false, bool SIXTH = Floods<N>::PACKED, class Clear = NothingToClear>
 __device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, const Rules& cfg, const Move& mv, Tally& tally, Clear&& clear = Clear{}) {
   Ply out;
   using G = Geo<N>;
@@ -901,13 +903,13 @@ __device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, 
     }
     const uint32_t E = L.full & ~(own | opp);
     const uint32_t clrseed = released & aown;
-    if (!Floods<N>::PACKED && ballot(clrseed != 0u) != 0ull) aown &= ~flood_plain(clrseed, aown);   // (PACKED: below, the sixth flood)
+    if (!SIXTH && ballot(clrseed != 0u) != 0ull) aown &= ~flood_plain(clrseed, aown);   // (else below)
     // Liberty class of the new stone's chain (flood 0, through own stones) and of the surviving opposing neighbour chains,
     // which lost the liberty just filled (floods 1-4, through opposing stones).  A flood is decided as soon as two
     // liberties are known; one that converges with a single liberty has found a whole chain in atari.
     using FL = Floods<N>;
     uint32_t F[FL::WORDS], S[FL::WORDS], EE[FL::WORDS];
-    FL::spread(F, pbit, nbN & opp, nbS & opp, nbW & opp, nbE & opp, clrseed);
+    FL::spread(F, pbit, nbN & opp, nbS & opp, nbW & opp, nbE & opp, SIXTH ? clrseed : 0u);
     FL::spread(S, own, opp, opp, opp, opp, aown);
     FL::spread(EE, E, E, E, E, E, 0u);   // (the sixth flood counts no liberties and so runs until it stops growing)
     uint64_t libs;                 // liberties seen per flood, FL::count's fields
@@ -943,7 +945,7 @@ __device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, 
       }
       if (!any) break;
     }
-    if constexpr (FL::PACKED) aown &= ~FL::sixth(F);
+    if constexpr (SIXTH) aown &= ~FL::sixth(F);
     FL::atari(F, libs, aown, aopp);
     if (playing) {
       m.ko = ko_new; R.ko = ko_bit;
@@ -1588,7 +1590,7 @@ __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& 
   pre[2] = sk_window<N>(L, tab_r, sk_home<N>(c ^ 1, opp), mv.playing);
   Rules r0 = rules;
   r0.auto_reset = 0;   // the reset happens below, after the table work
-  ply = apply_move<N>(L, R, m, r0, mv, tally);
+  ply = apply_move<N, GATE, Floods<N>::PACKED && !GATE>(L, R, m, r0, mv, tally);
   const bool do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
   if (do_reset) reset_board<N>(L, R, m, rules.seed);   // a board that is reset takes no part in the table work below
   ply.reset = do_reset;

@@ -127,9 +127,6 @@ __device__ __forceinline__ uint32_t kept(uint32_t v) {
   asm volatile("" ::"v"(v));
   return v;
 }
-struct Halves {
-  uint32_t a, b;
-};
 __device__ __forceinline__ uint32_t dilate(uint32_t x) {
   const uint32_t a = kept(from_lane_below(x) | (x << 1)), b = kept(from_lane_above(x) | (x >> 1));
   return a | b;
@@ -793,22 +790,10 @@ struct Floods {
     else { w[0] = x0; w[1] = x1; w[2] = x2; w[3] = x3; w[4] = x4; }
   }
   static __device__ __forceinline__ uint32_t sixth(const uint32_t (&w)[WORDS]) { return w[1] >> 20; }   // PACKED only
-  // kBlindSteps growth steps of both words and the halves of one more.  Word by word a step is five instructions and an idle one: the compiler
-  // keeps two instructions between a value and the DPP instruction that takes it, and one word has nothing to put there.
+  // kBlindSteps growth steps of both words and the halves of one more
   static __device__ __forceinline__ void grow_both(uint32_t (&F)[WORDS], const uint32_t (&S)[WORDS], Halves& d0, Halves& d1) {
-    static_assert(kBlindSteps == 4, "written out below");
-#define PGX_HALVES                                                                                                           \
-  "v_lshl_or_b32 %2, %0, 1, %0\n\tv_lshrrev_b32_e32 %3, 1, %0\n\tv_lshl_or_b32 %4, %1, 1, %1\n\tv_lshrrev_b32_e32 %5, 1, %1\n\t" \
-  "v_or_b32_dpp %2, %0, %2 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"                                             \
-  "v_or_b32_dpp %3, %0, %3 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"                                             \
-  "v_or_b32_dpp %4, %1, %4 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"                                             \
-  "v_or_b32_dpp %5, %1, %5 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-#define PGX_STEP PGX_HALVES "v_bitop3_b32 %0, %2, %6, %3 bitop3:0xc8\n\tv_bitop3_b32 %1, %4, %7, %5 bitop3:0xc8\n\t"   // (first | third) & second
-    asm(PGX_STEP PGX_STEP PGX_STEP PGX_STEP PGX_HALVES
-        : "+v"(F[0]), "+v"(F[1]), "=&v"(d0.a), "=&v"(d0.b), "=&v"(d1.a), "=&v"(d1.b)
-        : "v"(S[0]), "v"(S[1]));
-#undef PGX_STEP
-#undef PGX_HALVES
+    static_assert(kBlindSteps == 4, "what grow_pair does");
+    grow_pair(F[0], F[1], S[0], S[1], d0, d1);
   }
   // puts the counts of word k's floods into this row's fields
   static __device__ __forceinline__ void count(int k, uint32_t w, uint32_t& lo, uint32_t& hi) {

@@ -145,6 +145,28 @@ __device__ __forceinline__ uint32_t from_lane_below(uint32_t x) {  // lane i rec
 __device__ __forceinline__ uint32_t from_lane_above(uint32_t x) {  // lane i receives lane i+1, lane 63 receives 0
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x130 /* wave_shl:1 */, 0xF, 0xF, true);
 }
+// A set and its neighbours, as two halves that are yet to be joined.
+struct Halves {
+  uint32_t a, b;
+};
+// Four growth steps of f0 within s0 and of f1 within s1 (rows of floods, whose neighbours are one bit or one lane away) and the halves of one
+// more of each.  Word by word a step is five instructions and an idle one: the compiler keeps two instructions between a value and the DPP
+// instruction that takes it, and one word has nothing to put there.  (The sets are read again after the floods are written, so a flood that
+// starts as its whole set has to be kept out of the set's register.)
+__device__ __forceinline__ void grow_pair(uint32_t& f0, uint32_t& f1, uint32_t s0, uint32_t s1, Halves& d0, Halves& d1) {
+#define PGX_HALVES                                                                                                           \
+  "v_lshl_or_b32 %2, %0, 1, %0\n\tv_lshrrev_b32_e32 %3, 1, %0\n\tv_lshl_or_b32 %4, %1, 1, %1\n\tv_lshrrev_b32_e32 %5, 1, %1\n\t" \
+  "v_or_b32_dpp %2, %0, %2 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"                                             \
+  "v_or_b32_dpp %3, %0, %3 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"                                             \
+  "v_or_b32_dpp %4, %1, %4 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"                                             \
+  "v_or_b32_dpp %5, %1, %5 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+#define PGX_STEP PGX_HALVES "v_bitop3_b32 %0, %2, %6, %3 bitop3:0xc8\n\tv_bitop3_b32 %1, %4, %7, %5 bitop3:0xc8\n\t"   // (first | third) & second
+  asm(PGX_STEP PGX_STEP PGX_STEP PGX_STEP PGX_HALVES
+      : "+&v"(f0), "+&v"(f1), "=&v"(d0.a), "=&v"(d0.b), "=&v"(d1.a), "=&v"(d1.b)
+      : "v"(s0), "v"(s1));
+#undef PGX_STEP
+#undef PGX_HALVES
+}
 // The lanes where p holds.  (HIP's own ballot takes an int: a condition that is already a lane mask goes through a register and back.)
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 // A fact about a whole board, known to every lane of the board: does `pred` hold in any of its rows?

@@ -752,9 +752,14 @@ class Tally {
   __device__ __forceinline__ uint64_t* present() const { return cells_ + (at_ + board_); }
 
  public:
+  // later: it is cleared by a call, before the first sum
   template <int N>
-  __device__ __forceinline__ Tally(TallyCells* of_block, int wavefront, const Lane<N>& L) : cells_(of_block->cell), at_((uint32_t)(kTallyCells * wavefront)), board_((uint32_t)L.j) {
+  __device__ __forceinline__ Tally(TallyCells* of_block, int wavefront, const Lane<N>& L, bool later = false)
+      : cells_(of_block->cell), at_((uint32_t)(kTallyCells * wavefront)), board_((uint32_t)L.j) {
     static_assert(63 / Geo<N>::STRIDE < kTallyCells / 2, "a cell for every board and for the lanes beyond them");
+    if (!later) clear();
+  }
+  __device__ __forceinline__ void clear() {
     present()[0] = 0u;
     present()[kTallyCells / 2] = 0u;
     wave_lds_fence();
@@ -1575,6 +1580,9 @@ __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& 
   pre[2] = sk_window<N>(L, tab_r, sk_home<N>(c ^ 1, opp), mv.playing);
   Rules r0 = rules;
   r0.auto_reset = 0;   // the reset happens below, after the table work
+  // go_step_superko_kernel clears the tally here, with the windows on their way, and not where it unpacks the state, before the walks (19x19, us a ply there / here:
+  // x 16384 26.57 / 26.42, x 20000 32.41 / 32.25, x 24000 38.8 / 38.6; small batches the same).
+  if constexpr (GATE && !EARLY) tally.clear();
   ply = apply_move<N, GATE, Floods<N>::PACKED && !GATE>(L, R, m, r0, mv, tally);
   const bool do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
   if (do_reset) reset_board<N>(L, R, m, rules.seed);   // a board that is reset takes no part in the table work below
@@ -1720,7 +1728,6 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   none.home = ~0u; none.e = make_uint2(1u, 0u);
   uint32_t forb = 0u;
   Ply ply;
-  Tally tally(tally_all, wib, L);
   // a6, a10 (mode 1 still holds the row and the table window: a fourth round at once, at 9x9 a third, would spill)
   auto board_final = [&](bool moved, bool reset) {
     push_history<N>(H, m.head, R.bk, R.wt, moved);
@@ -1729,6 +1736,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
   };
   if constexpr (MODE == 1) {
     const SkWin pre = sk_window_play<N>(L, tab, g, m, !skip);
+    Tally tally(tally_all, wib, L);   // (ahead of the window: 19x19 x 20000 30.5 us and not 30.1, x 24000 35.3 and not 34.8, 9x9 x 30001 13.54 and not 13.42)
     sk_step_core_play<N, true, true>(L, R, m, g, a.rules, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally, ply, pre,
                                      board_final, [&](Row<N>& Rr, Meta& mr, bool which) {   // the state is stored below: memory still holds it as loaded
                                        Row<N> T;
@@ -1741,6 +1749,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, 6) go_step_superko_kernel
                                      });
   } else {
     forb = sk_forb_loaded<N>(L, tab, g, R, m, none, lds_mask_all[wib]);
+    Tally tally(tally_all, wib, L, true);
     sk_step_core<N, true, false>(L, R, m, g, forb, a.rules, skip, act == G::P, in_range, bit_of<N>(L, in_range, pr, pc), pr, pc, tab, tab, zt, L.b, lds_mask_all[wib], tally, ply, false, none, board_final);
     g.fw = sk_forb_word<N>(L, forb);
   }

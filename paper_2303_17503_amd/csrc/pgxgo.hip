@@ -851,10 +851,12 @@ struct Ply {
 struct NothingToClear {
   __device__ __forceinline__ void operator()() const {}
 };
-// RARE_IN_LINE: the end of a game stands among the rest.  Out of the way it saves the usual ply its jumps, each of them a fetch, but go_rollout_kernel at 19x19
-// then needs two registers more than it has.  SIXTH: the flood that clears the mover's atari set runs in the sixth field where there is one.  Plies with the
-// rule in the mask by single wavefronts, which are run beyond 16384 games where the instructions of several wavefronts count and not one's chain, are 1.5 % slower that way (9x9 x
-// 30001 16.2 / 16.4 us).
+// RARE_IN_LINE: the end of a game stands among the rest.  Out of the way it saves the usual ply its jumps, each of them a fetch (9x9, rollouts by single wavefronts, in
+// line / out of it: 200 plies of 300 games 194.6 / 189.5 us, 16 of 18000 71.6 / 71.3), but go_rollout_kernel at 19x19 then needs two registers more than it has.
+// SIXTH: the flood that clears the mover's atari set runs in the sixth field where there is one, us a ply of 9x9 in a loop of its own / there: x 6000 5.55 / 5.52, x 65536
+// without observation 14.46 / 14.38, with the rule at play time x 512 6.51 / 6.45, x 16384 9.67 / 9.63.  With the rule in the mask by single wavefronts the loop is faster at every size:
+// two boards per wavefront x 512 7.99 / 8.20, pitches of its own x 1000 8.90 / 9.07, x 20000 14.45 / 14.66, x 50000 without observation 19.38 / 19.65 (search the same:
+// 64 entries 11.1 either way, 1024 14.9).
 template <int N, bool RARE_IN_LINE = false, bool SIXTH = Floods<N>::PACKED, class Clear = NothingToClear>
 __device__ __forceinline__ Ply apply_move(const Lane<N>& L, Row<N>& R, Meta& m, const Rules& cfg, const Move& mv, Tally& tally, Clear&& clear = Clear{}) {
   Ply out;
@@ -1583,7 +1585,7 @@ __device__ __forceinline__ void sk_step_core(const Lane<N>& L, Row<N>& R, Meta& 
   // go_step_superko_kernel clears the tally here, with the windows on their way, and not where it unpacks the state, before the walks (19x19, us a ply there / here:
   // x 16384 26.57 / 26.42, x 20000 32.41 / 32.25, x 24000 38.8 / 38.6; small batches the same).
   if constexpr (GATE && !EARLY) tally.clear();
-  ply = apply_move<N, GATE, Floods<N>::PACKED && !GATE>(L, R, m, r0, mv, tally);
+  ply = apply_move<N, false, Floods<N>::PACKED && !GATE>(L, R, m, r0, mv, tally);
   const bool do_reset = !skip && !mv.frozen && m.term && rules.auto_reset != 0;
   if (do_reset) reset_board<N>(L, R, m, rules.seed);   // a board that is reset takes no part in the table work below
   ply.reset = do_reset;
@@ -2236,7 +2238,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, SK ? 4 : 6) go_rollout_ke
     Ply ply;
     const int dr = d.row(L), dc = SK ? d.column() : 0;
     if constexpr (!SK) {
-      ply = apply_move<N, true>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.bit, 0, 0), tally,
+      ply = apply_move<N, N == 19>(L, R, m, a.rules, gate_move<N, false>(L, R, m, skip, d.pass, d.point, d.bit, 0, 0), tally,
                           [&]() { clear_points<N>(Q); });
       push_kept<N, AS_STORED>(Q, m.head, R.bk, R.wt, ply.moved);
       legal = legal_row<N>(L, R, m.wtm);

@@ -209,6 +209,13 @@ def go_kernel(env, B, with_obs, steps=0, slices=1, fused=True, superko=0):
     return name, math.ceil(B / (wb or env.set_boards_per_wavefront(0))) * waves / 1024.0
 
 
+def hex_rollout_kernel(env, steps, with_obs):
+    """name of the kernel that runs such a rollout"""
+    if env.rollout_in_time_slots(steps, obs=with_obs)[1]:   # (games at once: 0 with a row per lane)
+        return "hex_rollout_lane_kernel"
+    return "hex_rollout_team_kernel" if env.boards_per_team(steps, obs=with_obs)[0] else "hex_rollout_kernel"
+
+
 def one_group(cfg, env, with_obs, fused=True, superko=0, line_padded=False):
     """A stepper whose plies are those of one group of boards of the kernel that steps `env`: a team with one board where that kernel is
     run by teams, else one wavefront full of boards."""
@@ -559,8 +566,7 @@ def bench_hex(args, cfg):
             env.rollout(Lr, seed, pre + Wm + i * Lr, **bufs)
         ev1.record()
         torch.cuda.synchronize()
-        most = (10240 if Lr < 4 else 16384) if obs is not None else 5120 if Lr < 4 else 12288 if Lr < 16 else 16384   # games that are run by teams
-        kname = "hex_rollout_lane_kernel" if env.rollout_in_time_slots(Lr)[1] else "hex_rollout_team_kernel" if B <= most and Lr > 1 else "hex_rollout_kernel"   # (games at once: 0 with a row per lane)
+        kname = hex_rollout_kernel(env, Lr, with_obs)
     else:
         acts = [torch.empty(B, dtype=torch.int32, device="cuda") for _ in range(2)]
         env.random_actions(seed, pre, out=acts[pre & 1])

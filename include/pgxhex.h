@@ -103,6 +103,9 @@ int pgxhex_rollout(pgxhex_t h, int32_t steps, int32_t slices, uint32_t seed, uin
 /* As pgxgo_rollout_in_time_slots (pgxgo.h).  games_at_once is 0 with a board row per lane, which is never written in time slots. */
 int pgxhex_rollout_in_time_slots(pgxhex_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int64_t* games_at_once);
 
+/* As pgxgo_boards_per_team (pgxgo.h); step calls (steps = 0) have no teams.  It does not depend on the slices. */
+int pgxhex_boards_per_team(pgxhex_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int32_t* wavefronts);
+
 /* Getters for the current state; each enqueues one kernel or copy into the caller's buffer. */
 int pgxhex_legal_mask(pgxhex_t h, uint8_t* dst_dev /* [batch][122] */);
 int pgxhex_observe(pgxhex_t h, uint8_t* dst_dev /* [batch][484] */);
@@ -122,8 +125,8 @@ int pgxhex_import_state(pgxhex_t h, const int8_t* board_dev, const int8_t* to_pl
 
 /* Launch-shape knob of pgxhex_step / pgxhex_step_sample / pgxhex_rollout: 1 = a board row per lane (5 boards per wavefront), 2 = a whole
  * board per lane (64 boards per wavefront; pays from about 28 k games on, in the rollout kernel from about 20 k), 0 = the
- * automatic choice by batch size, which runs rollouts of small batches by teams of wavefronts with a board row per lane as well.  Results do not depend on it.  Returns the mapping the step calls now use (1 or 2), or
- * a negative error code. */
+ * automatic choice by batch size, which runs rollouts of small batches by teams of wavefronts with a board row per lane as well
+ * (pgxhex_boards_per_team).  Results do not depend on it.  Returns the mapping the step calls now use (1 or 2), or a negative error code. */
 int pgxhex_set_mapping(pgxhex_t h, int32_t mapping);
 
 /* Waits for the handle's stream. */

@@ -941,7 +941,7 @@ PaceArgs rollout_pace(const pgxhex_ctx* h, int steps, int slices, bool with_mask
 // 4 plies 0.95 x 16384, 1.13 x 20000; 16 plies 0.90 x 16384, 1.08 x 20000; without observation 2 plies 0.92 x 5120, 0.98 x 6000, 1.02 x 8192; 4 plies 0.92 x
 // 12000, 1.04 x 16384; 16 plies 0.92 x 16384.
 bool teams_for_rollout(const pgxhex_ctx* h, int steps, bool with_mask, bool with_obs) {
-  if (h->mapping != 0 || steps < 2 || !(with_mask || with_obs)) return false;   // (nothing to take off the wavefront with the rules)
+  if (h->mapping != 0 || board_per_lane(h, true) || steps < 2 || !(with_mask || with_obs)) return false;   // (nothing to take off the wavefront with the rules)
   constexpr int K = 1024;
   return h->B <= (with_obs ? (steps < 4 ? 10 * K : 16 * K) : steps < 4 ? 5 * K : steps < 16 ? 12 * K : 16 * K);
 }
@@ -1081,6 +1081,13 @@ int pgxhex_rollout_in_time_slots(pgxhex_t h, int32_t steps, int32_t slices, int3
   const PaceArgs p = rollout_pace(h, steps, slices, with_mask != 0, with_obs != 0);
   if (games_at_once) *games_at_once = (int64_t)8 * p.held * 64;
   return p.ply != 0u ? 1 : 0;
+}
+
+int pgxhex_boards_per_team(pgxhex_t h, int32_t steps, int32_t slices, int32_t with_mask, int32_t with_obs, int32_t* wavefronts) {
+  if (!h || steps < 0 || slices < 1) return PGXHEX_EINVAL;
+  const bool teams = teams_for_rollout(h, steps, with_mask != 0, with_obs != 0);
+  if (wavefronts) *wavefronts = teams ? rollout_team_waves(with_obs != 0) : 1;
+  return teams ? W : 0;
 }
 
 int pgxhex_random_actions(pgxhex_t h, uint32_t seed, uint32_t t, const int32_t* start_t_dev, int32_t* actions_dev) {

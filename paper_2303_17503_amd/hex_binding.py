@@ -33,6 +33,7 @@ def lib():
         L.pgxhex_step_sample.argtypes = [vp, vp, u32, u32, vp, vp]
         L.pgxhex_rollout.argtypes = [vp, i32, i32, u32, u32, vp, vp, vp, vp, vp, vp]
         L.pgxhex_rollout_in_time_slots.argtypes = [vp, i32, i32, i32, i32, C.POINTER(C.c_int64)]
+        L.pgxhex_boards_per_team.argtypes = [vp, i32, i32, i32, i32, C.POINTER(i32)]
         for n in ("legal_mask", "observe", "rewards", "terminated", "current_player"):
             getattr(L, "pgxhex_" + n).argtypes = [vp, vp]
         L.pgxhex_export_state.argtypes = [vp] * 8
@@ -168,6 +169,14 @@ class HexEnv:
         if rc < 0:
             _check(rc, "pgxhex_rollout_in_time_slots")
         return bool(rc), games.value
+
+    def boards_per_team(self, steps=0, slices=1, mask=True, obs=True):
+        """(boards per team, wavefronts of a team) of such a rollout; (0, 1) where one wavefront does everything, as in step calls (steps = 0)"""
+        waves = C.c_int32()
+        rc = lib().pgxhex_boards_per_team(self._h, int(steps), int(slices), int(bool(mask)), int(bool(obs)), C.byref(waves))
+        if rc < 0:
+            _check(rc, "pgxhex_boards_per_team")
+        return rc, waves.value
 
     def _get(self, name, shape, dtype, out):
         out = torch.empty(shape, dtype=dtype, device=self.device) if out is None else _need(out, dtype, shape, name)

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import bench
 import paper_2303_17503_amd as pg
 
 pytestmark = pytest.mark.gpu
@@ -16,6 +17,8 @@ pytestmark = pytest.mark.gpu
 def test_rollouts_by_teams_and_by_single_wavefronts_agree(B, steps, slices, mask, obs, auto_reset):
     envs = [pg.HexEnv(B, seed=6, auto_reset=auto_reset) for _ in range(2)]
     envs[1].set_mapping(1)
+    by_teams = (B, steps, obs) not in [(5121, 3, False), (10241, 2, True)]   # the other side of a line
+    assert [e.boards_per_team(steps, slices, mask=mask, obs=obs) for e in envs] == [(5, 3 if obs else 2) if by_teams else (0, 1), (0, 1)]
     start = torch.as_tensor(np.random.default_rng(B).integers(-3, 40, size=B).astype(np.int32), device="cuda")   # some wait through a whole launch
     got = []
     for e in envs:
@@ -31,3 +34,20 @@ def test_rollouts_by_teams_and_by_single_wavefronts_agree(B, steps, slices, mask
         got.append(seen)
     for i, (x, y) in enumerate(zip(*got)):
         assert torch.equal(x, y), i
+
+
+@pytest.mark.parametrize("B,steps,obs,team", [
+    (16384, 0, True, (0, 1)), (16384, 1, True, (0, 1)), (10240, 2, True, (5, 3)), (10241, 3, True, (0, 1)), (16384, 4, True, (5, 3)), (16385, 99, True, (0, 1)),
+    (5120, 2, False, (5, 2)), (5121, 3, False, (0, 1)), (12288, 4, False, (5, 2)), (12289, 15, False, (0, 1)), (16384, 16, False, (5, 2)), (16385, 16, False, (0, 1)),
+    (20480, 16, True, (0, 1))])
+def test_which_rollouts_go_by_teams(B, steps, obs, team):
+    env = pg.HexEnv(B)
+    assert env.boards_per_team(steps, obs=obs) == team
+    assert env.boards_per_team(steps, mask=False, obs=False) == (0, 1)
+    if steps:
+        assert bench.hex_rollout_kernel(env, steps, obs) == ("hex_rollout_team_kernel" if team[0] else "hex_rollout_lane_kernel" if B == 20480 else "hex_rollout_kernel")
+    for mapping in (1, 2):
+        env.set_mapping(mapping)
+        assert env.boards_per_team(steps, obs=obs) == (0, 1)
+    env.set_mapping(0)
+    assert env.boards_per_team(steps, obs=obs) == team

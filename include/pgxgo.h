@@ -244,6 +244,9 @@ int pgxgo_empty_probe(void* stream, int32_t count);
  * seen from above, for in_dev[0..63].  Used by the tests to check the lane layout the kernels rely on. */
 int pgxgo_lane_shift_probe(const uint32_t* in_dev, uint32_t* out_dev, void* stream);
 
+/* Harness helper: the remainder that the action draws take, out_dev[i] = n_dev[i] mod d_dev[i] for 1 <= d_dev[i] <= 1024. */
+int pgxgo_remainder_probe(const uint32_t* n_dev, const uint32_t* d_dev, uint32_t* out_dev, int32_t count, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

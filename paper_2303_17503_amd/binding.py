@@ -79,6 +79,7 @@ def lib():
         L.pgxgo_strerror.argtypes = [C.c_int]
         L.pgxgo_last_hip_error.restype = C.c_int
         L.pgxgo_lane_shift_probe.argtypes = [vp, vp, vp]
+        L.pgxgo_remainder_probe.argtypes = [vp, vp, vp, i32, vp]
         _fast = _load_fast()
         _lib = L
     return _lib
@@ -361,3 +362,11 @@ def lane_shift_probe(values):
     out = torch.empty(128, dtype=torch.int32, device=values.device)
     _check(lib().pgxgo_lane_shift_probe(_ptr(values), _ptr(out), C.c_void_p(torch.cuda.current_stream().cuda_stream)), "pgxgo_lane_shift_probe")
     return out[:64], out[64:]
+
+
+def remainder_probe(n, d):
+    """n mod d as the action draws take it; n, d: int32 cuda tensors of one shape (bits of uint32), d from 1 to 1024."""
+    _need(d, torch.int32, tuple(_need(n, torch.int32, tuple(n.shape), "n").shape), "d")
+    out = torch.empty_like(n)
+    _check(lib().pgxgo_remainder_probe(_ptr(n), _ptr(d), _ptr(out), n.numel(), C.c_void_p(torch.cuda.current_stream().cuda_stream)), "pgxgo_remainder_probe")
+    return out

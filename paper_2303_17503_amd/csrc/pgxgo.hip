@@ -2609,6 +2609,11 @@ __global__ void lane_shift_probe_kernel(const uint32_t* in, uint32_t* out) {
   out[64 + threadIdx.x] = from_lane_above(x);
 }
 
+__global__ void __launch_bounds__(256) remainder_probe_kernel(const uint32_t* n, const uint32_t* d, uint32_t* out, uint32_t count) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  if (i < count) out[i] = remainder_of(n[i], d[i]);
+}
+
 // Measurement helpers: a plain fill with 16-byte stores (the practical write ceiling of the machine on the same
 // buffers the step kernel writes) and an empty kernel (the gap between dependent launches on one stream).
 template <int ST>
@@ -3414,6 +3419,13 @@ int pgxgo_empty_probe(void* stream, int32_t count) {
 int pgxgo_lane_shift_probe(const uint32_t* in_dev, uint32_t* out_dev, void* stream) {
   if (!in_dev || !out_dev) return PGXGO_EINVAL;
   hipLaunchKernelGGL(lane_shift_probe_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, in_dev, out_dev);
+  HIPCHK(hipGetLastError());
+  return PGXGO_OK;
+}
+
+int pgxgo_remainder_probe(const uint32_t* n_dev, const uint32_t* d_dev, uint32_t* out_dev, int32_t count, void* stream) {
+  if (!n_dev || !d_dev || !out_dev || count <= 0) return PGXGO_EINVAL;
+  hipLaunchKernelGGL(remainder_probe_kernel, dim3(((unsigned)count + 255u) / 256u), dim3(256), 0, (hipStream_t)stream, n_dev, d_dev, out_dev, (uint32_t)count);
   HIPCHK(hipGetLastError());
   return PGXGO_OK;
 }

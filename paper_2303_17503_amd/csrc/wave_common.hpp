@@ -11,6 +11,8 @@
 
 #include <type_traits>
 
+#include "remainder.hpp"
+
 namespace pgxwave {
 
 // counter-based hash of (seed, tag, env, t); tag 0 = action draw, tag 1 = seat draw (t = episode)
@@ -22,16 +24,6 @@ __device__ __forceinline__ uint32_t mixer(uint32_t x) {
 }
 __device__ __forceinline__ uint32_t env_hash(uint32_t seed, uint32_t tag, uint32_t env, uint32_t t) {
   return mixer(mixer(mixer(seed + 0x9E3779B9u * (tag + 1u)) ^ env) ^ t);
-}
-
-// n mod d for 1 <= d <= 1024, any n.  The quotient in floats is off by at most 2^10 / d + 1, so what is left of n lies within 2^10 + d of [0, d) and its own
-// quotient, taken half a unit up, cannot round to the wrong side.  (Checked for every d with reciprocals one unit in the last place off
-// either way, as the instruction may give them.)  The general division takes four of the slow 32-bit products where this takes one, in a chain
-// that nothing else fills.
-__device__ __forceinline__ uint32_t remainder_of(uint32_t n, uint32_t d) {
-  const float f = __builtin_amdgcn_rcpf((float)d);
-  const uint32_t left = n - (uint32_t)__builtin_fminf((float)n * f, 4294967040.0f) * d;
-  return left - (uint32_t)__mul24((int)__builtin_floorf(__builtin_fmaf((float)(int32_t)left, f, 0.5f * f)), (int)d);
 }
 
 // index of the calling wavefront within its block, as a value the compiler knows to be the same in every lane

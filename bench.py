@@ -186,11 +186,14 @@ def bound_statement(kern_us, floor_us, fill_us, waves_per_simd):
     """Which limit binds, by a stated rule on quantities measured in this run (the counters are in profiles/)."""
     rule = ("latency if kernel <= 1.5 x the ply of ONE group of boards (launch gap + load -> rules -> emit -> store of a single wavefront, "
             "or team of wavefronts, of the same kernel); else hbm if a plain fill of the same output bytes takes 0.6 to 1 of the kernel (a "
-            "fill that takes longer than the kernel that wrote as much is a launch, not memory); else valu issue")
+            "fill that takes longer than the kernel that wrote as much is a launch, not memory); else latency if there are fewer than two wavefronts "
+            "per SIMD, as then little else is issued while one waits; else valu issue")
     if kern_us <= 1.5 * floor_us:
         b = "launch gap + serial latency of one group"
     elif 0.6 <= fill_us / kern_us <= 1.0:
         b = "hbm (output stores)"
+    elif waves_per_simd < 2.0:
+        b = "serial latency of the groups"
     else:
         b = "valu issue"
     return {"bound_by": b, "rule": rule, "one_group_ply_us": floor_us, "fill_of_outputs_us": fill_us, "wavefronts_per_simd": waves_per_simd}

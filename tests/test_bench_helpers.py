@@ -49,3 +49,7 @@ def test_bound_statement_rule():
     assert bench.bound_statement(22.0, 5.5, 17.0, 5.3)["bound_by"].startswith("hbm")
     assert bench.bound_statement(40.0, 5.0, 23.0, 51.0)["bound_by"] == "valu issue"
     assert bench.bound_statement(5.4, 2.9, 7.1, 3.2)["bound_by"] == "valu issue"   # the kernel has written as much in less time than the fill
+    # one wavefront per SIMD: whatever it waits for, nothing else is issued meanwhile
+    assert bench.bound_statement(7.0, 4.5, 7.1, 1.0)["bound_by"].startswith("serial latency")
+    assert bench.bound_statement(7.0, 4.5, 7.1, 2.0)["bound_by"] == "valu issue"
+    assert bench.bound_statement(7.0, 4.5, 5.0, 1.0)["bound_by"].startswith("hbm")

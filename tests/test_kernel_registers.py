@@ -33,7 +33,8 @@ def kernels(tmp_path):
 def test_no_kernel_keeps_vector_registers_in_memory(tmp_path):
     found = kernels(tmp_path)
     names = " ".join(name for name, _ in found)
-    for part in ("go_step_kernel", "go_step_superko_kernel", "go_rollout_kernel", "go_step_slots_kernel", "go_step_team_kernel", "go_rollout_team_kernel", "go_step_slots_team_kernel", "hex_step_kernel", "hex_step_lane_kernel", "hex_rollout_lane_kernel"):
+    for part in ("go_step_kernel", "go_step_superko_kernel", "go_rollout_kernel", "go_step_slots_kernel", "go_step_team_kernel", "go_rollout_team_kernel", "go_step_slots_team_kernel",
+                 "go_step_superko_team_kernel", "hex_step_kernel", "hex_step_lane_kernel", "hex_rollout_kernel", "hex_rollout_lane_kernel", "hex_rollout_team_kernel"):
         assert part in names
     value = lambda block, key: int(re.search(rf"\.{key}: +(\d+)", block).group(1))  # noqa: E731
     spilled = {name: value(block, "vgpr_spill_count") for name, block in found if value(block, "vgpr_spill_count") or value(block, "private_segment_fixed_size")}

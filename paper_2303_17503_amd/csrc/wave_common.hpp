@@ -211,9 +211,12 @@ __device__ __forceinline__ void team_barrier() {
 // The wavefront with the rules goes first where its SIMD has a team's other wavefront to issue from as well (more than one team per compute unit,
 // 256) and no second one with rules (up to one team per SIMD, 1024): the team waits for it.  eighth: teams / 8.  us, without / with: a ply of 9x9 x 4096
 // 4.88 / 4.49, x 3000 4.67 / 4.51; 32 plies of 9x9 in one launch without observation x 1000 38.4 / 36.2, x 5001 43.5 / 40.8, x 6000 43.9 / 41.0, with it x 1000 37.9 / 36.1,
-// x 4096 53.0 / 52.1; 16 plies of 19x19 x 1500 without observation 29.5 / 27.1, with it 32.6 / 32.0; search x 4096 of 9x9 4.18 / 4.04; superko 9x9 x 4096 8.2 / 8.1.
+// x 4096 53.0 / 52.1; 16 plies of 19x19 x 1500 without observation 29.5 / 27.1, with it 32.6 / 32.0; search x 4096 of 9x9 4.18 / 4.04.  With the repetition rule: 16 plies at
+// play time 9x9 x 1000 36.7 / 35.9, x 5001 46.5 / 42.0, 19x19 x 2000 53.0 / 47.9, in the mask 9x9 x 5001 80.8 / 78.7, 19x19 x 2000 82.1 / 78.8; a ply in the mask 9x9 x 4096
+// 8.25 / 8.10, 19x19 x 2000 8.67 / 8.52.  Hex, 16 plies x 1500 18.0 / 17.5, x 4000 20.2 / 17.7, x 5120 20.1 / 17.7, without observation 18.3 / 17.1.
 // Beyond 1024 teams the outputs, which start later, lose what the rules gain or more: 32 plies of 9x9 x 8000 61.1 / 64.3, x 15000 119 / 140; search of 19x19 x 6144
-// 9.2 / 9.8.  With one team per compute unit nothing is gained (16 plies of 19x19 x 256 23.0 / 23.4).
+// 9.2 / 9.8; 16 plies of Hex x 16384 45.3 / 46.7.  (Not everywhere: Hex x 8192 27.6 / 26.1, with the repetition rule 16 plies of 19x19 x 3400 63.5 / 57.3.)  With one team per
+// compute unit nothing is gained (16 plies of 19x19 x 256 23.0 / 23.4, at play time 38.4 / 38.6).
 __device__ __forceinline__ void rules_first(uint32_t eighth) {
   if (eighth > 32u && eighth <= 128u) __builtin_amdgcn_s_setprio(3);
 }
